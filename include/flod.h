@@ -314,10 +314,12 @@ typedef struct {
 flod_status flod_ctx_stats(const flod_ctx *ctx, flod_stats *out);
 
 /* Device pointers to the last render's intermediate buffers, owned by ctx, valid until
-   the next call on ctx. For inspection and tests. May run one kernel and wait for it (see
-   grad2d); FLOD_ERR_DEVICE if that fails. */
+   the next call on ctx. For inspection and tests. May run a kernel and wait for it (see
+   tile_ids, grad2d; FLOD_ERR_DEVICE if that fails) and take workspace for tile_ids
+   (FLOD_ERR_WORKSPACE if refused). */
 typedef struct {
-  const uint32_t *tile_ids;     /* [n_instances] tile id of each sorted instance          */
+  const uint32_t *tile_ids;     /* [n_instances] tile id of each sorted instance (written
+                                   by the first view after a render: no render needs them) */
   const uint32_t *values;       /* [n_instances] Gaussian (global) index, sorted by
                                    (tile, depth bits, index)                              */
   const uint32_t *ranges;       /* [tiles,2] [start, end) of each tile in the list          */
@@ -353,11 +355,13 @@ flod_status flod_ctx_view(const flod_ctx *ctx, flod_view *out);
 enum {
   FLOD_STAGE_PREPROCESS = 0,  /* selection (eq. 6), activation (eq. 4), projection, SH */
   FLOD_STAGE_DEPTH_SORT,      /* radix sort by depth; its first pass compacts the visible
-                                 set, its last writes the tile counts in depth order   */
-  FLOD_STAGE_OFFSETS,         /* scan of the tile counts, count readback             */
-  FLOD_STAGE_EMIT,            /* (tile, Gaussian) instance emission                  */
-  FLOD_STAGE_TILE_SORT,       /* stable radix sort of instances by tile              */
-  FLOD_STAGE_RANGES,          /* per-tile [start, end)                               */
+                                 set and takes the frame's counts (read by the host),
+                                 its last writes the tile rectangles in depth order    */
+  FLOD_STAGE_OFFSETS,         /* offsets of each workgroup's pairs per supertile     */
+  FLOD_STAGE_EMIT,            /* the tile lists, from the grouped pairs              */
+  FLOD_STAGE_TILE_SORT,       /* pairs grouped by supertile in depth order, their
+                                 instances counted per tile                           */
+  FLOD_STAGE_RANGES,          /* per-tile [start, end) and the blend's tile order    */
   FLOD_STAGE_BLEND,           /* front-to-back compositing (eq. 2)                   */
   FLOD_STAGE_BLEND_BWD,       /* reverse compositing kernel (its tile order excluded) */
   FLOD_STAGE_PREPROCESS_BWD,  /* chain rule to the 3D attributes                     */
@@ -368,7 +372,7 @@ enum {
    and, for single-level renders, each Gaussian's colour Jacobian (48 bytes per Gaussian).
    keep == 0: renders keep none of it and take no workspace for it; a backward after such a
    render returns FLOD_ERR_UNSUPPORTED. For callers that only render (a server), which then
-   need about a third less workspace per instance. Applies from the next render. */
+   need a third of the workspace per instance. Applies from the next render. */
 flod_status flod_ctx_keep_backward_state(flod_ctx *ctx, int keep);
 /* enable != 0 records every stage. */
 flod_status flod_ctx_set_timing(flod_ctx *ctx, int enable);

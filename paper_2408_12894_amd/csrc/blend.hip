@@ -15,7 +15,7 @@
 // relative 1e-4 margin around the stop threshold that the parity checks flag.
 // The workgroup leaves the list as soon as all 256 pixels have stopped.
 //
-// Workgroups take the tiles in order of decreasing list length (k_tile_order). Each tile also
+// Workgroups take the tiles in order of decreasing list length (see tile_order). Each tile also
 // lists the entries it blended into some pixel, the only ones its backward pass processes:
 // (list position, Gaussian) pairs in list order at the start of the tile's range, and their
 // count, from which the backward orders its tiles.
@@ -201,13 +201,6 @@ hipError_t launch_blend(const uint2 *ranges, const uint32_t *values, const float
   hipLaunchKernelGGL(kernel, dim3(n_tiles), dim3(kTile * kTile / kFwdPix), 0, s, ranges, values, xyab, cop, blue,
                      cam.W, cam.H, cam.tiles_x, n_tiles, bg[0], bg[1], bg[2], image, final_T, n_contrib, n_blended,
                      blended, tile_blended, order);
-  return hipGetLastError();
-}
-
-hipError_t launch_tile_order_by_length(const uint2 *ranges, int n_tiles, uint32_t *order, hipStream_t s) {
-  if (n_tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_tile_order<ListLengthCost>, dim3(1), dim3(kOrderThreads), 0, s, ListLengthCost{ranges},
-                     n_tiles, order, TileSplit{0.0f, 0.0f, -1, -1});
   return hipGetLastError();
 }
 

@@ -67,20 +67,19 @@ __device__ __forceinline__ int cost_bucket(uint32_t c) {
   return min(kOrderBuckets - 1, 8 + (e - 3) * 8 + m);
 }
 
-struct ListLengthCost {   // forward: entries in the tile's list
-  const uint2 *ranges;
-  __device__ __forceinline__ uint32_t operator()(int t) const { return ranges[t].y - ranges[t].x; }
-};
-
-struct CountCost {        // backward: entries the forward blended somewhere in the tile
+// A count per tile: the length of its list (forward), or the entries of it that the forward
+// blended somewhere in the tile (backward).
+struct CountCost {
   const uint32_t *count;
   __device__ __forceinline__ uint32_t operator()(int t) const { return count[t]; }
 };
 
-// The tile order as one workgroup of kOrderThreads threads (the body of k_tile_order, which
-// the backward also runs beside other work in one launch).
+// The tile order as one workgroup of kOrderThreads threads. With ranges, the costs are the
+// lengths of the tiles' lists and their exclusive prefix in tile order gives each tile's
+// [start, end).
 template <class Cost>
-__device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restrict__ order, TileSplit split) {
+__device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restrict__ order, TileSplit split,
+                                           uint2 *__restrict__ ranges = nullptr) {
   constexpr int W = kOrderThreads / 64;
   // per-wave bucket counts (contention only inside a wave), then per (bucket, wave) offsets
   __shared__ uint32_t s_cnt[W][kOrderBuckets];
@@ -158,21 +157,30 @@ __device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restric
     }
   }
   __syncthreads();
-  for (int base = t0 + lane; base < t1; base += 64 * kOrderLoads) {
+  uint32_t start = 0u;   // the tiles before this wave's: their costs
+  for (int k = 0; k < w; ++k) start += (uint32_t)s_csum[k];
+  for (int b0 = t0; b0 < t1; b0 += 64 * kOrderLoads) {
+    const int base = b0 + lane;
     uint32_t c[kOrderLoads];
 #pragma unroll
-    for (int u = 0; u < kOrderLoads; ++u) c[u] = cost(min(base + 64 * u, t1 - 1));   // in bounds: base < t1
+    for (int u = 0; u < kOrderLoads; ++u) c[u] = cost(min(base + 64 * u, t1 - 1));   // in bounds: b0 < t1
 #pragma unroll
-    for (int u = 0; u < kOrderLoads; ++u)
-      if (base + 64 * u < t1) order[atomicAdd(&s_cnt[w][cost_bucket(c[u])], 1u)] = (uint32_t)(base + 64 * u);
+    for (int u = 0; u < kOrderLoads; ++u) {
+      const bool in = base + 64 * u < t1;
+      if (in) order[atomicAdd(&s_cnt[w][cost_bucket(c[u])], 1u)] = (uint32_t)(base + 64 * u);
+      if (ranges) {
+        uint32_t end = in ? c[u] : 0u;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t x = __shfl_up(end, o, 64);
+          if (lane >= o) end += x;
+        }
+        if (in) ranges[base + 64 * u] = make_uint2(start + end - c[u], start + end);
+        start += __shfl(end, 63, 64);
+      }
+    }
   }
   if (split.cap2 >= 0 && tid < 2) order[n + tid] = s_split[tid];
-}
-
-template <class Cost>
-__global__ __launch_bounds__(kOrderThreads) void k_tile_order(Cost cost, int n, uint32_t *__restrict__ order,
-                                                              TileSplit split) {
-  tile_order(cost, n, order, split);
 }
 
 }  // namespace flod

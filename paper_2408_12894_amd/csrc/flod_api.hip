@@ -55,9 +55,10 @@ struct Buf {
 
 enum BufId {
   B_XYAB, B_COP, B_BLUE, B_DEPTH, B_BIN, B_TILES, B_BLOCKVIS, B_PREFIX,
-  B_DKEY0, B_DKEY1, B_DVAL0, B_DVAL1, B_TBSUM, B_TPREFIX,
-  B_TKEY0, B_TKEY1, B_TVAL0, B_TVAL1, B_HIST, B_SCAN, B_TOT, B_RANGES, B_COUNTERS,
-  B_G2D, B_SSIM, B_BLENDED, B_TILE_BLENDED, B_TILE_ORDER, B_STILES, B_SHJAC, B_COUNT
+  B_DKEY0, B_DKEY1, B_DVAL0, B_DVAL1, B_RECT, B_SRECT,
+  B_PAIR_ID, B_PAIR_MASK, B_CHUNKS, B_CHUNK_CNT, B_SUPERS, B_TILE_LEN, B_VALUES, B_TILE_IDS,
+  B_HIST, B_SCAN, B_TOT, B_RANGES, B_COUNTERS,
+  B_G2D, B_SSIM, B_BLENDED, B_TILE_BLENDED, B_TILE_ORDER, B_SHJAC, B_COUNT
 };
 
 struct Saved {
@@ -69,9 +70,7 @@ struct Saved {
   float bg[3] = {0, 0, 0};
   const float *final_T = nullptr;
   const int32_t *n_contrib = nullptr;
-  int sorted_vals = 0;   // which of B_TVAL0/B_TVAL1 holds the sorted values
-  int sorted_keys = 0;
-  int depth_buf = 0;
+  bool has_tile_ids = false;     // B_TILE_IDS holds the list's tile ids (see flod_ctx_view)
   bool has_grad2d = false;
   bool grad2d_moments = false;   // B_G2D still holds the backward's moment sums (see flod_ctx_view)
   bool has_blended = false;      // the render listed its blended entries (the backward needs them)
@@ -89,8 +88,8 @@ struct flod_ctx {
   bool has_stream = false;
   hipEvent_t ev_switch = nullptr;       // orders a call on a new stream after the last one
   size_t required = 0;
-  unsigned long long *host_counters = nullptr;   // pinned: [visible u32 | K u32], [K u64]
-  // coherent pinned memory the offsets scan writes the counts into, as four 64-bit words
+  unsigned long long *host_counters = nullptr;   // pinned copy of the device counters' first 24 bytes
+  // coherent pinned memory the totals kernel writes the counts into, as five 64-bit words
   // tagged with the render's sequence number (null: copy instead), and its device address
   unsigned long long *host_counts = nullptr;
   unsigned long long *host_counts_dev = nullptr;
@@ -235,12 +234,12 @@ hipError_t wait_event(hipEvent_t ev) {
 
 hipError_t wait_marked(flod_ctx *c) { return wait_event(c->ev_sync); }
 
-// Wait until all four count words carry `seq` (the scan kernel writes them whole): polling,
+// Wait until all five count words carry `seq` (the totals kernel writes them whole): polling,
 // and after about 2 s a blocking wait for the stream, then one last look.
 hipError_t wait_counts(flod_ctx *c, hipStream_t s, uint32_t seq) {
   const volatile unsigned long long *w = c->host_counts;
   auto ready = [&]() {
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < 5; ++k)
       if ((uint32_t)(w[k] >> 32) != seq) return false;
     return true;
   };
@@ -252,12 +251,6 @@ hipError_t wait_counts(flod_ctx *c, hipStream_t s, uint32_t seq) {
   hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
   return ready() ? hipSuccess : hipErrorUnknown;
-}
-
-int ceil_log2(int64_t v) {
-  int b = 0;
-  while (b < 62 && ((int64_t)1 << b) < v) ++b;
-  return b;
 }
 
 bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -294,30 +287,32 @@ DevCamera dev_camera(const flod_camera *cam) {
 
 float sq32(float d) { return isinf(d) ? INFINITY : (float)((double)d * (double)d); }
 
-// Instances the tail buffers (tile keys and values, both ping-pong halves, the list of blended
-// entries) hold.
+// Instances the list buffers (the list, the list of blended entries) hold.
 int64_t instance_capacity(const flod_ctx *c) {
-  size_t b = c->buf[B_TKEY0].cap;
-  for (BufId id : {B_TKEY1, B_TVAL0, B_TVAL1}) b = b < c->buf[id].cap ? b : c->buf[id].cap;
-  int64_t k = (int64_t)(b / 4);
+  int64_t k = (int64_t)(c->buf[B_VALUES].cap / 4);
   if (c->keep_backward) {
     const int64_t t = (int64_t)(c->buf[B_BLENDED].cap / 8);
     if (t < k) k = t;
   }
-  if (k > 0xFFFFFFFEll) k = 0xFFFFFFFEll;
-  return k > 0 ? k : 0;
+  return k < 0xFFFFFFFEll ? k : 0xFFFFFFFEll;
 }
 
-size_t hist_bytes(int64_t n_max) { return radix_hist_bytes(n_max); }
+// (supertile, Gaussian) pairs the pair buffers hold.
+int64_t pair_capacity(const flod_ctx *c) {
+  const int64_t a = (int64_t)(c->buf[B_PAIR_ID].cap / 4), b = (int64_t)(c->buf[B_PAIR_MASK].cap / 8);
+  const int64_t p = a < b ? a : b;
+  return p < 0xFFFFFFFEll ? p : 0xFFFFFFFEll;
+}
 
 // The forward pipeline over the candidate set described by p.
 //
-// The instance count K is known on the device only after the tile-count scan. The emission,
-// tile sort, ranges and blend that follow are enqueued at once, sized for the instances the
-// context's buffers hold (cap); the scan hands them K when K <= cap and 0 otherwise, in which
-// case they do nothing. Meanwhile the host reads K back (stream-ordered, 16 bytes) for the
-// statistics and the capacity check: when K > cap it grows the buffers and enqueues the scan's
-// count and the tail again. A context's first render (cap = 0) waits for K before enqueuing.
+// The counts of instances K and of pairs P are known on the device only after the preprocess.
+// What follows the depth sort is enqueued at once, sized for what the context's buffers hold
+// (cap, cap_p); the totals hand it P when both fit and 0 otherwise, in which case it does
+// nothing. Meanwhile the host waits for the counts (taken beside the depth sort's first pass)
+// for the statistics and the capacity check: when they do not fit it grows the buffers, takes
+// the totals again and enqueues the tail again. A context's first render (cap = 0) waits for the
+// counts before enqueuing.
 // level: a single-level render, which keeps what its backward needs (when the context keeps
 // backward state)
 flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const float bg[3],
@@ -326,38 +321,47 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   if (use_stream(c, s) != hipSuccess) return FLOD_ERR_DEVICE;
   c->saved.valid = false;
   c->saved.has_grad2d = false;
+  c->saved.has_tile_ids = false;
   timing_flush(c);
   StageTimer tm(c, s);
   const int64_t N = p.n_total;
   const DevCamera &cam = p.cam;
   const int n_tiles = cam.tiles_x * cam.tiles_y;
   const int nb = (int)((N + kBlock - 1) / kBlock);
-  int64_t cap = instance_capacity(c);
+  const int n_supers = super_count(cam);
+  int64_t cap = instance_capacity(c), cap_p = pair_capacity(c);
   size_t extra = 0;
   flod_status st = FLOD_OK;
   auto need = [&](BufId id, size_t bytes) {
     flod_status r = ensure(c, id, bytes, s, &extra);
     if (r != FLOD_OK) st = r;
   };
-  const size_t hist = hist_bytes(N) > hist_bytes(cap) ? hist_bytes(N) : hist_bytes(cap);
+  auto need_chunks = [&]() {
+    const size_t n = (size_t)chunk_capacity(cam, cap_p);
+    need(B_CHUNKS, 16 * n);
+    need(B_CHUNK_CNT, 256 * n);
+  };
+  const size_t hist_d = radix_hist_bytes(N), hist_p = pair_hist_bytes(cam, N);
+  const size_t hist = hist_d > hist_p ? hist_d : hist_p;
   need(B_XYAB, 16 * (size_t)N);
   need(B_COP, 16 * (size_t)N);
   need(B_BLUE, 8 * (size_t)N);
   need(B_DEPTH, 4 * (size_t)N);
   need(B_BIN, 32 * (size_t)N);
   need(B_TILES, 4 * (size_t)N);
-  need(B_BLOCKVIS, 4 * (size_t)nb);
-  need(B_PREFIX, 8 * (size_t)nb);
+  need(B_BLOCKVIS, 32 * (size_t)nb);
   need(B_DKEY0, 4 * (size_t)N);
   need(B_DKEY1, 4 * (size_t)N);
   need(B_DVAL0, 4 * (size_t)N);
   need(B_DVAL1, 4 * (size_t)N);
-  need(B_TBSUM, 4 * (size_t)nb);
-  need(B_TPREFIX, 8 * (size_t)nb);
-  need(B_STILES, 4 * (size_t)N);
+  need(B_RECT, 8 * (size_t)N);
+  need(B_SRECT, 8 * (size_t)N);
   need(B_HIST, hist);
   need(B_SCAN, hist);
-  need(B_TOT, 4 * (size_t)kRadix);
+  need(B_TOT, 4 * (size_t)(n_supers > kRadix ? n_supers : kRadix));
+  need(B_SUPERS, 8 * (size_t)n_supers);
+  need_chunks();
+  need(B_TILE_LEN, 4 * (size_t)n_tiles);
   need(B_RANGES, 8 * (size_t)n_tiles);
   need(B_TILE_BLENDED, 4 * (size_t)n_tiles);
   need(B_TILE_ORDER, 4 * ((size_t)n_tiles + 2));
@@ -369,19 +373,16 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     return st;
   }
   uint32_t *counters = P<uint32_t>(c, B_COUNTERS);
-  const bool speculate = N > 0 && cap > 0;
+  const bool speculate = N > 0 && cap > 0 && cap_p > 0;
   int dres = 0;
-  uint32_t *sorted_tiles = nullptr;
-  // tile counts in depth order and their scan; K (guarded by `guard`) to counters[kCntInstances]
-  // and, when `to_host`, the counts straight to the host, tagged with this render's number
+  // the counts, guarded by the capacities; straight to the host when `to_host`, tagged with this
+  // render's number
   const bool direct = c->host_counts_dev != nullptr;
   if (direct && ++c->count_seq == 0u) c->count_seq = 1u;   // 0 is the buffer's initial tag
   const uint32_t seq = direct ? c->count_seq : 0u;
-  auto offsets = [&](int64_t guard, bool to_host) -> hipError_t {
-    return launch_scan_blocks(P<uint32_t>(c, B_TBSUM), counters + kCntVisible, kBlock,
-                              P<unsigned long long>(c, B_TPREFIX), counters + kCntInstances,
-                              reinterpret_cast<unsigned long long *>(counters + kCntTotal64), nb, s,
-                              (unsigned long long)guard, to_host ? c->host_counts_dev : nullptr, seq);
+  auto totals = [&](int64_t guard_k, int64_t guard_p, bool to_host) {
+    return FrameTotals{P<uint4>(c, B_BLOCKVIS), nb, counters, (unsigned long long)guard_k, (unsigned long long)guard_p,
+                       to_host ? c->host_counts_dev : nullptr, seq};
   };
   if (N > 0) {
     PreOut o;
@@ -391,8 +392,8 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     o.depth = P<uint32_t>(c, B_DEPTH);
     o.bin = P<float4>(c, B_BIN);
     o.tiles = P<uint32_t>(c, B_TILES);
-    o.block_vis = P<uint32_t>(c, B_BLOCKVIS);
-    o.zero_sums = P<uint32_t>(c, B_TBSUM);
+    o.rect = P<uint2>(c, B_RECT);
+    o.block_sums = P<uint4>(c, B_BLOCKVIS);
     o.n_selected = reinterpret_cast<unsigned long long *>(n_selected);
     o.shjac = jac ? P<float4>(c, B_SHJAC) : nullptr;
     tm.begin(FLOD_STAGE_PREPROCESS);
@@ -401,56 +402,55 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     tm.begin(FLOD_STAGE_DEPTH_SORT);
     uint32_t *dk[2] = {P<uint32_t>(c, B_DKEY0), P<uint32_t>(c, B_DKEY1)};
     uint32_t *dv[2] = {P<uint32_t>(c, B_DVAL0), P<uint32_t>(c, B_DVAL1)};
-    // the first pass reads every candidate's depth key and keeps the rendered ones (the
-    // compaction of the visible set; their count goes to counters[kCntVisible]); the last pass
-    // also writes the tile counts in depth order and their sums per workgroup of the emission
-    // (zeroed by the preprocess)
-    sorted_tiles = P<uint32_t>(c, B_STILES);
+    const int64_t no_cap = 0xFFFFFFFEll;
+    const DepthSort ds{o.depth, o.rect, P<uint2>(c, B_SRECT), o.block_sums, o.block_sums + nb,
+                       totals(speculate ? cap : no_cap, speculate ? cap_p : no_cap, direct)};
     if (launch_radix_sort(dk, dv, counters + kCntVisible, N, 32, P<uint32_t>(c, B_HIST), P<uint32_t>(c, B_SCAN),
-                          P<uint32_t>(c, B_TOT), &dres, s, o.tiles, sorted_tiles, P<uint32_t>(c, B_TBSUM),
-                          o.depth) != hipSuccess)
+                          P<uint32_t>(c, B_TOT), &dres, s, &ds) != hipSuccess)
       return FLOD_ERR_DEVICE;
-    tm.end();
-    tm.begin(FLOD_STAGE_OFFSETS);
-    if (offsets(speculate ? cap : 0xFFFFFFFEll, direct) != hipSuccess) return FLOD_ERR_DEVICE;
-    // the count read-back, [visible u32 | guarded K u32], [K u64]: written by the scan itself
-    // (direct), else copied
-    if (!direct && (hipMemcpyAsync(c->host_counters, counters, 16, hipMemcpyDeviceToHost, s) != hipSuccess ||
+    // the count read-back: written by the totals themselves (direct), else copied
+    if (!direct && (hipMemcpyAsync(c->host_counters, counters, 24, hipMemcpyDeviceToHost, s) != hipSuccess ||
                     mark_stream(c, s) != hipSuccess))
       return FLOD_ERR_DEVICE;
     tm.end();
   }
-  int tres = 0;
-  // emission, tile sort, ranges and blend for at most k_max instances
-  auto tail = [&](int64_t k_max) -> flod_status {
-    uint32_t *tk[2] = {P<uint32_t>(c, B_TKEY0), P<uint32_t>(c, B_TKEY1)};
-    uint32_t *tv[2] = {P<uint32_t>(c, B_TVAL0), P<uint32_t>(c, B_TVAL1)};
-    tres = 0;
-    if (k_max > 0) {
-      uint32_t *dv = dres ? P<uint32_t>(c, B_DVAL1) : P<uint32_t>(c, B_DVAL0);
-      tm.begin(FLOD_STAGE_EMIT);
-      if (launch_emit(dv, counters + kCntVisible, counters + kCntInstances, N, k_max, sorted_tiles, P<float4>(c, B_BIN),
-                      P<unsigned long long>(c, B_TPREFIX), cam.tiles_x, cam.tiles_y, tk[0], tv[0],
-                      P<uint2>(c, B_RANGES), s) != hipSuccess)
+  // the tile lists of at most what the buffers hold, and the blend
+  auto tail = [&]() -> flod_status {
+    uint32_t *ids = dres ? P<uint32_t>(c, B_DVAL1) : P<uint32_t>(c, B_DVAL0);
+    uint32_t *hist_a = P<uint32_t>(c, B_HIST), *scan_a = P<uint32_t>(c, B_SCAN), *tot = P<uint32_t>(c, B_TOT);
+    uint32_t *tile_len = P<uint32_t>(c, B_TILE_LEN), *order = P<uint32_t>(c, B_TILE_ORDER);
+    const int64_t max_chunks = chunk_capacity(cam, cap_p);
+    if (N > 0) {
+      tm.begin(FLOD_STAGE_OFFSETS);
+      if (launch_pair_offsets(ids, counters, P<uint2>(c, B_SRECT), P<float4>(c, B_BIN), cam, N, hist_a, scan_a, tot,
+                              s) != hipSuccess)
         return FLOD_ERR_DEVICE;
       tm.end();
       tm.begin(FLOD_STAGE_TILE_SORT);
-      const int bits = ceil_log2(n_tiles);
-      if (bits > 0 && launch_radix_sort(tk, tv, counters + kCntInstances, k_max, bits, P<uint32_t>(c, B_HIST),
-                                        P<uint32_t>(c, B_SCAN), P<uint32_t>(c, B_TOT), &tres, s) != hipSuccess)
+      if (launch_pair_place(ids, counters, P<uint2>(c, B_SRECT), P<float4>(c, B_BIN), cam, N, scan_a, tot,
+                            P<uint32_t>(c, B_PAIR_ID), P<unsigned long long>(c, B_PAIR_MASK), P<uint4>(c, B_CHUNKS),
+                            P<uint2>(c, B_SUPERS), s) != hipSuccess ||
+          launch_chunk_counts(counters, P<uint4>(c, B_CHUNKS), P<unsigned long long>(c, B_PAIR_MASK),
+                              P<uint2>(c, B_SUPERS), cam, max_chunks, P<uint32_t>(c, B_CHUNK_CNT), tile_len, s) !=
+              hipSuccess)
+        return FLOD_ERR_DEVICE;
+      tm.end();
+    } else if (launch_fill_u32(tile_len, 0u, n_tiles, s) != hipSuccess) {
+      return FLOD_ERR_DEVICE;
+    }
+    tm.begin(FLOD_STAGE_RANGES);
+    if (launch_tile_starts(tile_len, n_tiles, P<uint2>(c, B_RANGES), order, s) != hipSuccess) return FLOD_ERR_DEVICE;
+    tm.end();
+    if (N > 0) {
+      tm.begin(FLOD_STAGE_EMIT);
+      if (launch_chunk_expand(counters, P<uint4>(c, B_CHUNKS), P<uint32_t>(c, B_PAIR_ID),
+                              P<unsigned long long>(c, B_PAIR_MASK), P<uint32_t>(c, B_CHUNK_CNT), P<uint2>(c, B_RANGES),
+                              cam, max_chunks, P<uint32_t>(c, B_VALUES), s) != hipSuccess)
         return FLOD_ERR_DEVICE;
       tm.end();
     }
-    tm.begin(FLOD_STAGE_RANGES);
-    // the emission zeroed the ranges when it ran
-    if (launch_ranges(tk[tres], counters + kCntInstances, k_max, n_tiles, P<uint2>(c, B_RANGES), k_max > 0, s) !=
-        hipSuccess)
-      return FLOD_ERR_DEVICE;
-    tm.end();
     tm.begin(FLOD_STAGE_BLEND);
-    uint32_t *order = P<uint32_t>(c, B_TILE_ORDER);
-    if (launch_tile_order_by_length(P<uint2>(c, B_RANGES), n_tiles, order, s) != hipSuccess ||
-        launch_blend(P<uint2>(c, B_RANGES), tv[tres], P<float4>(c, B_XYAB), P<float4>(c, B_COP),
+    if (launch_blend(P<uint2>(c, B_RANGES), P<uint32_t>(c, B_VALUES), P<float4>(c, B_XYAB), P<float4>(c, B_COP),
                      P<float2>(c, B_BLUE), cam, bg, out->image, out->final_T, out->n_contrib, out->n_blended,
                      c->keep_backward ? P<uint2>(c, B_BLENDED) : nullptr,
                      c->keep_backward ? P<uint32_t>(c, B_TILE_BLENDED) : nullptr, order, s) != hipSuccess)
@@ -458,19 +458,21 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     tm.end();
     return FLOD_OK;
   };
-  if (speculate && (st = tail(cap)) != FLOD_OK) return st;
+  if (speculate && (st = tail()) != FLOD_OK) return st;
   int64_t n_vis = 0;
-  unsigned long long K = 0;
+  unsigned long long K = 0, n_pairs = 0;
   if (N > 0) {
     if (direct) {
       if (wait_counts(c, s, seq) != hipSuccess) return FLOD_ERR_DEVICE;
       const volatile unsigned long long *w = c->host_counts;
       n_vis = (uint32_t)w[0];
-      K = (unsigned long long)(uint32_t)w[2] | ((unsigned long long)(uint32_t)w[3] << 32);
+      K = (unsigned long long)(uint32_t)w[1] | ((unsigned long long)(uint32_t)w[2] << 32);
+      n_pairs = (unsigned long long)(uint32_t)w[3] | ((unsigned long long)(uint32_t)w[4] << 32);
     } else {
       if (wait_marked(c) != hipSuccess) return FLOD_ERR_DEVICE;
       n_vis = reinterpret_cast<const uint32_t *>(c->host_counters)[kCntVisible];
-      K = c->host_counters[1];
+      K = c->host_counters[kCntTotal64 / 2];
+      n_pairs = c->host_counters[kCntPairs64 / 2];
     }
   }
   c->stats.n_candidates = N;
@@ -480,27 +482,29 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   c->stats.tiles_y = cam.tiles_y;
   c->stats.width = cam.W;
   c->stats.height = cam.H;
-  if (K >= 0xFFFFFFFFull) return FLOD_ERR_OVERFLOW;
-  if (!speculate || (int64_t)K > cap) {
-    if ((int64_t)K > cap) {
-      const int64_t Kn = (int64_t)K;
-      need(B_TKEY0, 4 * (size_t)Kn);
-      need(B_TKEY1, 4 * (size_t)Kn);
-      need(B_TVAL0, 4 * (size_t)Kn);
-      need(B_TVAL1, 4 * (size_t)Kn);
-      if (c->keep_backward) need(B_BLENDED, 8 * (size_t)Kn);
+  if (K >= 0xFFFFFFFFull || n_pairs >= 0xFFFFFFFFull) return FLOD_ERR_OVERFLOW;
+  if (!speculate || (int64_t)K > cap || (int64_t)n_pairs > cap_p) {
+    if ((int64_t)K > cap || (int64_t)n_pairs > cap_p) {
+      if ((int64_t)K > cap) {
+        need(B_VALUES, 4 * (size_t)K);
+        if (c->keep_backward) need(B_BLENDED, 8 * (size_t)K);
+      }
+      if ((int64_t)n_pairs > cap_p) {
+        need(B_PAIR_ID, 4 * (size_t)n_pairs);
+        need(B_PAIR_MASK, 8 * (size_t)n_pairs);
+      }
       if (st == FLOD_OK) {
         cap = instance_capacity(c);
-        need(B_HIST, hist_bytes(cap));
-        need(B_SCAN, hist_bytes(cap));
+        cap_p = pair_capacity(c);
+        need_chunks();
       }
       if (st != FLOD_OK) {
         c->required = ws_bytes(c) + extra;
         return st;
       }
-      if (speculate && offsets(cap, false) != hipSuccess) return FLOD_ERR_DEVICE;
+      if (speculate && launch_frame_totals(totals(cap, cap_p, false), s) != hipSuccess) return FLOD_ERR_DEVICE;
     }
-    if ((st = tail(N > 0 ? cap : 0)) != FLOD_OK) return st;
+    if ((st = tail()) != FLOD_OK) return st;
   }
   Saved &sv = c->saved;
   sv.valid = true;
@@ -508,9 +512,6 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   sv.bg[0] = bg[0]; sv.bg[1] = bg[1]; sv.bg[2] = bg[2];
   sv.final_T = out->final_T;
   sv.n_contrib = out->n_contrib;
-  sv.sorted_vals = tres;
-  sv.sorted_keys = tres;
-  sv.depth_buf = dres;
   sv.sh_degree = p.sh_degree;
   sv.has_blended = c->keep_backward;
   return FLOD_OK;
@@ -740,8 +741,8 @@ flod_status compact_pass(flod_ctx *ctx, int64_t n, hipStream_t s, CountFn count,
   }
   uint32_t *counters = P<uint32_t>(ctx, B_COUNTERS);
   if (count(P<uint32_t>(ctx, B_BLOCKVIS)) != hipSuccess ||
-      launch_scan_blocks(P<uint32_t>(ctx, B_BLOCKVIS), nullptr, kBlock, P<unsigned long long>(ctx, B_PREFIX),
-                         counters + kCntVisible, nullptr, nb, s) != hipSuccess ||
+      launch_scan_blocks(P<uint32_t>(ctx, B_BLOCKVIS), P<unsigned long long>(ctx, B_PREFIX), counters + kCntVisible, nb,
+                         s) != hipSuccess ||
       hipMemcpyAsync(ctx->host_counters, counters, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return FLOD_ERR_DEVICE;
@@ -875,7 +876,7 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
         launch_radix_sort(dk, dv, counters + kCntVisible, n, bits, P<uint32_t>(ctx, B_HIST),
                           P<uint32_t>(ctx, B_SCAN), P<uint32_t>(ctx, B_TOT), &res, s) != hipSuccess ||
         launch_prune_gather(level->means, dv[res], n, P<float4>(ctx, B_XYAB), s) != hipSuccess ||
-        launch_ranges(dk[res], counters + kCntVisible, n, (int)buckets, P<uint2>(ctx, B_RANGES), false, s) !=
+        launch_ranges(dk[res], counters + kCntVisible, n, (int)buckets, P<uint2>(ctx, B_RANGES), s) !=
             hipSuccess ||
         launch_prune_cost(pts, ranges, n, d_op, reinterpret_cast<unsigned long long *>(counters + kCntTotal64),
                           s) != hipSuccess ||
@@ -1089,8 +1090,22 @@ flod_status flod_ctx_view(const flod_ctx *ctx, flod_view *out) {
   const Saved &sv = ctx->saved;
   memset(out, 0, sizeof(*out));
   if (!sv.valid) return FLOD_ERR_UNSUPPORTED;
-  out->tile_ids = sv.sorted_keys ? P<uint32_t>(c, B_TKEY1) : P<uint32_t>(c, B_TKEY0);
-  out->values = sv.sorted_vals ? P<uint32_t>(c, B_TVAL1) : P<uint32_t>(c, B_TVAL0);
+  if (!sv.has_tile_ids) {
+    // the list holds no tile ids: the first view after a render writes them from the ranges
+    size_t extra = 0;
+    if (hipSetDevice(ctx->device) != hipSuccess) return FLOD_ERR_DEVICE;
+    if (ensure(c, B_TILE_IDS, 4 * (size_t)c->stats.n_instances, c->last_stream, &extra) != FLOD_OK) {
+      c->required = ws_bytes(c) + extra;
+      return FLOD_ERR_WORKSPACE;
+    }
+    if (launch_tile_ids(P<uint2>(c, B_RANGES), sv.cam.tiles_x * sv.cam.tiles_y, P<uint32_t>(c, B_TILE_IDS),
+                        c->last_stream) != hipSuccess ||
+        hipStreamSynchronize(c->last_stream) != hipSuccess)
+      return FLOD_ERR_DEVICE;
+    c->saved.has_tile_ids = true;
+  }
+  out->tile_ids = P<uint32_t>(c, B_TILE_IDS);
+  out->values = P<uint32_t>(c, B_VALUES);
   out->ranges = P<uint32_t>(c, B_RANGES);
   out->depth_bits = P<uint32_t>(c, B_DEPTH);
   out->bin = P<float>(c, B_BIN);

@@ -18,6 +18,15 @@ constexpr int kSortItemsSmall = 8;        // 2048-key workgroups for sorts below
 constexpr int64_t kRadixBigSort = 4 << 20;
 constexpr int kSortItemsHuge = 16;        // 4096-key workgroups for sorts of kRadixHugeSort keys or more
 constexpr int64_t kRadixHugeSort = 32 << 20;
+constexpr int kSuper = 8;                 // a supertile is kSuper x kSuper tiles (one bit each of a 64-bit mask)
+constexpr int kSuperWindow = 512;         // supertiles counted in LDS at once
+constexpr int kPairBlock = 256;           // depth-sorted Gaussians per workgroup of the pair kernels
+constexpr int kChunk = 256;               // pairs of one supertile expanded by one workgroup
+constexpr int kPairRectMax = 16;          // largest rectangle (in supertiles) listed whole
+// A Gaussian's tile rectangle as the binning reads it: x0 | y0 << 16 and x1 | y1 << 16 with two
+// flags: the footprint is the whole rectangle; its supertiles are listed row by row (see
+// pairs_of_rect) instead of the whole rectangle's.
+constexpr uint32_t kRectFull = 1u << 31, kRectBanded = 1u << 30;
 constexpr size_t kGaussianBytes = (3 + 3 + 4 + 1 + FLOD_SH_COEFFS * 3) * 4;   // 236 B per stored Gaussian
 constexpr unsigned long long kPruneMaxScan = 1ull << 36;   // overlap-pruning neighbour-scan limit
 
@@ -70,8 +79,8 @@ struct PreOut {
   float4 *bin;        // binning record, two per candidate: (mu'x, mu'y, conic a, conic b) and
                       // (conic c, support bound Q_g, bits of x0 | y0 << 16, bits of x1 | y1 << 16)
   uint32_t *tiles;    // tiles touched, 0 when culled or not selected
-  uint32_t *block_vis;  // per-workgroup count of visible candidates
-  uint32_t *zero_sums;  // one word per workgroup, zeroed (the depth sort's tile-count sums; may be null)
+  uint2 *rect;        // tile rectangle and flags of rendered candidates (kRectFull, kRectBanded)
+  uint4 *block_sums;  // per workgroup: visible candidates, tiles and (supertile, Gaussian) pairs
   unsigned long long *n_selected;   // per-level selected counts (may be null)
   float4 *shjac;      // three planes of n_total float4, per visible candidate the colour's Jacobian in
                       // the unit view direction, J[ch][a] row-major, then the three colours before the
@@ -102,37 +111,144 @@ struct AdamArgs {
 // Counters in device memory (one small array per context).
 enum : int {
   kCntVisible = 0,      // u32 count of visible candidates
-  kCntInstances = 1,    // u32 count of instances; 0 when it exceeds the instance buffers
-  kCntTotal64 = 2,      // u64 scratch for totals (two u32 slots: 2, 3)
+  kCntTotal64 = 2,      // u64 count of instances (or other totals; two u32 slots: 2, 3)
+  kCntPairs64 = 4,      // u64 count of (supertile, Gaussian) pairs (slots 4, 5)
+  kCntPairs = 6,        // u32 count of pairs; 0 when instances or pairs exceed their buffers
+  kCntChunks = 7,       // u32 count of chunks of pairs
   kCntSlots = 8
 };
 
+// Sums of the preprocess's per-workgroup counts, taken by one workgroup of kBlock threads:
+// visible candidates, instances K and pairs P, to the device counters and, when host_out is
+// given (coherent host memory), to the host. kCntPairs receives P when K <= cap_k and
+// P <= cap_p and 0 otherwise: kernels sized for those capacities read it and then do nothing.
+// host_out receives five 64-bit words, each host_seq in its high half and in its low half the
+// visible count and the low and high halves of K and of P: system-scope stores of whole words,
+// so a host that polls them sees every word either old or complete and needs neither a copy
+// nor an event.
+struct FrameTotals {
+  const uint4 *sums;
+  int nb;
+  uint32_t *counters;
+  unsigned long long cap_k, cap_p;
+  unsigned long long *host_out;
+  uint32_t host_seq;
+};
+
+__device__ __forceinline__ void frame_totals(const FrameTotals &t) {
+  constexpr int U = 8, W = kBlock / 64;
+  __shared__ unsigned long long s_sum[3][W];
+  unsigned long long v = 0, k = 0, p = 0;
+  for (int i0 = threadIdx.x; i0 < t.nb; i0 += kBlock * U) {
+    uint4 x[U];   // loaded together
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * kBlock;
+      x[u] = i < t.nb ? t.sums[i] : make_uint4(0u, 0u, 0u, 0u);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v += x[u].x;
+      k += x[u].y;
+      p += x[u].z;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    v += __shfl_xor(v, o, 64);
+    k += __shfl_xor(k, o, 64);
+    p += __shfl_xor(p, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    s_sum[0][threadIdx.x >> 6] = v;
+    s_sum[1][threadIdx.x >> 6] = k;
+    s_sum[2][threadIdx.x >> 6] = p;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  v = k = p = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    v += s_sum[0][w];
+    k += s_sum[1][w];
+    p += s_sum[2][w];
+  }
+  t.counters[kCntVisible] = (uint32_t)v;
+  *reinterpret_cast<unsigned long long *>(t.counters + kCntTotal64) = k;
+  *reinterpret_cast<unsigned long long *>(t.counters + kCntPairs64) = p;
+  t.counters[kCntPairs] = k <= t.cap_k && p <= t.cap_p ? (uint32_t)p : 0u;
+  if (t.host_out) {
+    const unsigned long long tag = (unsigned long long)t.host_seq << 32;
+    const unsigned long long w[5] = {tag | v, tag | (k & 0xFFFFFFFFull), tag | (k >> 32), tag | (p & 0xFFFFFFFFull),
+                                     tag | (p >> 32)};
+#pragma unroll
+    for (int i = 0; i < 5; ++i) __hip_atomic_store(&t.host_out[i], w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+// Block of a workgroup: workgroups go to the 8 XCDs round-robin, and each XCD takes runs of
+// kXcdRun consecutive blocks. What adjacent blocks write then shares cache lines inside one
+// XCD's L2 and moves as whole lines (spread over the 8 XCDs, the radix histograms went out as 8
+// partial writes of every line: 8x their bytes).
+constexpr uint32_t kXcdRun = 16;
+
+__device__ __forceinline__ uint32_t xcd_block(uint32_t wg) {
+  const uint32_t x = wg % 8u, j = wg / 8u;
+  return (j / kXcdRun) * (8u * kXcdRun) + x * kXcdRun + (j % kXcdRun);
+}
+
+inline unsigned xcd_grid(int64_t blocks) {
+  const int64_t g = 8 * (int64_t)kXcdRun;
+  return (unsigned)(((blocks + g - 1) / g) * g);
+}
+
 // ---- launches (each file defines its own) ----
 hipError_t launch_preprocess(const PreParams &p, const PreOut &o, hipStream_t s);
-hipError_t launch_scan_blocks(const uint32_t *in, const uint32_t *n_items, int items_per_block,
-                              unsigned long long *prefix, uint32_t *total32,
-                              unsigned long long *total64, int max_blocks, hipStream_t s,
-                              unsigned long long cap32 = 0xFFFFFFFFull, unsigned long long *host_out = nullptr,
-                              uint32_t host_seq = 0);
+hipError_t launch_scan_blocks(const uint32_t *in, unsigned long long *prefix, uint32_t *total, int blocks,
+                              hipStream_t s);
 int radix_items(int64_t n_max);        // keys per thread the radix sort of n_max keys uses
 size_t radix_hist_bytes(int64_t n_max);  // bytes of each of its hist and scan arrays
-// With tiles_of (tile count per value), the last pass also writes tiles_out[pos] =
-// tiles_of[sorted value] and adds the counts into block_sum[pos / 256] (zeroed beforehand).
-// With first_keys, the first pass reads first_keys[0, n_max) instead of keys[0] and vals[0],
-// takes each key's index as its value and skips keys equal to kDepthNone; it writes the count
-// it kept to *n_ptr, which the later passes read.
+// The render's depth sort: the first pass reads keys[0, n_max) of every candidate, takes each
+// key's index as its value and skips keys equal to kDepthNone (it writes the count it kept to
+// *n_ptr, which the later passes read), its digit scan also takes the frame's totals, and the
+// last pass also writes rect_out[pos] = rect_of[sorted value].
+struct DepthSort {
+  const uint32_t *keys;
+  const uint2 *rect_of;
+  uint2 *rect_out;
+  const uint4 *sums;      // the preprocess's counts per workgroup
+  uint4 *part;            // as many words of scratch: their sums per sort workgroup
+  FrameTotals totals;     // its sums and nb are set to part's
+};
 hipError_t launch_radix_sort(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_ptr,
                              int64_t n_max, int bits, uint32_t *hist, uint32_t *scan,
-                             uint32_t *tot, int *result_buf, hipStream_t s, const uint32_t *tiles_of = nullptr,
-                             uint32_t *tiles_out = nullptr, uint32_t *block_sum = nullptr,
-                             const uint32_t *first_keys = nullptr);
-hipError_t launch_emit(const uint32_t *sorted_ids, const uint32_t *n_ptr, const uint32_t *k_ptr,
-                       int64_t n_max, int64_t k_max, const uint32_t *sorted_tiles, const float4 *bin,
-                       const unsigned long long *prefix, int tiles_x, int tiles_y, uint32_t *tile_ids,
-                       uint32_t *values, uint2 *ranges, hipStream_t s);   // also zeroes ranges
-// zeroed: ranges already zeroed (by the emission); otherwise zeroed here first
-hipError_t launch_ranges(const uint32_t *tile_ids, const uint32_t *k_ptr, int64_t k_max, int n_tiles,
-                         uint2 *ranges, bool zeroed, hipStream_t s);
+                             uint32_t *tot, int *result_buf, hipStream_t s, const DepthSort *depth = nullptr);
+// Exclusive prefix of each of `rows` rows of ceil(*n_ptr / tile) counts, and the rows' sums.
+hipError_t launch_row_scan(const uint32_t *n_ptr, const uint32_t *hist, uint32_t *scan, uint32_t *tot, int rows,
+                           int stride, int tile, hipStream_t s);
+// Binning through supertiles (tilebin.hip)
+int super_count(const DevCamera &cam);
+size_t pair_hist_bytes(const DevCamera &cam, int64_t n);       // bytes of its hist and scan arrays
+int64_t chunk_capacity(const DevCamera &cam, int64_t pairs);   // the most chunks that many pairs make
+hipError_t launch_pair_offsets(const uint32_t *ids, const uint32_t *counters, const uint2 *srect, const float4 *bin,
+                               const DevCamera &cam, int64_t n, uint32_t *hist, uint32_t *scan, uint32_t *tot,
+                               hipStream_t s);
+hipError_t launch_pair_place(const uint32_t *ids, uint32_t *counters, const uint2 *srect, const float4 *bin,
+                             const DevCamera &cam, int64_t n, const uint32_t *scan, const uint32_t *tot,
+                             uint32_t *pair_id, unsigned long long *pair_mask, uint4 *chunks, uint2 *supers,
+                             hipStream_t s);
+hipError_t launch_chunk_counts(const uint32_t *counters, const uint4 *chunks, const unsigned long long *pair_mask,
+                               const uint2 *supers, const DevCamera &cam, int64_t max_chunks, uint32_t *cnt,
+                               uint32_t *tile_len, hipStream_t s);
+hipError_t launch_tile_starts(const uint32_t *tile_len, int n_tiles, uint2 *ranges, uint32_t *order, hipStream_t s);
+hipError_t launch_chunk_expand(const uint32_t *counters, const uint4 *chunks, const uint32_t *pair_id,
+                               const unsigned long long *pair_mask, const uint32_t *prefix, const uint2 *ranges,
+                               const DevCamera &cam, int64_t max_chunks, uint32_t *values, hipStream_t s);
+hipError_t launch_frame_totals(const FrameTotals &t, hipStream_t s);
+hipError_t launch_tile_ids(const uint2 *ranges, int n_tiles, uint32_t *tile_ids, hipStream_t s);
+// [start, end) of every bucket in the sorted ids (ranges zeroed here first)
+hipError_t launch_ranges(const uint32_t *ids, const uint32_t *k_ptr, int64_t k_max, int n_ranges, uint2 *ranges,
+                         hipStream_t s);
 // blended: per tile, the (list position, Gaussian) pairs of the entries the forward blended
 // into some pixel, in list order at the start of the tile's range; tile_blended: their count
 // (both may be null: the render keeps no backward state)
@@ -151,7 +267,6 @@ hipError_t launch_blend_bwd(const uint2 *ranges, const float4 *xyab, const float
                             hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // the most blocks the backward's split tiles add beyond one per tile
 int bwd_split_extra(int n_tiles);
-hipError_t launch_tile_order_by_length(const uint2 *ranges, int n_tiles, uint32_t *order, hipStream_t s);
 // The blend backward's per-Gaussian moment sums into dL/d(mu', conic) in place (inspection).
 hipError_t launch_g2d_from_moments(int64_t n, const uint32_t *tiles, const float4 *xyab, const float4 *cop,
                                    float *g2d, hipStream_t s);

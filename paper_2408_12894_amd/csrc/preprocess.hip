@@ -21,6 +21,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
   bool vis = false;
   bool selected = false;
   int lvl = 0;
+  uint32_t tiles = 0, pairs = 0;
   if (i < p.n_total) {
     lvl = level_of(p, i);
     const DevLevel L = level_at(p, lvl);
@@ -31,7 +32,6 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
       float d2 = dist2(m0, m1, m2, p.centre);
       selected = (L.lo2 <= d2) && (d2 < L.hi2);
     }
-    uint32_t tiles = 0;
     if (selected) {
       Proj pr;
       view_transform(p.cam, m0, m1, m2, pr);
@@ -46,6 +46,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
           const float ca = (float)pr.ca, cb = (float)pr.cb, cc = (float)pr.cc;
           Footprint fp;
           uint32_t rx0 = 0xFFFFu, rx1 = 0u;
+          uint32_t bx0 = 0xFFFFu, bx1 = 0u, band_pairs = 0u;   // the current supertile row's columns
           const float qg = support_q(logit);
           if (footprint(hx, hy, ca, cb, cc, support_span(qg), p.cam.tiles_y, fp)) {
             for (int ty = fp.ty0; ty <= fp.ty1; ++ty) {
@@ -54,6 +55,13 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
                 tiles += (uint32_t)(tx1 - tx0 + 1);
                 rx0 = min(rx0, (uint32_t)tx0);
                 rx1 = max(rx1, (uint32_t)tx1);
+                bx0 = min(bx0, (uint32_t)tx0);
+                bx1 = max(bx1, (uint32_t)tx1);
+              }
+              if ((ty % kSuper == kSuper - 1 || ty == fp.ty1) && bx0 <= bx1) {
+                band_pairs += bx1 / kSuper - bx0 / kSuper + 1u;
+                bx0 = 0xFFFFu;
+                bx1 = 0u;
               }
             }
           }
@@ -120,8 +128,15 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
             o.blue[i] = make_float2(col[2], __uint_as_float(pack_mu_lo(pr.mx, pr.my, hx, hy)));
             o.depth[i] = __float_as_uint((float)pr.tz);
             o.bin[2 * i] = make_float4(hx, hy, ca, cb);
-            o.bin[2 * i + 1] = make_float4(cc, qg, __uint_as_float(rx0 | ((uint32_t)fp.ty0 << 16)),
-                                           __uint_as_float(rx1 | ((uint32_t)fp.ty1 << 16)));
+            const uint32_t r0 = rx0 | ((uint32_t)fp.ty0 << 16), r1 = rx1 | ((uint32_t)fp.ty1 << 16);
+            o.bin[2 * i + 1] = make_float4(cc, qg, __uint_as_float(r0), __uint_as_float(r1));
+            // the supertiles it will be listed in: the whole rectangle's while those are few,
+            // else row by row (a long diagonal footprint misses most of its rectangle)
+            const uint32_t w = rx1 - rx0 + 1u, h = (uint32_t)(fp.ty1 - fp.ty0 + 1);
+            pairs = (rx1 / kSuper - rx0 / kSuper + 1u) * (uint32_t)(fp.ty1 / kSuper - fp.ty0 / kSuper + 1);
+            const bool banded = pairs > (uint32_t)kPairRectMax;
+            if (banded) pairs = band_pairs;
+            o.rect[i] = make_uint2(r0, r1 | (w * h == tiles ? kRectFull : 0u) | (banded ? kRectBanded : 0u));
           }
         }
       }
@@ -129,7 +144,6 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
     o.tiles[i] = tiles;
     if (!vis) o.depth[i] = kDepthNone;   // the depth sort's first pass skips it
   }
-  if (o.zero_sums && threadIdx.x == 0) o.zero_sums[blockIdx.x] = 0u;
   // per-level selected counts, aggregated per wave
   if (o.n_selected) {
     const int lane = threadIdx.x & 63;
@@ -138,8 +152,28 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
       if (lane == 0 && m) atomicAdd(&o.n_selected[k], (unsigned long long)__popcll(m));
     }
   }
-  int cnt = __syncthreads_count(vis);
-  if (threadIdx.x == 0) o.block_vis[blockIdx.x] = (uint32_t)cnt;
+  // the workgroup's counts of visible candidates, tiles and pairs
+  __shared__ uint32_t s_sum[3][kBlock / 64];
+  const uint32_t cnt = (uint32_t)__popcll(__ballot(vis));
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    tiles += __shfl_xor(tiles, d, 64);
+    pairs += __shfl_xor(pairs, d, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    s_sum[0][threadIdx.x >> 6] = cnt;
+    s_sum[1][threadIdx.x >> 6] = tiles;
+    s_sum[2][threadIdx.x >> 6] = pairs;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t t[3] = {0u, 0u, 0u};
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int w = 0; w < kBlock / 64; ++w) t[k] += s_sum[k][w];
+    o.block_sums[blockIdx.x] = make_uint4(t[0], t[1], t[2], 0u);
+  }
 }
 
 hipError_t launch_preprocess(const PreParams &p, const PreOut &o, hipStream_t s) {

@@ -1,0 +1,70 @@
+"""The tile lists against the oracle's sorted instance list, bit-exact, where the binning through
+supertiles (8 x 8 tiles, pairs in workgroups of 256 Gaussians and chunks of 256) has its edges:
+frames around a tile, a supertile and a window of 512 supertiles, Gaussian counts around a
+workgroup, footprints from one tile to whole frames and long diagonal ones, and buffers that
+must grow for instances or for pairs alone."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2408_12894_amd import synth
+from parity import check_instances, check_keys
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _renderer():
+    from paper_2408_12894_amd import render
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return render.Renderer(0)
+
+
+def _needles(n, seed):
+    """Long thin Gaussians in every direction: footprints that miss most of their rectangle."""
+    sc = synth.uniform_scene(n, seed=seed, extent=0.8)
+    sc.log_scales[:] = np.float32(-6.0)
+    sc.log_scales[:, 0] = np.random.default_rng(seed).uniform(-2.0, 0.5, n).astype(np.float32)
+    sc.opacity_logits[:] = np.float32(2.0)
+    return sc
+
+
+SCENES = {
+    "specks": lambda n: synth.uniform_scene(n, seed=81, s_mu=-5.5, s_sigma=0.3, extent=1.5),
+    "mixed": lambda n: synth.uniform_scene(n, seed=82, s_mu=-3.0, s_sigma=1.0),
+    "blobs": lambda n: synth.uniform_scene(n, seed=83, s_mu=0.0, s_sigma=0.4, s_min=0.2),
+    "needles": lambda n: _needles(n, 84),
+}
+
+
+def _check(r, scene, w, h):
+    from paper_2408_12894_amd import render
+    cam = synth.look_at_camera((0.4, -0.2, -3.7), (0, 0, 0), w, h)
+    r.render_level(render.GaussianLevel.from_scene(scene), cam)
+    torch.cuda.synchronize()
+    view = r.view()
+    k = oracle.keys(*scene.arrays()[:4], scene.s_min, cam)
+    check_keys(view, k)
+    check_instances(view, k)
+    return view
+
+
+@pytest.mark.parametrize("kind,n,w,h", [
+    ("specks", 1, 16, 16), ("mixed", 255, 128, 128), ("mixed", 256, 129, 127), ("mixed", 257, 1, 300),
+    ("specks", 3000, 144, 272), ("blobs", 70, 1024, 528), ("needles", 300, 1920, 1080), ("mixed", 513, 2903, 2903),
+    ("needles", 130, 4096, 2304),
+])
+def test_lists_at_the_edges(kind, n, w, h):
+    print(f"[case] tile lists {kind} n={n} {w}x{h}", flush=True)
+    _check(_renderer(), SCENES[kind](n), w, h)
+
+
+def test_buffers_grow_for_instances_or_pairs_alone():
+    """Few whole-frame Gaussians (many instances, few pairs), then many specks (fewer instances,
+    more pairs), then both ways round on a context whose buffers hold neither."""
+    r = _renderer()
+    for kind, n in (("blobs", 12), ("specks", 20_000), ("blobs", 60), ("specks", 3000)):
+        print(f"[case] growing buffers {kind} n={n}", flush=True)
+        view = _check(r, SCENES[kind](n), 800, 608)
+        print(f"  K={view['stats']['n_instances']}", flush=True)
