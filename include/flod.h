@@ -180,8 +180,8 @@ flod_status flod_select_compact(flod_ctx *ctx, const flod_level *levels, int n_l
    removal changes another's neighbours). A level of fewer than four Gaussians keeps all.
    keep: device uint8[n], 1 = keep, 0 = remove. d_avg: device double[n] or NULL; receives
    d_avg exactly when the three nearest lie within 3 d_op (1 + 1e-9), +inf otherwise (such a
-   Gaussian is kept). n_keep: host, the number kept. Workspace about 44 B per Gaussian plus
-   8 B per hash bucket (2^ceil(log2 n) buckets). One host synchronisation (the count) and
+   Gaussian is kept). n_keep: host, the number kept. Workspace about 48 B per Gaussian plus
+   20 B per hash bucket (2^ceil(log2 n) buckets). One host synchronisation (the count) and
    one check of the neighbour-search size: when the means are so dense relative to d_op
    that the scan would exceed 2^36 distance evaluations, returns FLOD_ERR_UNSUPPORTED
    without writing keep. n <= 2^30. */

@@ -743,7 +743,7 @@ flod_status compact_pass(flod_ctx *ctx, int64_t n, hipStream_t s, CountFn count,
   if (count(P<uint32_t>(ctx, B_BLOCKVIS)) != hipSuccess ||
       launch_scan_blocks(P<uint32_t>(ctx, B_BLOCKVIS), P<unsigned long long>(ctx, B_PREFIX), counters + kCntVisible, nb,
                          s) != hipSuccess ||
-      hipMemcpyAsync(ctx->host_counters, counters, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipMemcpyAsync(ctx->host_counters, counters, 16, hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return FLOD_ERR_DEVICE;
   const int64_t kept = reinterpret_cast<const uint32_t *>(ctx->host_counters)[kCntVisible];
@@ -854,6 +854,9 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
     need(B_DVAL1, 4 * (size_t)n);
     need(B_XYAB, 16 * (size_t)n);
     need(B_RANGES, 8 * (size_t)buckets);
+    need(B_TILES, 4 * (size_t)n);          // the points around each
+    need(B_RECT, 4 * (size_t)buckets);     // the run table's tags
+    need(B_SRECT, 8 * (size_t)buckets);    // and runs
     need(B_HIST, radix_hist_bytes(n));
     need(B_SCAN, radix_hist_bytes(n));
     need(B_TOT, 4 * (size_t)kRadix);
@@ -865,7 +868,12 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
   }
   uint32_t *counters = P<uint32_t>(ctx, B_COUNTERS);
   const float4 *pts = P<float4>(ctx, B_XYAB);
-  const uint2 *ranges = P<uint2>(ctx, B_RANGES);
+  uint2 *ranges = P<uint2>(ctx, B_RANGES);
+  uint32_t *tags = P<uint32_t>(ctx, B_RECT);
+  uint2 *runs = P<uint2>(ctx, B_SRECT);
+  uint32_t *around = P<uint32_t>(ctx, B_TILES);
+  unsigned long long *cost = reinterpret_cast<unsigned long long *>(counters + kCntTotal64);
+  const int sub_bits = 3 * prune_levels(n);
   if (d_op > 0.0f) {
     uint32_t *dk[2] = {P<uint32_t>(ctx, B_DKEY0), P<uint32_t>(ctx, B_DKEY1)};
     uint32_t *dv[2] = {P<uint32_t>(ctx, B_DVAL0), P<uint32_t>(ctx, B_DVAL1)};
@@ -873,22 +881,25 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
     if (launch_fill_u32(counters + kCntVisible, (uint32_t)n, 1, s) != hipSuccess ||
         launch_fill_u32(counters + kCntTotal64, 0u, 2, s) != hipSuccess ||
         launch_prune_keys(level->means, n, d_op, dk[0], dv[0], s) != hipSuccess ||
-        launch_radix_sort(dk, dv, counters + kCntVisible, n, bits, P<uint32_t>(ctx, B_HIST),
+        launch_radix_sort(dk, dv, counters + kCntVisible, n, bits + sub_bits, P<uint32_t>(ctx, B_HIST),
                           P<uint32_t>(ctx, B_SCAN), P<uint32_t>(ctx, B_TOT), &res, s) != hipSuccess ||
         launch_prune_gather(level->means, dv[res], n, P<float4>(ctx, B_XYAB), s) != hipSuccess ||
-        launch_ranges(dk[res], counters + kCntVisible, n, (int)buckets, P<uint2>(ctx, B_RANGES), s) !=
-            hipSuccess ||
-        launch_prune_cost(pts, ranges, n, d_op, reinterpret_cast<unsigned long long *>(counters + kCntTotal64),
-                          s) != hipSuccess ||
-        hipMemcpyAsync(ctx->host_counters, counters, 16, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
+        launch_ranges(dk[res], sub_bits, counters + kCntVisible, n, (int)buckets, ranges, s) != hipSuccess ||
+        launch_prune_runs(dk[res], ranges, n, d_op, tags, runs, s) != hipSuccess ||
+        launch_prune_cost(pts, ranges, n, d_op, around, cost, s) != hipSuccess)
       return FLOD_ERR_DEVICE;
-    if (ctx->host_counters[1] > kPruneMaxScan) return FLOD_ERR_UNSUPPORTED;
   }
-  if (launch_prune_query(pts, ranges, n, d_op, keep, d_avg, s) != hipSuccess) return FLOD_ERR_DEVICE;
+  // the device refuses a scan beyond the limit (nothing is written); the host learns of it with
+  // the kept count
+  if (launch_prune_query(pts, ranges, tags, runs, around, n, d_op, cost, keep, d_avg, s) != hipSuccess) return FLOD_ERR_DEVICE;
   auto count = [&](uint32_t *bc) { return launch_mask_count(keep, n, bc, s); };
   auto no_copy = [&](const unsigned long long *, const flod_level &) { return hipSuccess; };
-  return compact_pass(ctx, n, s, count, no_copy, nullptr, level->s_min, n_keep);
+  st = compact_pass(ctx, n, s, count, no_copy, nullptr, level->s_min, n_keep);
+  if (st == FLOD_OK && d_op > 0.0f && ctx->host_counters[kCntTotal64 / 2] > kPruneMaxScan) {
+    *n_keep = 0;
+    return FLOD_ERR_UNSUPPORTED;
+  }
+  return st;
 }
 
 flod_status flod_l1_ssim_forward(flod_ctx *ctx, const float *image, const float *target, int channels, int height,

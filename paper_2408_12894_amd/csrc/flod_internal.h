@@ -246,9 +246,9 @@ hipError_t launch_chunk_expand(const uint32_t *counters, const uint4 *chunks, co
                                const DevCamera &cam, int64_t max_chunks, uint32_t *values, hipStream_t s);
 hipError_t launch_frame_totals(const FrameTotals &t, hipStream_t s);
 hipError_t launch_tile_ids(const uint2 *ranges, int n_tiles, uint32_t *tile_ids, hipStream_t s);
-// [start, end) of every bucket in the sorted ids (ranges zeroed here first)
-hipError_t launch_ranges(const uint32_t *ids, const uint32_t *k_ptr, int64_t k_max, int n_ranges, uint2 *ranges,
-                         hipStream_t s);
+// [start, end) of every bucket (id >> shift) in the sorted ids (ranges zeroed here first)
+hipError_t launch_ranges(const uint32_t *ids, int shift, const uint32_t *k_ptr, int64_t k_max, int n_ranges,
+                         uint2 *ranges, hipStream_t s);
 // blended: per tile, the (list position, Gaussian) pairs of the entries the forward blended
 // into some pixel, in list order at the start of the tile's range; tile_blended: their count
 // (both may be null: the render keeps no backward state)
@@ -294,13 +294,19 @@ hipError_t launch_l1_forward(const float *x, const float *y, int64_t n, double *
 hipError_t launch_l1_backward(const float *x, const float *y, int64_t n, const double *dloss, float *dx,
                               hipStream_t s);
 int prune_table_bits(int64_t n);   // log2 of the overlap-pruning hash table size for n points
+int prune_levels(int64_t n);       // halvings of a cell its sort keys hold (3 bits each below the bucket)
 hipError_t launch_prune_keys(const float *means, int64_t n, float d_op, uint32_t *keys, uint32_t *vals,
                              hipStream_t s);
 hipError_t launch_prune_gather(const float *means, const uint32_t *sorted_vals, int64_t n, float4 *pts,
                                hipStream_t s);
-hipError_t launch_prune_cost(const float4 *pts, const uint2 *ranges, int64_t n, float d_op,
+// around: per point in key order, the points in the 27 buckets around it (itself included)
+hipError_t launch_prune_cost(const float4 *pts, const uint2 *ranges, int64_t n, float d_op, uint32_t *around,
                              unsigned long long *cost, hipStream_t s);
-hipError_t launch_prune_query(const float4 *pts, const uint2 *ranges, int64_t n, float d_op, uint8_t *keep,
-                              double *d_avg, hipStream_t s);
+// tags, runs: 2^prune_table_bits(n) slots each (tags zeroed here first)
+hipError_t launch_prune_runs(const uint32_t *keys, const uint2 *ranges, int64_t n, float d_op, uint32_t *tags,
+                             uint2 *runs, hipStream_t s);
+hipError_t launch_prune_query(const float4 *pts, const uint2 *ranges, const uint32_t *tags, const uint2 *runs,
+                              const uint32_t *around, int64_t n, float d_op, const unsigned long long *cost, uint8_t *keep, double *d_avg,
+                              hipStream_t s);
 
 }  // namespace flod

@@ -9,13 +9,20 @@
 //
 //   1. cell of each mean (FP64 floor of x / c, clamped to 21 bits per axis: a monotone map,
 //      so points closer than c along an axis stay in the same or adjacent cells), hashed to
-//      a table of T = 2^b >= n buckets (MurmurHash3's 64-bit finaliser, top b bits);
-//   2. stable radix sort of (bucket, index), then the means gathered into bucket order
-//      (16 B per point, index in the fourth word), and per-bucket [start, end);
-//   3. one thread per point, in bucket order so that a wave's threads read the same
-//      buckets: scan the 27 neighbour buckets, keep the three smallest squared distances
-//      (FP64, from the FP32 means, summed x, y, z), skipping itself and any point already
-//      kept (two neighbour cells can share a bucket);
+//      a table of T = 2^b >= n buckets (MurmurHash3's 64-bit finaliser, top b bits); below
+//      the bucket in the key, the Morton index of the point's subcell (3 bits for each of
+//      up to three halvings of the cell);
+//   2. stable radix sort of (key, index), then the means gathered into key order (16 B per
+//      point, index in the fourth word), and per-bucket [start, end). The points of a subcell
+//      of any level are then consecutive too: their runs go to an open-addressed table, for
+//      the buckets and levels that are searched by subcell;
+//   3. a point with fewer than three others in the 27 cells around its own is kept. The others
+//      are searched by whole waves (k_prune_query), each group of points sharing a subcell
+//      among the candidates of the finest level whose subcells hold about one point or more.
+//      Every point within a subcell's edge lies in the searched subcells, so when the third
+//      smallest distance found is below the edge the three are the true nearest; otherwise the
+//      next coarser level is searched, down to the 27 cells. Squared distances are FP64, from
+//      the FP32 means, summed x, y, z;
 //   4. d_avg = ((d_1 + d_2) + d_3) / 3 in FP64 when d_3 < R (then these are the true three
 //      nearest), +inf otherwise; keep = !(d_avg < d_op).
 // Distances, their order of summation and the comparison are the same FP64 operations a
@@ -30,7 +37,19 @@ constexpr double kCellHalf = (double)(1 << (kCellBits - 1));
 struct Grid {
   double inv_c;
   int shift;    // 64 - table bits
+  int bits;     // table bits
+  int levels;   // halvings of a cell the keys hold
 };
+
+// Halvings of a cell that fit the 32-bit keys and the run table's tags (one bit more).
+constexpr int kPruneLevels = 3;
+
+// A bucket of at least kSubcellMin[l - 1] points is searched by subcells of level l (the cell's
+// edge / 2^l): from 12, 96 and 768 points its subcells of level 1, 2, 3 hold 1.5 or more on
+// average and the sphere of their edge about six, so a first search mostly ends there.
+// Buckets below are scanned whole. Their runs number at most 0.8 n: a bucket of m points has at
+// most 8 runs of level 1 (m >= 12), 64 of level 2 (m >= 96) and 512 of level 3 (m >= 768).
+__device__ __forceinline__ uint32_t subcell_min(int level) { return 12u << (3 * (level - 1)); }
 
 __device__ __forceinline__ int32_t cell_of(float x, double inv_c) {
   double f = floor((double)x * inv_c);
@@ -52,14 +71,30 @@ __device__ __forceinline__ uint32_t bucket_of(int32_t ix, int32_t iy, int32_t iz
   return (uint32_t)(k >> shift);
 }
 
+// Fine coordinate (eight per cell): its upper bits are cell_of's cell, since scaling by 8 is
+// exact.
+__device__ __forceinline__ int32_t fine_of(float x, double inv_c) {
+  const double f = floor((double)x * inv_c * 8.0);
+  return (int32_t)fmin(fmax(f, -8.0 * kCellHalf), 8.0 * kCellHalf - 1.0);
+}
+
+// Morton index of a subcell of level l from the low bits of fine coordinates >> (3 - l).
+__device__ __forceinline__ uint32_t morton(uint32_t x, uint32_t y, uint32_t z, int l) {
+  uint32_t m = 0u;
+  for (int k = 0; k < l; ++k) m |= (((x >> k) & 1u) << (3 * k)) | (((y >> k) & 1u) << (3 * k + 1)) | (((z >> k) & 1u) << (3 * k + 2));
+  return m;
+}
+
 __global__ __launch_bounds__(kBlock) void k_prune_keys(const float *means, int64_t n, Grid g, uint32_t *keys,
                                                        uint32_t *vals) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
-  const int32_t ix = cell_of(means[i * 3 + 0], g.inv_c);
-  const int32_t iy = cell_of(means[i * 3 + 1], g.inv_c);
-  const int32_t iz = cell_of(means[i * 3 + 2], g.inv_c);
-  keys[i] = bucket_of(ix, iy, iz, g.shift);
+  const int32_t fx = fine_of(means[i * 3 + 0], g.inv_c);
+  const int32_t fy = fine_of(means[i * 3 + 1], g.inv_c);
+  const int32_t fz = fine_of(means[i * 3 + 2], g.inv_c);
+  const int d = kPruneLevels - g.levels;
+  keys[i] = (bucket_of(fx >> 3, fy >> 3, fz >> 3, g.shift) << (3 * g.levels)) |
+            morton((uint32_t)(fx & 7) >> d, (uint32_t)(fy & 7) >> d, (uint32_t)(fz & 7) >> d, g.levels);
   vals[i] = (uint32_t)i;
 }
 
@@ -72,50 +107,241 @@ __global__ __launch_bounds__(kBlock) void k_prune_gather(const float *means, con
                        __uint_as_float(j));
 }
 
-__global__ __launch_bounds__(kBlock) void k_prune_query(const float4 *__restrict__ pts, const uint2 *__restrict__ ranges,
-                                                        int64_t n, Grid g, double radius, double d_op,
-                                                        uint8_t *keep, double *d_avg) {
+// Run table: a run's tag is its key of bits + 3 l bits under a leading one, so the levels differ.
+// Its 2^bits slots, of which at most 0.8 n <= 0.8 2^bits are taken, are probed in groups of four
+// (one 16-byte load; slot by slot, a wave waited for the longest of its 64 probe sequences at
+// each of 27 subcells).
+__device__ __forceinline__ uint32_t run_group(uint32_t tag, int bits) { return (tag * 2654435769u) >> (34 - bits); }
+
+__device__ __forceinline__ uint32_t run_tag(uint32_t key, int level, const Grid &g) {
+  return (1u << (g.bits + 3 * level)) | (key >> (3 * (g.levels - level)));
+}
+
+// One thread per point in key order: the first and the last of a run find or take the run's
+// slot and write its start and end.
+__global__ __launch_bounds__(kBlock) void k_prune_runs(const uint32_t *__restrict__ keys,
+                                                       const uint2 *__restrict__ ranges, int64_t n, Grid g,
+                                                       uint32_t *__restrict__ tags, uint32_t *__restrict__ runs) {
   const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (p >= n) return;
-  const float4 a = pts[p];
-  const int32_t cx = cell_of(a.x, g.inv_c), cy = cell_of(a.y, g.inv_c), cz = cell_of(a.z, g.inv_c);
-  const double ax = a.x, ay = a.y, az = a.z;
-  double b0 = INFINITY, b1 = INFINITY, b2 = INFINITY;
-  uint32_t q0 = 0xFFFFFFFFu, q1 = 0xFFFFFFFFu, q2 = 0xFFFFFFFFu;
-  for (int dz = -1; dz <= 1; ++dz)
-    for (int dy = -1; dy <= 1; ++dy)
-      for (int dx = -1; dx <= 1; ++dx) {
-        const uint2 r = ranges[bucket_of(cx + dx, cy + dy, cz + dz, g.shift)];
-        for (uint32_t q = r.x; q < r.y; ++q) {
-          if (q == (uint32_t)p) continue;
-          const float4 b = pts[q];
-          const double ex = (double)b.x - ax, ey = (double)b.y - ay, ez = (double)b.z - az;
-          const double d2 = (ex * ex + ey * ey) + ez * ez;
-          if (!(d2 < b2) || q == q0 || q == q1 || q == q2) continue;
-          if (d2 < b1) {
-            b2 = b1; q2 = q1;
-            if (d2 < b0) {
-              b1 = b0; q1 = q0;
-              b0 = d2; q0 = q;
-            } else {
-              b1 = d2; q1 = q;
-            }
-          } else {
-            b2 = d2; q2 = q;
+  const uint32_t key = keys[p];
+  const uint32_t before = p > 0 ? keys[p - 1] : ~key, after = p + 1 < n ? keys[p + 1] : ~key;
+  const uint2 r = ranges[key >> (3 * g.levels)];
+  const uint32_t mask = (1u << (g.bits - 2)) - 1u;
+  for (int l = 1; l <= g.levels && r.y - r.x >= subcell_min(l); ++l) {
+    const int s = 3 * (g.levels - l);
+    const bool first = (before >> s) != (key >> s) || p == 0, last = (after >> s) != (key >> s) || p + 1 == n;
+    if (!first && !last) continue;
+    const uint32_t tag = run_tag(key, l, g);
+    uint32_t h = 4u * run_group(tag, g.bits);
+    for (;;) {
+      const uint32_t was = atomicCAS(&tags[h], 0u, tag);
+      if (was == 0u || was == tag) break;
+      h = (h & 3u) != 3u ? h + 1u : 4u * (((h >> 2) + 1u) & mask);
+    }
+    if (first) runs[2 * (size_t)h] = (uint32_t)p;
+    if (last) runs[2 * (size_t)h + 1] = (uint32_t)(p + 1);
+  }
+}
+
+// 64-bit value of a lane 1, 2, 4 or 8 further on in its row of 16 (cyclic).
+template <int N>
+__device__ __forceinline__ double row_ror64(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x120 + N, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), 0x120 + N, 0xF, 0xF, true);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+__device__ __forceinline__ double row_min16(double v) {
+  v = fmin(v, row_ror64<8>(v));
+  v = fmin(v, row_ror64<4>(v));
+  v = fmin(v, row_ror64<2>(v));
+  return fmin(v, row_ror64<1>(v));
+}
+
+constexpr int kPruneHold = 192;   // candidates held in LDS at once
+
+// One wave per `per` (at most 64) consecutive points in key order. The wave takes the points of one subcell after the other
+// (of the level above the searched one, so that one set of candidates serves them all): lane i
+// looks up the i-th of the 4 x 4 x 4 subcells around it (at level 0 the i-th of 27 cells), the
+// candidates are gathered into LDS, and each row of 16 lanes goes through them for one point,
+// every lane keeping the three smallest squared distances it meets; the row then draws the
+// three smallest of all. Points not settled there are searched again one level coarser.
+//
+// Why so: one thread per point, walking its own 27 places, left a wave waiting at every place
+// for its longest list and its slowest lookup (500k points at d_op 0.025, about 830 in the 27
+// cells around each: 1.35 ms, 0.73 with subcells; this kernel 0.34 ms, VALU busy 62%, 228
+// instructions per point).
+__global__ __launch_bounds__(64) void k_prune_query(const float4 *__restrict__ pts, const uint2 *__restrict__ ranges,
+                                                    const uint4 *__restrict__ tags, const uint2 *__restrict__ runs,
+                                                    const uint32_t *__restrict__ around, int64_t n, int per, Grid g,
+                                                    double radius, double d_op, const unsigned long long *cost,
+                                                    uint8_t *keep, double *d_avg) {
+  __shared__ double2 s_xy[kPruneHold];   // the candidates, converted once for all points
+  __shared__ double s_z[kPruneHold];
+  __shared__ uint32_t s_who[kPruneHold];
+  __shared__ double s_best[64][3];
+  __shared__ uint8_t s_lane[64];
+  __shared__ uint32_t s_seen[128];
+  if (*cost > kPruneMaxScan) return;   // refused: nothing is written
+  const int lane = threadIdx.x, l16 = lane & 15, row = lane >> 4;
+  const int64_t p = (int64_t)blockIdx.x * per + lane;
+  const bool valid = lane < per && p < n;
+  const float4 a = valid ? pts[p] : make_float4(0.f, 0.f, 0.f, 0.f);
+  const int fx = fine_of(a.x, g.inv_c), fy = fine_of(a.y, g.inv_c), fz = fine_of(a.z, g.inv_c);
+  int level = 0;   // the point's level: the finest its own bucket's count allows
+  bool pending = valid && around[p] > 3u;
+  if (pending) {
+    const uint2 own = ranges[bucket_of(fx >> 3, fy >> 3, fz >> 3, g.shift)];
+    while (level < g.levels && own.y - own.x >= subcell_min(level + 1)) ++level;
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) s_best[lane][k] = INFINITY;
+  const unsigned long long below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  const uint32_t mask = (1u << (g.bits - 2)) - 1u;
+  for (unsigned long long todo = __ballot(pending); todo; todo = __ballot(pending)) {
+    // the group: the pending points of the first one's subcell and level
+    const int src = __ffsll((long long)todo) - 1;
+    const int l = __builtin_amdgcn_readlane(level, src);
+    const int up = l > 0 ? kPruneLevels + 1 - l : kPruneLevels;   // fine coordinate >> up: the subcell
+    const int gx = __builtin_amdgcn_readlane(fx, src) >> up, gy = __builtin_amdgcn_readlane(fy, src) >> up,
+              gz = __builtin_amdgcn_readlane(fz, src) >> up;
+    const bool in = pending && level == l && fx >> up == gx && fy >> up == gy && fz >> up == gz;
+    const unsigned long long group = __ballot(in);
+    const int count = __popcll(group);
+    if (in) {
+      s_lane[__popcll(group & below)] = (uint8_t)lane;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) s_best[lane][k] = INFINITY;
+    }
+    // this lane's place and its run of points
+    uint2 run = make_uint2(0u, 0u);
+    if (l == 0) {
+      if (lane < 27)
+        run = ranges[bucket_of(gx + lane % 3 - 1, gy + (lane / 3) % 3 - 1, gz + lane / 9 - 1, g.shift)];
+    } else {
+      const int bx = 2 * gx - 1, by = 2 * gy - 1, bz = 2 * gz - 1;
+      const int x = bx + (lane & 3), y = by + ((lane >> 2) & 3), z = bz + (lane >> 4);
+      const uint32_t bucket = bucket_of(x >> l, y >> l, z >> l, g.shift);
+      const uint2 r = ranges[bucket];
+      // a bucket with fewer points has runs of a coarser level k, or is one run (k = 0): the
+      // first of the places in it takes it
+      int k = l;
+      while (k > 0 && r.y - r.x < subcell_min(k)) --k;
+      const int d = l - k, low = (1 << d) - 1;
+      const bool first = ((x & low) == 0 || x == bx) && ((y & low) == 0 || y == by) && ((z & low) == 0 || z == bz);
+      if (first && r.y != r.x) {
+        if (k == 0) {
+          run = r;
+        } else {
+          const uint32_t top = (1u << k) - 1u;
+          const uint32_t tag = (1u << (g.bits + 3 * k)) | (bucket << (3 * k)) |
+                               morton((uint32_t)(x >> d) & top, (uint32_t)(y >> d) & top, (uint32_t)(z >> d) & top, k);
+          for (uint32_t h = run_group(tag, g.bits);; h = (h + 1u) & mask) {
+            const uint4 w = tags[h];   // filled from the first slot on
+            const uint32_t at = w.x == tag ? 0u : w.y == tag ? 1u : w.z == tag ? 2u : w.w == tag ? 3u : 4u;
+            if (at < 4u) run = runs[4u * h + at];
+            if (at < 4u || w.w == 0u) break;
           }
         }
       }
+    }
+    // two cells can share a bucket: of the lanes with the same run one keeps it (a lane is
+    // settled when it wins its slot or meets its own run there)
+    bool open = run.y > run.x;
+    while (__any(open)) {
+      const uint32_t slot = (run.x * 2654435769u) >> 25;
+      if (open) s_seen[slot] = (uint32_t)lane;
+      __syncthreads();
+      const uint32_t who = open ? s_seen[slot] : (uint32_t)lane;
+      const uint32_t its = __shfl(run.x, (int)who, 64);
+      if (open && who != (uint32_t)lane && its == run.x) run.y = run.x;
+      if (who == (uint32_t)lane || its == run.x) open = false;
+      __syncthreads();
+    }
+    const uint32_t len = run.y - run.x;
+    uint32_t end = len;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t t = __shfl_up(end, o, 64);
+      if (lane >= o) end += t;
+    }
+    const uint32_t total = __shfl(end, 63, 64);
+    const uint32_t shift = run.x - (end - len);   // candidate c of this lane's run is point c + shift
+    for (uint32_t c0 = 0; c0 < total; c0 += kPruneHold) {
+      const uint32_t held = min((uint32_t)kPruneHold, total - c0);
+      for (uint32_t e = lane; e < ((held + 63u) & ~63u); e += 64) {
+        // the lane whose run holds candidate c: the number of lanes with end <= c
+        const uint32_t c = min(c0 + e, total - 1u);
+        int o = 0;
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1)
+          if (__shfl(end, o + step - 1, 64) <= c) o += step;
+        const float4 b = pts[c + __shfl(shift, o, 64)];
+        s_xy[e] = make_double2((double)b.x, (double)b.y);
+        s_z[e] = (double)b.z;
+        s_who[e] = __float_as_uint(b.w);
+      }
+      __syncthreads();
+      for (int j0 = 0; j0 < count; j0 += 4) {
+        const int j = j0 + row;
+        const int who = s_lane[min(j, count - 1)];
+        const double ax = __shfl(a.x, who, 64), ay = __shfl(a.y, who, 64), az = __shfl(a.z, who, 64);
+        const uint32_t self = __float_as_uint(__shfl(a.w, who, 64));
+        // the row's first lane starts from what earlier candidates gave
+        double b0 = l16 == 0 ? s_best[who][0] : (double)INFINITY, b1 = l16 == 0 ? s_best[who][1] : (double)INFINITY,
+               b2 = l16 == 0 ? s_best[who][2] : (double)INFINITY;
+        for (uint32_t e = l16; e < held; e += 16) {
+          const double2 b = s_xy[e];
+          const double ex = b.x - ax, ey = b.y - ay, ez = s_z[e] - az;
+          double d = fmin((ex * ex + ey * ey) + ez * ez, (double)INFINITY);   // NaN: infinite
+          if (s_who[e] == self) d = INFINITY;
+          const double t1 = fmax(b0, d), t2 = fmax(b1, t1);
+          b0 = fmin(b0, d);
+          b1 = fmin(b1, t1);
+          b2 = fmin(b2, t2);
+        }
+        double best[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          best[k] = row_min16(b0);
+          // the first lane of the row that holds it gives it up
+          const uint32_t hold = (uint32_t)(__ballot(b0 == best[k]) >> (16 * row)) & 0xFFFFu;
+          if (l16 == __ffs((int)hold) - 1) {
+            b0 = b1;
+            b1 = b2;
+            b2 = INFINITY;
+          }
+        }
+        if (l16 == 0 && j < count) {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) s_best[who][k] = best[k];
+        }
+      }
+      __syncthreads();
+    }
+    // the edge of a subcell is above radius / 2^l (see make_grid), so nothing nearer is outside
+    const double edge = radius / (double)(1 << l);
+    if (in) {
+      pending = l > 0 && !(s_best[lane][2] < edge * edge);
+      level = l - 1;
+    }
+  }
+  if (!valid) return;
   double avg = INFINITY;
-  const double d3 = sqrt(b2);
-  if (d3 < radius) avg = ((sqrt(b0) + sqrt(b1)) + d3) / 3.0;
+  const double d3 = sqrt(s_best[lane][2]);
+  if (d3 < radius) avg = ((sqrt(s_best[lane][0]) + sqrt(s_best[lane][1])) + d3) / 3.0;
   const uint32_t j = __float_as_uint(a.w);
   keep[j] = (avg < d_op) ? 0 : 1;
   if (d_avg) d_avg[j] = avg;
 }
 
-// Size of the neighbour scan: the sum over points of their 27 buckets' occupancy.
+// Size of the neighbour scan over whole cells: per point its 27 buckets' occupancy (to around),
+// and their sum.
 __global__ __launch_bounds__(kBlock) void k_prune_cost(const float4 *__restrict__ pts, const uint2 *__restrict__ ranges,
-                                                       int64_t n, Grid g, unsigned long long *cost) {
+                                                       int64_t n, Grid g, uint32_t *__restrict__ around,
+                                                       unsigned long long *cost) {
   __shared__ unsigned long long s_sum[kBlock / 64];
   const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   unsigned long long c = 0;
@@ -128,6 +354,7 @@ __global__ __launch_bounds__(kBlock) void k_prune_cost(const float4 *__restrict_
           const uint2 r = ranges[bucket_of(cx + dx, cy + dy, cz + dz, g.shift)];
           c += r.y - r.x;
         }
+    around[p] = (uint32_t)(c < 0xFFFFFFFFull ? c : 0xFFFFFFFFull);
   }
   for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
   if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = c;
@@ -154,10 +381,18 @@ int prune_table_bits(int64_t n) {
   return b;
 }
 
+// Halvings of a cell in the keys: a run's tag of bits + 3 levels + 1 bits fits 32.
+int prune_levels(int64_t n) {
+  const int l = (31 - prune_table_bits(n)) / 3;
+  return l < kPruneLevels ? l : kPruneLevels;
+}
+
 static Grid make_grid(double radius, int64_t n) {
   Grid g;
   g.inv_c = 1.0 / (radius * 1.001);
-  g.shift = 64 - prune_table_bits(n);
+  g.bits = prune_table_bits(n);
+  g.shift = 64 - g.bits;
+  g.levels = prune_levels(n);
   return g;
 }
 
@@ -178,24 +413,42 @@ hipError_t launch_prune_gather(const float *means, const uint32_t *sorted_vals, 
   return hipGetLastError();
 }
 
-hipError_t launch_prune_cost(const float4 *pts, const uint2 *ranges, int64_t n, float d_op,
+hipError_t launch_prune_cost(const float4 *pts, const uint2 *ranges, int64_t n, float d_op, uint32_t *around,
                              unsigned long long *cost, hipStream_t s) {
   if (n <= 0 || !(d_op > 0.0f)) return hipSuccess;
   hipLaunchKernelGGL(k_prune_cost, dim3(grid_of(n)), dim3(kBlock), 0, s, pts, ranges, n,
-                     make_grid(prune_radius(d_op), n), cost);
+                     make_grid(prune_radius(d_op), n), around, cost);
   return hipGetLastError();
 }
 
-hipError_t launch_prune_query(const float4 *pts, const uint2 *ranges, int64_t n, float d_op, uint8_t *keep,
-                              double *d_avg, hipStream_t s) {
+hipError_t launch_prune_runs(const uint32_t *keys, const uint2 *ranges, int64_t n, float d_op, uint32_t *tags,
+                             uint2 *runs, hipStream_t s) {
+  if (n <= 0 || !(d_op > 0.0f)) return hipSuccess;
+  const Grid g = make_grid(prune_radius(d_op), n);
+  hipError_t e = launch_fill_u32(tags, 0u, (int64_t)1 << g.bits, s);
+  if (e != hipSuccess || g.levels == 0) return e;
+  hipLaunchKernelGGL(k_prune_runs, dim3(grid_of(n)), dim3(kBlock), 0, s, keys, ranges, n, g, tags,
+                     reinterpret_cast<uint32_t *>(runs));
+  return hipGetLastError();
+}
+
+hipError_t launch_prune_query(const float4 *pts, const uint2 *ranges, const uint32_t *tags, const uint2 *runs,
+                              const uint32_t *around, int64_t n, float d_op, const unsigned long long *cost, uint8_t *keep, double *d_avg,
+                              hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (!(d_op > 0.0f)) {
     hipLaunchKernelGGL(k_prune_none, dim3(grid_of(n)), dim3(kBlock), 0, s, n, keep, d_avg);
     return hipGetLastError();
   }
   const double radius = prune_radius(d_op);
-  hipLaunchKernelGGL(k_prune_query, dim3(grid_of(n)), dim3(kBlock), 0, s, pts, ranges, n, make_grid(radius, n),
-                     radius, (double)d_op, keep, d_avg);
+  // points per wave: a wave takes its groups one after the other, each a chain of lookups, so
+  // few points are spread over as many waves as the device holds (about 8,192): 69.6k points
+  // at d_op 0.0125, mostly alone in their cell, take 50 us at 8 per wave, about 120 at 64
+  int per = 64;
+  while (per > 8 && n < (int64_t)per * 8192) per /= 2;
+  hipLaunchKernelGGL(k_prune_query, dim3((unsigned)((n + per - 1) / per)), dim3(64), 0, s, pts, ranges,
+                     reinterpret_cast<const uint4 *>(tags), runs, around, n, per,
+                     make_grid(radius, n), radius, (double)d_op, cost, keep, d_avg);
   return hipGetLastError();
 }
 

@@ -418,7 +418,7 @@ hipError_t launch_row_scan(const uint32_t *n_ptr, const uint32_t *hist, uint32_t
 // Bucket ranges from the sorted bucket ids (ranges zeroed beforehand); the id count is read on
 // the device, the grid covers k_max ids.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_ranges(const uint32_t *__restrict__ ids, const uint32_t *k_ptr,
+__global__ __launch_bounds__(kBlock) void k_ranges(const uint32_t *__restrict__ ids, int shift, const uint32_t *k_ptr,
                                                    uint2 *__restrict__ ranges) {
   const uint32_t K = *k_ptr;
   const uint32_t k0 = 4u * (blockIdx.x * kBlock + threadIdx.x);   // four ids per thread
@@ -431,7 +431,9 @@ __global__ __launch_bounds__(kBlock) void k_ranges(const uint32_t *__restrict__ 
 #pragma unroll
     for (int i = 0; i < 4; ++i) t[i] = (k0 + i < K) ? ids[k0 + i] : 0u;
   }
-  uint32_t prev = (k0 > 0u) ? ids[k0 - 1u] : 0xFFFFFFFFu;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) t[i] >>= shift;
+  uint32_t prev = (k0 > 0u) ? ids[k0 - 1u] >> shift : 0xFFFFFFFFu;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const uint32_t k = k0 + i;
@@ -468,13 +470,13 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_ranges(const uint32_t *ids, const uint32_t *k_ptr, int64_t k_max, int n_ranges, uint2 *ranges,
-                         hipStream_t s) {
+hipError_t launch_ranges(const uint32_t *ids, int shift, const uint32_t *k_ptr, int64_t k_max, int n_ranges,
+                         uint2 *ranges, hipStream_t s) {
   hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t *>(ranges), 0u, 2 * (int64_t)n_ranges, s);
   if (e != hipSuccess || k_max <= 0) return e;
   const int64_t threads = (k_max + 3) / 4;
-  hipLaunchKernelGGL(k_ranges, dim3((unsigned)((threads + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, ids, k_ptr,
-                     ranges);
+  hipLaunchKernelGGL(k_ranges, dim3((unsigned)((threads + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, ids, shift,
+                     k_ptr, ranges);
   return hipGetLastError();
 }
 
