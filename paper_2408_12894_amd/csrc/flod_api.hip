@@ -234,12 +234,12 @@ hipError_t wait_event(hipEvent_t ev) {
 
 hipError_t wait_marked(flod_ctx *c) { return wait_event(c->ev_sync); }
 
-// Wait until all five count words carry `seq` (the totals kernel writes them whole): polling,
+// Wait until the first n count words carry `seq` (their kernel writes them whole): polling,
 // and after about 2 s a blocking wait for the stream, then one last look.
-hipError_t wait_counts(flod_ctx *c, hipStream_t s, uint32_t seq) {
+hipError_t wait_counts(flod_ctx *c, hipStream_t s, uint32_t seq, int n) {
   const volatile unsigned long long *w = c->host_counts;
   auto ready = [&]() {
-    for (int k = 0; k < 5; ++k)
+    for (int k = 0; k < n; ++k)
       if ((uint32_t)(w[k] >> 32) != seq) return false;
     return true;
   };
@@ -251,6 +251,12 @@ hipError_t wait_counts(flod_ctx *c, hipStream_t s, uint32_t seq) {
   hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
   return ready() ? hipSuccess : hipErrorUnknown;
+}
+
+// The tag of the next counts the device writes to the host; 0 is the buffer's initial tag.
+uint32_t next_seq(flod_ctx *c) {
+  if (++c->count_seq == 0u) c->count_seq = 1u;
+  return c->count_seq;
 }
 
 bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -365,7 +371,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   need(B_RANGES, 8 * (size_t)n_tiles);
   need(B_TILE_BLENDED, 4 * (size_t)n_tiles);
   need(B_TILE_ORDER, 4 * ((size_t)n_tiles + 2));
-  need(B_COUNTERS, 8 * (size_t)kCntSlots);
+  need(B_COUNTERS, 4 * (size_t)kCntSlots);
   const bool jac = level && c->keep_backward;   // the colour Jacobians for the backward
   if (jac) need(B_SHJAC, 48 * (size_t)N);
   if (st != FLOD_OK) {
@@ -378,8 +384,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   // the counts, guarded by the capacities; straight to the host when `to_host`, tagged with this
   // render's number
   const bool direct = c->host_counts_dev != nullptr;
-  if (direct && ++c->count_seq == 0u) c->count_seq = 1u;   // 0 is the buffer's initial tag
-  const uint32_t seq = direct ? c->count_seq : 0u;
+  const uint32_t seq = direct ? next_seq(c) : 0u;
   auto totals = [&](int64_t guard_k, int64_t guard_p, bool to_host) {
     return FrameTotals{P<uint4>(c, B_BLOCKVIS), nb, counters, (unsigned long long)guard_k, (unsigned long long)guard_p,
                        to_host ? c->host_counts_dev : nullptr, seq};
@@ -463,7 +468,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   unsigned long long K = 0, n_pairs = 0;
   if (N > 0) {
     if (direct) {
-      if (wait_counts(c, s, seq) != hipSuccess) return FLOD_ERR_DEVICE;
+      if (wait_counts(c, s, seq, 5) != hipSuccess) return FLOD_ERR_DEVICE;
       const volatile unsigned long long *w = c->host_counts;
       n_vis = (uint32_t)w[0];
       K = (unsigned long long)(uint32_t)w[1] | ((unsigned long long)(uint32_t)w[2] << 32);
@@ -717,45 +722,78 @@ bool level_arrays_ok(const flod_level &o) {
                       aligned(o.opacity_logits, 4));
 }
 
-// Count the kept Gaussians of one level (per-workgroup counts, scan, a 4-byte read back)
-// and, when `out` is given, copy them in index order. count(block_cnt) and copy(prefix, out)
-// enqueue the two passes.
+// One level's compaction: count(block_cnt) and copy(prefix, out) enqueue the two passes.
+struct Compaction {
+  int64_t n = 0;
+  float s_min = 0.0f;
+  flod_level *out = nullptr;   // null: count only
+  int64_t kept = 0;
+};
+
+// Count the kept Gaussians of `levels` compactions (at most FLOD_MAX_LEVELS; per-workgroup counts
+// and a scan for each), wait once for all the counts and, where `out` is given, copy the kept
+// Gaussians in index order. The counts come through coherent host memory (else a copy), and with
+// them, when asked for (a single compaction), the counters' 64-bit total (*total64).
 template <class CountFn, class CopyFn>
-flod_status compact_pass(flod_ctx *ctx, int64_t n, hipStream_t s, CountFn count, CopyFn copy, flod_level *out,
-                         float s_min, int64_t *kept_out) {
-  *kept_out = 0;
-  if (n == 0) {
-    if (out) {
-      out->n = 0;
-      out->s_min = s_min;
+flod_status compact_pass(flod_ctx *ctx, Compaction *job, int levels, hipStream_t s, CountFn count, CopyFn copy,
+                         unsigned long long *total64 = nullptr) {
+  int64_t blocks[FLOD_MAX_LEVELS], first[FLOD_MAX_LEVELS], total = 0;
+  for (int l = 0; l < levels; ++l) {
+    first[l] = total;
+    blocks[l] = (job[l].n + kBlock - 1) / kBlock;
+    total += blocks[l];
+  }
+  if (total > 0) {
+    size_t extra = 0;
+    if (ensure(ctx, B_BLOCKVIS, 4 * (size_t)total, s, &extra) != FLOD_OK ||
+        ensure(ctx, B_PREFIX, 8 * (size_t)total, s, &extra) != FLOD_OK ||
+        ensure(ctx, B_COUNTERS, 4 * (size_t)kCntSlots, s, &extra) != FLOD_OK) {
+      ctx->required = ws_bytes(ctx) + extra;
+      return FLOD_ERR_WORKSPACE;
     }
-    return FLOD_OK;
+    uint32_t *counters = P<uint32_t>(ctx, B_COUNTERS);
+    const unsigned long long *also =
+        total64 ? reinterpret_cast<const unsigned long long *>(counters + kCntTotal64) : nullptr;
+    const bool direct = ctx->host_counts_dev != nullptr;
+    const uint32_t seq = direct ? next_seq(ctx) : 0u;
+    int waited = 0;
+    for (int l = 0; l < levels; ++l) {
+      if (blocks[l] == 0) continue;
+      uint32_t *cnt = P<uint32_t>(ctx, B_BLOCKVIS) + first[l];
+      if (count(l, cnt) != hipSuccess ||
+          launch_scan_blocks(cnt, P<unsigned long long>(ctx, B_PREFIX) + first[l], counters + kCntKept + l,
+                             (int)blocks[l], direct ? ctx->host_counts_dev + waited : nullptr, seq, s, also) !=
+              hipSuccess)
+        return FLOD_ERR_DEVICE;
+      ++waited;
+    }
+    if (direct) {
+      if (wait_counts(ctx, s, seq, waited + (also ? 2 : 0)) != hipSuccess) return FLOD_ERR_DEVICE;
+    } else if (hipMemcpyAsync(ctx->host_counters, counters, 4 * (size_t)kCntSlots, hipMemcpyDeviceToHost, s) !=
+                   hipSuccess ||
+               hipStreamSynchronize(s) != hipSuccess) {
+      return FLOD_ERR_DEVICE;
+    }
+    const volatile unsigned long long *w = ctx->host_counts;
+    const uint32_t *copied = reinterpret_cast<const uint32_t *>(ctx->host_counters) + kCntKept;
+    for (int l = 0, k = 0; l < levels; ++l)
+      if (blocks[l] > 0) job[l].kept = direct ? (uint32_t)w[k++] : copied[l];
+    if (total64)
+      *total64 = direct ? (unsigned long long)(uint32_t)w[1] | ((unsigned long long)(uint32_t)w[2] << 32)
+                        : ctx->host_counters[kCntTotal64 / 2];
   }
-  const int nb = (int)((n + kBlock - 1) / kBlock);
-  size_t extra = 0;
-  if (ensure(ctx, B_BLOCKVIS, 4 * (size_t)nb, s, &extra) != FLOD_OK ||
-      ensure(ctx, B_PREFIX, 8 * (size_t)nb, s, &extra) != FLOD_OK ||
-      ensure(ctx, B_COUNTERS, 8 * (size_t)kCntSlots, s, &extra) != FLOD_OK) {
-    ctx->required = ws_bytes(ctx) + extra;
-    return FLOD_ERR_WORKSPACE;
+  for (int l = 0; l < levels; ++l) {
+    flod_level *out = job[l].out;
+    if (!out) continue;
+    if (out->n < job[l].kept) {
+      ctx->required = (size_t)job[l].kept * kGaussianBytes;
+      return FLOD_ERR_WORKSPACE;
+    }
+    if (job[l].kept > 0 && copy(l, P<unsigned long long>(ctx, B_PREFIX) + first[l], *out) != hipSuccess)
+      return FLOD_ERR_DEVICE;
+    out->n = job[l].kept;
+    out->s_min = job[l].s_min;
   }
-  uint32_t *counters = P<uint32_t>(ctx, B_COUNTERS);
-  if (count(P<uint32_t>(ctx, B_BLOCKVIS)) != hipSuccess ||
-      launch_scan_blocks(P<uint32_t>(ctx, B_BLOCKVIS), P<unsigned long long>(ctx, B_PREFIX), counters + kCntVisible, nb,
-                         s) != hipSuccess ||
-      hipMemcpyAsync(ctx->host_counters, counters, 16, hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return FLOD_ERR_DEVICE;
-  const int64_t kept = reinterpret_cast<const uint32_t *>(ctx->host_counters)[kCntVisible];
-  *kept_out = kept;
-  if (!out) return FLOD_OK;
-  if (out->n < kept) {
-    ctx->required = (size_t)kept * kGaussianBytes;
-    return FLOD_ERR_WORKSPACE;
-  }
-  if (copy(P<unsigned long long>(ctx, B_PREFIX), *out) != hipSuccess) return FLOD_ERR_DEVICE;
-  out->n = kept;
-  out->s_min = s_min;
   return FLOD_OK;
 }
 
@@ -789,20 +827,26 @@ flod_status flod_select_compact(flod_ctx *ctx, const flod_level *levels, int n_l
   hipStream_t s = (hipStream_t)stream;
   if ((st = begin_level_op(ctx, s)) != FLOD_OK) return st;
   for (int l = 0; l < n_levels; ++l) n_out[l] = 0;
+  Compaction job[FLOD_MAX_LEVELS];
   for (int l = l_start; l <= l_end; ++l) {
-    const flod_level &lv = levels[l - 1];
-    // eq. 6 band of level l, with d_proj^(l_end) = 0 and d_proj^(l_start - 1) = infinity
-    const float hi = (l == l_start) ? INFINITY : d_proj[l - 2];
-    const float lo = (l == l_end) ? 0.0f : d_proj[l - 1];
-    const float lo2 = sq32(lo), hi2 = sq32(hi);
-    auto count = [&](uint32_t *bc) { return launch_select_count(lv.means, lv.n, centre, lo2, hi2, bc, s); };
-    auto copy = [&](const unsigned long long *prefix, const flod_level &o) {
-      return launch_select_copy(lv, centre, lo2, hi2, prefix, o, s);
-    };
-    if ((st = compact_pass(ctx, lv.n, s, count, copy, out ? &out[l - 1] : nullptr, lv.s_min, &n_out[l - 1])) !=
-        FLOD_OK)
-      return st;
+    job[l - l_start].n = levels[l - 1].n;
+    job[l - l_start].s_min = levels[l - 1].s_min;
+    job[l - l_start].out = out ? &out[l - 1] : nullptr;
   }
+  // eq. 6 band of level l, with d_proj^(l_end) = 0 and d_proj^(l_start - 1) = infinity
+  auto lo2 = [&](int l) { return sq32(l == l_end ? 0.0f : d_proj[l - 1]); };
+  auto hi2 = [&](int l) { return sq32(l == l_start ? INFINITY : d_proj[l - 2]); };
+  auto count = [&](int k, uint32_t *bc) {
+    const int l = l_start + k;
+    return launch_select_count(levels[l - 1].means, levels[l - 1].n, centre, lo2(l), hi2(l), bc, s);
+  };
+  auto copy = [&](int k, const unsigned long long *prefix, const flod_level &o) {
+    const int l = l_start + k;
+    return launch_select_copy(levels[l - 1], centre, lo2(l), hi2(l), prefix, o, s);
+  };
+  st = compact_pass(ctx, job, l_end - l_start + 1, s, count, copy);
+  for (int l = l_start; l <= l_end; ++l) n_out[l - 1] = job[l - l_start].kept;
+  if (st != FLOD_OK) return st;
   if (out)
     for (int l = 1; l <= n_levels; ++l)
       if (l < l_start || l > l_end) out[l - 1].n = 0;
@@ -822,11 +866,17 @@ flod_status flod_compact_level(flod_ctx *ctx, const flod_level *in, const uint8_
   }
   hipStream_t s = (hipStream_t)stream;
   if ((st = begin_level_op(ctx, s)) != FLOD_OK) return st;
-  auto count = [&](uint32_t *bc) { return launch_mask_count(keep, in->n, bc, s); };
-  auto copy = [&](const unsigned long long *prefix, const flod_level &o) {
+  auto count = [&](int, uint32_t *bc) { return launch_mask_count(keep, in->n, bc, s); };
+  auto copy = [&](int, const unsigned long long *prefix, const flod_level &o) {
     return launch_mask_copy(*in, keep, prefix, o, s);
   };
-  return compact_pass(ctx, in->n, s, count, copy, out, in->s_min, n_out);
+  Compaction job;
+  job.n = in->n;
+  job.s_min = in->s_min;
+  job.out = out;
+  st = compact_pass(ctx, &job, 1, s, count, copy);
+  *n_out = job.kept;
+  return st;
 }
 
 flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_op, uint8_t *keep, double *d_avg,
@@ -861,7 +911,7 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
     need(B_SCAN, radix_hist_bytes(n));
     need(B_TOT, 4 * (size_t)kRadix);
   }
-  need(B_COUNTERS, 8 * (size_t)kCntSlots);
+  need(B_COUNTERS, 4 * (size_t)kCntSlots);
   if (st != FLOD_OK) {
     ctx->required = ws_bytes(ctx) + extra;
     return st;
@@ -892,14 +942,16 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
   // the device refuses a scan beyond the limit (nothing is written); the host learns of it with
   // the kept count
   if (launch_prune_query(pts, ranges, tags, runs, around, n, d_op, cost, keep, d_avg, s) != hipSuccess) return FLOD_ERR_DEVICE;
-  auto count = [&](uint32_t *bc) { return launch_mask_count(keep, n, bc, s); };
-  auto no_copy = [&](const unsigned long long *, const flod_level &) { return hipSuccess; };
-  st = compact_pass(ctx, n, s, count, no_copy, nullptr, level->s_min, n_keep);
-  if (st == FLOD_OK && d_op > 0.0f && ctx->host_counters[kCntTotal64 / 2] > kPruneMaxScan) {
-    *n_keep = 0;
-    return FLOD_ERR_UNSUPPORTED;
-  }
-  return st;
+  auto count = [&](int, uint32_t *bc) { return launch_mask_count(keep, n, bc, s); };
+  auto no_copy = [&](int, const unsigned long long *, const flod_level &) { return hipSuccess; };
+  Compaction job;
+  job.n = n;
+  unsigned long long scan = 0;
+  st = compact_pass(ctx, &job, 1, s, count, no_copy, d_op > 0.0f ? &scan : nullptr);
+  if (st != FLOD_OK) return st;
+  if (d_op > 0.0f && scan > kPruneMaxScan) return FLOD_ERR_UNSUPPORTED;
+  *n_keep = job.kept;
+  return FLOD_OK;
 }
 
 flod_status flod_l1_ssim_forward(flod_ctx *ctx, const float *image, const float *target, int channels, int height,

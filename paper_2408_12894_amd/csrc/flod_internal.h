@@ -115,7 +115,8 @@ enum : int {
   kCntPairs64 = 4,      // u64 count of (supertile, Gaussian) pairs (slots 4, 5)
   kCntPairs = 6,        // u32 count of pairs; 0 when instances or pairs exceed their buffers
   kCntChunks = 7,       // u32 count of chunks of pairs
-  kCntSlots = 8
+  kCntKept = 8,         // u32 counts of the Gaussians a compaction keeps, one per level (slots 8 .. 15)
+  kCntSlots = 16
 };
 
 // Sums of the preprocess's per-workgroup counts, taken by one workgroup of kBlock threads:
@@ -205,7 +206,8 @@ inline unsigned xcd_grid(int64_t blocks) {
 // ---- launches (each file defines its own) ----
 hipError_t launch_preprocess(const PreParams &p, const PreOut &o, hipStream_t s);
 hipError_t launch_scan_blocks(const uint32_t *in, unsigned long long *prefix, uint32_t *total, int blocks,
-                              hipStream_t s);
+                              unsigned long long *host_out, uint32_t host_seq, hipStream_t s,
+                              const unsigned long long *extra = nullptr);
 int radix_items(int64_t n_max);        // keys per thread the radix sort of n_max keys uses
 size_t radix_hist_bytes(int64_t n_max);  // bytes of each of its hist and scan arrays
 // The render's depth sort: the first pass reads keys[0, n_max) of every candidate, takes each

@@ -45,12 +45,16 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *total)
 }
 
 // ---------------------------------------------------------------------------------------
-// Scan of per-workgroup counts (one workgroup): 64-bit exclusive prefixes and the total.
+// Scan of per-workgroup counts (one workgroup): 64-bit exclusive prefixes and the total; with
+// host_out (coherent host memory) the total also goes there, tagged as the frame's counts are
+// (see FrameTotals), and behind it, when given, the low and high halves of *extra.
 // ---------------------------------------------------------------------------------------
 constexpr int kScanThreads = 1024;
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_blocks(const uint32_t *in, unsigned long long *prefix,
-                                                              uint32_t *total32, int nb) {
+                                                              uint32_t *total32, int nb,
+                                                              unsigned long long *host_out, uint32_t host_seq,
+                                                              const unsigned long long *extra) {
   __shared__ unsigned long long s_w[kScanThreads / 64];
   // thread t owns the contiguous counts [t per, (t + 1) per): its sum, a workgroup scan of the
   // sums, then its exclusive prefixes (a second read of its counts, from cache)
@@ -91,12 +95,23 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_blocks(const uint32_t *in
     prefix[k] = run;
     run += in[k];
   }
-  if (threadIdx.x == 0) *total32 = (uint32_t)total;
+  if (threadIdx.x == 0) {
+    *total32 = (uint32_t)total;
+    if (host_out) {
+      const unsigned long long tag = (unsigned long long)host_seq << 32, x = extra ? *extra : 0ull;
+      const unsigned long long w[3] = {tag | (uint32_t)total, tag | (uint32_t)x, tag | (x >> 32)};
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k == 0 || extra) __hip_atomic_store(&host_out[k], w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
 }
 
 hipError_t launch_scan_blocks(const uint32_t *in, unsigned long long *prefix, uint32_t *total, int blocks,
-                              hipStream_t s) {
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, in, prefix, total, blocks);
+                              unsigned long long *host_out, uint32_t host_seq, hipStream_t s,
+                              const unsigned long long *extra) {
+  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, in, prefix, total, blocks, host_out, host_seq,
+                     extra);
   return hipGetLastError();
 }
 
