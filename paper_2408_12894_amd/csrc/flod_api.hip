@@ -372,6 +372,9 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   need(B_TILE_BLENDED, 4 * (size_t)n_tiles);
   need(B_TILE_ORDER, 4 * ((size_t)n_tiles + 2));
   need(B_COUNTERS, 4 * (size_t)kCntSlots);
+  // every level's scale floor is at least eight pixels wide at unit depth
+  bool large = true;
+  for (int l = 0; l < p.n_levels; ++l) large = large && p.lv[l].s_min * cam.fx >= 8.0f;
   const bool jac = level && c->keep_backward;   // the colour Jacobians for the backward
   if (jac) need(B_SHJAC, 48 * (size_t)N);
   if (st != FLOD_OK) {
@@ -458,7 +461,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     if (launch_blend(P<uint2>(c, B_RANGES), P<uint32_t>(c, B_VALUES), P<float4>(c, B_XYAB), P<float4>(c, B_COP),
                      P<float2>(c, B_BLUE), cam, bg, out->image, out->final_T, out->n_contrib, out->n_blended,
                      c->keep_backward ? P<uint2>(c, B_BLENDED) : nullptr,
-                     c->keep_backward ? P<uint32_t>(c, B_TILE_BLENDED) : nullptr, order, s) != hipSuccess)
+                     c->keep_backward ? P<uint32_t>(c, B_TILE_BLENDED) : nullptr, order, large, s) != hipSuccess)
       return FLOD_ERR_DEVICE;
     tm.end();
     return FLOD_OK;
