@@ -315,8 +315,8 @@ flod_status flod_ctx_stats(const flod_ctx *ctx, flod_stats *out);
 
 /* Device pointers to the last render's intermediate buffers, owned by ctx, valid until
    the next call on ctx. For inspection and tests. May run a kernel and wait for it (see
-   tile_ids, grad2d; FLOD_ERR_DEVICE if that fails) and take workspace for tile_ids
-   (FLOD_ERR_WORKSPACE if refused). */
+   tile_ids, bin, grad2d; FLOD_ERR_DEVICE if that fails) and take workspace for tile_ids
+   and bin (FLOD_ERR_WORKSPACE if refused). */
 typedef struct {
   const uint32_t *tile_ids;     /* [n_instances] tile id of each sorted instance (written
                                    by the first view after a render: no render needs them) */
@@ -326,7 +326,8 @@ typedef struct {
   const uint32_t *depth_bits;   /* [n_candidates] bits of the view-space depth (FP32)       */
   const float *bin;             /* [n_candidates,8] binning record of rendered candidates:
                                    mu'x, mu'y, conic a, b, c, support bound Q_g, then (bits)
-                                   the tile rectangle x0 | y0<<16 and x1 | y1<<16, inclusive */
+                                   the tile rectangle x0 | y0<<16 and x1 | y1<<16, inclusive
+                                   (written by the first view after a render)               */
   const uint32_t *tiles_touched;/* [n_candidates] 0 = not rendered                          */
   const float *xy_conic;        /* [n_candidates,4] mu'x, mu'y (FP32 rounding of the FP64
                                    projection), conic a, conic b                            */

@@ -54,9 +54,9 @@ struct Buf {
 };
 
 enum BufId {
-  B_XYAB, B_COP, B_BLUE, B_DEPTH, B_BIN, B_TILES, B_BLOCKVIS, B_PREFIX,
-  B_DKEY0, B_DKEY1, B_DVAL0, B_DVAL1, B_RECT, B_SRECT,
-  B_PAIR_ID, B_PAIR_MASK, B_CHUNKS, B_CHUNK_CNT, B_SUPERS, B_TILE_LEN, B_VALUES, B_TILE_IDS,
+  B_XYAB, B_COP, B_BLUE, B_DEPTH, B_QSUP, B_TILES, B_BLOCKVIS, B_PREFIX,
+  B_DKEY0, B_DKEY1, B_DVAL0, B_DVAL1, B_RECT, B_SRECT, B_SPANS,
+  B_PAIR_ID, B_PAIR_MASK, B_CHUNKS, B_CHUNK_CNT, B_SUPERS, B_TILE_LEN, B_VALUES, B_TILE_IDS, B_BIN,
   B_HIST, B_SCAN, B_TOT, B_RANGES, B_COUNTERS,
   B_G2D, B_SSIM, B_BLENDED, B_TILE_BLENDED, B_TILE_ORDER, B_SHJAC, B_COUNT
 };
@@ -150,6 +150,10 @@ flod_status ensure(flod_ctx *c, BufId id, size_t bytes, hipStream_t s, size_t *e
 }
 
 template <class T> T *P(flod_ctx *c, BufId id) { return reinterpret_cast<T *>(c->buf[id].p); }
+
+BinIn bin_in(flod_ctx *c) {
+  return BinIn{P<float4>(c, B_XYAB), P<float4>(c, B_COP), P<float>(c, B_QSUP), P<uint4>(c, B_SPANS)};
+}
 
 flod_status dev(hipError_t e) { return e == hipSuccess ? FLOD_OK : FLOD_ERR_DEVICE; }
 
@@ -353,7 +357,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   need(B_COP, 16 * (size_t)N);
   need(B_BLUE, 8 * (size_t)N);
   need(B_DEPTH, 4 * (size_t)N);
-  need(B_BIN, 32 * (size_t)N);
+  need(B_QSUP, 4 * (size_t)N);
   need(B_TILES, 4 * (size_t)N);
   need(B_BLOCKVIS, 32 * (size_t)nb);
   need(B_DKEY0, 4 * (size_t)N);
@@ -362,6 +366,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   need(B_DVAL1, 4 * (size_t)N);
   need(B_RECT, 8 * (size_t)N);
   need(B_SRECT, 8 * (size_t)N);
+  need(B_SPANS, 16 * (size_t)N);
   need(B_HIST, hist);
   need(B_SCAN, hist);
   need(B_TOT, 4 * (size_t)(n_supers > kRadix ? n_supers : kRadix));
@@ -398,9 +403,10 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     o.cop = P<float4>(c, B_COP);
     o.blue = P<float2>(c, B_BLUE);
     o.depth = P<uint32_t>(c, B_DEPTH);
-    o.bin = P<float4>(c, B_BIN);
+    o.qsup = P<float>(c, B_QSUP);
     o.tiles = P<uint32_t>(c, B_TILES);
     o.rect = P<uint2>(c, B_RECT);
+    o.spans = P<uint4>(c, B_SPANS);
     o.block_sums = P<uint4>(c, B_BLOCKVIS);
     o.n_selected = reinterpret_cast<unsigned long long *>(n_selected);
     o.shjac = jac ? P<float4>(c, B_SHJAC) : nullptr;
@@ -430,12 +436,12 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     const int64_t max_chunks = chunk_capacity(cam, cap_p);
     if (N > 0) {
       tm.begin(FLOD_STAGE_OFFSETS);
-      if (launch_pair_offsets(ids, counters, P<uint2>(c, B_SRECT), P<float4>(c, B_BIN), cam, N, hist_a, scan_a, tot,
+      if (launch_pair_offsets(ids, counters, P<uint2>(c, B_SRECT), bin_in(c), cam, N, hist_a, scan_a, tot,
                               s) != hipSuccess)
         return FLOD_ERR_DEVICE;
       tm.end();
       tm.begin(FLOD_STAGE_TILE_SORT);
-      if (launch_pair_place(ids, counters, P<uint2>(c, B_SRECT), P<float4>(c, B_BIN), cam, N, scan_a, tot,
+      if (launch_pair_place(ids, counters, P<uint2>(c, B_SRECT), bin_in(c), cam, N, scan_a, tot,
                             P<uint32_t>(c, B_PAIR_ID), P<unsigned long long>(c, B_PAIR_MASK), P<uint4>(c, B_CHUNKS),
                             P<uint2>(c, B_SUPERS), s) != hipSuccess ||
           launch_chunk_counts(counters, P<uint4>(c, B_CHUNKS), P<unsigned long long>(c, B_PAIR_MASK),
@@ -1157,15 +1163,21 @@ flod_status flod_ctx_view(const flod_ctx *ctx, flod_view *out) {
   memset(out, 0, sizeof(*out));
   if (!sv.valid) return FLOD_ERR_UNSUPPORTED;
   if (!sv.has_tile_ids) {
-    // the list holds no tile ids: the first view after a render writes them from the ranges
+    // the render writes neither the list's tile ids nor the binning records: the first view after
+    // it does, from the ranges and from what the records repeat
     size_t extra = 0;
+    const int64_t n = c->stats.n_candidates;
     if (hipSetDevice(ctx->device) != hipSuccess) return FLOD_ERR_DEVICE;
-    if (ensure(c, B_TILE_IDS, 4 * (size_t)c->stats.n_instances, c->last_stream, &extra) != FLOD_OK) {
+    const flod_status ids = ensure(c, B_TILE_IDS, 4 * (size_t)c->stats.n_instances, c->last_stream, &extra);
+    const flod_status bin = ensure(c, B_BIN, 32 * (size_t)n, c->last_stream, &extra);
+    if (ids != FLOD_OK || bin != FLOD_OK) {
       c->required = ws_bytes(c) + extra;
       return FLOD_ERR_WORKSPACE;
     }
     if (launch_tile_ids(P<uint2>(c, B_RANGES), sv.cam.tiles_x * sv.cam.tiles_y, P<uint32_t>(c, B_TILE_IDS),
                         c->last_stream) != hipSuccess ||
+        launch_bin_records(n, P<uint32_t>(c, B_TILES), P<uint2>(c, B_RECT), bin_in(c), P<float4>(c, B_BIN),
+                           c->last_stream) != hipSuccess ||
         hipStreamSynchronize(c->last_stream) != hipSuccess)
       return FLOD_ERR_DEVICE;
     c->saved.has_tile_ids = true;

@@ -22,11 +22,14 @@ constexpr int kSuper = 8;                 // a supertile is kSuper x kSuper tile
 constexpr int kSuperWindow = 512;         // supertiles counted in LDS at once
 constexpr int kPairBlock = 256;           // depth-sorted Gaussians per workgroup of the pair kernels
 constexpr int kChunk = 256;               // pairs of one supertile expanded by one workgroup
+constexpr int kSpanBox = 16;              // largest footprint (tiles a side) whose row spans are stored
 constexpr int kPairRectMax = 16;          // largest rectangle (in supertiles) listed whole
-// A Gaussian's tile rectangle as the binning reads it: x0 | y0 << 16 and x1 | y1 << 16 with two
-// flags: the footprint is the whole rectangle; its supertiles are listed row by row (see
-// pairs_of_rect) instead of the whole rectangle's.
-constexpr uint32_t kRectFull = 1u << 31, kRectBanded = 1u << 30;
+// A Gaussian's tile rectangle as the binning reads it: x0 | y0 << 16 and x1 | y1 << 16 (frames have
+// at most 1024 x 1024 tiles) with what else it has to know: the footprint is the whole rectangle;
+// its supertiles are listed row by row instead of the whole rectangle's; its row spans are stored
+// (kSpanNone), counted from the rectangle's first column or (BoxLeft) from the one before it.
+constexpr uint32_t kRectFull = 1u << 31, kRectBanded = 1u << 30, kRectBoxed = 1u << 29, kRectBoxLeft = 1u << 28;
+constexpr uint32_t kRectCorner = 0x0FFFFFFFu;
 constexpr size_t kGaussianBytes = (3 + 3 + 4 + 1 + FLOD_SH_COEFFS * 3) * 4;   // 236 B per stored Gaussian
 constexpr unsigned long long kPruneMaxScan = 1ull << 36;   // overlap-pruning neighbour-scan limit
 
@@ -76,15 +79,22 @@ struct PreOut {
   float4 *cop;        // conic c, opacity, red, green
   float2 *blue;       // blue, packed bf16 residuals of mu' (bits)
   uint32_t *depth;    // FP32 bits of the view-space depth
-  float4 *bin;        // binning record, two per candidate: (mu'x, mu'y, conic a, conic b) and
-                      // (conic c, support bound Q_g, bits of x0 | y0 << 16, bits of x1 | y1 << 16)
+  float *qsup;        // support bound Q_g
   uint32_t *tiles;    // tiles touched, 0 when culled or not selected
-  uint2 *rect;        // tile rectangle and flags of rendered candidates (kRectFull, kRectBanded)
+  uint2 *rect;        // tile rectangle and flags of rendered candidates (kRectFull ...)
+  uint4 *spans;       // row spans of those with kRectBoxed (see kSpanNone)
   uint4 *block_sums;  // per workgroup: visible candidates, tiles and (supertile, Gaussian) pairs
   unsigned long long *n_selected;   // per-level selected counts (may be null)
   float4 *shjac;      // three planes of n_total float4, per visible candidate the colour's Jacobian in
                       // the unit view direction, J[ch][a] row-major, then the three colours before the
                       // clamp (J00 J01 J02 J10 | J11 J12 J20 J21 | J22 c0 c1 c2); may be null
+};
+
+// What the binning reads of a candidate besides its rectangle.
+struct BinIn {
+  const float4 *xyab, *cop;
+  const float *qsup;
+  const uint4 *spans;
 };
 
 // One attribute array of a level in an Adam step: parameter, gradient and the two moment
@@ -232,10 +242,10 @@ hipError_t launch_row_scan(const uint32_t *n_ptr, const uint32_t *hist, uint32_t
 int super_count(const DevCamera &cam);
 size_t pair_hist_bytes(const DevCamera &cam, int64_t n);       // bytes of its hist and scan arrays
 int64_t chunk_capacity(const DevCamera &cam, int64_t pairs);   // the most chunks that many pairs make
-hipError_t launch_pair_offsets(const uint32_t *ids, const uint32_t *counters, const uint2 *srect, const float4 *bin,
+hipError_t launch_pair_offsets(const uint32_t *ids, const uint32_t *counters, const uint2 *srect, const BinIn &bin,
                                const DevCamera &cam, int64_t n, uint32_t *hist, uint32_t *scan, uint32_t *tot,
                                hipStream_t s);
-hipError_t launch_pair_place(const uint32_t *ids, uint32_t *counters, const uint2 *srect, const float4 *bin,
+hipError_t launch_pair_place(const uint32_t *ids, uint32_t *counters, const uint2 *srect, const BinIn &bin,
                              const DevCamera &cam, int64_t n, const uint32_t *scan, const uint32_t *tot,
                              uint32_t *pair_id, unsigned long long *pair_mask, uint4 *chunks, uint2 *supers,
                              hipStream_t s);
@@ -247,6 +257,8 @@ hipError_t launch_chunk_expand(const uint32_t *counters, const uint4 *chunks, co
                                const unsigned long long *pair_mask, const uint32_t *prefix, const uint2 *ranges,
                                const DevCamera &cam, int64_t max_chunks, uint32_t *values, hipStream_t s);
 hipError_t launch_frame_totals(const FrameTotals &t, hipStream_t s);
+hipError_t launch_bin_records(int64_t n, const uint32_t *tiles, const uint2 *rect, const BinIn &in, float4 *out,
+                              hipStream_t s);
 hipError_t launch_tile_ids(const uint2 *ranges, int n_tiles, uint32_t *tile_ids, hipStream_t s);
 // [start, end) of every bucket (id >> shift) in the sorted ids (ranges zeroed here first)
 hipError_t launch_ranges(const uint32_t *ids, int shift, const uint32_t *k_ptr, int64_t k_max, int n_ranges,

@@ -3,8 +3,10 @@
 // thread per candidate Gaussian.
 //
 // Memory: one pass over the attributes (12 + 12 + 16 + 4 + 192 bytes per Gaussian, the SH
-// row read as 12 dwordx4 loads), 80 bytes written per visible Gaussian (128 when the render
-// keeps the backward's state: the colour Jacobian below). The projection runs in FP64
+// row read as 12 dwordx4 loads), 60 bytes written per visible Gaussian, 16 more where it stores
+// the row spans, 48 more when the render keeps the backward's state (the colour Jacobian below);
+// at 1M Gaussians the pass is near the memory's rate, and the binning record that repeats most
+// of them (32 bytes, written for inspection only now) cost it 9 of 101 us. The projection runs in FP64
 // (see project.h); mu' is stored as its FP32 rounding plus a bf16 residual so that the blend
 // kernels can form pixel offsets to better than 1e-6 px. Rejected candidates stop
 // after reading the mean (selection) or the mean and logit (near-plane / opacity culls).
@@ -17,6 +19,10 @@ namespace flod {
 // coefficients (reading 48 bytes per Gaussian instead of 192).
 template <bool JAC>
 __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
+  __shared__ union {
+    uint8_t b[kSpanBox];
+    uint4 v;
+  } s_box[kBlock];   // each thread's row spans, should they fit
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   bool vis = false;
   bool selected = false;
@@ -47,11 +53,15 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
           Footprint fp;
           uint32_t rx0 = 0xFFFFu, rx1 = 0u;
           uint32_t bx0 = 0xFFFFu, bx1 = 0u, band_pairs = 0u;   // the current supertile row's columns
+          int box_x0 = 0;
           const float qg = support_q(logit);
           if (footprint(hx, hy, ca, cb, cc, support_span(qg), p.cam.tiles_y, fp)) {
+            box_x0 = span_box_column(fp, p.cam.tiles_x);
+            s_box[threadIdx.x].v = make_uint4(kSpanNone, kSpanNone, kSpanNone, kSpanNone);
             for (int ty = fp.ty0; ty <= fp.ty1; ++ty) {
               int tx0, tx1;
               if (row_span(fp, ty, p.cam.tiles_x, tx0, tx1)) {
+                s_box[threadIdx.x].b[(ty - fp.ty0) & (kSpanBox - 1)] = (uint8_t)((tx0 - box_x0) | ((tx1 - box_x0) << 4));
                 tiles += (uint32_t)(tx1 - tx0 + 1);
                 rx0 = min(rx0, (uint32_t)tx0);
                 rx1 = max(rx1, (uint32_t)tx1);
@@ -127,16 +137,20 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
             o.cop[i] = make_float4(cc, opac, col[0], col[1]);
             o.blue[i] = make_float2(col[2], __uint_as_float(pack_mu_lo(pr.mx, pr.my, hx, hy)));
             o.depth[i] = __float_as_uint((float)pr.tz);
-            o.bin[2 * i] = make_float4(hx, hy, ca, cb);
+            o.qsup[i] = qg;
             const uint32_t r0 = rx0 | ((uint32_t)fp.ty0 << 16), r1 = rx1 | ((uint32_t)fp.ty1 << 16);
-            o.bin[2 * i + 1] = make_float4(cc, qg, __uint_as_float(r0), __uint_as_float(r1));
             // the supertiles it will be listed in: the whole rectangle's while those are few,
             // else row by row (a long diagonal footprint misses most of its rectangle)
             const uint32_t w = rx1 - rx0 + 1u, h = (uint32_t)(fp.ty1 - fp.ty0 + 1);
             pairs = (rx1 / kSuper - rx0 / kSuper + 1u) * (uint32_t)(fp.ty1 / kSuper - fp.ty0 / kSuper + 1);
             const bool banded = pairs > (uint32_t)kPairRectMax;
             if (banded) pairs = band_pairs;
-            o.rect[i] = make_uint2(r0, r1 | (w * h == tiles ? kRectFull : 0u) | (banded ? kRectBanded : 0u));
+            uint32_t flags = w * h == tiles ? kRectFull : banded ? kRectBanded : 0u;
+            if (flags == 0u && h <= (uint32_t)kSpanBox && (int)rx1 < box_x0 + kSpanBox && rx0 - (uint32_t)box_x0 <= 1u) {
+              o.spans[i] = s_box[threadIdx.x].v;
+              flags = kRectBoxed | (box_x0 < (int)rx0 ? kRectBoxLeft : 0u);
+            }
+            o.rect[i] = make_uint2(r0, r1 | flags);
           }
         }
       }

@@ -133,8 +133,8 @@ __device__ __forceinline__ bool project_cov(const DevCamera &cam, const float ls
 // ellipse over the row's band of pixel centres is found in closed form (the right boundary
 // is concave in dy, so its maximum over the band is the ellipse's rightmost point when that
 // lies in the band, else a band end; the left boundary mirrors it). Computed in FP64 from the
-// stored FP32 mu', conic and Q_g by the preprocess (to count) and the emission (to write), so
-// both agree exactly.
+// stored FP32 mu', conic and Q_g by the preprocess (to count, and to store the spans of
+// smaller footprints) and the binning (the larger ones' spans), so both agree exactly.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ float support_q(float logit) {
   const float o = (float)(1.0 / (1.0 + exp(-(double)logit)));
@@ -145,24 +145,27 @@ __device__ __forceinline__ double support_span(float qg) { return (double)qg * 1
 
 
 struct Footprint {
-  double mx, my, a, b, c, det, ia, hx, hy, dyr, Q;
+  float mx, my, b;
+  double qa, det, ia, hx, hy, dyr;
   int ty0, ty1;
 };
 
 __device__ __forceinline__ bool footprint(float mx, float my, float a, float b, float c, double Q, int tiles_y,
                                           Footprint &f) {
-  f.mx = mx; f.my = my; f.a = a; f.b = b; f.c = c; f.Q = Q;
-  f.det = f.a * f.c - f.b * f.b;
-  if (!(f.det > 0.0) || !(f.a > 0.0)) return false;
+  const double da = a, db = b, dc = c;
+  f.mx = mx; f.my = my; f.b = b;
+  f.det = da * dc - db * db;
+  if (!(f.det > 0.0) || !(da > 0.0)) return false;
   // reciprocals taken once; the rows multiply by them
   const double idet = 1.0 / f.det;
-  f.ia = 1.0 / f.a;
-  const double sxx = f.c * idet, syy = f.a * idet, sxy = -f.b * idet;
+  f.ia = 1.0 / da;
+  const double sxx = dc * idet, syy = da * idet, sxy = -db * idet;
+  f.qa = Q * da;
   f.hx = sqrt(Q * sxx);
   f.hy = sqrt(Q * syy);
   f.dyr = sxy * sqrt(Q / sxx);
-  double y0 = floor((f.my - f.hy) * 0.0625);
-  double y1 = floor((f.my + f.hy) * 0.0625);
+  double y0 = floor(((double)my - f.hy) * 0.0625);
+  double y1 = floor(((double)my + f.hy) * 0.0625);
   y0 = fmax(y0, 0.0);
   y1 = fmin(y1, (double)(tiles_y - 1));
   if (!(y0 <= y1)) return false;
@@ -173,22 +176,42 @@ __device__ __forceinline__ bool footprint(float mx, float my, float a, float b, 
 
 // Tiles [tx0, tx1] of tile row ty that the footprint reaches; false if none.
 __device__ __forceinline__ bool row_span(const Footprint &f, int ty, int tiles_x, int &tx0, int &tx1) {
-  const double dlo = fmax((16.0 * ty + 0.5) - f.my, -f.hy);
-  const double dhi = fmin((16.0 * ty + 15.5) - f.my, f.hy);
+  const double my = f.my, mx = f.mx, b = f.b;
+  const double dlo = fmax((16.0 * ty + 0.5) - my, -f.hy);
+  const double dhi = fmin((16.0 * ty + 15.5) - my, f.hy);
   if (!(dlo <= dhi)) return false;
-  const double qa = f.Q * f.a;
-  const double rlo = sqrt(fmax(0.0, qa - f.det * dlo * dlo));
-  const double rhi = sqrt(fmax(0.0, qa - f.det * dhi * dhi));
-  const double right = (dlo <= f.dyr && f.dyr <= dhi) ? f.hx : fmax((-f.b * dlo + rlo) * f.ia, (-f.b * dhi + rhi) * f.ia);
-  const double left = (dlo <= -f.dyr && -f.dyr <= dhi) ? -f.hx : fmin((-f.b * dlo - rlo) * f.ia, (-f.b * dhi - rhi) * f.ia);
-  double x0 = floor((f.mx + left) * 0.0625);
-  double x1 = floor((f.mx + right) * 0.0625);
+  const double rlo = sqrt(fmax(0.0, f.qa - f.det * dlo * dlo));
+  const double rhi = sqrt(fmax(0.0, f.qa - f.det * dhi * dhi));
+  const double right = (dlo <= f.dyr && f.dyr <= dhi) ? f.hx : fmax((-b * dlo + rlo) * f.ia, (-b * dhi + rhi) * f.ia);
+  const double left = (dlo <= -f.dyr && -f.dyr <= dhi) ? -f.hx : fmin((-b * dlo - rlo) * f.ia, (-b * dhi - rhi) * f.ia);
+  double x0 = floor((mx + left) * 0.0625);
+  double x1 = floor((mx + right) * 0.0625);
   x0 = fmax(x0, 0.0);
   x1 = fmin(x1, (double)(tiles_x - 1));
   if (!(x0 <= x1)) return false;
   tx0 = (int)x0;
   tx1 = (int)x1;
   return true;
+}
+
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t t = __shfl_up(v, o, 64);
+    if (lane >= o) v += t;
+  }
+  return v;
+}
+
+// Row spans of a footprint of at most kSpanBox rows and columns in 16 bytes: byte r is row r's
+// (first column - x0) | (last column - x0) << 4, of an empty row kSpanNone. x0 is the column of
+// the support's left end, which is known before the rows; the rows mostly reach it.
+constexpr uint32_t kSpanNone = 0x01010101u;
+
+__device__ __forceinline__ int span_box_column(const Footprint &f, int tiles_x) {
+  return (int)fmin(fmax(floor(((double)f.mx - f.hx) * 0.0625), 0.0), (double)tiles_x);
 }
 
 // bf16 (round to nearest even) of an FP32 value, in the upper half of a 32-bit word.

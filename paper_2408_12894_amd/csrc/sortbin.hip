@@ -15,16 +15,6 @@
 
 namespace flod {
 
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t t = __shfl_up(v, o, 64);
-    if (lane >= o) v += t;
-  }
-  return v;
-}
-
 // Exclusive scan over a kBlock-thread workgroup; *total receives the sum.
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *total) {
   __shared__ uint32_t s_w[kBlock / 64];

@@ -37,33 +37,26 @@ struct Supers {
   int nx, n;   // supertiles per row, in all
 };
 
-__device__ __forceinline__ uint32_t tb_incl_scan(uint32_t v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t t = __shfl_up(v, o, 64);
-    if (lane >= o) v += t;
-  }
-  return v;
-}
-
 // One Gaussian's rows of tiles: its rectangle, and the row spans recomputed in FP64 exactly as
 // the preprocess counted them unless the footprint fills the rectangle.
 struct PairRows {
   int x0, y0, x1, y1;
-  bool full, banded;
+  int bx;   // the column that the stored spans count from
+  bool full, banded, boxed;
   Footprint fp;
   __device__ __forceinline__ void load(uint2 r) {
     x0 = (int)(r.x & 0xFFFFu);
     y0 = (int)(r.x >> 16);
     x1 = (int)(r.y & 0xFFFFu);
-    y1 = (int)((r.y >> 16) & 0x3FFFu);
+    y1 = (int)((r.y >> 16) & 0xFFFu);
     full = (r.y & kRectFull) != 0u;
     banded = (r.y & kRectBanded) != 0u;
+    boxed = (r.y & kRectBoxed) != 0u;
+    bx = x0 - ((r.y & kRectBoxLeft) != 0u ? 1 : 0);
   }
-  __device__ __forceinline__ void load_footprint(const float4 *bin, uint32_t g, int tiles_y) {
-    const float4 a = bin[2 * (size_t)g], b = bin[2 * (size_t)g + 1];
-    footprint(a.x, a.y, a.z, a.w, b.x, support_span(b.y), tiles_y, fp);
+  __device__ __forceinline__ void load_footprint(const BinIn &bin, uint32_t g, int tiles_y) {
+    const float4 a = bin.xyab[g];
+    footprint(a.x, a.y, a.z, a.w, bin.cop[g].x, support_span(bin.qsup[g]), tiles_y, fp);
   }
   __device__ __forceinline__ bool span(int ty, int tiles_x, int &tx0, int &tx1) const {
     if (full) {
@@ -101,7 +94,7 @@ struct PairRows {
 __global__ __launch_bounds__(kPairBlock) void k_pair_hist(const uint32_t *__restrict__ ids,
                                                           const uint32_t *__restrict__ counters,
                                                           const uint2 *__restrict__ srect,
-                                                          const float4 *__restrict__ bin, Supers su,
+                                                          BinIn bin, Supers su,
                                                           uint32_t *__restrict__ hist, int stride) {
   __shared__ uint32_t s_cnt[kSuperWindow];
   const uint32_t n = counters[kCntVisible];
@@ -142,11 +135,55 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_hist(const uint32_t *__rest
   }
 }
 
+// Row spans of footprints, the rows of a wave's Gaussians dealt to its lanes in order: those whose
+// spans the preprocess stored need none, and of the others, few and tall, a wave would repeat the
+// FP64 rows as often as the tallest has rows. rows: this lane's count of rows (0: none), incl:
+// its inclusive sum over the lanes. The span of a lane's row r goes to spans[incl - rows + r] as
+// x0 | x1 << 16, an empty one as 1. Every lane of the wave takes part; spans is the wave's own.
+constexpr int kSpanHold = 1024;   // row spans a wave has room for; no footprint has more rows (frames
+                                  // are at most 16384 pixels high)
+
+__device__ __forceinline__ int owner_lane(uint32_t incl, uint32_t v) {
+  int lo = 0;   // the number of lanes with incl <= v
+#pragma unroll
+  for (int step = 32; step > 0; step >>= 1) {
+    const uint32_t x = __shfl(incl, lo + step - 1, 64);
+    if (x <= v) lo += step;
+  }
+  return lo;
+}
+
+__device__ __forceinline__ void wave_row_spans(const Footprint &f, int y0, uint32_t rows, uint32_t incl, int tiles_x,
+                                               uint32_t *spans) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t total = __shfl(incl, 63, 64);
+  const int first = y0 - (int)(incl - rows);   // row v of the wave's is tile row v + first of its owner
+  for (uint32_t v0 = 0; v0 < total; v0 += 64) {
+    const uint32_t v = min(v0 + lane, total - 1u);
+    const int o = owner_lane(incl, v);
+    Footprint g;
+    g.mx = __shfl(f.mx, o, 64); g.my = __shfl(f.my, o, 64); g.b = __shfl(f.b, o, 64);
+    g.qa = __shfl(f.qa, o, 64); g.det = __shfl(f.det, o, 64); g.ia = __shfl(f.ia, o, 64);
+    g.hx = __shfl(f.hx, o, 64); g.hy = __shfl(f.hy, o, 64); g.dyr = __shfl(f.dyr, o, 64);
+    int a, e;
+    const bool ok = row_span(g, (int)v + __shfl(first, o, 64), tiles_x, a, e);
+    if (v0 + lane < total) spans[v] = ok ? (uint32_t)a | ((uint32_t)e << 16) : 1u;
+  }
+}
+
+// Orders a wave's LDS writes before its lanes' later reads of each other's.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Exclusive scan of two values per thread over the workgroup.
 __device__ __forceinline__ void block_excl_scan2(uint32_t &a, uint32_t &b, uint32_t &ta, uint32_t &tb) {
   __shared__ uint32_t s_a[kPairWaves], s_b[kPairWaves];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const uint32_t ia = tb_incl_scan(a), ib = tb_incl_scan(b);
+  const uint32_t ia = wave_incl_scan(a), ib = wave_incl_scan(b);
   __syncthreads();
   if (lane == 63) {
     s_a[w] = ia;
@@ -170,25 +207,34 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t &a, uint32_t &b, uint3
 // ---------------------------------------------------------------------------------------
 // The pairs, each at its supertile's start + the earlier workgroups' pairs there + its rank
 // among the workgroup's. Ranks: one bit per (supertile, Gaussian) in LDS, its prefix over the
-// words of a supertile, and a bit count inside the word. Rows: each thread computes the spans
-// of two supertile rows (16 tile rows) at a time into LDS, one row after the other from its
-// own first (lanes then waste no FP64 rows on each other's alignment), and builds its masks
-// from those.
-// Workgroup 0 writes the supertiles' (first chunk, chunks) and the count of chunks.
-// Bound by VALU issue (FP64 rows, mask assembly) at three waves per SIMD: 73 us at 1M Gaussians /
-// 1080p, 392 us at 2.5M / 3840x2160.
+// words of a supertile, and a bit count inside the word. Rows: read where the preprocess stored
+// them (16 bytes for a footprint of up to 16 x 16 tiles), else computed by the wave into LDS
+// (wave_row_spans; as many Gaussians at a time as fit, one at least). Masks: per supertile row
+// and four supertiles, each tile row's tiles as 32 bits, whose bytes are then the rows of the
+// four masks. Also writes the supertiles' (first chunk, chunks), the chunks' descriptors and
+// their count.
+// Bound by VALU issue (58% of the cycles) and the scattered 12-byte writes. Each thread computing
+// its rows in FP64 and assembling each mask bit range by bit range took 73 us at 1M Gaussians /
+// 1080p (1% of the footprints beyond 16 x 16 tiles) and 391 us at 2.5M / 3840x2160 (15%); this
+// 42 and 222, for 4 more bytes read and 12 fewer written per Gaussian by the preprocess.
 // ---------------------------------------------------------------------------------------
-constexpr int kRowHold = 2 * kSuper;
-
-__global__ __launch_bounds__(kPairBlock) void k_pair_place(
+__global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
     const uint32_t *__restrict__ ids, uint32_t *counters, const uint2 *__restrict__ srect,
-    const float4 *__restrict__ bin, Supers su, const uint32_t *__restrict__ scan, const uint32_t *__restrict__ tot,
-    int stride, uint32_t *__restrict__ pair_id, unsigned long long *__restrict__ pair_mask,
+    BinIn bin, Supers su, const uint32_t *__restrict__ scan, const uint32_t *__restrict__ tot, int stride, uint32_t *__restrict__ pair_id, unsigned long long *__restrict__ pair_mask,
     uint4 *__restrict__ chunks, uint2 *__restrict__ supers) {
-  __shared__ uint32_t s_bits[kSuperWindow][kPairWords + 1];
-  __shared__ uint16_t s_pre[kSuperWindow][kPairWords + 2];
-  __shared__ uint32_t s_row[kRowHold][kPairBlock];
-  __shared__ uint32_t s_first[kSuperWindow], s_goff[kSuperWindow], s_chunk[kSuperWindow], s_tot[kSuperWindow];
+  // word w of a supertile's bits at w ^ bits_at(s), which spreads 64 supertiles over the banks
+  __shared__ uint32_t s_bits[kSuperWindow][kPairWords];
+  __shared__ union {
+    uint8_t b[kPairWords];   // of the earlier words' bits, at most 224
+    uint2 v;
+  } s_pre[kSuperWindow];
+  __shared__ uint32_t s_goff[kSuperWindow];
+  __shared__ union {
+    uint32_t span[kPairWaves][kSpanHold];
+    uint4 chunk[kSuperWindow];   // first pair, pairs, first chunk, chunks
+  } s_u;
+  uint4 *s_chunk = s_u.chunk;
+  const auto bits_at = [](int s) { return (s >> 3) & (kPairWords - 1); };
   const uint32_t n = counters[kCntVisible];
   if (counters[kCntPairs] == 0u) return;
   const uint32_t nb = (n + kPairBlock - 1) / kPairBlock;
@@ -200,10 +246,22 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_place(
   r.load(make_uint2(0u, 0u));
   r.y1 = -1;
   uint32_t g = 0u;
+  unsigned long long v[3] = {0ull, 0ull, 0ull};
   if (j < n) {
     g = ids[j];
     r.load(srect[j]);
-    if (!r.full) r.load_footprint(bin, g, su.tiles_y);
+    if (r.boxed) {
+      // byte q of v is tile row q of the supertile rows from the footprint's first on
+      uint4 e = bin.spans[g];
+      e = make_uint4(e.x ^ kSpanNone, e.y ^ kSpanNone, e.z ^ kSpanNone, e.w ^ kSpanNone);   // rows beyond it: none
+      const int sh = 8 * (r.y0 % kSuper);
+      const unsigned long long lo = ((unsigned long long)e.y << 32) | e.x, hi = ((unsigned long long)e.w << 32) | e.z;
+      v[0] = lo << sh;
+      v[1] = (hi << sh) | (lo >> 1 >> (63 - sh));
+      v[2] = hi >> 1 >> (63 - sh);
+    } else if (!r.full) {
+      r.load_footprint(bin, g, su.tiles_y);
+    }
   }
   const int word = tid >> 5;
   const uint32_t bit = 1u << (tid & 31);
@@ -227,11 +285,8 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_place(
     for (int k = 0; k < kWinPer; ++k) {
       const int s = tid * kWinPer + k;
       const uint32_t nc = (t[k] + kChunk - 1) / kChunk;
-      s_first[s] = sp;
       s_goff[s] = sp + (w0 + s < w1 ? scan[(size_t)(w0 + s) * stride + b] : 0u);
-      s_chunk[s] = sc;
-      s_tot[s] = t[k];
-      if (b == 0u && w0 + s < w1) supers[w0 + s] = make_uint2(sc, nc);
+      s_chunk[s] = make_uint4(sp, t[k], sc, nc);
       sp += t[k];
       sc += nc;
 #pragma unroll
@@ -240,6 +295,13 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_place(
     carry_p += tp;
     carry_c += tc;
     __syncthreads();
+    // the chunks' descriptors: supertile s by workgroup s mod nb
+    for (uint32_t s = b + ((uint32_t)w0 > b ? ((uint32_t)w0 - b + nb - 1) / nb * nb : 0u); s < (uint32_t)w1; s += nb) {
+      const uint4 c = s_chunk[s - w0];
+      if (tid == 0) supers[s] = make_uint2(c.z, c.w);
+      for (uint32_t i = tid; i < c.w; i += kPairBlock)
+        chunks[c.z + i] = make_uint4(c.x + i * kChunk, min((uint32_t)kChunk, c.y - i * kChunk), s, 0u);
+    }
     for (int sy = r.y0 / kSuper; sy * kSuper <= r.y1; ++sy) {
       const int first = sy * su.nx;
       if (first >= w1 || first + su.nx <= w0) continue;
@@ -247,74 +309,101 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_place(
       r.columns(sy, su.tiles_x, c0, c1);
       c0 = max(c0, w0 - first);
       c1 = min(c1, w1 - 1 - first);
-      for (int c = c0; c <= c1; ++c) atomicOr(&s_bits[first + c - w0][word], bit);
+      for (int c = c0; c <= c1; ++c) {
+        const int s = first + c - w0;
+        atomicOr(&s_bits[s][word ^ bits_at(s)], bit);
+      }
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kWinPer; ++k) {
       const int s = tid + k * kPairBlock;
-      uint32_t acc = 0u;
+      uint32_t acc = 0u, p[2] = {0u, 0u};
 #pragma unroll
       for (int w = 0; w < kPairWords; ++w) {
-        s_pre[s][w] = (uint16_t)acc;
-        acc += (uint32_t)__popc(s_bits[s][w]);
+        p[w >> 2] |= acc << (8 * (w & 3));
+        acc += (uint32_t)__popc(s_bits[s][w ^ bits_at(s)]);
       }
+      s_pre[s].v = make_uint2(p[0], p[1]);
     }
     __syncthreads();
-    for (int sy = r.y0 / kSuper; sy * kSuper <= r.y1; sy += 2) {
-      const int row0 = sy * su.nx;
-      if (row0 >= w1 || row0 + 2 * su.nx <= w0) continue;
-      // spans of the tile rows of supertile rows sy and sy + 1, x0 | x1 << 16 (an empty row
-      // 1 | 0 << 16)
-      const int ya = max(r.y0, sy * kSuper), yb = min(r.y1, (sy + 2) * kSuper - 1);
-      for (int ty = ya; ty <= yb; ++ty) {
-        int a, c;
-        const bool ok = r.span(ty, su.tiles_x, a, c);
-        s_row[ty - sy * kSuper][tid] = ok ? (uint32_t)a | ((uint32_t)c << 16) : 1u;
-      }
+    // this wave's Gaussians, those whose rows fit the spans' room at a time
+    uint32_t *spans = s_u.span[tid >> 6];
+    bool pending = r.y1 >= r.y0;
+    while (__any(pending)) {
+      const uint32_t need = pending && !r.full && !r.boxed ? (uint32_t)(r.y1 - r.y0 + 1) : 0u;
+      const uint32_t upto = wave_incl_scan(need);   // every lane takes part
+      const bool now = pending && upto <= (uint32_t)kSpanHold;
+      const uint32_t rows = now ? need : 0u;
+      const uint32_t incl = wave_incl_scan(rows);
+      wave_row_spans(r.fp, r.y0, rows, incl, su.tiles_x, spans);
+      wave_lds_fence();
+      if (now) {
+        const uint32_t *mine = spans + (incl - rows);
+        for (int sy = r.y0 / kSuper; sy * kSuper <= r.y1; ++sy) {
+          const int first = sy * su.nx;
+          if (first >= w1 || first + su.nx <= w0) continue;
+          int ra[kSuper], re[kSuper];   // first and last column, first above last for none
+          int c0 = r.x0 / kSuper, c1 = r.x1 / kSuper;
+          if (r.boxed) {
+            const int k = sy - r.y0 / kSuper;
+            const unsigned long long x = (k == 0 ? v[0] : k == 1 ? v[1] : v[2]) ^ 0x0101010101010101ull;
+            const uint32_t xl = (uint32_t)x, xh = (uint32_t)(x >> 32);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int first = row0 + h * su.nx;
-        if ((sy + h) * kSuper > r.y1 || first >= w1 || first + su.nx <= w0) continue;
-        uint32_t rows[kSuper];
-        int u0 = 0x7FFFFFFF, u1 = -1;
+            for (int q = 0; q < kSuper; ++q) {
+              const uint32_t y = q < 4 ? xl : xh;
+              ra[q] = r.bx + (int)((y >> (8 * (q & 3))) & 15u);
+              re[q] = r.bx + (int)((y >> (8 * (q & 3) + 4)) & 15u);
+            }
+          } else {
+            int u0 = 0x7FFFFFFF, u1 = -1;
 #pragma unroll
-        for (int q = 0; q < kSuper; ++q) {
-          const int ty = (sy + h) * kSuper + q;
-          rows[q] = ty >= r.y0 && ty <= r.y1 ? s_row[h * kSuper + q][tid] : 1u;
-          const int a = (int)(rows[q] & 0xFFFFu), c = (int)(rows[q] >> 16);
-          if (a <= c) {
-            u0 = min(u0, a);
-            u1 = max(u1, c);
+            for (int q = 0; q < kSuper; ++q) {
+              const int ty = sy * kSuper + q;
+              const bool in = ty >= r.y0 && ty <= r.y1;
+              const uint32_t s = r.full ? (uint32_t)r.x0 | ((uint32_t)r.x1 << 16) : mine[in ? ty - r.y0 : 0];
+              ra[q] = in ? (int)(s & 0xFFFFu) : 1;
+              re[q] = in ? (int)(s >> 16) : 0;
+              u0 = ra[q] <= re[q] ? min(u0, ra[q]) : u0;
+              u1 = ra[q] <= re[q] ? max(u1, re[q]) : u1;
+            }
+            if (r.banded && !r.full) {
+              c0 = u0 / kSuper;
+              c1 = u1 < 0 ? -1 : u1 / kSuper;
+            }
+          }
+          c0 = max(c0, w0 - first);
+          c1 = min(c1, w1 - 1 - first);
+          for (int g0 = c0; g0 <= c1; g0 += 4) {
+            uint32_t bits[kSuper];   // the row's tiles of four supertiles
+#pragma unroll
+            for (int q = 0; q < kSuper; ++q) {
+              const int a = ra[q] - g0 * kSuper, e = re[q] - g0 * kSuper;
+              const uint32_t m = (~0u << min(max(a, 0), 31)) & (~0u >> (31 - min(max(e, 0), 31)));
+              bits[q] = a <= e && a < 32 && e >= 0 ? m : 0u;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              if (g0 + k > c1) break;
+              uint32_t m[2];
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const uint32_t *q = bits + 4 * h;   // byte k of the four rows
+                const uint32_t sel = (uint32_t)((4 + k) << 8 | k);
+                const uint32_t lo = __builtin_amdgcn_perm(q[1], q[0], sel), hi = __builtin_amdgcn_perm(q[3], q[2], sel);
+                m[h] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+              }
+              const int s = first + g0 + k - w0;
+              const uint32_t rank = s_pre[s].b[word] + (uint32_t)__popc(s_bits[s][word ^ bits_at(s)] & (bit - 1u));
+              const uint32_t p = s_goff[s] + rank;
+              pair_id[p] = g;
+              pair_mask[p] = ((unsigned long long)m[1] << 32) | m[0];
+            }
           }
         }
-        int c0 = r.x0 / kSuper, c1 = r.x1 / kSuper;
-        if (r.banded && !r.full) {
-          c0 = u0 / kSuper;
-          c1 = u1 < 0 ? -1 : u1 / kSuper;
-        }
-        c0 = max(c0, w0 - first);
-        c1 = min(c1, w1 - 1 - first);
-        for (int c = c0; c <= c1; ++c) {
-          uint32_t m[2] = {0u, 0u};
-#pragma unroll
-          for (int q = 0; q < kSuper; ++q) {
-            const int a = max((int)(rows[q] & 0xFFFFu) - c * kSuper, 0);
-            const int e = min((int)(rows[q] >> 16) - c * kSuper, kSuper - 1);
-            const uint32_t byte = a <= e ? (0xFFu >> (7 - e)) & (0xFFu << a) : 0u;
-            m[q >> 2] |= byte << (8 * (q & 3));
-          }
-          const int s = first + c - w0;
-          const uint32_t rank = s_pre[s][word] + (uint32_t)__popc(s_bits[s][word] & (bit - 1u));
-          const uint32_t p = s_goff[s] + rank;
-          pair_id[p] = g;
-          pair_mask[p] = ((unsigned long long)m[1] << 32) | m[0];
-          const uint32_t idx = p - s_first[s];
-          if (idx % kChunk == 0u)
-            chunks[s_chunk[s] + idx / kChunk] =
-                make_uint4(p, min((uint32_t)kChunk, s_tot[s] - idx), (uint32_t)(w0 + s), 0u);
-        }
+        pending = false;
       }
+      wave_lds_fence();
     }
     __syncthreads();
   }
@@ -480,7 +569,7 @@ __global__ __launch_bounds__(kChunk) void k_chunk_expand(const uint32_t *__restr
       before += k < w ? x : 0u;
       len += x;
     }
-    const uint32_t lbase = tb_incl_scan(len) - len;
+    const uint32_t lbase = wave_incl_scan(len) - len;
     if (w == 0) {
       s_lbase[lane] = lbase;
       s_len[lane] = len;
@@ -513,6 +602,17 @@ __global__ __launch_bounds__(kBlock) void k_tile_ids(const uint2 *__restrict__ r
   for (uint32_t i = r.x + threadIdx.x; i < r.y; i += kBlock) tile_ids[i] = blockIdx.x;
 }
 
+// The binning record of each rendered candidate (inspection): mu', conic, support bound, rectangle.
+__global__ __launch_bounds__(kBlock) void k_bin_records(int64_t n, const uint32_t *__restrict__ tiles,
+                                                        const uint2 *__restrict__ rect, BinIn in,
+                                                        float4 *__restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n || tiles[i] == 0u) return;
+  const uint2 r = rect[i];
+  out[2 * i] = in.xyab[i];
+  out[2 * i + 1] = make_float4(in.cop[i].x, in.qsup[i], __uint_as_float(r.x), __uint_as_float(r.y & kRectCorner));
+}
+
 static Supers supers_of(const DevCamera &cam) {
   Supers s;
   s.tiles_x = cam.tiles_x;
@@ -532,7 +632,7 @@ size_t pair_hist_bytes(const DevCamera &cam, int64_t n) {
 
 int64_t chunk_capacity(const DevCamera &cam, int64_t pairs) { return pairs / kChunk + supers_of(cam).n; }
 
-hipError_t launch_pair_offsets(const uint32_t *ids, const uint32_t *counters, const uint2 *srect, const float4 *bin,
+hipError_t launch_pair_offsets(const uint32_t *ids, const uint32_t *counters, const uint2 *srect, const BinIn &bin,
                                const DevCamera &cam, int64_t n, uint32_t *hist, uint32_t *scan, uint32_t *tot,
                                hipStream_t s) {
   if (n <= 0) return hipSuccess;
@@ -543,7 +643,7 @@ hipError_t launch_pair_offsets(const uint32_t *ids, const uint32_t *counters, co
   return launch_row_scan(counters + kCntVisible, hist, scan, tot, su.n, stride, kPairBlock, s);
 }
 
-hipError_t launch_pair_place(const uint32_t *ids, uint32_t *counters, const uint2 *srect, const float4 *bin,
+hipError_t launch_pair_place(const uint32_t *ids, uint32_t *counters, const uint2 *srect, const BinIn &bin,
                              const DevCamera &cam, int64_t n, const uint32_t *scan, const uint32_t *tot,
                              uint32_t *pair_id, unsigned long long *pair_mask, uint4 *chunks, uint2 *supers,
                              hipStream_t s) {
@@ -586,6 +686,14 @@ hipError_t launch_chunk_expand(const uint32_t *counters, const uint4 *chunks, co
 
 hipError_t launch_frame_totals(const FrameTotals &t, hipStream_t s) {
   hipLaunchKernelGGL(k_frame_totals, dim3(1), dim3(kBlock), 0, s, t);
+  return hipGetLastError();
+}
+
+hipError_t launch_bin_records(int64_t n, const uint32_t *tiles, const uint2 *rect, const BinIn &in, float4 *out,
+                              hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_bin_records, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, tiles, rect, in,
+                     out);
   return hipGetLastError();
 }
 

@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 from paper_2408_12894_amd import synth
-from parity import check_instances, check_keys
+from parity import check_instances, check_keys, unpack_rect
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -58,6 +58,26 @@ def _check(r, scene, w, h):
 def test_lists_at_the_edges(kind, n, w, h):
     print(f"[case] tile lists {kind} n={n} {w}x{h}", flush=True)
     _check(_renderer(), SCENES[kind](n), w, h)
+
+
+def _ladder(n, stretch, seed):
+    """Standard deviations from under a pixel to 80 pixels: footprints of 1 to about 30 tiles a
+    side, through the 16 x 16 tiles up to which their row spans are stored."""
+    sc = synth.uniform_scene(n, seed=seed, extent=1.2)
+    sc.log_scales[:] = np.linspace(-6.5, -0.4, n, dtype=np.float32)[:, None]
+    sc.log_scales[:, 0] += np.float32(stretch)
+    sc.opacity_logits[:] = np.linspace(3.0, -3.0, n, dtype=np.float32)[np.random.default_rng(seed).permutation(n)]
+    return sc
+
+
+@pytest.mark.parametrize("stretch,w,h", [(0.0, 512, 512), (1.2, 640, 480), (-3.0, 333, 700)])
+def test_footprints_around_the_stored_spans(stretch, w, h):
+    print(f"[case] footprint ladder stretch={stretch} {w}x{h}", flush=True)
+    view = _check(_renderer(), _ladder(600, stretch, 85), w, h)
+    vis = view["tiles_touched"] > 0
+    x0, y0, x1, y1 = unpack_rect(view["rect"][vis]).T
+    side = np.maximum(x1 - x0, y1 - y0) + 1
+    assert side.min() == 1 and (side == 16).any() and (side == 17).any() and side.max() > 18
 
 
 def test_buffers_grow_for_instances_or_pairs_alone():
