@@ -95,6 +95,8 @@ struct flod_ctx {
   unsigned long long *host_counts_dev = nullptr;
   uint32_t count_seq = 0;
   Saved saved;
+  bool far_depths = false;            // the last render had depths beyond the depth sort's three passes,
+                                      // so the next one launches four
   bool keep_backward = true;          // renders list their blended entries (flod_ctx_keep_backward_state)
   flod_stats stats{};
   // timing
@@ -351,7 +353,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     need(B_CHUNKS, 16 * n);
     need(B_CHUNK_CNT, 256 * n);
   };
-  const size_t hist_d = radix_hist_bytes(N), hist_p = pair_hist_bytes(cam, N);
+  const size_t hist_d = radix_hist_bytes(N, true), hist_p = pair_hist_bytes(cam, N);
   const size_t hist = hist_d > hist_p ? hist_d : hist_p;
   need(B_XYAB, 16 * (size_t)N);
   need(B_COP, 16 * (size_t)N);
@@ -369,7 +371,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   need(B_SPANS, 16 * (size_t)N);
   need(B_HIST, hist);
   need(B_SCAN, hist);
-  need(B_TOT, 4 * (size_t)(n_supers > kRadix ? n_supers : kRadix));
+  need(B_TOT, 4 * (size_t)(n_supers > kDepthRadix ? n_supers : kDepthRadix));
   need(B_SUPERS, 8 * (size_t)n_supers);
   need_chunks();
   need(B_TILE_LEN, 4 * (size_t)n_tiles);
@@ -397,6 +399,17 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     return FrameTotals{P<uint4>(c, B_BLOCKVIS), nb, counters, (unsigned long long)guard_k, (unsigned long long)guard_p,
                        to_host ? c->host_counts_dev : nullptr, seq};
   };
+  auto depth_sort = [&](bool far) {
+    uint32_t *dk[2] = {P<uint32_t>(c, B_DKEY0), P<uint32_t>(c, B_DKEY1)};
+    uint32_t *dv[2] = {P<uint32_t>(c, B_DVAL0), P<uint32_t>(c, B_DVAL1)};
+    const int64_t no_cap = 0xFFFFFFFEll;
+    uint4 *sums = P<uint4>(c, B_BLOCKVIS);
+    const DepthSort ds{P<uint32_t>(c, B_DEPTH), P<uint2>(c, B_RECT), P<uint2>(c, B_SRECT), sums, sums + nb,
+                       totals(speculate ? cap : no_cap, speculate ? cap_p : no_cap, direct), far};
+    if (N <= kSmallSort) return launch_depth_sort_small(ds, N, nb, dv[0], s);
+    return launch_radix_sort(dk, dv, counters + kCntVisible, N, 32, P<uint32_t>(c, B_HIST), P<uint32_t>(c, B_SCAN),
+                             P<uint32_t>(c, B_TOT), &dres, s, &ds);
+  };
   if (N > 0) {
     PreOut o;
     o.xyab = P<float4>(c, B_XYAB);
@@ -414,14 +427,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     if (launch_preprocess(p, o, s) != hipSuccess) return FLOD_ERR_DEVICE;
     tm.end();
     tm.begin(FLOD_STAGE_DEPTH_SORT);
-    uint32_t *dk[2] = {P<uint32_t>(c, B_DKEY0), P<uint32_t>(c, B_DKEY1)};
-    uint32_t *dv[2] = {P<uint32_t>(c, B_DVAL0), P<uint32_t>(c, B_DVAL1)};
-    const int64_t no_cap = 0xFFFFFFFEll;
-    const DepthSort ds{o.depth, o.rect, P<uint2>(c, B_SRECT), o.block_sums, o.block_sums + nb,
-                       totals(speculate ? cap : no_cap, speculate ? cap_p : no_cap, direct)};
-    if (launch_radix_sort(dk, dv, counters + kCntVisible, N, 32, P<uint32_t>(c, B_HIST), P<uint32_t>(c, B_SCAN),
-                          P<uint32_t>(c, B_TOT), &dres, s, &ds) != hipSuccess)
-      return FLOD_ERR_DEVICE;
+    if (depth_sort(c->far_depths) != hipSuccess) return FLOD_ERR_DEVICE;
     // the count read-back: written by the totals themselves (direct), else copied
     if (!direct && (hipMemcpyAsync(c->host_counters, counters, 24, hipMemcpyDeviceToHost, s) != hipSuccess ||
                     mark_stream(c, s) != hipSuccess))
@@ -475,18 +481,21 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   if (speculate && (st = tail()) != FLOD_OK) return st;
   int64_t n_vis = 0;
   unsigned long long K = 0, n_pairs = 0;
+  bool far = false;
   if (N > 0) {
     if (direct) {
-      if (wait_counts(c, s, seq, 5) != hipSuccess) return FLOD_ERR_DEVICE;
+      if (wait_counts(c, s, seq, 6) != hipSuccess) return FLOD_ERR_DEVICE;
       const volatile unsigned long long *w = c->host_counts;
       n_vis = (uint32_t)w[0];
       K = (unsigned long long)(uint32_t)w[1] | ((unsigned long long)(uint32_t)w[2] << 32);
       n_pairs = (unsigned long long)(uint32_t)w[3] | ((unsigned long long)(uint32_t)w[4] << 32);
+      far = (uint32_t)w[5] != 0u;
     } else {
       if (wait_marked(c) != hipSuccess) return FLOD_ERR_DEVICE;
       n_vis = reinterpret_cast<const uint32_t *>(c->host_counters)[kCntVisible];
       K = c->host_counters[kCntTotal64 / 2];
       n_pairs = c->host_counters[kCntPairs64 / 2];
+      far = reinterpret_cast<const uint32_t *>(c->host_counters)[kCntFar] != 0u;
     }
   }
   c->stats.n_candidates = N;
@@ -497,7 +506,11 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   c->stats.width = cam.W;
   c->stats.height = cam.H;
   if (K >= 0xFFFFFFFFull || n_pairs >= 0xFFFFFFFFull) return FLOD_ERR_OVERFLOW;
-  if (!speculate || (int64_t)K > cap || (int64_t)n_pairs > cap_p) {
+  // depths beyond the three passes that were launched: the order is wrong, and is taken again
+  const bool again = far && !c->far_depths && N > kSmallSort;
+  c->far_depths = far;
+  if (again && depth_sort(true) != hipSuccess) return FLOD_ERR_DEVICE;
+  if (again || !speculate || (int64_t)K > cap || (int64_t)n_pairs > cap_p) {
     if ((int64_t)K > cap || (int64_t)n_pairs > cap_p) {
       if ((int64_t)K > cap) {
         need(B_VALUES, 4 * (size_t)K);

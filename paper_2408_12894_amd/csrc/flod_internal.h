@@ -12,6 +12,13 @@ constexpr int kTile = FLOD_TILE;          // 16x16 pixel tiles
 constexpr int kBlock = 256;               // threads per workgroup (4 wave64)
 constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;   // 256 buckets per radix pass
+// The depth sort's digits: the bits of a rendered depth are at least kDepthBase (0.125; the near plane
+// is 0.2), and below 8192 they exceed it by less than 2^27: three passes of 9 bits. A frame with
+// a depth beyond takes four passes of 8 (kDepthFarBits). Three against four passes: 65 against
+// 78 us at 857k keys, 26 against 35 at 8k.
+constexpr int kDepthBits = 9, kDepthRadix = 1 << kDepthBits, kDepthFarBits = 31;
+constexpr uint32_t kDepthBase = 0x3E000000u;
+constexpr int64_t kSmallSort = 8192;      // candidates up to which one workgroup sorts the frame
 constexpr int kSortItems = 12;            // keys per thread in a radix pass (measured 8 / 12 / 16)
 constexpr int kSortTile = kBlock * kSortItems;   // 3072 keys per workgroup
 constexpr int kSortItemsSmall = 8;        // 2048-key workgroups for sorts below kRadixBigSort (2 / 4 / 8)
@@ -83,7 +90,8 @@ struct PreOut {
   uint32_t *tiles;    // tiles touched, 0 when culled or not selected
   uint2 *rect;        // tile rectangle and flags of rendered candidates (kRectFull ...)
   uint4 *spans;       // row spans of those with kRectBoxed (see kSpanNone)
-  uint4 *block_sums;  // per workgroup: visible candidates, tiles and (supertile, Gaussian) pairs
+  uint4 *block_sums;  // per workgroup: visible candidates, tiles, (supertile, Gaussian) pairs and
+                      // candidates beyond the depth sort's three passes
   unsigned long long *n_selected;   // per-level selected counts (may be null)
   float4 *shjac;      // three planes of n_total float4, per visible candidate the colour's Jacobian in
                       // the unit view direction, J[ch][a] row-major, then the three colours before the
@@ -125,6 +133,7 @@ enum : int {
   kCntPairs64 = 4,      // u64 count of (supertile, Gaussian) pairs (slots 4, 5)
   kCntPairs = 6,        // u32 count of pairs; 0 when instances or pairs exceed their buffers
   kCntChunks = 7,       // u32 count of chunks of pairs
+  kCntFar = 1,          // u32 count of visible candidates beyond the depth sort's three passes
   kCntKept = 8,         // u32 counts of the Gaussians a compaction keeps, one per level (slots 8 .. 15)
   kCntSlots = 16
 };
@@ -133,8 +142,8 @@ enum : int {
 // visible candidates, instances K and pairs P, to the device counters and, when host_out is
 // given (coherent host memory), to the host. kCntPairs receives P when K <= cap_k and
 // P <= cap_p and 0 otherwise: kernels sized for those capacities read it and then do nothing.
-// host_out receives five 64-bit words, each host_seq in its high half and in its low half the
-// visible count and the low and high halves of K and of P: system-scope stores of whole words,
+// host_out receives six 64-bit words, each host_seq in its high half and in its low half the
+// visible count, the low and high halves of K and of P, and the count of far ones: system-scope stores of whole words,
 // so a host that polls them sees every word either old or complete and needs neither a copy
 // nor an event.
 struct FrameTotals {
@@ -148,8 +157,8 @@ struct FrameTotals {
 
 __device__ __forceinline__ void frame_totals(const FrameTotals &t) {
   constexpr int U = 8, W = kBlock / 64;
-  __shared__ unsigned long long s_sum[3][W];
-  unsigned long long v = 0, k = 0, p = 0;
+  __shared__ unsigned long long s_sum[4][W];
+  unsigned long long v = 0, k = 0, p = 0, far = 0;
   for (int i0 = threadIdx.x; i0 < t.nb; i0 += kBlock * U) {
     uint4 x[U];   // loaded together
 #pragma unroll
@@ -162,6 +171,7 @@ __device__ __forceinline__ void frame_totals(const FrameTotals &t) {
       v += x[u].x;
       k += x[u].y;
       p += x[u].z;
+      far += x[u].w;
     }
   }
 #pragma unroll
@@ -169,31 +179,35 @@ __device__ __forceinline__ void frame_totals(const FrameTotals &t) {
     v += __shfl_xor(v, o, 64);
     k += __shfl_xor(k, o, 64);
     p += __shfl_xor(p, o, 64);
+    far += __shfl_xor(far, o, 64);
   }
   if ((threadIdx.x & 63) == 0) {
     s_sum[0][threadIdx.x >> 6] = v;
     s_sum[1][threadIdx.x >> 6] = k;
     s_sum[2][threadIdx.x >> 6] = p;
+    s_sum[3][threadIdx.x >> 6] = far;
   }
   __syncthreads();
   if (threadIdx.x != 0) return;
-  v = k = p = 0;
+  v = k = p = far = 0;
 #pragma unroll
   for (int w = 0; w < W; ++w) {
     v += s_sum[0][w];
     k += s_sum[1][w];
     p += s_sum[2][w];
+    far += s_sum[3][w];
   }
   t.counters[kCntVisible] = (uint32_t)v;
+  t.counters[kCntFar] = (uint32_t)far;
   *reinterpret_cast<unsigned long long *>(t.counters + kCntTotal64) = k;
   *reinterpret_cast<unsigned long long *>(t.counters + kCntPairs64) = p;
   t.counters[kCntPairs] = k <= t.cap_k && p <= t.cap_p ? (uint32_t)p : 0u;
   if (t.host_out) {
     const unsigned long long tag = (unsigned long long)t.host_seq << 32;
-    const unsigned long long w[5] = {tag | v, tag | (k & 0xFFFFFFFFull), tag | (k >> 32), tag | (p & 0xFFFFFFFFull),
-                                     tag | (p >> 32)};
+    const unsigned long long w[6] = {tag | v, tag | (k & 0xFFFFFFFFull), tag | (k >> 32), tag | (p & 0xFFFFFFFFull),
+                                     tag | (p >> 32), tag | far};
 #pragma unroll
-    for (int i = 0; i < 5; ++i) __hip_atomic_store(&t.host_out[i], w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    for (int i = 0; i < 6; ++i) __hip_atomic_store(&t.host_out[i], w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -219,7 +233,7 @@ hipError_t launch_scan_blocks(const uint32_t *in, unsigned long long *prefix, ui
                               unsigned long long *host_out, uint32_t host_seq, hipStream_t s,
                               const unsigned long long *extra = nullptr);
 int radix_items(int64_t n_max);        // keys per thread the radix sort of n_max keys uses
-size_t radix_hist_bytes(int64_t n_max);  // bytes of each of its hist and scan arrays
+size_t radix_hist_bytes(int64_t n_max, bool depth = false);  // bytes of each of its hist and scan arrays
 // The render's depth sort: the first pass reads keys[0, n_max) of every candidate, takes each
 // key's index as its value and skips keys equal to kDepthNone (it writes the count it kept to
 // *n_ptr, which the later passes read), its digit scan also takes the frame's totals, and the
@@ -231,7 +245,10 @@ struct DepthSort {
   const uint4 *sums;      // the preprocess's counts per workgroup
   uint4 *part;            // as many words of scratch: their sums per sort workgroup
   FrameTotals totals;     // its sums and nb are set to part's
+  bool far;               // some depth may be 8192 or more
 };
+// The same for n <= kSmallSort candidates in one launch; blocks: the preprocess's workgroups.
+hipError_t launch_depth_sort_small(const DepthSort &d, int64_t n, int blocks, uint32_t *vals_out, hipStream_t s);
 hipError_t launch_radix_sort(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_ptr,
                              int64_t n_max, int bits, uint32_t *hist, uint32_t *scan,
                              uint32_t *tot, int *result_buf, hipStream_t s, const DepthSort *depth = nullptr);

@@ -24,7 +24,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
     uint4 v;
   } s_box[kBlock];   // each thread's row spans, should they fit
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  bool vis = false;
+  bool vis = false, is_far = false;
   bool selected = false;
   int lvl = 0;
   uint32_t tiles = 0, pairs = 0;
@@ -136,7 +136,9 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
             o.xyab[i] = make_float4(hx, hy, ca, cb);
             o.cop[i] = make_float4(cc, opac, col[0], col[1]);
             o.blue[i] = make_float2(col[2], __uint_as_float(pack_mu_lo(pr.mx, pr.my, hx, hy)));
-            o.depth[i] = __float_as_uint((float)pr.tz);
+            const uint32_t key = __float_as_uint((float)pr.tz);
+            is_far = key - kDepthBase >= 1u << (3 * kDepthBits);
+            o.depth[i] = key;
             o.qsup[i] = qg;
             const uint32_t r0 = rx0 | ((uint32_t)fp.ty0 << 16), r1 = rx1 | ((uint32_t)fp.ty1 << 16);
             // the supertiles it will be listed in: the whole rectangle's while those are few,
@@ -167,8 +169,8 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
     }
   }
   // the workgroup's counts of visible candidates, tiles and pairs
-  __shared__ uint32_t s_sum[3][kBlock / 64];
-  const uint32_t cnt = (uint32_t)__popcll(__ballot(vis));
+  __shared__ uint32_t s_sum[4][kBlock / 64];
+  const uint32_t cnt = (uint32_t)__popcll(__ballot(vis)), far = (uint32_t)__popcll(__ballot(vis && is_far));
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) {
     tiles += __shfl_xor(tiles, d, 64);
@@ -178,15 +180,16 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
     s_sum[0][threadIdx.x >> 6] = cnt;
     s_sum[1][threadIdx.x >> 6] = tiles;
     s_sum[2][threadIdx.x >> 6] = pairs;
+    s_sum[3][threadIdx.x >> 6] = far;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint32_t t[3] = {0u, 0u, 0u};
+    uint32_t t[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
       for (int w = 0; w < kBlock / 64; ++w) t[k] += s_sum[k][w];
-    o.block_sums[blockIdx.x] = make_uint4(t[0], t[1], t[2], 0u);
+    o.block_sums[blockIdx.x] = make_uint4(t[0], t[1], t[2], t[3]);
   }
 }
 

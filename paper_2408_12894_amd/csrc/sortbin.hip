@@ -1,7 +1,8 @@
 // Sorting and scans: the stable radix sort (of the visible Gaussians by depth, and of the overlap
 // pruning's points by bucket), row scans of counts and bucket ranges.
 //
-// The depth sort's first pass reads every candidate's depth key in index order and drops the
+// A frame of up to kSmallSort candidates is depth-sorted by one workgroup. Else the depth sort's
+// first pass reads every candidate's depth key in index order and drops the
 // candidates not rendered (key kDepthNone), so it also compacts the visible set.
 //
 // The radix pass is a reduce-then-scan design (no inter-workgroup spinning, which would
@@ -10,6 +11,7 @@
 // (wave64 ballots over the digit bits), reorders them by digit in LDS and writes each
 // digit run contiguously.
 #include <algorithm>
+#include <type_traits>
 
 #include "project.h"
 
@@ -122,13 +124,14 @@ hipError_t launch_scan_blocks(const uint32_t *in, unsigned long long *prefix, ui
 // workgroup also adds up the preprocess's counts of its ITEMS workgroups (sums to part), so that
 // the one workgroup that takes the totals reads ITEMS times fewer (alone over all 17,149 of a
 // 4.39M-Gaussian stack it took 22 us).
-template <int ITEMS, bool FIRST>
+template <int RB, int ITEMS, bool FIRST>
 __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint32_t *keys, const uint32_t *n_ptr, uint32_t n_all,
                                                     int shift, uint32_t dmask, uint32_t *hist, int stride,
                                                     const uint4 *__restrict__ sums, uint4 *__restrict__ part) {
   constexpr uint32_t TILE = kBlock * ITEMS;
   static_assert(ITEMS <= 64, "one wave adds a workgroup's counts");
-  __shared__ uint32_t h[kRadix];
+  constexpr int DIGITS = 1 << RB;
+  __shared__ uint32_t h[DIGITS];
   const uint32_t n = FIRST ? n_all : *n_ptr;
   const uint32_t nb = (n + TILE - 1) / TILE;
   const uint32_t b = xcd_block(blockIdx.x);
@@ -140,14 +143,16 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint32_t *keys, const 
     const uint32_t idx = base + r * kBlock + threadIdx.x;
     kr[r] = idx < n ? keys[idx] : 0u;
   }
-  h[threadIdx.x] = 0;
+#pragma unroll
+  for (int k = 0; k < DIGITS; k += kBlock) h[k + threadIdx.x] = 0;
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r)
     if (base + r * kBlock + threadIdx.x < n && (!FIRST || kr[r] != kDepthNone))
-      atomicAdd(&h[(kr[r] >> shift) & dmask], 1u);
+      atomicAdd(&h[((FIRST ? kr[r] - kDepthBase : kr[r]) >> shift) & dmask], 1u);
   __syncthreads();
-  hist[(size_t)threadIdx.x * stride + b] = h[threadIdx.x];
+#pragma unroll
+  for (int k = 0; k < DIGITS; k += kBlock) hist[(size_t)(k + threadIdx.x) * stride + b] = h[k + threadIdx.x];
   if (FIRST && threadIdx.x < 64) {
     const uint32_t i = b * ITEMS + threadIdx.x;
     uint4 x = make_uint4(0u, 0u, 0u, 0u);
@@ -157,6 +162,7 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint32_t *keys, const 
       x.x += __shfl_xor(x.x, o, 64);
       x.y += __shfl_xor(x.y, o, 64);
       x.z += __shfl_xor(x.z, o, 64);
+      x.w += __shfl_xor(x.w, o, 64);
     }
     if (threadIdx.x == 0) part[b] = x;
   }
@@ -228,7 +234,7 @@ __global__ __launch_bounds__(kBlock) void k_rs_scan(const uint32_t *n_ptr, uint3
 // key's value is its index, keys equal to kDepthNone are dropped (the output is the rendered
 // candidates, compacted and ordered by the first digit), and workgroup 0 writes the count kept
 // to *n_out for the later passes.
-template <int ITEMS, bool RECTS, bool FIRST>
+template <int RB, int ITEMS, bool RECTS, bool FIRST>
 __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restrict__ keys_in,
                                                        const uint32_t *__restrict__ vals_in,
                                                        uint32_t *__restrict__ keys_out,
@@ -241,10 +247,11 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restric
   constexpr uint32_t TILE = kBlock * ITEMS;
   constexpr int WAVES = kBlock / 64;
   constexpr uint32_t WTILE = 64 * ITEMS;
+  constexpr int DIGITS = 1 << RB, DP = DIGITS / kBlock;   // thread t has digits DP t .. DP t + DP - 1
   __shared__ uint32_t s_keys[TILE];
   __shared__ uint32_t s_vals[TILE];
-  __shared__ uint32_t s_goff[kRadix];
-  __shared__ uint32_t s_wcnt[WAVES][kRadix];
+  __shared__ uint32_t s_goff[DIGITS];
+  __shared__ uint32_t s_wcnt[WAVES][DIGITS];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // the count first (grids are sized for the capacity, which can far exceed it); then the
   // tile's keys and values, loaded together with the digit offsets below, so that their
@@ -262,21 +269,40 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restric
   for (int r = 0; r < ITEMS; ++r) {
     const uint32_t li = (uint32_t)w * WTILE + (uint32_t)r * 64u + (uint32_t)lane;
     kr[r] = li < count ? keys_in[base + li] : (FIRST ? kDepthNone : 0u);
+    if (FIRST && kr[r] != kDepthNone) kr[r] -= kDepthBase;
     vr[r] = FIRST ? base + li : (li < count ? vals_in[base + li] : 0u);
   }
-  // digit bases over the whole array and this workgroup's local digit bases (the three
+  // digit bases over the whole array and this workgroup's local digit bases (the
   // loads issued together, ahead of the scans' barriers)
-  const uint32_t tot_d = tot[tid];
-  const uint32_t cnt = hist[(size_t)tid * stride + b];
-  const uint32_t sc = scan[(size_t)tid * stride + b];
-  uint32_t t_all;
-  const uint32_t dbase = block_excl_scan(tot_d, &t_all);
-  uint32_t t_loc;   // the keys this workgroup writes (FIRST: the rendered ones)
-  const uint32_t lbase = block_excl_scan(cnt, &t_loc);
-  if (FIRST && b == 0 && tid == 0) *n_out = t_all;
-  s_goff[tid] = dbase + sc - lbase;
+  uint32_t tot_d[DP], cnt[DP], sc[DP], sum_t = 0u, sum_c = 0u;
 #pragma unroll
-  for (int k = 0; k < WAVES; ++k) s_wcnt[k][tid] = 0;
+  for (int k = 0; k < DP; ++k) {
+    const int d = DP * tid + k;
+    tot_d[k] = tot[d];
+    cnt[k] = hist[(size_t)d * stride + b];
+    sc[k] = scan[(size_t)d * stride + b];
+  }
+#pragma unroll
+  for (int k = 0; k < DP; ++k) {
+    sum_t += tot_d[k];
+    sum_c += cnt[k];
+  }
+  uint32_t t_all;
+  uint32_t dbase = block_excl_scan(sum_t, &t_all);
+  uint32_t t_loc;   // the keys this workgroup writes (FIRST: the rendered ones)
+  const uint32_t lbase = block_excl_scan(sum_c, &t_loc);
+  if (FIRST && b == 0 && tid == 0) *n_out = t_all;
+  uint32_t lb = lbase;
+#pragma unroll
+  for (int k = 0; k < DP; ++k) {
+    s_goff[DP * tid + k] = dbase + sc[k] - lb;
+    dbase += tot_d[k];
+    lb += cnt[k];
+  }
+#pragma unroll
+  for (int k = 0; k < WAVES; ++k)
+#pragma unroll
+    for (int d = 0; d < DIGITS; d += kBlock) s_wcnt[k][d + tid] = 0;
   __syncthreads();
   const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
@@ -287,7 +313,7 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restric
     const uint32_t d = (key >> shift) & dmask;   // bits above the pass's digit are zero
     unsigned long long peers = __ballot(valid);
 #pragma unroll
-    for (int bit = 0; bit < kRadixBits; ++bit) {
+    for (int bit = 0; bit < RB; ++bit) {
       const bool set = (d >> bit) & 1u;
       const unsigned long long bb = __ballot(set);
       peers &= set ? bb : ~bb;
@@ -299,13 +325,15 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restric
   }
   __syncthreads();
   {
-    uint32_t acc = lbase;   // this thread's digit is tid
+    uint32_t acc = lbase;
 #pragma unroll
-    for (int k = 0; k < WAVES; ++k) {
-      const uint32_t c = s_wcnt[k][tid];
-      s_wcnt[k][tid] = acc;
-      acc += c;
-    }
+    for (int j = 0; j < DP; ++j)
+#pragma unroll
+      for (int k = 0; k < WAVES; ++k) {
+        const uint32_t c = s_wcnt[k][DP * tid + j];
+        s_wcnt[k][DP * tid + j] = acc;
+        acc += c;
+      }
   }
   __syncthreads();
 #pragma unroll
@@ -329,6 +357,149 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restric
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// The whole depth sort of a small frame in one workgroup: the keys stay in registers and LDS, the
+// passes are as many as the keys' range needs, and a second workgroup takes the frame's totals.
+// A frame of this size is a chain of launches, each mostly latency: the 12 launches of four 8-bit
+// passes took 43 us at 2000 candidates, this 11 (17 at 4096). Its time grows with the keys per
+// thread: 30 us at 8192, where the nine launches of three passes take 35 and hardly grow yet, so
+// the line lies there.
+// ---------------------------------------------------------------------------------------
+constexpr int kSmallThreads = 1024;
+
+template <int ITEMS>
+__global__ __launch_bounds__(kSmallThreads) void k_depth_sort_small(const uint32_t *__restrict__ depth, uint32_t n,
+                                                                    uint32_t *__restrict__ vals_out,
+                                                                    const uint2 *__restrict__ rect_of,
+                                                                    uint2 *__restrict__ rect_out, FrameTotals totals) {
+  constexpr int WAVES = kSmallThreads / 64, DIGITS = 1 << kDepthBits, SCAN_WAVES = DIGITS / 64;
+  constexpr uint32_t WTILE = 64 * ITEMS;
+  __shared__ uint32_t s_keys[kSmallThreads * ITEMS], s_vals[kSmallThreads * ITEMS];
+  __shared__ uint32_t s_wcnt[WAVES][DIGITS];
+  __shared__ uint32_t s_red[2][WAVES], s_scan[SCAN_WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (blockIdx.x == 1) {
+    if (tid < kBlock) frame_totals(totals);   // whole waves
+    return;
+  }
+  uint32_t kr[ITEMS], vr[ITEMS], rr[ITEMS];
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const uint32_t i = (uint32_t)w * WTILE + (uint32_t)r * 64u + (uint32_t)lane;
+    kr[r] = i < n ? depth[i] : kDepthNone;
+    vr[r] = i;
+  }
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    lo = min(lo, kr[r]);
+    hi = kr[r] != kDepthNone ? max(hi, kr[r]) : hi;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor(lo, o, 64));
+    hi = max(hi, (uint32_t)__shfl_xor(hi, o, 64));
+  }
+  if (lane == 0) {
+    s_red[0][w] = lo;
+    s_red[1][w] = hi;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < WAVES; ++k) {
+    lo = min(lo, s_red[0][k]);
+    hi = max(hi, s_red[1][k]);
+  }
+  const uint32_t range = hi > lo ? hi - lo : 0u;
+  uint32_t kept = n;
+  bool valid[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    valid[r] = kr[r] != kDepthNone;
+    kr[r] -= lo;
+  }
+  const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  for (int shift = 0; shift == 0 || (shift < 32 && (range >> shift) != 0u); shift += kDepthBits) {
+#pragma unroll
+    for (int d = 0; d < DIGITS; d += 64) s_wcnt[w][d + lane] = 0u;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const uint32_t d = (kr[r] >> shift) & (DIGITS - 1);
+      unsigned long long peers = __ballot(valid[r]);
+#pragma unroll
+      for (int bit = 0; bit < kDepthBits; ++bit) {
+        const bool set = (d >> bit) & 1u;
+        const unsigned long long bb = __ballot(set);
+        peers &= set ? bb : ~bb;
+      }
+      const uint32_t in_round = (uint32_t)__popcll(peers & lt);
+      const uint32_t prev = s_wcnt[w][d];
+      rr[r] = prev + in_round;
+      if (valid[r] && in_round == 0) s_wcnt[w][d] = prev + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    // thread d < DIGITS: digit d's keys before it, then per wave
+    uint32_t sum = 0u, inc = 0u;
+    if (w < SCAN_WAVES) {
+#pragma unroll
+      for (int k = 0; k < WAVES; ++k) sum += s_wcnt[k][tid];
+      inc = wave_incl_scan(sum);
+      if (lane == 63) s_scan[w] = inc;
+    }
+    __syncthreads();
+    if (w < SCAN_WAVES) {
+      uint32_t acc = inc - sum;
+#pragma unroll
+      for (int k = 0; k < SCAN_WAVES; ++k) acc += k < w ? s_scan[k] : 0u;
+#pragma unroll
+      for (int k = 0; k < WAVES; ++k) {
+        const uint32_t c = s_wcnt[k][tid];
+        s_wcnt[k][tid] = acc;
+        acc += c;
+      }
+    }
+    if (shift == 0) {
+      kept = 0u;
+#pragma unroll
+      for (int k = 0; k < SCAN_WAVES; ++k) kept += s_scan[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r)
+      if (valid[r]) {
+        const uint32_t pos = s_wcnt[w][(kr[r] >> shift) & (DIGITS - 1)] + rr[r];
+        s_keys[pos] = kr[r];
+        s_vals[pos] = vr[r];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const uint32_t i = (uint32_t)w * WTILE + (uint32_t)r * 64u + (uint32_t)lane;
+      valid[r] = i < kept;
+      kr[r] = valid[r] ? s_keys[i] : 0u;
+      vr[r] = valid[r] ? s_vals[i] : 0u;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const uint32_t i = (uint32_t)w * WTILE + (uint32_t)r * 64u + (uint32_t)lane;
+    if (valid[r]) {
+      vals_out[i] = vr[r];
+      rect_out[i] = rect_of[vr[r]];
+    }
+  }
+}
+
+hipError_t launch_depth_sort_small(const DepthSort &d, int64_t n, int blocks, uint32_t *vals_out, hipStream_t s) {
+  FrameTotals t = d.totals;
+  t.sums = d.sums;
+  t.nb = blocks;
+  const auto kernel = n <= 2 * kSmallThreads ? k_depth_sort_small<2> : n <= 4 * kSmallThreads ? k_depth_sort_small<4>
+                                                                                               : k_depth_sort_small<8>;
+  hipLaunchKernelGGL(kernel, dim3(2), dim3(kSmallThreads), 0, s, d.keys, (uint32_t)n, vals_out, d.rect_of, d.rect_out, t);
+  return hipGetLastError();
+}
+
 // Keys per thread from the sort's capacity (measured: 16 takes the 161M-key tile sort of level 5
 // at 3840x2160 from 2.05 to 1.83 ms, but is slower than 12 at 8.5M keys).
 int radix_items(int64_t n_max) {
@@ -340,7 +511,9 @@ static int64_t radix_stride(int64_t n_max) {
   return ((n_max + tile - 1) / tile + 7) & ~(int64_t)7;
 }
 
-size_t radix_hist_bytes(int64_t n_max) { return 4 * (size_t)kRadix * (size_t)radix_stride(n_max); }
+size_t radix_hist_bytes(int64_t n_max, bool depth) {
+  return 4 * (size_t)(depth ? kDepthRadix : kRadix) * (size_t)radix_stride(n_max);
+}
 
 static FrameTotals first_totals(const DepthSort &d, int blocks) {
   FrameTotals t = d.totals;
@@ -354,7 +527,7 @@ static FrameTotals first_totals(const DepthSort &d, int blocks) {
 // hold radix_hist_bytes(n_max) each (16-byte aligned). Workgroups take 2048 keys below
 // kRadixBigSort keys of capacity, 3072 up to kRadixHugeSort and 4096 beyond. `depth`: see
 // DepthSort.
-template <int ITEMS>
+template <int RB, int ITEMS>
 static void radix_passes(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_ptr, int64_t n_max, int bits,
                          uint32_t *hist, uint32_t *scan, uint32_t *tot, int *cur_out, const DepthSort *depth,
                          hipStream_t s) {
@@ -364,9 +537,8 @@ static void radix_passes(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_ptr, 
   const uint32_t n_all = (uint32_t)n_max;
   const unsigned grid = xcd_grid(nb_max);
   int cur = 0;
-  // the fewest passes of at most kRadixBits digit bits, the bits spread evenly over them (the
-  // 13-bit tile ids of a 1080p frame as 7 + 6 rather than 8 + 5 bits)
-  const int passes = (bits + kRadixBits - 1) / kRadixBits;
+  // the fewest passes of at most RB digit bits, the bits spread evenly over them
+  const int passes = (bits + RB - 1) / RB;
   for (int pass = 0, shift = 0; pass < passes; ++pass) {
     const int nbits = bits / passes + (pass < bits % passes ? 1 : 0);
     const uint32_t dmask = (1u << nbits) - 1u;
@@ -374,22 +546,22 @@ static void radix_passes(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_ptr, 
     const bool last = pass == passes - 1 && depth;
     const uint32_t *kin = first ? depth->keys : keys[cur];
     if (first)
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rs_hist<ITEMS, true>), dim3(grid), dim3(kBlock), 0, s, kin, n_ptr, n_all,
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rs_hist<RB, ITEMS, true>), dim3(grid), dim3(kBlock), 0, s, kin, n_ptr, n_all,
                          shift, dmask, hist, stride, depth->sums, depth->part);
     else
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rs_hist<ITEMS, false>), dim3(grid), dim3(kBlock), 0, s, kin, n_ptr, n_all,
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_rs_hist<RB, ITEMS, false>), dim3(grid), dim3(kBlock), 0, s, kin, n_ptr, n_all,
                          shift, dmask, hist, stride, nullptr, nullptr);
     // the first pass's workgroups cover all candidates; the later passes' the count it kept
     if (first)
-      hipLaunchKernelGGL(k_rs_scan<true>, dim3(kRadix + 1), dim3(kBlock), 0, s, nullptr, n_all, hist, scan, tot, stride,
-                         TILE, first_totals(*depth, nb_max));
+      hipLaunchKernelGGL(k_rs_scan<true>, dim3((1 << RB) + 1), dim3(kBlock), 0, s, nullptr, n_all, hist, scan, tot,
+                         stride, TILE, first_totals(*depth, nb_max));
     else
-      hipLaunchKernelGGL(k_rs_scan<false>, dim3(kRadix), dim3(kBlock), 0, s, n_ptr, n_all, hist, scan, tot, stride, TILE,
+      hipLaunchKernelGGL(k_rs_scan<false>, dim3(1 << RB), dim3(kBlock), 0, s, n_ptr, n_all, hist, scan, tot, stride, TILE,
                          FrameTotals{});
     const uint2 *rect_of = last ? depth->rect_of : nullptr;
     uint2 *rect_out = last ? depth->rect_out : nullptr;
-    auto kernel = first ? k_rs_scatter<ITEMS, false, true> : last ? k_rs_scatter<ITEMS, true, false>
-                                                                  : k_rs_scatter<ITEMS, false, false>;
+    auto kernel = first ? k_rs_scatter<RB, ITEMS, false, true> : last ? k_rs_scatter<RB, ITEMS, true, false>
+                                                                      : k_rs_scatter<RB, ITEMS, false, false>;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, s, kin, vals[cur], keys[cur ^ 1], vals[cur ^ 1], n_ptr,
                        n_all, n_ptr, shift, dmask, hist, scan, tot, stride, rect_of, rect_out);
     cur ^= 1;
@@ -402,12 +574,19 @@ hipError_t launch_radix_sort(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_p
                              int bits, uint32_t *hist, uint32_t *scan, uint32_t *tot, int *result_buf,
                              hipStream_t s, const DepthSort *depth) {
   *result_buf = 0;
+  if (depth) bits = depth->far ? kDepthFarBits : 3 * kDepthBits;
   if (n_max <= 0) return hipSuccess;
-  if (depth && bits <= kRadixBits) return hipErrorInvalidValue;   // its first and last passes differ
+  const auto run = [&](auto items) {
+    constexpr int I = decltype(items)::value;
+    if (depth && !depth->far)
+      radix_passes<kDepthBits, I>(keys, vals, n_ptr, n_max, bits, hist, scan, tot, result_buf, depth, s);
+    else
+      radix_passes<kRadixBits, I>(keys, vals, n_ptr, n_max, bits, hist, scan, tot, result_buf, depth, s);
+  };
   switch (radix_items(n_max)) {
-    case kSortItemsHuge: radix_passes<kSortItemsHuge>(keys, vals, n_ptr, n_max, bits, hist, scan, tot, result_buf, depth, s); break;
-    case kSortItems: radix_passes<kSortItems>(keys, vals, n_ptr, n_max, bits, hist, scan, tot, result_buf, depth, s); break;
-    default: radix_passes<kSortItemsSmall>(keys, vals, n_ptr, n_max, bits, hist, scan, tot, result_buf, depth, s); break;
+    case kSortItemsHuge: run(std::integral_constant<int, kSortItemsHuge>{}); break;
+    case kSortItems: run(std::integral_constant<int, kSortItems>{}); break;
+    default: run(std::integral_constant<int, kSortItemsSmall>{}); break;
   }
   return hipGetLastError();
 }
