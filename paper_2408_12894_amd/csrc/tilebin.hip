@@ -531,7 +531,12 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_starts(const uint32_t *_
 // ---------------------------------------------------------------------------------------
 // The list entries of one chunk (one workgroup): its masks transposed, each tile's pairs
 // (their 8-bit index in the chunk) staged in LDS in order, then every tile's run written with
-// consecutive stores by 16 lanes. 157.6M entries (631 MB) in 220 us, 8.4M in 23 us.
+// consecutive stores by 16 lanes. 157.6M entries (631 MB, 92 us at the rate of a fill) in 208 us,
+// 8.4M in 21 us, bound by VALU issue (placing the indices) and the two dependent LDS reads per
+// entry. Chunks by xcd_block, so that the runs of a tile's consecutive chunks meet in one L2 (212
+// against 220 us), the indices placed per 32-bit half (208). Waves storing each tile's entries
+// by ballot, without LDS, took 230 us there and 28 for the 8.4M; runs begun at a 64-byte
+// boundary 210 and 23.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kChunk) void k_chunk_expand(const uint32_t *__restrict__ counters,
                                                          const uint4 *__restrict__ chunks,
@@ -548,7 +553,7 @@ __global__ __launch_bounds__(kChunk) void k_chunk_expand(const uint32_t *__restr
   if (counters[kCntPairs] == 0u) return;
   const uint32_t nc = counters[kCntChunks];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
+  for (uint32_t c = xcd_block(blockIdx.x); c < nc; c += gridDim.x) {
     const uint4 d = chunks[c];
     const bool in = (uint32_t)tid < d.y;
     const unsigned long long m = in ? pair_mask[d.x + tid] : 0ull;
@@ -574,11 +579,9 @@ __global__ __launch_bounds__(kChunk) void k_chunk_expand(const uint32_t *__restr
       s_lbase[lane] = lbase;
       s_len[lane] = len;
     }
-    uint32_t k = lbase + before;
-    while (col) {
-      s_stage[k++] = (uint8_t)(w * 64 + __ffsll((long long)col) - 1);
-      col &= col - 1ull;
-    }
+    uint8_t *out = s_stage + lbase + before;
+    for (uint32_t x = (uint32_t)col; x; x &= x - 1u) *out++ = (uint8_t)(w * 64 + __builtin_ctz(x));
+    for (uint32_t x = (uint32_t)(col >> 32); x; x &= x - 1u) *out++ = (uint8_t)(w * 64 + 32 + __builtin_ctz(x));
     __syncthreads();
     const int q = tid >> 4, l16 = tid & 15;
 #pragma unroll
@@ -678,7 +681,7 @@ hipError_t launch_tile_starts(const uint32_t *tile_len, int n_tiles, uint2 *rang
 hipError_t launch_chunk_expand(const uint32_t *counters, const uint4 *chunks, const uint32_t *pair_id,
                                const unsigned long long *pair_mask, const uint32_t *prefix, const uint2 *ranges,
                                const DevCamera &cam, int64_t max_chunks, uint32_t *values, hipStream_t s) {
-  const unsigned grid = (unsigned)std::min<int64_t>(max_chunks, 8192);
+  const unsigned grid = xcd_grid(std::min<int64_t>(max_chunks, 8192));
   hipLaunchKernelGGL(k_chunk_expand, dim3(grid), dim3(kChunk), 0, s, counters, chunks, pair_id,
                      pair_mask, prefix, ranges, supers_of(cam), values);
   return hipGetLastError();
