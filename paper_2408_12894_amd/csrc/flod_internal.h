@@ -33,10 +33,11 @@ constexpr int kSpanBox = 16;              // largest footprint (tiles a side) wh
 constexpr int kPairRectMax = 16;          // largest rectangle (in supertiles) listed whole
 // A Gaussian's tile rectangle as the binning reads it: x0 | y0 << 16 and x1 | y1 << 16 (frames have
 // at most 1024 x 1024 tiles) with what else it has to know: the footprint is the whole rectangle;
-// its supertiles are listed row by row instead of the whole rectangle's; its row spans are stored
-// (kSpanNone), counted from the rectangle's first column or (BoxLeft) from the one before it.
-constexpr uint32_t kRectFull = 1u << 31, kRectBanded = 1u << 30, kRectBoxed = 1u << 29, kRectBoxLeft = 1u << 28;
-constexpr uint32_t kRectCorner = 0x0FFFFFFFu;
+// its supertiles are listed row by row instead of the whole rectangle's; its row spans, or of a
+// banded one its supertile rows' columns, are stored (kSpanNone), counted from a column that many
+// (four bits at kRectBefore of the first word) before the rectangle's first.
+constexpr uint32_t kRectFull = 1u << 31, kRectBanded = 1u << 30, kRectBoxed = 1u << 29;
+constexpr uint32_t kRectCorner = 0x0FFFFFFFu, kRectBefore = 10;
 constexpr size_t kGaussianBytes = (3 + 3 + 4 + 1 + FLOD_SH_COEFFS * 3) * 4;   // 236 B per stored Gaussian
 constexpr unsigned long long kPruneMaxScan = 1ull << 36;   // overlap-pruning neighbour-scan limit
 

@@ -22,7 +22,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
   __shared__ union {
     uint8_t b[kSpanBox];
     uint4 v;
-  } s_box[kBlock];   // each thread's row spans, should they fit
+  } s_box[kBlock], s_band[kBlock];   // each thread's row spans and supertile rows' columns, should they fit
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   bool vis = false, is_far = false;
   bool selected = false;
@@ -58,6 +58,7 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
           if (footprint(hx, hy, ca, cb, cc, support_span(qg), p.cam.tiles_y, fp)) {
             box_x0 = span_box_column(fp, p.cam.tiles_x);
             s_box[threadIdx.x].v = make_uint4(kSpanNone, kSpanNone, kSpanNone, kSpanNone);
+            s_band[threadIdx.x].v = make_uint4(kSpanNone, kSpanNone, kSpanNone, kSpanNone);
             for (int ty = fp.ty0; ty <= fp.ty1; ++ty) {
               int tx0, tx1;
               if (row_span(fp, ty, p.cam.tiles_x, tx0, tx1)) {
@@ -69,7 +70,9 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
                 bx1 = max(bx1, (uint32_t)tx1);
               }
               if ((ty % kSuper == kSuper - 1 || ty == fp.ty1) && bx0 <= bx1) {
-                band_pairs += bx1 / kSuper - bx0 / kSuper + 1u;
+                const uint32_t c0 = bx0 / kSuper - (uint32_t)(box_x0 / kSuper), c1 = bx1 / kSuper - (uint32_t)(box_x0 / kSuper);
+                s_band[threadIdx.x].b[(ty / kSuper - fp.ty0 / kSuper) & (kSpanBox - 1)] = (uint8_t)(c0 | (c1 << 4));
+                band_pairs += c1 - c0 + 1u;
                 bx0 = 0xFFFFu;
                 bx1 = 0u;
               }
@@ -148,11 +151,18 @@ __global__ __launch_bounds__(kBlock) void k_preprocess(PreParams p, PreOut o) {
             const bool banded = pairs > (uint32_t)kPairRectMax;
             if (banded) pairs = band_pairs;
             uint32_t flags = w * h == tiles ? kRectFull : banded ? kRectBanded : 0u;
-            if (flags == 0u && h <= (uint32_t)kSpanBox && (int)rx1 < box_x0 + kSpanBox && rx0 - (uint32_t)box_x0 <= 1u) {
+            uint32_t before = 0u;   // columns from the one counted from to the rectangle's first
+            if (flags == 0u && h <= (uint32_t)kSpanBox && (int)rx0 >= box_x0 && (int)rx1 < box_x0 + kSpanBox) {
               o.spans[i] = s_box[threadIdx.x].v;
-              flags = kRectBoxed | (box_x0 < (int)rx0 ? kRectBoxLeft : 0u);
+              flags = kRectBoxed;
+              before = rx0 - (uint32_t)box_x0;
+            } else if (flags == kRectBanded && fp.ty1 / kSuper - fp.ty0 / kSuper < kSpanBox && (int)rx0 >= box_x0 &&
+                       (int)rx1 / kSuper < box_x0 / kSuper + kSpanBox) {
+              o.spans[i] = s_band[threadIdx.x].v;
+              flags |= kRectBoxed;
+              before = rx0 / kSuper - (uint32_t)(box_x0 / kSuper);
             }
-            o.rect[i] = make_uint2(r0, r1 | flags);
+            o.rect[i] = make_uint2(r0 | (before << kRectBefore), r1 | flags);
           }
         }
       }

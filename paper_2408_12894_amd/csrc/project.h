@@ -207,7 +207,8 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
 
 // Row spans of a footprint of at most kSpanBox rows and columns in 16 bytes: byte r is row r's
 // (first column - x0) | (last column - x0) << 4, of an empty row kSpanNone. x0 is the column of
-// the support's left end, which is known before the rows; the rows mostly reach it.
+// the support's left end, which is known before the rows. A larger footprint that is listed row
+// by row stores its supertile rows' supertile columns in the same form.
 constexpr uint32_t kSpanNone = 0x01010101u;
 
 __device__ __forceinline__ int span_box_column(const Footprint &f, int tiles_x) {

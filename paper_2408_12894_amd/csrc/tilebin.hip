@@ -37,41 +37,41 @@ struct Supers {
   int nx, n;   // supertiles per row, in all
 };
 
-// One Gaussian's rows of tiles: its rectangle, and the row spans recomputed in FP64 exactly as
-// the preprocess counted them unless the footprint fills the rectangle.
+// One Gaussian's rows of tiles: its rectangle and, where neither the rectangle nor what the
+// preprocess stored says all, the footprint, whose rows come out as the preprocess counted them.
 struct PairRows {
   int x0, y0, x1, y1;
-  int bx;   // the column that the stored spans count from
-  bool full, banded, boxed;
+  int before;   // the stored spans count from x0 - before (of a banded one, from its supertile - before)
+  bool full, banded, boxed, bands;
   Footprint fp;
   __device__ __forceinline__ void load(uint2 r) {
-    x0 = (int)(r.x & 0xFFFFu);
+    x0 = (int)(r.x & 0x3FFu);
     y0 = (int)(r.x >> 16);
     x1 = (int)(r.y & 0xFFFFu);
     y1 = (int)((r.y >> 16) & 0xFFFu);
     full = (r.y & kRectFull) != 0u;
     banded = (r.y & kRectBanded) != 0u;
-    boxed = (r.y & kRectBoxed) != 0u;
-    bx = x0 - ((r.y & kRectBoxLeft) != 0u ? 1 : 0);
+    boxed = !banded && (r.y & kRectBoxed) != 0u;
+    bands = banded && (r.y & kRectBoxed) != 0u;
+    before = (int)(r.x >> kRectBefore) & 15;
   }
   __device__ __forceinline__ void load_footprint(const BinIn &bin, uint32_t g, int tiles_y) {
     const float4 a = bin.xyab[g];
     footprint(a.x, a.y, a.z, a.w, bin.cop[g].x, support_span(bin.qsup[g]), tiles_y, fp);
   }
-  __device__ __forceinline__ bool span(int ty, int tiles_x, int &tx0, int &tx1) const {
-    if (full) {
-      tx0 = x0;
-      tx1 = x1;
-      return true;
-    }
-    return row_span(fp, ty, tiles_x, tx0, tx1);
-  }
   // supertile columns of supertile row sy that the Gaussian is listed in (the preprocess
   // counted the same): the rectangle's, or of a banded one the union of the row spans
-  __device__ __forceinline__ void columns(int sy, int tiles_x, int &c0, int &c1) const {
+  __device__ __forceinline__ void columns(int sy, const BinIn &bin, uint32_t g, int tiles_x, int &c0, int &c1) const {
     c0 = x0 / kSuper;
     c1 = x1 / kSuper;
-    if (!banded || full) return;
+    if (!banded) return;
+    if (bands) {
+      const uint32_t byte = reinterpret_cast<const uint8_t *>(bin.spans + g)[sy - y0 / kSuper];
+      const int c = x0 / kSuper - before;
+      c0 = c + (int)(byte & 15u);
+      c1 = c + (int)(byte >> 4);
+      return;
+    }
     int u0 = 0x7FFFFFFF, u1 = -1;
     for (int ty = max(y0, sy * kSuper); ty <= min(y1, sy * kSuper + kSuper - 1); ++ty) {
       int a, b;
@@ -88,13 +88,16 @@ struct PairRows {
 // ---------------------------------------------------------------------------------------
 // Pairs of each workgroup's 256 Gaussians per supertile: hist[s * stride + block], for the
 // per-supertile scan over the blocks. Supertiles are taken in windows that fit the LDS counts
-// (one window up to 4K frames). Bound by the strided count writes: 17 us at 135 supertiles (1M
-// Gaussians, 1080p), 64 us at 510 (2.5M, 3840x2160).
+// (one window up to 4K frames). The columns of large footprints listed row by row are read where
+// the preprocess stored them: recomputing their rows in FP64, a serial chain of up to 10 us in
+// the few waves that have one, took 17 instead of 8 us at 1M Gaussians / 1080p (0.001% of them)
+// and 63 instead of 29 at 2.5M / 3840x2160 (0.14%). What remains there is the 4.3M strided
+// 4-byte writes; eight blocks per workgroup, writing 32 bytes at a time, gained nothing (29 us;
+// 15 instead of 11 at 2.1M / 1280x720).
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kPairBlock) void k_pair_hist(const uint32_t *__restrict__ ids,
                                                           const uint32_t *__restrict__ counters,
-                                                          const uint2 *__restrict__ srect,
-                                                          BinIn bin, Supers su,
+                                                          const uint2 *__restrict__ srect, BinIn bin, Supers su,
                                                           uint32_t *__restrict__ hist, int stride) {
   __shared__ uint32_t s_cnt[kSuperWindow];
   const uint32_t n = counters[kCntVisible];
@@ -107,9 +110,11 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_hist(const uint32_t *__rest
   PairRows r;
   r.load(make_uint2(0u, 0u));
   r.y1 = -1;
+  uint32_t g = 0u;
   if (j < n) {
     r.load(srect[j]);
-    if (r.banded && !r.full) r.load_footprint(bin, ids[j], su.tiles_y);
+    if (r.banded) g = ids[j];
+    if (r.banded && !r.bands) r.load_footprint(bin, g, su.tiles_y);
   }
   for (int w0 = 0; w0 < su.n; w0 += kSuperWindow) {
 #pragma unroll
@@ -120,7 +125,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_hist(const uint32_t *__rest
       const int first = sy * su.nx;
       if (first >= w1 || first + su.nx <= w0) continue;
       int c0, c1;
-      r.columns(sy, su.tiles_x, c0, c1);
+      r.columns(sy, bin, g, su.tiles_x, c0, c1);
       c0 = max(c0, w0 - first);
       c1 = min(c1, w1 - 1 - first);
       for (int c = c0; c <= c1; ++c) atomicAdd(&s_cnt[first + c - w0], 1u);
@@ -216,7 +221,7 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t &a, uint32_t &b, uint3
 // Bound by VALU issue (58% of the cycles) and the scattered 12-byte writes. Each thread computing
 // its rows in FP64 and assembling each mask bit range by bit range took 73 us at 1M Gaussians /
 // 1080p (1% of the footprints beyond 16 x 16 tiles) and 391 us at 2.5M / 3840x2160 (15%); this
-// 42 and 222, for 4 more bytes read and 12 fewer written per Gaussian by the preprocess.
+// 40 and 178, for 12 bytes fewer written per Gaussian by the preprocess.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
     const uint32_t *__restrict__ ids, uint32_t *counters, const uint2 *__restrict__ srect,
@@ -246,19 +251,19 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
   r.load(make_uint2(0u, 0u));
   r.y1 = -1;
   uint32_t g = 0u;
-  unsigned long long v[3] = {0ull, 0ull, 0ull};
   if (j < n) {
     g = ids[j];
     r.load(srect[j]);
     if (r.boxed) {
-      // byte q of v is tile row q of the supertile rows from the footprint's first on
+      // in place of a footprint its spans: byte q of the three words is tile row q of the supertile
+      // rows from its first on
       uint4 e = bin.spans[g];
       e = make_uint4(e.x ^ kSpanNone, e.y ^ kSpanNone, e.z ^ kSpanNone, e.w ^ kSpanNone);   // rows beyond it: none
       const int sh = 8 * (r.y0 % kSuper);
       const unsigned long long lo = ((unsigned long long)e.y << 32) | e.x, hi = ((unsigned long long)e.w << 32) | e.z;
-      v[0] = lo << sh;
-      v[1] = (hi << sh) | (lo >> 1 >> (63 - sh));
-      v[2] = hi >> 1 >> (63 - sh);
+      r.fp.qa = __longlong_as_double((long long)(lo << sh));
+      r.fp.det = __longlong_as_double((long long)((hi << sh) | (lo >> 1 >> (63 - sh))));
+      r.fp.ia = __longlong_as_double((long long)(hi >> 1 >> (63 - sh)));
     } else if (!r.full) {
       r.load_footprint(bin, g, su.tiles_y);
     }
@@ -306,7 +311,7 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
       const int first = sy * su.nx;
       if (first >= w1 || first + su.nx <= w0) continue;
       int c0, c1;
-      r.columns(sy, su.tiles_x, c0, c1);
+      r.columns(sy, bin, g, su.tiles_x, c0, c1);
       c0 = max(c0, w0 - first);
       c1 = min(c1, w1 - 1 - first);
       for (int c = c0; c <= c1; ++c) {
@@ -347,13 +352,14 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
           int c0 = r.x0 / kSuper, c1 = r.x1 / kSuper;
           if (r.boxed) {
             const int k = sy - r.y0 / kSuper;
-            const unsigned long long x = (k == 0 ? v[0] : k == 1 ? v[1] : v[2]) ^ 0x0101010101010101ull;
+            const double v = k == 0 ? r.fp.qa : k == 1 ? r.fp.det : r.fp.ia;
+            const unsigned long long x = (unsigned long long)__double_as_longlong(v) ^ 0x0101010101010101ull;
             const uint32_t xl = (uint32_t)x, xh = (uint32_t)(x >> 32);
 #pragma unroll
             for (int q = 0; q < kSuper; ++q) {
               const uint32_t y = q < 4 ? xl : xh;
-              ra[q] = r.bx + (int)((y >> (8 * (q & 3))) & 15u);
-              re[q] = r.bx + (int)((y >> (8 * (q & 3) + 4)) & 15u);
+              ra[q] = r.x0 - r.before + (int)((y >> (8 * (q & 3))) & 15u);
+              re[q] = r.x0 - r.before + (int)((y >> (8 * (q & 3) + 4)) & 15u);
             }
           } else {
             int u0 = 0x7FFFFFFF, u1 = -1;
@@ -367,7 +373,7 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
               u0 = ra[q] <= re[q] ? min(u0, ra[q]) : u0;
               u1 = ra[q] <= re[q] ? max(u1, re[q]) : u1;
             }
-            if (r.banded && !r.full) {
+            if (r.banded) {
               c0 = u0 / kSuper;
               c1 = u1 < 0 ? -1 : u1 / kSuper;
             }
@@ -613,7 +619,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_records(int64_t n, const uint32_
   if (i >= n || tiles[i] == 0u) return;
   const uint2 r = rect[i];
   out[2 * i] = in.xyab[i];
-  out[2 * i + 1] = make_float4(in.cop[i].x, in.qsup[i], __uint_as_float(r.x), __uint_as_float(r.y & kRectCorner));
+  out[2 * i + 1] = make_float4(in.cop[i].x, in.qsup[i], __uint_as_float(r.x & ~(15u << kRectBefore)), __uint_as_float(r.y & kRectCorner));
 }
 
 static Supers supers_of(const DevCamera &cam) {
