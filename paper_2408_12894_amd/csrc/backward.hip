@@ -71,10 +71,10 @@ constexpr int kLdsRound2MinTiles = 3072;
 // Without CHECK the caller guarantees that the walk has reached the entry in every pixel of the
 // wave.
 template <int PPT, bool CLAMP, bool CHECK>
-__device__ __forceinline__ bool decide(const float (&fy)[PPT], const int (&last)[PPT], int jpos, float my, float r,
+__device__ __forceinline__ uint32_t decide(const float (&fy)[PPT], const int (&last)[PPT], int jpos, float my, float r,
                                        float dx, float ck, float thr, float t, float (&dyv)[PPT], float (&aev)[PPT],
                                        float (&gmv)[PPT]) {
-  bool contrib = false;
+  uint32_t live = 0u;   // bit k: some lane's pixel k takes part
 #pragma unroll
   for (int k = 0; k < PPT; ++k) {
     const float dy = fy[k] - my;
@@ -88,9 +88,9 @@ __device__ __forceinline__ bool decide(const float (&fy)[PPT], const int (&last)
     } else {
       aev[k] = ok ? a0 : 0.0f;   // gmv: alpha itself (the caller reads aev)
     }
-    contrib = contrib || ok;
+    if (__ballot(ok) != 0ull) live |= 1u << k;
   }
-  return contrib;
+  return live;
 }
 
 // Per-entry reduction through LDS: component c of lane l at s_red[c * kRedStride + l]. The
@@ -242,7 +242,8 @@ __device__ __forceinline__ void bwd_part(
         auto entry = [&](auto clamp_tag) {
           constexpr bool CLAMP = decltype(clamp_tag)::value;
           float dyv[PPT], aev[PPT], gmv[PPT];
-          if (!__any(decide<PPT, CLAMP, CHECK>(fy, last, jpos, A.y, A.z, dx, B.x, BL.x, t, dyv, aev, gmv))) return;
+          const uint32_t live = decide<PPT, CLAMP, CHECK>(fy, last, jpos, A.y, A.z, dx, B.x, BL.x, t, dyv, aev, gmv);
+          if (live == 0u) return;
           {
           // the gradient arithmetic may contract into FMAs (the decision above must not: it
           // repeats the forward's, bit for bit)
@@ -258,6 +259,11 @@ __device__ __forceinline__ void bwd_part(
           float E0 = 0.0f, E1 = 0.0f, E2 = 0.0f;
 #pragma unroll
           for (int k = 0; k < PPT; ++k) {
+            // a band of rows that no lane's pixel takes part in adds exact zeros and keeps T and V:
+            // its half of the arithmetic is skipped (the kernel is bound by VALU issue; 1080p / 1M
+            // 165 -> 155 us, 720p / 500k 137 -> 129; two bands at a time 161 and 131). The registers
+            // stay at those of six waves per SIMD (at five the skip lost: 200 us)
+            if (PPT > 1 && !(live & (1u << k))) continue;
             const float alpha = aev[k], dy = dyv[k];
             const float Ti = T[k] * __builtin_amdgcn_rcpf(1.0f - alpha);
             const float wT = alpha * Ti;
@@ -355,7 +361,7 @@ constexpr float kBwdSplit4Factor = FLOD_BWD_SPLIT4;
 // walk the quarters, the next 2 (h2 - h4) the halves, the next n_tiles - h2 whole tiles, and
 // any past those have nothing to do.
 template <bool LDS_ROUND2>
-__global__ __launch_bounds__(64) void k_blend_bwd(
+__global__ __launch_bounds__(64, 6) void k_blend_bwd(
     const uint2 *__restrict__ ranges, const float4 *__restrict__ xyab, const float4 *__restrict__ cop,
     const float2 *__restrict__ blue, int W, int H, int tiles_x, int n_tiles, float bg0, float bg1, float bg2,
     const float *__restrict__ final_T, const int32_t *__restrict__ n_contrib, const float *__restrict__ dimg,
