@@ -1,8 +1,9 @@
 // Front-to-back alpha compositing (Preliminary section: eq. 2 and blending in depth order).
 //
-// One workgroup per 16x16 tile, one pixel per thread. The tile's
-// sorted list is consumed in batches of 256 entries (48 bytes each in LDS: mu' and its
-// residual, conic, opacity, colour, decoded once per entry). Per pixel:
+// One workgroup per 16x16 tile, one pixel per thread, one quadrant of 8x8 pixels per wave. The
+// tile's sorted list is consumed in batches of 256 entries (48 bytes each in LDS: mu' and its
+// residual, conic, opacity, colour, decoded once per entry), of which each wave walks those
+// that may reach its quadrant (reach_mask). Per pixel:
 //   q = d^T conic d (d = pixel centre - mu', mu' = hi + lo); skip if q > 9 (evaluated as
 //   k q in the completed-square form of conic_stage, k the scale of exp2)
 //   alpha = min(0.99, o exp(-q/2)); skip if alpha < 1/255
@@ -52,6 +53,34 @@ __device__ __forceinline__ void append_blended(const uint8_t *s_taken, const uin
   }
 }
 
+// The quadrants (8 x 8 pixels, bit = column + 2 row) of its tile that a staged entry may reach: those
+// whose box of pixel centres meets the ellipse P = l2o - thr, P = E dx^2 + C (dy + r dx)^2 = -k q. The
+// least P over the box lies on the side nearest the mean in x or the one nearest in y. The walk's
+// own P of a pixel, in FP32 from the same staged values, is off by a few ulp and by what the
+// rounding of dy + r dx makes, at most 2^-22 M of its terms' size M: its root is then at least the
+// root of the least P, less sqrt(C) 2^-22 M. The margins are four times that, 1e-5 in P and a
+// relative 1e-5, and only a comparison that holds drops a quadrant (so none for NaN).
+__device__ __forceinline__ uint32_t reach_mask(const float4 &a, const float4 &b, float thr) {
+  const float E = -a.w, C = -b.x, r = a.z;
+  if (!(E > 0.0f && C > 0.0f)) return 15u;
+  const float xl = 0.5f - a.x, yl = 0.5f - a.y;
+  const float M = fabsf(r) * fmaxf(fabsf(xl), fabsf(xl + 15.0f)) + fmaxf(fabsf(yl), fabsf(yl + 15.0f));
+  float lim = sqrtf(fmaxf(b.y - thr, 0.0f) + 1e-5f) + 0x1p-20f * sqrtf(C) * M;
+  lim = lim * lim * 1.00001f;
+  const float g = -C * r * __builtin_amdgcn_rcpf(fmaf(C * r, r, E));   // the least P of a row lies at dx = g dy
+  uint32_t mask = 0u;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float xa = xl + 8.0f * (float)(q & 1), ya = yl + 8.0f * (float)(q >> 1);
+    const float xe = fminf(fmaxf(0.0f, xa), xa + 7.0f), ye = fminf(fmaxf(0.0f, ya), ya + 7.0f);
+    const float y1 = fminf(fmaxf(-r * xe, ya), ya + 7.0f), x2 = fminf(fmaxf(g * ye, xa), xa + 7.0f);
+    const float v1 = fmaf(r, xe, y1), v2 = fmaf(r, x2, ye);
+    const float P1 = fmaf(E * xe, xe, C * v1 * v1), P2 = fmaf(E * x2, x2, C * v2 * v2);
+    if (!(P1 > lim && P2 > lim)) mask |= 1u << q;
+  }
+  return mask;
+}
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t or_dpp(uint32_t v) {
   return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
@@ -79,17 +108,19 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
 // has T kept and Tw = 0, so that further weights are 0. A weight of 0 may not meet a colour that
 // is not finite: batches that hold one select the sums instead.
 //
-// Groups (k_blend per frame, us): one entry at a time with branches, as it was; U = 4 branches;
-// U = 4, 8, 16 predicated
-//   2k at 128x128, 64 tiles              42.4 | 39.6 |   -   33.1  28.3
-//   levels 1-2 at 640x360, 920 tiles    153.5 | 142.6 |   -  107.3  95.4
-//   500k at 1280x720, 3,600 tiles        81.5 |  78.8 |  84.4  76.4  72.2
-//   1M at 1920x1080, 8,160 tiles        127.7 | 123.0 | 138.2 132.0 142.9
-//   levels 1-5 at 1920x1080             125.7 | 121.7 | 111.7 108.5 117.5
-//   2.5M (floor 0.0125) at 3840x2160    357.2 | 345.4 | 329.6 339.1 392.5
-// U = 16 takes 125 registers (four waves per SIMD), U = 8 78, branches with U = 4 64 (eight
-// waves); branches with U = 8 or 16 hold the group's colours in registers to no use (154, 254 us
-// at 1M). Skipping an entry that no pixel of the wave takes cost as much as it saved.
+// Groups (k_blend per frame, us): one entry at a time with branches over the whole list, as it was;
+// then over the entries that reach the wave's quadrant, U = 4 branches; U = 4, 8, 16 predicated
+//   2k at 128x128, 64 tiles              42.4 |   -   |  21.4  18.3  19.2
+//   levels 1-2 at 640x360, 920 tiles    153.5 |   -   | 101.0  89.5  96.2
+//   500k at 1280x720, 3,600 tiles        81.5 |   -   |  64.8  60.8  64.4
+//   1M at 1920x1080, 8,160 tiles        127.7 | 107.7 | 111.2 117.0    -
+//   levels 1-5 at 1920x1080             125.7 | 116.4 | 104.4 105.6 123.2
+//   2.5M (floor 0.0125) at 3840x2160    357.2 | 349.5 | 331.1 360.2 422.9
+// Over the whole list the best were 28.3 (U = 16), 95.4 (16), 72.2 (16), 123.0 (branches), 108.5 (8)
+// and 329.6 us (4): what a quadrant's list leaves out is a third of the entries where footprints
+// are a few tiles, a tenth where they are many. The more entries a group, the more registers it
+// holds (U = 16 four waves per SIMD). Branches with U = 8 or 16 hold the group's colours in
+// registers to no use (154, 254 us at 1M), U = 2 waits more often (116).
 //
 // COUNT: the caller wants each pixel's count of blended entries (n_blended).
 template <int U, bool PRED, bool COUNT>
@@ -105,18 +136,25 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
                                                          const uint32_t *__restrict__ order) {
   constexpr int NT = kTile * kTile;
   static_assert(kBatch == NT && kBatch % U == 0, "one staged entry per thread, whole groups");
-  __shared__ float4 s_a[kBatch];
-  __shared__ float4 s_b[kBatch];
-  __shared__ float4 s_c[kBatch];
+  constexpr int W4 = NT / 64;
+  // the staged entries, and behind them one that no pixel takes
+  __shared__ float4 s_a[kBatch + 1];
+  __shared__ float4 s_b[kBatch + 1];
+  __shared__ float4 s_c[kBatch + 1];
+  __shared__ __align__(16) uint16_t s_off[W4][kBatch + U];   // each wave's entries: byte offsets into s_a
+  __shared__ uint8_t s_reach[kBatch];                        // the waves each entry may reach
   __shared__ uint8_t s_taken[kBatch];
   __shared__ uint32_t s_id[kBatch];
   __shared__ uint32_t s_wcnt[NT / 64];
   const int tile = (int)order[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63;
   const int x0 = (tile % tiles_x) * kTile, y0 = (tile / tiles_x) * kTile;
-  const int px = x0 + (tid & (kTile - 1)), py = y0 + (tid >> 4);
+  // each wave a quadrant of 8 x 8 pixels
+  const int w = (int)__builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
+  const int qx = (w & 1) * 8 + (lane & 7), qy = (w >> 1) * 8 + (lane >> 3);
+  const int px = x0 + qx, py = y0 + qy;
   // pixel centres relative to the tile's corner
-  const float fx = (float)(tid & (kTile - 1)) + 0.5f, fy = (float)(tid >> 4) + 0.5f;
+  const float fx = (float)qx + 0.5f, fy = (float)qy + 0.5f;
   const bool inside = px < W && py < H;
   float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
   int last = 0, nbl = 0;
@@ -126,39 +164,66 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
   const int n = (int)(rg.y - rg.x);
   int last_start = -1;   // start of the last batch walked
   uint32_t n_bl = 0;     // blended entries listed so far
+  if (tid == 0) {
+    s_a[kBatch] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    s_b[kBatch] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    s_c[kBatch] = make_float4(INFINITY, 0.0f, 0.0f, 0.0f);
+  }
   for (int start = 0; start < n; start += kBatch) {
     if (__syncthreads_and(done)) break;
     // the previous batch's blended entries join the list, this batch's flags start at zero
     if (blended && start > 0)
       append_blended<NT>(s_taken, s_id, s_wcnt, start - kBatch, n, blended + rg.x, n_bl, tid);
     s_taken[tid] = 0;
+    bool finite = true;   // PRED: every staged colour is
+    uint32_t reach = 0u;
     if (start + tid < n) {
       const uint32_t g = values[rg.x + start + tid];
       s_id[tid] = g;
-      stage_entry(xyab, cop, blue, g, x0, y0, s_a[tid], s_b[tid], s_c[tid]);
-    } else if (start + tid < n + U) {
-      // past the list up to a whole group: entries that no pixel takes
-      s_a[tid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      s_b[tid] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      s_c[tid] = make_float4(INFINITY, 0.0f, 0.0f, 0.0f);
+      float4 a, b, c;
+      stage_entry(xyab, cop, blue, g, x0, y0, a, b, c);
+      s_a[tid] = a;
+      s_b[tid] = b;
+      s_c[tid] = c;
+      reach = reach_mask(a, b, c.x);
+      finite = isfinite(b.z) && isfinite(b.w) && isfinite(c.y);
     }
-    bool finite = true;   // PRED: every staged colour is
+    s_reach[tid] = (uint8_t)reach;
     if (PRED)
-      finite = __syncthreads_and(start + tid >= n ||
-                                 (isfinite(s_b[tid].z) && isfinite(s_b[tid].w) && isfinite(s_c[tid].y)));
+      finite = __syncthreads_and(finite);
     else
       __syncthreads();
-    // the count is the same in every lane (read from the first: the loop's exit test is then a
-    // scalar compare instead of a VALU one per entry)
-    const int cnt = __builtin_amdgcn_readfirstlane(min(kBatch, n - start));
+    // this wave's entries, in list order and filled up to a whole group
+    int cnt = 0;
+#pragma unroll
+    for (int k = 0; k < kBatch; k += 64) {
+      const bool in = (s_reach[k + lane] >> w) & 1u;
+      const unsigned long long m = __ballot(in);
+      if (in)
+        s_off[w][cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+            (uint16_t)((k + lane) * sizeof(float4));
+      cnt += (int)__popcll(m);
+    }
+    if (lane < U) s_off[w][cnt + lane] = (uint16_t)(kBatch * sizeof(float4));
+    wave_lds_fence();
+    int last_at = -1;   // the last entry taken in this batch, as a place in the wave's list
     for (int j0 = 0; j0 < cnt; j0 += U) {
       if (!__any(PRED ? Tw != 0.0f : !done)) break;
       float l[U], thr[U], c0[U], c1[U], c2[U];
+      uint32_t off[U / 2];   // two entries a word
+#pragma unroll
+      for (int k = 0; k < U / 2; k += 2) {
+        const uint2 o = *reinterpret_cast<const uint2 *>(&s_off[w][j0 + 2 * k]);
+        off[k] = o.x;
+        off[k + 1] = o.y;
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const float4 A = s_a[j0 + u];
-        const float4 B = s_b[j0 + u];
-        const float2 BL = *reinterpret_cast<const float2 *>(&s_c[j0 + u]);   // threshold on l, blue
+        const uint32_t e = (u & 1 ? off[u >> 1] >> 16 : off[u >> 1] & 0xFFFFu);
+        const float4 A = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_a) + e);
+        const float4 B = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_b) + e);
+        // threshold on l, blue
+        const float2 BL = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(s_c) + e);
         const float dx = fx - A.x;
         const float t = conic_column(A.w, dx, B.y);
         l[u] = conic_kq(B.x, A.z, dx, fy - A.y, t);   // k q + log2 o
@@ -200,11 +265,11 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
           walk(std::true_type{});
         else
           walk(std::false_type{});
-        if (bits) last = start + j0 + U + 1 - __ffs((int)bits);
+        if (bits) last_at = j0 + U - __ffs((int)bits);
         if (COUNT) nbl += __popc(bits);
         if (blended) {
           const uint32_t any = wave_or(bits);
-          if (lane < U && ((any >> (U - 1 - lane)) & 1u)) s_taken[j0 + lane] = 1;
+          if (lane < U && ((any >> (U - 1 - lane)) & 1u)) s_taken[s_off[w][j0 + lane] / sizeof(float4)] = 1;
         }
         done = Tw == 0.0f;
       } else
@@ -222,11 +287,12 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
         C1 = fmaf(wgt, c1[u], C1);
         C2 = fmaf(wgt, c2[u], C2);
         T = Tn;
-        last = start + j0 + u + 1;
+        last_at = j0 + u;
         if (COUNT) ++nbl;
-        s_taken[j0 + u] = 1;
+        s_taken[(u & 1 ? off[u >> 1] >> 16 : off[u >> 1] & 0xFFFFu) / sizeof(float4)] = 1;
       }
     }
+    if (last_at >= 0) last = start + (int)(s_off[w][last_at] / sizeof(float4)) + 1;
     last_start = start;
   }
   // the blended entries of the last batch walked (the walk blends nothing after it)
@@ -251,11 +317,11 @@ hipError_t launch_blend(const uint2 *ranges, const uint32_t *values, const float
                         int32_t *n_contrib, int32_t *n_blended, uint2 *blended, uint32_t *tile_blended,
                         const uint32_t *order, bool large, hipStream_t s) {
   const int n_tiles = cam.tiles_x * cam.tiles_y;
-  // 16 predicated entries per group while the frame has few waves for the device; beyond, eight
+  // eight predicated entries per group while the frame has few waves for the device; beyond, four
   // where the levels' scale floors make footprints large, else branches (see the table)
   const int way = n_tiles <= kFewTiles ? 0 : large ? 1 : 2;
-  auto kernel = way == 0 ? n_blended ? k_blend<16, true, true> : k_blend<16, true, false>
-                : way == 1 ? n_blended ? k_blend<8, true, true> : k_blend<8, true, false>
+  auto kernel = way == 0 ? n_blended ? k_blend<8, true, true> : k_blend<8, true, false>
+                : way == 1 ? n_blended ? k_blend<4, true, true> : k_blend<4, true, false>
                            : n_blended ? k_blend<4, false, true> : k_blend<4, false, false>;
   hipLaunchKernelGGL(kernel, dim3(n_tiles), dim3(kTile * kTile), 0, s, ranges, values, xyab, cop, blue, cam.W, cam.H,
                      cam.tiles_x, bg[0], bg[1], bg[2], image, final_T, n_contrib, n_blended, blended, tile_blended,

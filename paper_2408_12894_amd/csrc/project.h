@@ -205,6 +205,14 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return v;
 }
 
+// Orders a wave's LDS writes before its lanes' later reads of each other's.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Row spans of a footprint of at most kSpanBox rows and columns in 16 bytes: byte r is row r's
 // (first column - x0) | (last column - x0) << 4, of an empty row kSpanNone. x0 is the column of
 // the support's left end, which is known before the rows. A larger footprint that is listed row

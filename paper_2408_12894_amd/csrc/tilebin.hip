@@ -176,14 +176,6 @@ __device__ __forceinline__ void wave_row_spans(const Footprint &f, int y0, uint3
   }
 }
 
-// Orders a wave's LDS writes before its lanes' later reads of each other's.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Exclusive scan of two values per thread over the workgroup.
 __device__ __forceinline__ void block_excl_scan2(uint32_t &a, uint32_t &b, uint32_t &ta, uint32_t &tb) {
   __shared__ uint32_t s_a[kPairWaves], s_b[kPairWaves];
