@@ -1,7 +1,7 @@
 // Backward pass of the rasterizer (the rasterize-and-backpropagate step of Algorithm 1).
 //
-// Blend backward: one wave per tile (4 pixels per lane), walking the tile list back to
-// front from the last blended entry. The per-pixel transmittance before entry i is
+// Blend backward: one wave per tile (4 pixels per lane; small frames several waves per quarter of
+// a tile, see k_blend_bwd_few), walking the tile list back to front from the last blended entry. The per-pixel transmittance before entry i is
 // recovered from the saved final T as T_i = T_{i+1} / (1 - alpha_i) (alpha <= 0.99, FP32
 // reciprocal: about one rounding per blended contributor, so the relative error after m of
 // them grows like sqrt(m) ulp, far below the FP32 summation error of the gradients), and
@@ -56,11 +56,18 @@ __device__ __forceinline__ float row_sum16(float v) {
   return add_row_ror<1>(add_row_ror<2>(add_row_ror<4>(add_row_ror<8>(v))));
 }
 
-// Frames with at least this many tiles reduce each entry's gradient with a second LDS round,
-// smaller ones with DPP (see the kernel). With heavy tiles split and the priority by remaining
-// work, 720p (3,600 tiles) measured 0.141 ms with the LDS rounds against 0.144 with DPP (at
-// 6144, the earlier threshold, it had been the other way round).
-constexpr int kLdsRound2MinTiles = 3072;
+// Frames of up to this many tiles are walked by workgroups of four waves, of two (k_blend_bwd_few),
+// larger ones by one wave per tile (k_blend_bwd); us per kernel:
+//                                       wave per tile   four waves  two waves
+//   2k Gaussians at 253x187, 192 tiles             49         17          27
+//   20k at 400x300, 475                           159         38          60
+//   50k at 640x360, 920                           150         66          72
+//   100k at 800x600, 1,900                        174        100          92
+//   clusters, 200k at 800x600                     221        152         132
+//   clusters, 300k at 1000x700, 2,772             199        206         176
+//   clusters, 500k at 1280x720, 3,600             130        223         185
+// (Waves per tile: the first six with the reduction's second round in DPP, as it was for them.)
+constexpr int kFewBwdTiles4 = 1024, kFewBwdTiles2 = 3071;
 
 // The per-pixel decision of one entry, repeating the forward's bit for bit: the pixel takes
 // part when its walk has reached the entry and l = k q + log2 o reaches the entry's threshold
@@ -121,7 +128,7 @@ struct __align__(16) BwdShared {
   float4 a[kBwdBatch], b[kBwdBatch], c[kBwdBatch];   // the staged entries (see stage_entry;
                                                       // c.w holds the Gaussian's index)
   int pos[kBwdBatch];                                 // their positions in the tile's list
-  float red2[4 * kG2d];                               // its first round's partials (LDS form)
+  float red2[4 * kG2d];                               // its first round's partials
 };
 
 // One wave walks one part of a tile: the pixel rows r0 + lane / 16 + 4 k, k < PPT (PPT = 4:
@@ -131,7 +138,7 @@ struct __align__(16) BwdShared {
 // combination per step, so its error does not grow along the chain). Per entry each lane sums
 // its pixels' 9 gradient components in registers and the wave reduces them (see below) before
 // one atomic instruction adds the nine sums.
-template <int PPT, bool LDS_ROUND2>
+template <int PPT>
 __device__ __forceinline__ void bwd_part(
     BwdShared &sh, int tile, int r0, const uint2 *__restrict__ ranges, const float4 *__restrict__ xyab,
     const float4 *__restrict__ cop, const float2 *__restrict__ blue, int W, int H, int tiles_x, float bg0,
@@ -144,20 +151,14 @@ __device__ __forceinline__ void bwd_part(
   float4 *s_a = sh.a, *s_b = sh.b, *s_c = sh.c;
   int *s_pos = sh.pos;
   float *s_red = sh.red, *s_red2 = sh.red2;
-  constexpr int RS = LDS_ROUND2 ? kRedStride : 64;   // component stride of the reduction
   const int tid = threadIdx.x, lane = tid & 63;
   // float4 slots each lane reads in the reduction's rounds (clamped: lanes past the last
-  // slot read a valid one and discard it). LDS form: lane 4 c + h (c < 9, h < 4) sums the
-  // float4 slots h, h + 4, h + 8, h + 12 of component c in the first round, lane c < 9 the
-  // four partials of component c in the second; DPP form: slots lane, lane + 64, lane + 128
+  // slot read a valid one and discard it): lane 4 c + h (c < 9, h < 4) sums the float4 slots
+  // h, h + 4, h + 8, h + 12 of component c in the first round, lane c < 9 the four partials of
+  // component c in the second
   const int red_l36 = min(lane, 4 * kG2d - 1);
   const int red_r1 = (red_l36 >> 2) * (kRedStride / 4) + (red_l36 & 3);
-  const int red_hi = min(lane + 128, kG2d * 16 - 1), red_lo9 = min(lane, kG2d - 1);
-  // zero in a vector register, opaque to the compiler: added to the DPP form's lane-0 atomic
-  // address, which the compiler would otherwise see as uniform and send through its atomic
-  // combining path (a lane loop plus a wait for all outstanding memory operations per entry)
-  int vzero = 0;
-  asm volatile("" : "+v"(vzero));
+  const int red_lo9 = min(lane, kG2d - 1);
   const int x0 = (tile % tiles_x) * kTile, y0 = (tile / tiles_x) * kTile;
   const int px = x0 + (tid & (kTile - 1));
   const float fx = (float)(tid & (kTile - 1)) + 0.5f;   // pixel centres relative to the tile's corner
@@ -292,43 +293,24 @@ __device__ __forceinline__ void bwd_part(
           gr[5] = E0;
           {
             // the nine components summed over the wave: each lane writes its nine values to LDS
-            // component-major. LDS form: 36 lanes each add 16 values of one component (four float4
-            // reads), then lane c < 9 adds the four partials of component c to the Gaussian's 36-byte
-            // row (one atomic instruction). DPP form: each lane adds three float4 (4 lanes' values of
-            // components l / 16, 4 + l / 16 and, lanes below 16, 8), DPP sums over each row of 16 lanes
-            // follow (lanes 0, 16, 32, 48 then hold the sums; three atomic instructions). DPP costs
-            // about two VALU issue slots per operation, an LDS round a wait: the LDS form for frames
-            // with enough tiles to hide the wait (8 waves per SIMD at 1080p: 0.233 against 0.254 ms
-            // with a three-float4 first round), DPP for small ones (720p, 3.5 waves per SIMD: 0.238
-            // against 0.248 ms). The workgroup is one wave, so its barriers only order the LDS
-            // accesses.
+            // component-major, 36 lanes each add 16 values of one component (four float4 reads),
+            // then lane c < 9 adds the four partials of component c to the Gaussian's 36-byte row
+            // (one atomic instruction; 1080p 0.233 against 0.254 ms with a three-float4 first
+            // round). The workgroup is one wave, so its barriers only order the LDS accesses.
 #pragma unroll
-            for (int c = 0; c < kG2d; ++c) s_red[c * RS + lane] = gr[c];
+            for (int c = 0; c < kG2d; ++c) s_red[c * kRedStride + lane] = gr[c];
             __syncthreads();
             const float4 *r4 = reinterpret_cast<const float4 *>(s_red);
             const size_t row = (size_t)__float_as_uint(BL.w) * kG2d;
-            if (LDS_ROUND2) {
-              // lane 4 c + h: 16 values of component c (lanes 4 h .. 4 h + 3 of each group of 16)
-              const float4 q0 = r4[red_r1], q1 = r4[red_r1 + 4], q2 = r4[red_r1 + 8], q3 = r4[red_r1 + 12];
-              const float p = (((q0.x + q0.y) + (q0.z + q0.w)) + ((q1.x + q1.y) + (q1.z + q1.w))) +
-                              (((q2.x + q2.y) + (q2.z + q2.w)) + ((q3.x + q3.y) + (q3.z + q3.w)));
-              if (lane < 4 * kG2d) s_red2[lane] = p;
-              __syncthreads();
-              const float4 q = reinterpret_cast<const float4 *>(s_red2)[red_lo9];   // component lane (lanes 0..8)
-              const float x = (q.x + q.y) + (q.z + q.w);
-              if (lane < kG2d && x != 0.0f) atomicAdd(&g2d[row + lane], x);
-            } else {
-              const float4 ra = r4[lane], rb = r4[lane + 64], rc = r4[red_hi];
-              const float p0 = (ra.x + ra.y) + (ra.z + ra.w);   // component lane / 16
-              const float p1 = (rb.x + rb.y) + (rb.z + rb.w);   // component 4 + lane / 16
-              const float p2 = (rc.x + rc.y) + (rc.z + rc.w);   // component 8 (lanes 0..15)
-              const float s0 = row_sum16(p0), s1 = row_sum16(p1), s2 = row_sum16(p2);
-              if ((lane & 15) == 0) {
-                if (s0 != 0.0f) atomicAdd(&g2d[row + (lane >> 4)], s0);
-                if (s1 != 0.0f) atomicAdd(&g2d[row + 4 + (lane >> 4)], s1);
-                if (lane == 0 && s2 != 0.0f) atomicAdd(&g2d[row + 8 + vzero], s2);
-              }
-            }
+            // lane 4 c + h: 16 values of component c (lanes 4 h .. 4 h + 3 of each group of 16)
+            const float4 q0 = r4[red_r1], q1 = r4[red_r1 + 4], q2 = r4[red_r1 + 8], q3 = r4[red_r1 + 12];
+            const float p = (((q0.x + q0.y) + (q0.z + q0.w)) + ((q1.x + q1.y) + (q1.z + q1.w))) +
+                            (((q2.x + q2.y) + (q2.z + q2.w)) + ((q3.x + q3.y) + (q3.z + q3.w)));
+            if (lane < 4 * kG2d) s_red2[lane] = p;
+            __syncthreads();
+            const float4 q = reinterpret_cast<const float4 *>(s_red2)[red_lo9];   // component lane (lanes 0..8)
+            const float x = (q.x + q.y) + (q.z + q.w);
+            if (lane < kG2d && x != 0.0f) atomicAdd(&g2d[row + lane], x);
           }
           }
         };
@@ -340,6 +322,148 @@ __device__ __forceinline__ void bwd_part(
     };
     walk(std::true_type{}, cnt, nlow);
     walk(std::false_type{}, nlow, 0);
+  }
+}
+
+// Small frames: a workgroup of WV waves per quarter of a tile (4 rows, one pixel per lane). The
+// device has few waves per SIMD then, and one that walks a tile by itself sets the kernel's time
+// by its heaviest tile: about 650 cycles per entry, issue of a single wave and the reduction's LDS
+// round, whether it has four pixels per lane or one and whether entries are taken singly or in
+// fours. Here the waves share the entries: of the next WV kFewGroup each takes kFewGroup. What
+// passes from entry to entry, T and V, is a product and an affine step per entry, so each wave
+// first forms its entries' as one step, the waves exchange those through LDS, and each walks
+// its own entries from its own T and V. See kFewBwdTiles4 for the times.
+constexpr int kFewGroup = 4;
+
+template <int WV>
+struct __align__(16) BwdFewShared {
+  float red[WV][kFewGroup * kG2d * 64];                // a wave's reduction: component-major, one value per lane
+  float4 a[kBwdBatch], b[kBwdBatch], c[kBwdBatch];    // the staged entries (see stage_entry)
+  int2 pos[kBwdBatch];                                 // their list positions and Gaussians
+  float comp[2][WV][3][64];                            // what each wave's entries do to T and V
+};
+
+template <int WV>
+__global__ __launch_bounds__(64 * WV) void k_blend_bwd_few(
+    const uint2 *__restrict__ ranges, const float4 *__restrict__ xyab, const float4 *__restrict__ cop,
+    const float2 *__restrict__ blue, int W, int H, int tiles_x, int n_tiles, float bg0, float bg1, float bg2,
+    const float *__restrict__ final_T, const int32_t *__restrict__ n_contrib, const float *__restrict__ dimg,
+    float *__restrict__ g2d, const uint2 *__restrict__ blended, const uint32_t *__restrict__ tile_blended,
+    const uint32_t *__restrict__ order) {
+  constexpr int U = kFewGroup, C = kG2d;
+  static_assert(U * C <= 64 && (U * C) % 4 == 0 && U * C / 4 <= 16, "one sum per lane");
+  static_assert(kBwdBatch % (WV * U) == 0, "whole steps");
+  __shared__ BwdFewShared<WV> sh;
+  const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float *red = sh.red[w];
+  const int tile = (int)order[blockIdx.x >> 2], r0 = ((int)blockIdx.x & 3) * (kTile / 4);
+  const int x0 = (tile % tiles_x) * kTile, y0 = (tile / tiles_x) * kTile;
+  const int px = x0 + (lane & (kTile - 1)), py = y0 + r0 + (lane >> 4);
+  const float fx = (float)(px - x0) + 0.5f, fy = (float)(py - y0) + 0.5f;
+  const size_t plane = (size_t)W * H;
+  const uint2 rg = ranges[tile];
+  const int list_len = (int)(rg.y - rg.x);
+  const int n_bl = min((int)tile_blended[tile], list_len);
+  float T = 1.0f, V = 0.0f, d0 = 0.0f, d1 = 0.0f, d2 = 0.0f;   // T and V after the next step's entries
+  int last = 0;
+  if (px < W && py < H) {
+    const size_t pix = (size_t)py * W + px;
+    T = final_T[pix];
+    last = min(max(n_contrib[pix], 0), list_len);
+    d0 = dimg[pix];
+    d1 = dimg[plane + pix];
+    d2 = dimg[2 * plane + pix];
+    V = d0 * bg0 + d1 * bg1 + d2 * bg2;
+  }
+  // this lane's sum of a group: component cc of entry ce
+  const int c_of = 4 * (lane & 15) + (lane >> 4), ce = min(c_of / C, U - 1), cc = c_of % C;
+  int buf = 0;
+  for (int end = n_bl; end > 0; end -= kBwdBatch) {
+    const int start = max(0, end - kBwdBatch), cnt = end - start;
+    lds_barrier();
+    if (w == 0 && lane < cnt) {
+      const uint2 pe = blended[rg.x + start + lane];   // (list position, Gaussian)
+      sh.pos[lane] = make_int2((int)pe.x, (int)pe.y);
+      stage_entry(xyab, cop, blue, pe.y, x0, y0, sh.a[lane], sh.b[lane], sh.c[lane]);
+    }
+    lds_barrier();
+    for (int j0 = cnt - 1; j0 >= 0; j0 -= WV * U) {
+      const int j1 = j0 - w * U;   // this wave's entries: j1, j1 - 1, ...; those below 0 are taken by no pixel
+      float al[U], gm[U], dx[U], dy[U], dcc[U];
+      bool some = false;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = max(j1 - u, 0);
+        const float4 A = sh.a[j], B = sh.b[j];
+        const float2 BL = *reinterpret_cast<const float2 *>(&sh.c[j]);   // threshold on l, blue
+        const int pos = sh.pos[j].x;
+        dx[u] = fx - A.x;
+        dy[u] = fy - A.y;
+        const float t = conic_column(A.w, dx[u], B.y);
+        const float l = conic_kq(B.x, A.z, dx[u], dy[u], t);   // the forward's decision, bit for bit
+        const float a0 = alpha_from_log2(l);
+        const bool ok = j1 - u >= 0 && pos < last && l >= BL.x;
+        al[u] = ok ? fminf(kAlphaMax, a0) : 0.0f;
+        gm[u] = ok && a0 <= kAlphaMax ? a0 : 0.0f;
+        dcc[u] = fmaf(d0, B.z, fmaf(d1, B.w, d2 * BL.y));      // dL/dC . c
+        some = some || ok;
+      }
+      const bool any = __any(some);
+      float inv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) inv[u] = __builtin_amdgcn_rcpf(1.0f - al[u]);
+      // the group as one step: T -> P T, V -> Q V + R; the earlier waves' steps give this wave's
+      // T and V, all of them the next step's (every wave keeps its own copy)
+      float P = 1.0f, Q = 1.0f, R = 0.0f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        P *= inv[u];
+        Q = fmaf(-al[u], Q, Q);
+        R = fmaf(al[u], dcc[u] - R, R);
+      }
+      float(*comp)[3][64] = sh.comp[buf];   // two buffers: one barrier a step
+      comp[w][0][lane] = P;
+      comp[w][1][lane] = Q;
+      comp[w][2][lane] = R;
+      lds_barrier();
+      buf ^= 1;
+      float Ti = T, Vi = V;
+#pragma unroll
+      for (int v = 0; v < WV; ++v) {
+        if (v == w) {
+          Ti = T;
+          Vi = V;
+        }
+        T *= comp[v][0][lane];
+        V = fmaf(comp[v][1][lane], V, comp[v][2][lane]);
+      }
+      if (!any) continue;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        Ti *= inv[u];
+        const float wT = al[u] * Ti, diff = dcc[u] - Vi;
+        const float e = (Ti * diff) * gm[u];
+        Vi = fmaf(al[u], diff, Vi);
+        const float ex = e * dx[u], ey = e * dy[u];
+        const float g[C] = {ex, ey, ex * dx[u], ey * dx[u], ey * dy[u], e, wT * d0, wT * d1, wT * d2};
+#pragma unroll
+        for (int c = 0; c < C; ++c) red[(u * C + c) * 64 + lane] = g[c];
+      }
+      wave_lds_fence();
+      // each read four values of four components, 16 lanes each; then lane 16 r + i keeps the
+      // sum of component 4 i + r
+      const float4 *r4 = reinterpret_cast<const float4 *>(red);
+      float mine = 0.0f;
+#pragma unroll
+      for (int i = 0; i < U * C / 4; ++i) {
+        const float4 q = r4[i * 64 + lane];
+        const float x = row_sum16((q.x + q.y) + (q.z + q.w));
+        mine = (lane & 15) == i ? x : mine;
+      }
+      const int g = sh.pos[max(j1 - ce, 0)].y;
+      if (c_of < U * C && mine != 0.0f) atomicAdd(&g2d[(size_t)(uint32_t)g * C + cc], mine);
+      wave_lds_fence();
+    }
   }
 }
 
@@ -360,7 +484,6 @@ constexpr float kBwdSplit4Factor = FLOD_BWD_SPLIT4;
 // pixel per lane), then h2 - h4 (h2 = order[n_tiles]) split in two; workgroups 0 .. 4 h4 - 1
 // walk the quarters, the next 2 (h2 - h4) the halves, the next n_tiles - h2 whole tiles, and
 // any past those have nothing to do.
-template <bool LDS_ROUND2>
 __global__ __launch_bounds__(64, 6) void k_blend_bwd(
     const uint2 *__restrict__ ranges, const float4 *__restrict__ xyab, const float4 *__restrict__ cop,
     const float2 *__restrict__ blue, int W, int H, int tiles_x, int n_tiles, float bg0, float bg1, float bg2,
@@ -372,31 +495,29 @@ __global__ __launch_bounds__(64, 6) void k_blend_bwd(
   const int b = (int)blockIdx.x;
   const int b2 = b - 4 * h4, b1 = b2 - 2 * (h2 - h4);
   if (b < 4 * h4)
-    bwd_part<1, LDS_ROUND2>(sh, (int)order[b >> 2], (b & 3) * (kTile / 4), ranges, xyab, cop, blue, W, H, tiles_x,
+    bwd_part<1>(sh, (int)order[b >> 2], (b & 3) * (kTile / 4), ranges, xyab, cop, blue, W, H, tiles_x,
                             bg0, bg1, bg2, final_T, n_contrib, dimg, g2d, blended, tile_blended);
   else if (b1 < 0)
-    bwd_part<2, LDS_ROUND2>(sh, (int)order[h4 + (b2 >> 1)], (b2 & 1) * (kTile / 2), ranges, xyab, cop, blue, W, H,
+    bwd_part<2>(sh, (int)order[h4 + (b2 >> 1)], (b2 & 1) * (kTile / 2), ranges, xyab, cop, blue, W, H,
                             tiles_x, bg0, bg1, bg2, final_T, n_contrib, dimg, g2d, blended, tile_blended);
   else if (b1 < n_tiles - h2)
-    bwd_part<4, LDS_ROUND2>(sh, (int)order[h2 + b1], 0, ranges, xyab, cop, blue, W, H, tiles_x, bg0, bg1, bg2,
+    bwd_part<4>(sh, (int)order[h2 + b1], 0, ranges, xyab, cop, blue, W, H, tiles_x, bg0, bg1, bg2,
                             final_T, n_contrib, dimg, g2d, blended, tile_blended);
 }
 
-template <bool LDS_ROUND2>
-static void launch_blend_bwd_t(const uint2 *ranges, const float4 *xyab, const float4 *cop, const float2 *blue,
+template <class Kernel>
+static void launch_blend_bwd_t(Kernel kernel, int grid, int threads, const uint2 *ranges, const float4 *xyab, const float4 *cop, const float2 *blue,
                                const DevCamera &cam, const float bg[3], const float *final_T, const int32_t *n_contrib,
                                const float *dL_dimage, float *g2d, const uint2 *blended, const uint32_t *tile_blended,
                                const uint32_t *order, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   const int n_tiles = cam.tiles_x * cam.tiles_y;
-  const int grid = n_tiles + bwd_split_extra(n_tiles);
-  auto kernel = k_blend_bwd<LDS_ROUND2>;
   if (ev_start || ev_stop) {
     // timed from the kernel's own dispatch: no event packets between it and its neighbours
-    hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, ev_start, ev_stop, 0, ranges, xyab, cop, blue, cam.W,
+    hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, ev_start, ev_stop, 0, ranges, xyab, cop, blue, cam.W,
                           cam.H, cam.tiles_x, n_tiles, bg[0], bg[1], bg[2], final_T, n_contrib, dL_dimage, g2d,
                           blended, tile_blended, order);
   } else {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, ranges, xyab, cop, blue, cam.W, cam.H, cam.tiles_x,
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, ranges, xyab, cop, blue, cam.W, cam.H, cam.tiles_x,
                        n_tiles, bg[0], bg[1], bg[2], final_T, n_contrib, dL_dimage, g2d, blended, tile_blended,
                        order);
   }
@@ -446,12 +567,17 @@ hipError_t launch_blend_bwd(const uint2 *ranges, const float4 *xyab, const float
                      CountCost{tile_blended}, n_tiles, order,
                      TileSplit{kBwdSplitFactor, kBwdSplit4Factor, split_cap2(n_tiles), split_cap4(n_tiles)}, g2d,
                      n_g2d);
-  if (n_tiles >= kLdsRound2MinTiles)
-    launch_blend_bwd_t<true>(ranges, xyab, cop, blue, cam, bg, final_T, n_contrib, dL_dimage, g2d, blended,
-                             tile_blended, order, s, ev_start, ev_stop);
+  const auto run = [&](auto kernel, int grid, int threads) {
+    launch_blend_bwd_t(kernel, grid, threads, ranges, xyab, cop, blue, cam, bg, final_T, n_contrib, dL_dimage, g2d, blended,
+                       tile_blended, order, s, ev_start, ev_stop);
+  };
+  const int split = n_tiles + bwd_split_extra(n_tiles);
+  if (n_tiles <= kFewBwdTiles4)
+    run(k_blend_bwd_few<4>, 4 * n_tiles, 256);
+  else if (n_tiles <= kFewBwdTiles2)
+    run(k_blend_bwd_few<2>, 4 * n_tiles, 128);
   else
-    launch_blend_bwd_t<false>(ranges, xyab, cop, blue, cam, bg, final_T, n_contrib, dL_dimage, g2d, blended,
-                              tile_blended, order, s, ev_start, ev_stop);
+    run(k_blend_bwd, split, 64);
   return hipGetLastError();
 }
 

@@ -228,6 +228,14 @@ inline unsigned xcd_grid(int64_t blocks) {
   return (unsigned)(((blocks + g - 1) / g) * g);
 }
 
+// A barrier for LDS accesses alone: global loads and atomics in flight stay in flight, where
+// __syncthreads waits for them too.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ---- launches (each file defines its own) ----
 hipError_t launch_preprocess(const PreParams &p, const PreOut &o, hipStream_t s);
 hipError_t launch_scan_blocks(const uint32_t *in, unsigned long long *prefix, uint32_t *total, int blocks,

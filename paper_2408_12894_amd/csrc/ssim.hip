@@ -83,14 +83,6 @@ __device__ __forceinline__ void window_rows(const SsimColumns<MAPS> &s, int row,
   }
 }
 
-// A barrier for LDS accesses alone: the loads in flight (the next step's rows) stay in flight,
-// where __syncthreads waits for them too.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Rows gy .. gy + N - 1 of column gx of a plane, the nearest inside it for those outside;
 // inside_rows makes those zero. Two steps, since a load whose value is only selected under a
 // condition becomes a branch around it and its own wait: the values pass through an empty asm
