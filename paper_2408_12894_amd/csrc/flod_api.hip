@@ -744,7 +744,8 @@ bool level_arrays_ok(const flod_level &o) {
                       aligned(o.opacity_logits, 4));
 }
 
-// One level's compaction: count(block_cnt) and copy(prefix, out) enqueue the two passes.
+// One level's compaction: count(block_cnt), for all levels, and copy(level, prefix, out) enqueue the
+// two passes.
 struct Compaction {
   int64_t n = 0;
   float s_min = 0.0f;
@@ -753,7 +754,7 @@ struct Compaction {
 };
 
 // Count the kept Gaussians of `levels` compactions (at most FLOD_MAX_LEVELS; per-workgroup counts
-// and a scan for each), wait once for all the counts and, where `out` is given, copy the kept
+// and their scans, a launch each), wait once for all the counts and, where `out` is given, copy the kept
 // Gaussians in index order. The counts come through coherent host memory (else a copy), and with
 // them, when asked for (a single compaction), the counters' 64-bit total (*total64).
 template <class CountFn, class CopyFn>
@@ -778,17 +779,17 @@ flod_status compact_pass(flod_ctx *ctx, Compaction *job, int levels, hipStream_t
         total64 ? reinterpret_cast<const unsigned long long *>(counters + kCntTotal64) : nullptr;
     const bool direct = ctx->host_counts_dev != nullptr;
     const uint32_t seq = direct ? next_seq(ctx) : 0u;
-    int waited = 0;
+    ScanJobs scans;
+    int waited = 0;   // levels with Gaussians, and so with a count to wait for
     for (int l = 0; l < levels; ++l) {
       if (blocks[l] == 0) continue;
-      uint32_t *cnt = P<uint32_t>(ctx, B_BLOCKVIS) + first[l];
-      if (count(l, cnt) != hipSuccess ||
-          launch_scan_blocks(cnt, P<unsigned long long>(ctx, B_PREFIX) + first[l], counters + kCntKept + l,
-                             (int)blocks[l], direct ? ctx->host_counts_dev + waited : nullptr, seq, s, also) !=
-              hipSuccess)
-        return FLOD_ERR_DEVICE;
+      scans.job[waited] = ScanJob{P<uint32_t>(ctx, B_BLOCKVIS) + first[l], P<unsigned long long>(ctx, B_PREFIX) + first[l],
+                                  counters + kCntKept + l, direct ? ctx->host_counts_dev + waited : nullptr,
+                                  (int)blocks[l]};
       ++waited;
     }
+    if (count(P<uint32_t>(ctx, B_BLOCKVIS)) != hipSuccess || launch_scan_blocks(scans, waited, seq, s, also) != hipSuccess)
+      return FLOD_ERR_DEVICE;
     if (direct) {
       if (wait_counts(ctx, s, seq, waited + (also ? 2 : 0)) != hipSuccess) return FLOD_ERR_DEVICE;
     } else if (hipMemcpyAsync(ctx->host_counters, counters, 4 * (size_t)kCntSlots, hipMemcpyDeviceToHost, s) !=
@@ -858,9 +859,20 @@ flod_status flod_select_compact(flod_ctx *ctx, const flod_level *levels, int n_l
   // eq. 6 band of level l, with d_proj^(l_end) = 0 and d_proj^(l_start - 1) = infinity
   auto lo2 = [&](int l) { return sq32(l == l_end ? 0.0f : d_proj[l - 1]); };
   auto hi2 = [&](int l) { return sq32(l == l_start ? INFINITY : d_proj[l - 2]); };
-  auto count = [&](int k, uint32_t *bc) {
-    const int l = l_start + k;
-    return launch_select_count(levels[l - 1].means, levels[l - 1].n, centre, lo2(l), hi2(l), bc, s);
+  auto count = [&](uint32_t *bc) {
+    BandCounts c;
+    c.levels = l_end - l_start + 1;
+    c.first[0] = 0;
+    for (int k = 0; k < c.levels; ++k) {
+      const flod_level &lv = levels[l_start + k - 1];
+      c.means[k] = lv.means;
+      c.n[k] = lv.n;
+      c.lo2[k] = lo2(l_start + k);
+      c.hi2[k] = hi2(l_start + k);
+      c.first[k + 1] = c.first[k] + (lv.n + kBlock - 1) / kBlock;
+    }
+    for (int a = 0; a < 3; ++a) c.centre[a] = centre[a];
+    return launch_select_count(c, bc, s);
   };
   auto copy = [&](int k, const unsigned long long *prefix, const flod_level &o) {
     const int l = l_start + k;
@@ -888,7 +900,7 @@ flod_status flod_compact_level(flod_ctx *ctx, const flod_level *in, const uint8_
   }
   hipStream_t s = (hipStream_t)stream;
   if ((st = begin_level_op(ctx, s)) != FLOD_OK) return st;
-  auto count = [&](int, uint32_t *bc) { return launch_mask_count(keep, in->n, bc, s); };
+  auto count = [&](uint32_t *bc) { return launch_mask_count(keep, in->n, bc, s); };
   auto copy = [&](int, const unsigned long long *prefix, const flod_level &o) {
     return launch_mask_copy(*in, keep, prefix, o, s);
   };
@@ -964,7 +976,7 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
   // the device refuses a scan beyond the limit (nothing is written); the host learns of it with
   // the kept count
   if (launch_prune_query(pts, ranges, tags, runs, around, n, d_op, cost, keep, d_avg, s) != hipSuccess) return FLOD_ERR_DEVICE;
-  auto count = [&](int, uint32_t *bc) { return launch_mask_count(keep, n, bc, s); };
+  auto count = [&](uint32_t *bc) { return launch_mask_count(keep, n, bc, s); };
   auto no_copy = [&](int, const unsigned long long *, const flod_level &) { return hipSuccess; };
   Compaction job;
   job.n = n;

@@ -238,8 +238,18 @@ __device__ __forceinline__ void lds_barrier() {
 
 // ---- launches (each file defines its own) ----
 hipError_t launch_preprocess(const PreParams &p, const PreOut &o, hipStream_t s);
-hipError_t launch_scan_blocks(const uint32_t *in, unsigned long long *prefix, uint32_t *total, int blocks,
-                              unsigned long long *host_out, uint32_t host_seq, hipStream_t s,
+// Scans of per-workgroup counts, one workgroup each.
+struct ScanJob {
+  const uint32_t *in;
+  unsigned long long *prefix;
+  uint32_t *total;
+  unsigned long long *host_out;   // may be null
+  int blocks;
+};
+struct ScanJobs {
+  ScanJob job[FLOD_MAX_LEVELS];
+};
+hipError_t launch_scan_blocks(const ScanJobs &jobs, int n_jobs, uint32_t host_seq, hipStream_t s,
                               const unsigned long long *extra = nullptr);
 int radix_items(int64_t n_max);        // keys per thread the radix sort of n_max keys uses
 size_t radix_hist_bytes(int64_t n_max, bool depth = false);  // bytes of each of its hist and scan arrays
@@ -315,8 +325,17 @@ hipError_t launch_g2d_from_moments(int64_t n, const uint32_t *tiles, const float
 hipError_t launch_preprocess_bwd(const PreParams &p, const uint32_t *tiles, const float *g2d,
                                  const float4 *shjac, const flod_grads &g, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
-hipError_t launch_select_count(const float *means, int64_t n, const float centre[3], float lo2, float hi2,
-                               uint32_t *block_cnt, hipStream_t s);
+// The kept Gaussians of several levels' bands, counted per workgroup: level k's workgroups are
+// first[k] .. first[k + 1] - 1 of the launch and of block_cnt.
+struct BandCounts {
+  const float *means[FLOD_MAX_LEVELS];
+  int64_t n[FLOD_MAX_LEVELS];
+  float lo2[FLOD_MAX_LEVELS], hi2[FLOD_MAX_LEVELS];
+  int64_t first[FLOD_MAX_LEVELS + 1];
+  float centre[3];
+  int levels;
+};
+hipError_t launch_select_count(const BandCounts &c, uint32_t *block_cnt, hipStream_t s);
 hipError_t launch_select_copy(const flod_level &in, const float centre[3], float lo2, float hi2,
                               const unsigned long long *prefix, const flod_level &out, hipStream_t s);
 hipError_t launch_mask_count(const uint8_t *mask, int64_t n, uint32_t *block_cnt, hipStream_t s);

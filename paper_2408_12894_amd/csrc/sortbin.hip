@@ -37,17 +37,19 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *total)
 }
 
 // ---------------------------------------------------------------------------------------
-// Scan of per-workgroup counts (one workgroup): 64-bit exclusive prefixes and the total; with
+// Scans of per-workgroup counts, one workgroup each: 64-bit exclusive prefixes and the total; with
 // host_out (coherent host memory) the total also goes there, tagged as the frame's counts are
 // (see FrameTotals), and behind it, when given, the low and high halves of *extra.
 // ---------------------------------------------------------------------------------------
 constexpr int kScanThreads = 1024;
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_blocks(const uint32_t *in, unsigned long long *prefix,
-                                                              uint32_t *total32, int nb,
-                                                              unsigned long long *host_out, uint32_t host_seq,
+__global__ __launch_bounds__(kScanThreads) void k_scan_blocks(ScanJobs jobs, uint32_t host_seq,
                                                               const unsigned long long *extra) {
   __shared__ unsigned long long s_w[kScanThreads / 64];
+  const ScanJob job = jobs.job[blockIdx.x];
+  const uint32_t *in = job.in;
+  unsigned long long *prefix = job.prefix, *host_out = job.host_out;
+  const int nb = job.blocks;
   // thread t owns the contiguous counts [t per, (t + 1) per): its sum, a workgroup scan of the
   // sums, then its exclusive prefixes (a second read of its counts, from cache)
   const int per = (nb + kScanThreads - 1) / kScanThreads;
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_blocks(const uint32_t *in
     run += in[k];
   }
   if (threadIdx.x == 0) {
-    *total32 = (uint32_t)total;
+    *job.total = (uint32_t)total;
     if (host_out) {
       const unsigned long long tag = (unsigned long long)host_seq << 32, x = extra ? *extra : 0ull;
       const unsigned long long w[3] = {tag | (uint32_t)total, tag | (uint32_t)x, tag | (x >> 32)};
@@ -99,11 +101,9 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_blocks(const uint32_t *in
   }
 }
 
-hipError_t launch_scan_blocks(const uint32_t *in, unsigned long long *prefix, uint32_t *total, int blocks,
-                              unsigned long long *host_out, uint32_t host_seq, hipStream_t s,
+hipError_t launch_scan_blocks(const ScanJobs &jobs, int n_jobs, uint32_t host_seq, hipStream_t s,
                               const unsigned long long *extra) {
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, in, prefix, total, blocks, host_out, host_seq,
-                     extra);
+  hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)n_jobs), dim3(kScanThreads), 0, s, jobs, host_seq, extra);
   return hipGetLastError();
 }
 
