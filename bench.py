@@ -90,7 +90,7 @@ FLOPS_BLEND_BWD = 46
 # step_1080p_1M_hbm_counters.md). A figure holds only for the kernel sources it was taken
 # with: the sha256 over the listed files must match, else the traffic is reported as null.
 PROFILED_TRAFFIC = {
-    "blend_bwd": {"bytes": 367981396, "sha256": "6ca6729009997e3935e52060e165db65d61653b0101d2999188c0c22c6851ced",
+    "blend_bwd": {"bytes": 371399953, "sha256": "e0f558e79a1a0cb7cd41c911b00c0c193a5714d32a5d6b2ef9db76c5b8b2bd37",
                   "sources": ['paper_2408_12894_amd/csrc/backward.hip', 'paper_2408_12894_amd/csrc/blend_common.h', 'paper_2408_12894_amd/csrc/project.h', 'paper_2408_12894_amd/csrc/flod_internal.h']},
 }
 
@@ -140,18 +140,24 @@ def timed(fn, n, warm, sync):
     return (time.perf_counter() - t0) / n
 
 
+# (supertile, Gaussian) pairs per visible Gaussian at 1080p / 1M cluster Gaussians
+PAIRS_PER_VISIBLE = 1.7
+
+
 def algorithmic_bytes(stage, N, n_vis, K, P, tiles):
-    """Bytes a stage cannot avoid moving in one launch (its reads and writes of each item once)."""
+    """Bytes a stage of this design cannot avoid moving in one launch (its reads and writes of each
+    item once)."""
+    pairs = PAIRS_PER_VISIBLE * n_vis
     return {
-        "preprocess": (236 + 80) * N,
-        "depth_sort": 4 * N + 8 * n_vis + 3 * 2 * 8 * n_vis,   # the first pass reads every candidate's key
+        "preprocess": 236 * N + (60 + 16 + 48) * n_vis,
+        "depth_sort": 2 * 4 * N + 8 * n_vis + 2 * (4 + 16) * n_vis + 16 * n_vis,   # the first pass reads every key
         "offsets": 8 * n_vis,
-        "emit": 40 * n_vis + 8 * K,
-        "tile_sort": 2 * (4 + 16) * K,
-        "ranges": 4 * K + 8 * tiles,
+        "tile_sort": (8 + 4 + 16) * n_vis + (12 + 8) * pairs,   # the pairs placed, their masks counted
+        "ranges": 16 * tiles,
+        "emit": 12 * pairs + 4 * K,
         "blend": 44 * K + 20 * P,
         "blend_bwd": 44 * K + 20 * P + 12 * P + 36 * K,
-        "preprocess_bwd": (236 + 4 + 36 + 236) * N,
+        "preprocess_bwd": (44 + 48 + 4 + 36 + 236) * N,
     }[stage]
 
 

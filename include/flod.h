@@ -22,7 +22,7 @@
  *
  * Streams: `stream` is a hipStream_t (NULL = the legacy default stream). All work is
  * enqueued on it. A render enqueues the whole frame before it waits for anything: the
- * emission, tile sort and blend are sized for the instances the context's buffers hold and
+ * pair and list kernels and the blend are sized for the instances the context's buffers hold and
  * read the instance count K on the device, doing nothing when K exceeds that capacity. The
  * host then waits for the counts, which the kernel that computes them writes to coherent
  * pinned host memory tagged with the render's sequence number (or a stream-ordered copy,
