@@ -122,8 +122,17 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
 // holds (U = 16 four waves per SIMD). Branches with U = 8 or 16 hold the group's colours in
 // registers to no use (154, 254 us at 1M), U = 2 waits more often (116).
 //
+// AHEAD: each group is read, and its alphas found, before the one in front of it is taken. Where a
+// SIMD has few waves none of them covers another's LDS reads; the two groups' registers (167) cost
+// nothing there. us per kernel, without and with: 2k at 253x187 (192 tiles) 12.1 11.7, 20k at 400x300
+// (475) 36.7 32.8, levels 1-2 at 640x360 (920) 88.9 80.8, 100k at 800x600 (1,900) 65.4 60.1, 300k
+// clusters at 1000x700 (2,772) 108 105, 500k clusters at 1280x720 (3,600) 127 129 and, floor 0.0125,
+// 62 69; U = 4 ahead 19.7 and 88.9 at 2k / 128x128 and levels 1-2, against 17.5 and 80.8. A walk of
+// several waves per quadrant, the alphas found by one or two and blended by another, took 17.1
+// and 88.4 at best there.
+//
 // COUNT: the caller wants each pixel's count of blended entries (n_blended).
-template <int U, bool PRED, bool COUNT>
+template <int U, bool PRED, bool AHEAD, bool COUNT>
 __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict__ ranges,
                                                          const uint32_t *__restrict__ values,
                                                          const float4 *__restrict__ xyab,
@@ -136,12 +145,14 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
                                                          const uint32_t *__restrict__ order) {
   constexpr int NT = kTile * kTile;
   static_assert(kBatch == NT && kBatch % U == 0, "one staged entry per thread, whole groups");
+  static_assert(PRED || !AHEAD, "ahead: the predicated way only");
+  constexpr int kFill = AHEAD ? 2 * U : U;   // places filled behind a wave's entries
   constexpr int W4 = NT / 64;
   // the staged entries, and behind them one that no pixel takes
   __shared__ float4 s_a[kBatch + 1];
   __shared__ float4 s_b[kBatch + 1];
   __shared__ float4 s_c[kBatch + 1];
-  __shared__ __align__(16) uint16_t s_off[W4][kBatch + U];   // each wave's entries: byte offsets into s_a
+  __shared__ __align__(16) uint16_t s_off[W4][kBatch + kFill];   // each wave's entries: byte offsets into s_a
   __shared__ uint8_t s_reach[kBatch];                        // the waves each entry may reach
   __shared__ uint8_t s_taken[kBatch];
   __shared__ uint32_t s_id[kBatch];
@@ -193,7 +204,7 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
       finite = __syncthreads_and(finite);
     else
       __syncthreads();
-    // this wave's entries, in list order and filled up to a whole group
+    // this wave's entries, in list order and filled up to whole groups
     int cnt = 0;
 #pragma unroll
     for (int k = 0; k < kBatch; k += 64) {
@@ -204,59 +215,61 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
             (uint16_t)((k + lane) * sizeof(float4));
       cnt += (int)__popcll(m);
     }
-    if (lane < U) s_off[w][cnt + lane] = (uint16_t)(kBatch * sizeof(float4));
+    if (lane < kFill) s_off[w][cnt + lane] = (uint16_t)(kBatch * sizeof(float4));
     wave_lds_fence();
     int last_at = -1;   // the last entry taken in this batch, as a place in the wave's list
-    for (int j0 = 0; j0 < cnt; j0 += U) {
-      if (!__any(PRED ? Tw != 0.0f : !done)) break;
-      float l[U], thr[U], c0[U], c1[U], c2[U];
-      uint32_t off[U / 2];   // two entries a word
+    // the offsets of the group at place j0 of the wave's list, two entries a word
+    const auto offsets = [&](int j0, uint32_t(&off)[U / 2]) {
 #pragma unroll
       for (int k = 0; k < U / 2; k += 2) {
         const uint2 o = *reinterpret_cast<const uint2 *>(&s_off[w][j0 + 2 * k]);
         off[k] = o.x;
         off[k + 1] = o.y;
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t e = (u & 1 ? off[u >> 1] >> 16 : off[u >> 1] & 0xFFFFu);
-        const float4 A = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_a) + e);
-        const float4 B = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_b) + e);
-        // threshold on l, blue
-        const float2 BL = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(s_c) + e);
-        const float dx = fx - A.x;
-        const float t = conic_column(A.w, dx, B.y);
-        l[u] = conic_kq(B.x, A.z, dx, fy - A.y, t);   // k q + log2 o
-        thr[u] = BL.x;
-        c0[u] = B.z;
-        c1[u] = B.w;
-        c2[u] = BL.y;
-      }
-      if (PRED) {
-        float al[U];   // alpha, 0 where the entry does not reach the pixel
+    };
+    if constexpr (PRED) {
+      struct Group {
+        float al[U], c0[U], c1[U], c2[U];   // alpha (0 where the entry does not reach the pixel), colour
+      };
+      const auto read = [&](int j0, Group &g) {
+        uint32_t off[U / 2];
+        offsets(j0, off);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const float a = fminf(kAlphaMax, alpha_from_log2(l[u]));
-          al[u] = l[u] < thr[u] ? 0.0f : a;
+          const uint32_t e = (u & 1 ? off[u >> 1] >> 16 : off[u >> 1] & 0xFFFFu);
+          const float4 A = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_a) + e);
+          const float4 B = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_b) + e);
+          // threshold on l, blue
+          const float2 BL = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(s_c) + e);
+          const float dx = fx - A.x;
+          const float t = conic_column(A.w, dx, B.y);
+          const float l = conic_kq(B.x, A.z, dx, fy - A.y, t);   // k q + log2 o
+          const float a = fminf(kAlphaMax, alpha_from_log2(l));
+          g.al[u] = l < BL.x ? 0.0f : a;
+          g.c0[u] = B.z;
+          g.c1[u] = B.w;
+          g.c2[u] = BL.y;
         }
+      };
+      const auto take = [&](int j0, const Group &g) {
         uint32_t bits = 0u;   // the pixel's taken entries, the last one in bit 0
         auto walk = [&](auto finite) {
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            const float Tn = fmaf(-al[u], Tw, Tw);
+            const float Tn = fmaf(-g.al[u], Tw, Tw);
             const bool stop = Tn < kTMin;                // also once Tw is 0
-            const float wgt = stop ? 0.0f : al[u] * Tw;
+            const float wgt = stop ? 0.0f : g.al[u] * Tw;
             const bool take = wgt > 0.0f;
             Tw = stop ? 0.0f : Tn;
             T = stop ? T : Tn;
             if (decltype(finite)::value) {
-              C0 = fmaf(wgt, c0[u], C0);
-              C1 = fmaf(wgt, c1[u], C1);
-              C2 = fmaf(wgt, c2[u], C2);
+              C0 = fmaf(wgt, g.c0[u], C0);
+              C1 = fmaf(wgt, g.c1[u], C1);
+              C2 = fmaf(wgt, g.c2[u], C2);
             } else {
-              C0 = take ? fmaf(wgt, c0[u], C0) : C0;
-              C1 = take ? fmaf(wgt, c1[u], C1) : C1;
-              C2 = take ? fmaf(wgt, c2[u], C2) : C2;
+              C0 = take ? fmaf(wgt, g.c0[u], C0) : C0;
+              C1 = take ? fmaf(wgt, g.c1[u], C1) : C1;
+              C2 = take ? fmaf(wgt, g.c2[u], C2) : C2;
             }
             bits = bits + bits + (take ? 1u : 0u);
           }
@@ -272,24 +285,63 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
           if (lane < U && ((any >> (U - 1 - lane)) & 1u)) s_taken[s_off[w][j0 + lane] / sizeof(float4)] = 1;
         }
         done = Tw == 0.0f;
-      } else
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (done || l[u] < thr[u]) continue;                      // q > 9 or alpha < 1/255
-        const float alpha = fminf(kAlphaMax, alpha_from_log2(l[u]));
-        const float wgt = alpha * T;
-        const float Tn = fmaf(-alpha, T, T);   // T (1 - alpha), one rounding
-        if (Tn < kTMin) {
-          done = true;
-          continue;
+      };
+      Group g0, g1;
+      if (AHEAD) read(0, g0);
+      for (int j0 = 0; j0 < cnt; j0 += AHEAD ? 2 * U : U) {
+        if (!__any(Tw != 0.0f)) break;
+        if (AHEAD) {
+          // each group is read before the one in front of it is taken: j0 < cnt here and j0 + U < cnt
+          // below, so what is read lies before place cnt + 2 U, the end of the fill
+          read(j0 + U, g1);
+          take(j0, g0);
+          if (j0 + U >= cnt || !__any(Tw != 0.0f)) break;
+          read(j0 + 2 * U, g0);
+          take(j0 + U, g1);
+        } else {
+          read(j0, g0);
+          take(j0, g0);
         }
-        C0 = fmaf(wgt, c0[u], C0);
-        C1 = fmaf(wgt, c1[u], C1);
-        C2 = fmaf(wgt, c2[u], C2);
-        T = Tn;
-        last_at = j0 + u;
-        if (COUNT) ++nbl;
-        s_taken[(u & 1 ? off[u >> 1] >> 16 : off[u >> 1] & 0xFFFFu) / sizeof(float4)] = 1;
+      }
+    } else {
+      for (int j0 = 0; j0 < cnt; j0 += U) {
+        if (!__any(!done)) break;
+        float l[U], thr[U], c0[U], c1[U], c2[U];
+        uint32_t off[U / 2];
+        offsets(j0, off);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t e = (u & 1 ? off[u >> 1] >> 16 : off[u >> 1] & 0xFFFFu);
+          const float4 A = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_a) + e);
+          const float4 B = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_b) + e);
+          // threshold on l, blue
+          const float2 BL = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(s_c) + e);
+          const float dx = fx - A.x;
+          const float t = conic_column(A.w, dx, B.y);
+          l[u] = conic_kq(B.x, A.z, dx, fy - A.y, t);   // k q + log2 o
+          thr[u] = BL.x;
+          c0[u] = B.z;
+          c1[u] = B.w;
+          c2[u] = BL.y;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (done || l[u] < thr[u]) continue;                      // q > 9 or alpha < 1/255
+          const float alpha = fminf(kAlphaMax, alpha_from_log2(l[u]));
+          const float wgt = alpha * T;
+          const float Tn = fmaf(-alpha, T, T);   // T (1 - alpha), one rounding
+          if (Tn < kTMin) {
+            done = true;
+            continue;
+          }
+          C0 = fmaf(wgt, c0[u], C0);
+          C1 = fmaf(wgt, c1[u], C1);
+          C2 = fmaf(wgt, c2[u], C2);
+          T = Tn;
+          last_at = j0 + u;
+          if (COUNT) ++nbl;
+          s_taken[(u & 1 ? off[u >> 1] >> 16 : off[u >> 1] & 0xFFFFu) / sizeof(float4)] = 1;
+        }
       }
     }
     if (last_at >= 0) last = start + (int)(s_off[w][last_at] / sizeof(float4)) + 1;
@@ -310,19 +362,21 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
   if (COUNT) n_blended[pix] = nbl;
 }
 
-constexpr int kFewTiles = 4096;
+constexpr int kFewTiles = 4096, kFewestTiles = 2048;
 
 hipError_t launch_blend(const uint2 *ranges, const uint32_t *values, const float4 *xyab, const float4 *cop,
                         const float2 *blue, const DevCamera &cam, const float bg[3], float *image, float *final_T,
                         int32_t *n_contrib, int32_t *n_blended, uint2 *blended, uint32_t *tile_blended,
                         const uint32_t *order, bool large, hipStream_t s) {
   const int n_tiles = cam.tiles_x * cam.tiles_y;
-  // eight predicated entries per group while the frame has few waves for the device; beyond, four
-  // where the levels' scale floors make footprints large, else branches (see the table)
-  const int way = n_tiles <= kFewTiles ? 0 : large ? 1 : 2;
-  auto kernel = way == 0 ? n_blended ? k_blend<8, true, true> : k_blend<8, true, false>
-                : way == 1 ? n_blended ? k_blend<4, true, true> : k_blend<4, true, false>
-                           : n_blended ? k_blend<4, false, true> : k_blend<4, false, false>;
+  // eight predicated entries per group while the frame has few waves for the device, read ahead where
+  // it has fewer still; beyond, four where the levels' scale floors make footprints large, else
+  // branches (see the table)
+  const int way = n_tiles <= kFewestTiles ? 0 : n_tiles <= kFewTiles ? 1 : large ? 2 : 3;
+  auto kernel = way == 0 ? n_blended ? k_blend<8, true, true, true> : k_blend<8, true, true, false>
+                : way == 1 ? n_blended ? k_blend<8, true, false, true> : k_blend<8, true, false, false>
+                : way == 2 ? n_blended ? k_blend<4, true, false, true> : k_blend<4, true, false, false>
+                           : n_blended ? k_blend<4, false, false, true> : k_blend<4, false, false, false>;
   hipLaunchKernelGGL(kernel, dim3(n_tiles), dim3(kTile * kTile), 0, s, ranges, values, xyab, cop, blue, cam.W, cam.H,
                      cam.tiles_x, bg[0], bg[1], bg[2], image, final_T, n_contrib, n_blended, blended, tile_blended,
                      order);
