@@ -534,8 +534,9 @@ int bwd_split_extra(int n_tiles) { return split_cap2(n_tiles) + 2 * split_cap4(n
 // 7 us at 1080p / 1M; together the step is 2.5 us shorter).
 __global__ __launch_bounds__(kOrderThreads) void k_bwd_order_fill(CountCost cost, int n_tiles, uint32_t *order,
                                                                   TileSplit split, float *p, int64_t n) {
+  __shared__ OrderShared<kOrderThreads / 64> sh;
   if (blockIdx.x == 0) {
-    tile_order(cost, n_tiles, order, split);
+    tile_order(cost, n_tiles, order, split, sh);
     return;
   }
   // the floats before the first 16-byte boundary, then whole uint4, then the rest

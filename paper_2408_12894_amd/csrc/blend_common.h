@@ -74,26 +74,29 @@ struct CountCost {
   __device__ __forceinline__ uint32_t operator()(int t) const { return count[t]; }
 };
 
-// The tile order as one workgroup of kOrderThreads threads. With ranges, the costs are the
-// lengths of the tiles' lists and their exclusive prefix in tile order gives each tile's
-// [start, end).
-template <class Cost>
-__device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restrict__ order, TileSplit split,
-                                           uint2 *__restrict__ ranges = nullptr) {
-  constexpr int W = kOrderThreads / 64;
+// The LDS of a tile order by a workgroup of W waves.
+template <int W>
+struct OrderShared {
   // per-wave bucket counts (contention only inside a wave), then per (bucket, wave) offsets
-  __shared__ uint32_t s_cnt[W][kOrderBuckets];
-  __shared__ uint32_t s_wsum[kOrderBuckets / 64];
-  __shared__ unsigned long long s_csum[W];
-  __shared__ uint32_t s_split[2];
+  uint32_t cnt[W][kOrderBuckets];
+  uint32_t wsum[kOrderBuckets / 64];
+  unsigned long long csum[W];
+  uint32_t split[2];
+};
+
+// The tile order as one workgroup of W waves (W >= 4: a thread per bucket).
+template <int W, class Cost>
+__device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restrict__ order, TileSplit split,
+                                           OrderShared<W> &sh) {
+  static_assert(64 * W >= kOrderBuckets, "a thread per bucket");
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  for (int k = tid; k < W * kOrderBuckets; k += kOrderThreads) (&s_cnt[0][0])[k] = 0u;
-  if (tid < 2) s_split[tid] = 0u;
+  for (int k = tid; k < W * kOrderBuckets; k += 64 * W) (&sh.cnt[0][0])[k] = 0u;
+  if (tid < 2) sh.split[tid] = 0u;
   __syncthreads();
   const int chunk = (n + W - 1) / W;
   const int t0 = w * chunk, t1 = min(n, t0 + chunk);
-  // kOrderLoads costs per lane loaded before any is used (one loop trip at 1080p: each wave
-  // takes at most 512 tiles there), the indices clamped into the wave's range rather than
+  // kOrderLoads costs per lane loaded before any is used (one loop trip of sixteen waves at 1080p:
+  // each takes at most 512 tiles there), the indices clamped into the wave's range rather than
   // guarded (a guard made each load a branch that waited for it); loaded one at a time, each
   // trip waited for its load
   unsigned long long csum = 0ull;
@@ -105,12 +108,12 @@ __device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restric
     for (int u = 0; u < kOrderLoads; ++u)
       if (base + 64 * u < t1) {
         csum += c[u];
-        atomicAdd(&s_cnt[w][cost_bucket(c[u])], 1u);
+        atomicAdd(&sh.cnt[w][cost_bucket(c[u])], 1u);
       }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) csum += __shfl_xor(csum, o, 64);
-  if (lane == 0) s_csum[w] = csum;
+  if (lane == 0) sh.csum[w] = csum;
   __syncthreads();
   // thread d < 256 takes bucket b = 255 - d (descending cost): its count over the waves, with
   // each wave's count replaced by the running sum before it
@@ -119,8 +122,8 @@ __device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restric
     const int b = kOrderBuckets - 1 - tid;
 #pragma unroll
     for (int k = 0; k < W; ++k) {
-      const uint32_t c = s_cnt[k][b];
-      s_cnt[k][b] = tot;
+      const uint32_t c = sh.cnt[k][b];
+      sh.cnt[k][b] = tot;
       tot += c;
     }
   }
@@ -131,20 +134,20 @@ __device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restric
     const uint32_t x = __shfl_up(inc, o, 64);
     if (lane >= o) inc += x;
   }
-  if (tid < kOrderBuckets && lane == 63) s_wsum[w] = inc;
+  if (tid < kOrderBuckets && lane == 63) sh.wsum[w] = inc;
   __syncthreads();
   if (tid < kOrderBuckets) {
     uint32_t base = inc - tot;
-    for (int k = 0; k < w; ++k) base += s_wsum[k];
+    for (int k = 0; k < w; ++k) base += sh.wsum[k];
     const int b = kOrderBuckets - 1 - tid;
 #pragma unroll
-    for (int k = 0; k < W; ++k) s_cnt[k][b] += base;
+    for (int k = 0; k < W; ++k) sh.cnt[k][b] += base;
     if (split.cap2 > 0) {
       // the tiles in the buckets above a threshold's lead the order: base + tot of the bucket
       // just above it
       unsigned long long total = 0ull;
 #pragma unroll
-      for (int k = 0; k < W; ++k) total += s_csum[k];
+      for (int k = 0; k < W; ++k) total += sh.csum[k];
       const double mean = (double)total / (double)max(n, 1);
       const float fs[2] = {split.f2, split.f4};
       const int caps[2] = {split.cap2, split.cap4};
@@ -152,35 +155,20 @@ __device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restric
       for (int i = 0; i < 2; ++i)
         if (fs[i] > 0.0f && caps[i] > 0) {
           const int bthr = cost_bucket((uint32_t)fmin((double)fs[i] * mean, 4.0e9)) + 1;
-          if (b == bthr) s_split[i] = min(base + tot, (uint32_t)caps[i]);
+          if (b == bthr) sh.split[i] = min(base + tot, (uint32_t)caps[i]);
         }
     }
   }
   __syncthreads();
-  uint32_t start = 0u;   // the tiles before this wave's: their costs
-  for (int k = 0; k < w; ++k) start += (uint32_t)s_csum[k];
-  for (int b0 = t0; b0 < t1; b0 += 64 * kOrderLoads) {
-    const int base = b0 + lane;
+  for (int base = t0 + lane; base < t1; base += 64 * kOrderLoads) {
     uint32_t c[kOrderLoads];
 #pragma unroll
-    for (int u = 0; u < kOrderLoads; ++u) c[u] = cost(min(base + 64 * u, t1 - 1));   // in bounds: b0 < t1
+    for (int u = 0; u < kOrderLoads; ++u) c[u] = cost(min(base + 64 * u, t1 - 1));   // in bounds: base < t1
 #pragma unroll
-    for (int u = 0; u < kOrderLoads; ++u) {
-      const bool in = base + 64 * u < t1;
-      if (in) order[atomicAdd(&s_cnt[w][cost_bucket(c[u])], 1u)] = (uint32_t)(base + 64 * u);
-      if (ranges) {
-        uint32_t end = in ? c[u] : 0u;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const uint32_t x = __shfl_up(end, o, 64);
-          if (lane >= o) end += x;
-        }
-        if (in) ranges[base + 64 * u] = make_uint2(start + end - c[u], start + end);
-        start += __shfl(end, 63, 64);
-      }
-    }
+    for (int u = 0; u < kOrderLoads; ++u)
+      if (base + 64 * u < t1) order[atomicAdd(&sh.cnt[w][cost_bucket(c[u])], 1u)] = (uint32_t)(base + 64 * u);
   }
-  if (split.cap2 >= 0 && tid < 2) order[n + tid] = s_split[tid];
+  if (split.cap2 >= 0 && tid < 2) order[n + tid] = sh.split[tid];
 }
 
 }  // namespace flod

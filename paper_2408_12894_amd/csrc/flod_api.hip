@@ -459,16 +459,14 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
       return FLOD_ERR_DEVICE;
     }
     tm.begin(FLOD_STAGE_RANGES);
-    if (launch_tile_starts(tile_len, n_tiles, P<uint2>(c, B_RANGES), order, s) != hipSuccess) return FLOD_ERR_DEVICE;
+    if (launch_tile_starts(tile_len, n_tiles, P<uint2>(c, B_RANGES), s) != hipSuccess) return FLOD_ERR_DEVICE;
     tm.end();
-    if (N > 0) {
-      tm.begin(FLOD_STAGE_EMIT);
-      if (launch_chunk_expand(counters, P<uint4>(c, B_CHUNKS), P<uint32_t>(c, B_PAIR_ID),
-                              P<unsigned long long>(c, B_PAIR_MASK), P<uint32_t>(c, B_CHUNK_CNT), P<uint2>(c, B_RANGES),
-                              cam, max_chunks, P<uint32_t>(c, B_VALUES), s) != hipSuccess)
-        return FLOD_ERR_DEVICE;
-      tm.end();
-    }
+    tm.begin(FLOD_STAGE_EMIT);
+    if (launch_chunk_expand(counters, P<uint4>(c, B_CHUNKS), P<uint32_t>(c, B_PAIR_ID),
+                            P<unsigned long long>(c, B_PAIR_MASK), P<uint32_t>(c, B_CHUNK_CNT), P<uint2>(c, B_RANGES),
+                            cam, N > 0 ? max_chunks : 0, P<uint32_t>(c, B_VALUES), tile_len, order, s) != hipSuccess)
+      return FLOD_ERR_DEVICE;
+    tm.end();
     tm.begin(FLOD_STAGE_BLEND);
     if (launch_blend(P<uint2>(c, B_RANGES), P<uint32_t>(c, B_VALUES), P<float4>(c, B_XYAB), P<float4>(c, B_COP),
                      P<float2>(c, B_BLUE), cam, bg, out->image, out->final_T, out->n_contrib, out->n_blended,

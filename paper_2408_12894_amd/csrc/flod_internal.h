@@ -288,10 +288,11 @@ hipError_t launch_pair_place(const uint32_t *ids, uint32_t *counters, const uint
 hipError_t launch_chunk_counts(const uint32_t *counters, const uint4 *chunks, const unsigned long long *pair_mask,
                                const uint2 *supers, const DevCamera &cam, int64_t max_chunks, uint32_t *cnt,
                                uint32_t *tile_len, hipStream_t s);
-hipError_t launch_tile_starts(const uint32_t *tile_len, int n_tiles, uint2 *ranges, uint32_t *order, hipStream_t s);
+hipError_t launch_tile_starts(const uint32_t *tile_len, int n_tiles, uint2 *ranges, hipStream_t s);
 hipError_t launch_chunk_expand(const uint32_t *counters, const uint4 *chunks, const uint32_t *pair_id,
                                const unsigned long long *pair_mask, const uint32_t *prefix, const uint2 *ranges,
-                               const DevCamera &cam, int64_t max_chunks, uint32_t *values, hipStream_t s);
+                               const DevCamera &cam, int64_t max_chunks, uint32_t *values, const uint32_t *tile_len,
+                               uint32_t *order, hipStream_t s);
 hipError_t launch_frame_totals(const FrameTotals &t, hipStream_t s);
 hipError_t launch_bin_records(int64_t n, const uint32_t *tiles, const uint2 *rect, const BinIn &in, float4 *out,
                               hipStream_t s);

@@ -12,8 +12,9 @@
 //                    inside it, and the descriptors of their chunks of 256
 //   4. k_chunk_count per chunk, the instances of each of the supertile's 64 tiles
 //   5. k_chunk_prefix  per supertile, their prefix over its chunks and each tile's total
-//   6. k_tile_starts   the tiles' [start, end) in tile order, and the blend's tile order
-//   7. k_chunk_expand  the list: each chunk's Gaussians of each tile, written as one run
+//   6. k_tile_starts   the tiles' [start, end) in tile order
+//   7. k_chunk_expand  the list: each chunk's Gaussians of each tile, written as one run; beside it
+//                      the blend's tile order
 // Order: workgroups, ranks inside one, chunks and bits inside one are all in depth order, so
 // each tile's list is ascending (depth bits, Gaussian index).
 //
@@ -519,11 +520,41 @@ __global__ __launch_bounds__(kPrefixThreads) void k_chunk_prefix(const uint32_t 
   if (w == 0 && tx < su.tiles_x && ty < su.tiles_y) tile_len[ty * su.tiles_x + tx] = total;
 }
 
-// The tiles' list ranges and, in the same workgroup, the blend's tile order.
+// The tiles' list ranges: the exclusive prefix of their lengths in tile order. Each workgroup takes
+// kStartTiles tiles, two per thread, and sums the lengths of all tiles before them itself (at most
+// 130 KB for 3840x2160, from L2), so that no workgroup waits for another; two adjacent tiles keep the
+// stores whole (eight per thread in one workgroup took 31 us at 32,400 tiles and 8.8 at 8,160). Bound
+// by latency: 4.8 and 4.5 us there, 2.5 at 64 tiles; 25, 8.9 and 7.2 as one workgroup that made the
+// blend's order too.
+constexpr int kStartTiles = 2 * kOrderThreads;
+
 __global__ __launch_bounds__(kOrderThreads) void k_tile_starts(const uint32_t *__restrict__ tile_len, int n,
-                                                               uint2 *__restrict__ ranges,
-                                                               uint32_t *__restrict__ order) {
-  tile_order(CountCost{tile_len}, n, order, TileSplit{0.0f, 0.0f, -1, -1}, ranges);
+                                                               uint2 *__restrict__ ranges) {
+  constexpr int W = kOrderThreads / 64, U = 8;
+  __shared__ uint32_t s_before[W], s_own[W];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int base = (int)blockIdx.x * kStartTiles, t = base + 2 * tid;
+  const uint32_t c0 = tile_len[min(t, n - 1)], c1 = tile_len[min(t + 1, n - 1)];   // those past the end go nowhere
+  uint32_t before = 0u;
+  for (int k = tid; k < base; k += kOrderThreads * U) {
+    uint32_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = tile_len[min(k + u * kOrderThreads, base - 1)];   // in bounds: base < n
+#pragma unroll
+    for (int u = 0; u < U; ++u) before += k + u * kOrderThreads < base ? v[u] : 0u;
+  }
+  before = wave_incl_scan(before);
+  const uint32_t incl = wave_incl_scan(c0 + c1);
+  if (lane == 63) {
+    s_before[w] = before;
+    s_own[w] = incl;
+  }
+  lds_barrier();
+  uint32_t at = incl - (c0 + c1);
+#pragma unroll
+  for (int k = 0; k < W; ++k) at += s_before[k] + (k < w ? s_own[k] : 0u);
+  if (t < n) ranges[t] = make_uint2(at, at + c0);
+  if (t + 1 < n) ranges[t + 1] = make_uint2(at + c0, at + c0 + c1);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -535,6 +566,9 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_starts(const uint32_t *_
 // against 220 us), the indices placed per 32-bit half (208). Waves storing each tile's entries
 // by ballot, without LDS, took 230 us there and 28 for the 8.4M; runs begun at a 64-byte
 // boundary 210 and 23.
+// Workgroup 0 makes the blend's tile order instead, which no other kernel before the blend needs: four
+// waves, done within the expansion's time (the kernel unchanged at 157.6M, 8.4M and 0.7M entries) but
+// where large frames show little (2k Gaussians at 3840x2160: 6 -> 39 us, 51 -> 44 with the ranges).
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kChunk) void k_chunk_expand(const uint32_t *__restrict__ counters,
                                                          const uint4 *__restrict__ chunks,
@@ -542,16 +576,24 @@ __global__ __launch_bounds__(kChunk) void k_chunk_expand(const uint32_t *__restr
                                                          const unsigned long long *__restrict__ pair_mask,
                                                          const uint32_t *__restrict__ prefix,
                                                          const uint2 *__restrict__ ranges, Supers su,
-                                                         uint32_t *__restrict__ values) {
+                                                         uint32_t *__restrict__ values,
+                                                         const uint32_t *__restrict__ tile_len, int n_tiles,
+                                                         uint32_t *__restrict__ order) {
   constexpr int W = kChunk / 64;
-  __shared__ uint8_t s_stage[kChunk * 64];
+  __shared__ __align__(16) uint8_t s_stage[kChunk * 64];
   __shared__ uint32_t s_id[kChunk];
   __shared__ uint32_t s_cnt[W][64];
   __shared__ uint32_t s_lbase[64], s_len[64], s_gbase[64];
+  if (blockIdx.x == 0) {
+    static_assert(sizeof(OrderShared<W>) <= sizeof(s_stage), "the order's LDS in place of the staged indices");
+    tile_order<W>(CountCost{tile_len}, n_tiles, order, TileSplit{0.0f, 0.0f, -1, -1},
+                  *reinterpret_cast<OrderShared<W> *>(s_stage));
+    return;
+  }
   if (counters[kCntPairs] == 0u) return;
   const uint32_t nc = counters[kCntChunks];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  for (uint32_t c = xcd_block(blockIdx.x); c < nc; c += gridDim.x) {
+  for (uint32_t c = xcd_block(blockIdx.x - 1u); c < nc; c += gridDim.x - 1u) {
     const uint4 d = chunks[c];
     const bool in = (uint32_t)tid < d.y;
     const unsigned long long m = in ? pair_mask[d.x + tid] : 0ull;
@@ -670,18 +712,23 @@ hipError_t launch_chunk_counts(const uint32_t *counters, const uint4 *chunks, co
   return hipGetLastError();
 }
 
-hipError_t launch_tile_starts(const uint32_t *tile_len, int n_tiles, uint2 *ranges, uint32_t *order, hipStream_t s) {
+hipError_t launch_tile_starts(const uint32_t *tile_len, int n_tiles, uint2 *ranges, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_tile_starts, dim3(1), dim3(kOrderThreads), 0, s, tile_len, n_tiles, ranges, order);
+  hipLaunchKernelGGL(k_tile_starts, dim3((unsigned)((n_tiles + kStartTiles - 1) / kStartTiles)), dim3(kOrderThreads),
+                     0, s, tile_len, n_tiles, ranges);
   return hipGetLastError();
 }
 
 hipError_t launch_chunk_expand(const uint32_t *counters, const uint4 *chunks, const uint32_t *pair_id,
                                const unsigned long long *pair_mask, const uint32_t *prefix, const uint2 *ranges,
-                               const DevCamera &cam, int64_t max_chunks, uint32_t *values, hipStream_t s) {
-  const unsigned grid = xcd_grid(std::min<int64_t>(max_chunks, 8192));
+                               const DevCamera &cam, int64_t max_chunks, uint32_t *values, const uint32_t *tile_len,
+                               uint32_t *order, hipStream_t s) {
+  const int n_tiles = cam.tiles_x * cam.tiles_y;
+  if (n_tiles <= 0) return hipSuccess;
+  // without candidates the order alone
+  const unsigned grid = 1u + xcd_grid(std::min<int64_t>(max_chunks, 8192));
   hipLaunchKernelGGL(k_chunk_expand, dim3(grid), dim3(kChunk), 0, s, counters, chunks, pair_id,
-                     pair_mask, prefix, ranges, supers_of(cam), values);
+                     pair_mask, prefix, ranges, supers_of(cam), values, tile_len, n_tiles, order);
   return hipGetLastError();
 }
 
