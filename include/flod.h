@@ -315,8 +315,8 @@ flod_status flod_ctx_stats(const flod_ctx *ctx, flod_stats *out);
 
 /* Device pointers to the last render's intermediate buffers, owned by ctx, valid until
    the next call on ctx. For inspection and tests. May run a kernel and wait for it (see
-   tile_ids, bin, grad2d; FLOD_ERR_DEVICE if that fails) and take workspace for tile_ids
-   and bin (FLOD_ERR_WORKSPACE if refused). */
+   tile_ids, bin, grad2d; FLOD_ERR_DEVICE if that fails) and take workspace for them
+   (FLOD_ERR_WORKSPACE if refused). */
 typedef struct {
   const uint32_t *tile_ids;     /* [n_instances] tile id of each sorted instance (written
                                    by the first view after a render: no render needs them) */
@@ -337,11 +337,11 @@ typedef struct {
   const float *grad2d;          /* [n_candidates, 9] after flod_render_backward: per
                                    Gaussian dL/d(mu'x, mu'y, conic a, b, c, opacity, red,
                                    green, blue), with b the off-diagonal conic entry; NULL
-                                   before a backward. The backward leaves moment sums there
-                                   (the conic and opacity factors are applied per Gaussian
+                                   before a backward. The backward leaves moment sums (the
+                                   conic and opacity factors are applied per Gaussian
                                    in its last step); the first view after it applies them
-                                   in place with the stored FP32 conic and opacity (one
-                                   kernel on the stream of the last call, waited for)      */
+                                   with the stored FP32 conic and opacity (one kernel on
+                                   the stream of the last call, waited for)                */
   const uint32_t *blended;      /* [n_instances][2] per tile, the sorted instances the forward
                                    blended into some pixel of the tile, as (position in the
                                    tile's list, Gaussian) pairs in list order at the start of

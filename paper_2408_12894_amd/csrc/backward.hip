@@ -14,7 +14,8 @@
 // Then alpha -> (opacity, q) unless the 0.99 clamp is active, q -> (conic, mu'): per entry the
 // wave sums nine per-Gaussian values through LDS (the moments of e = dL/dalpha alpha over its
 // pixels, e dx, e dy, e dx^2, e dx dy, e dy^2 and e, and the colour gradient) and nine lanes
-// issue one FP32 atomic each per (tile, Gaussian); the conic and opacity factors that turn the
+// issue one FP32 atomic each per (tile, Gaussian), in small frames one FP64 atomic each per
+// (quarter of a tile, Gaussian); the conic and opacity factors that turn the
 // moments into dL/d(mu', conic, opacity) are applied per Gaussian in the preprocess backward.
 //
 // Preprocess backward: one thread per Gaussian, recomputing the forward projection (FP64)
@@ -68,6 +69,8 @@ __device__ __forceinline__ float row_sum16(float v) {
 //   clusters, 500k at 1280x720, 3,600             130        223         185
 // (Waves per tile: the first six with the reduction's second round in DPP, as it was for them.)
 constexpr int kFewBwdTiles4 = 1024, kFewBwdTiles2 = 3071;
+
+bool bwd_sums_wide(int n_tiles) { return n_tiles <= kFewBwdTiles2; }
 
 // The per-pixel decision of one entry, repeating the forward's bit for bit: the pixel takes
 // part when its walk has reached the entry and l = k q + log2 o reaches the entry's threshold
@@ -333,6 +336,12 @@ __device__ __forceinline__ void bwd_part(
 // passes from entry to entry, T and V, is a product and an affine step per entry, so each wave
 // first forms its entries' as one step, the waves exchange those through LDS, and each walks
 // its own entries from its own T and V. See kFewBwdTiles4 for the times.
+//
+// The composed steps round T and V more often than a walk entry by entry, and a Gaussian's sum takes
+// four times the terms: in FP32 its error against 64 bits was 1.00 to 1.2 times that of one wave
+// per tile (RMS of each attribute's gradient, 14 scenes of 64x64 to 1000x700). In FP64 it is 0.57 to 1.00
+// times, for the same time here and, at 873k visible Gaussians, 4 us in the preprocess backward
+// (T and V in FP64 instead: 0.78 to 1.21, and 163 us instead of 142 at 1M / 512x512).
 constexpr int kFewGroup = 4;
 
 template <int WV>
@@ -348,7 +357,7 @@ __global__ __launch_bounds__(64 * WV) void k_blend_bwd_few(
     const uint2 *__restrict__ ranges, const float4 *__restrict__ xyab, const float4 *__restrict__ cop,
     const float2 *__restrict__ blue, int W, int H, int tiles_x, int n_tiles, float bg0, float bg1, float bg2,
     const float *__restrict__ final_T, const int32_t *__restrict__ n_contrib, const float *__restrict__ dimg,
-    float *__restrict__ g2d, const uint2 *__restrict__ blended, const uint32_t *__restrict__ tile_blended,
+    double *__restrict__ g2d, const uint2 *__restrict__ blended, const uint32_t *__restrict__ tile_blended,
     const uint32_t *__restrict__ order) {
   constexpr int U = kFewGroup, C = kG2d;
   static_assert(U * C <= 64 && (U * C) % 4 == 0 && U * C / 4 <= 16, "one sum per lane");
@@ -461,7 +470,7 @@ __global__ __launch_bounds__(64 * WV) void k_blend_bwd_few(
         mine = (lane & 15) == i ? x : mine;
       }
       const int g = sh.pos[max(j1 - ce, 0)].y;
-      if (c_of < U * C && mine != 0.0f) atomicAdd(&g2d[(size_t)(uint32_t)g * C + cc], mine);
+      if (c_of < U * C && mine != 0.0f) atomicAdd(&g2d[(size_t)(uint32_t)g * C + cc], (double)mine);
       wave_lds_fence();
     }
   }
@@ -505,10 +514,10 @@ __global__ __launch_bounds__(64, 6) void k_blend_bwd(
                             final_T, n_contrib, dimg, g2d, blended, tile_blended);
 }
 
-template <class Kernel>
+template <class Kernel, class Sum>
 static void launch_blend_bwd_t(Kernel kernel, int grid, int threads, const uint2 *ranges, const float4 *xyab, const float4 *cop, const float2 *blue,
                                const DevCamera &cam, const float bg[3], const float *final_T, const int32_t *n_contrib,
-                               const float *dL_dimage, float *g2d, const uint2 *blended, const uint32_t *tile_blended,
+                               const float *dL_dimage, Sum *g2d, const uint2 *blended, const uint32_t *tile_blended,
                                const uint32_t *order, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   const int n_tiles = cam.tiles_x * cam.tiles_y;
   if (ev_start || ev_stop) {
@@ -528,7 +537,7 @@ static int split_cap2(int n_tiles) { return n_tiles / 4; }
 static int split_cap4(int n_tiles) { return n_tiles / 16; }
 int bwd_split_extra(int n_tiles) { return split_cap2(n_tiles) + 2 * split_cap4(n_tiles); }
 
-// The backward's tile order (workgroup 0) and the zeroing of the n floats of the gradient
+// The backward's tile order (workgroup 0) and the zeroing of the n 32-bit words of the gradient
 // sums at p (the other workgroups) in one launch: the order is one latency-bound workgroup, the
 // fill is bound by bandwidth, and neither needs the other (one after the other they took 9 and
 // 7 us at 1080p / 1M; together the step is 2.5 us shorter).
@@ -555,38 +564,40 @@ __global__ __launch_bounds__(kOrderThreads) void k_bwd_order_fill(CountCost cost
 
 hipError_t launch_blend_bwd(const uint2 *ranges, const float4 *xyab, const float4 *cop, const float2 *blue,
                             const DevCamera &cam, const float bg[3], const float *final_T, const int32_t *n_contrib,
-                            const float *dL_dimage, float *g2d, int64_t n_g2d, const uint2 *blended,
+                            const float *dL_dimage, void *g2d, int64_t n_g2d, const uint2 *blended,
                             const uint32_t *tile_blended, uint32_t *order, hipStream_t s, hipEvent_t ev_start,
                             hipEvent_t ev_stop) {
   const int n_tiles = cam.tiles_x * cam.tiles_y;
-  if (n_tiles <= 0) return launch_fill_u32(reinterpret_cast<uint32_t *>(g2d), 0u, n_g2d, s);
+  const int64_t words = n_g2d * (bwd_sums_wide(n_tiles) ? 2 : 1);
+  if (n_tiles <= 0) return launch_fill_u32(reinterpret_cast<uint32_t *>(g2d), 0u, words, s);
   // tiles in order of decreasing listed-entry count, the ones split in four and in two first,
   // beside the zeroing of the gradient sums the walk adds into
-  const int64_t fill_blocks = std::max<int64_t>(1, std::min<int64_t>(512, (n_g2d / 4 + 4 * kOrderThreads - 1) /
+  const int64_t fill_blocks = std::max<int64_t>(1, std::min<int64_t>(512, (words / 4 + 4 * kOrderThreads - 1) /
                                                                                (4 * kOrderThreads)));
   hipLaunchKernelGGL(k_bwd_order_fill, dim3((unsigned)(1 + fill_blocks)), dim3(kOrderThreads), 0, s,
                      CountCost{tile_blended}, n_tiles, order,
-                     TileSplit{kBwdSplitFactor, kBwdSplit4Factor, split_cap2(n_tiles), split_cap4(n_tiles)}, g2d,
-                     n_g2d);
-  const auto run = [&](auto kernel, int grid, int threads) {
-    launch_blend_bwd_t(kernel, grid, threads, ranges, xyab, cop, blue, cam, bg, final_T, n_contrib, dL_dimage, g2d, blended,
-                       tile_blended, order, s, ev_start, ev_stop);
+                     TileSplit{kBwdSplitFactor, kBwdSplit4Factor, split_cap2(n_tiles), split_cap4(n_tiles)},
+                     reinterpret_cast<float *>(g2d), words);
+  const auto run = [&](auto kernel, int grid, int threads, auto *sums) {
+    launch_blend_bwd_t(kernel, grid, threads, ranges, xyab, cop, blue, cam, bg, final_T, n_contrib, dL_dimage, sums,
+                       blended, tile_blended, order, s, ev_start, ev_stop);
   };
   const int split = n_tiles + bwd_split_extra(n_tiles);
   if (n_tiles <= kFewBwdTiles4)
-    run(k_blend_bwd_few<4>, 4 * n_tiles, 256);
+    run(k_blend_bwd_few<4>, 4 * n_tiles, 256, reinterpret_cast<double *>(g2d));
   else if (n_tiles <= kFewBwdTiles2)
-    run(k_blend_bwd_few<2>, 4 * n_tiles, 128);
+    run(k_blend_bwd_few<2>, 4 * n_tiles, 128, reinterpret_cast<double *>(g2d));
   else
-    run(k_blend_bwd, split, 64);
+    run(k_blend_bwd, split, 64, reinterpret_cast<float *>(g2d));
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------
 
 // The chain rule for one visible Gaussian i; its SH gradient row goes to dsh (LDS).
+template <class Sum>
 __device__ __forceinline__ void preprocess_bwd_one(const PreParams &p, const DevLevel &L, int64_t i,
-                                                        const float *__restrict__ g2d,
+                                                        const Sum *__restrict__ g2d,
                                                         const float4 *__restrict__ shjac, const flod_grads &out,
                                                         float4 *dsh) {
   double g[kG2d];   // the blend backward's sums (moments of e, colour), turned into gradients below
@@ -760,8 +771,9 @@ __device__ __forceinline__ void preprocess_bwd_one(const PreParams &p, const Dev
 // lane of a store instruction hit a different cache line: 0.126 -> 0.097 ms at 1080p / 1M).
 constexpr int kShRow4 = FLOD_SH_COEFFS * 3 / 4;   // float4 per SH row
 
+template <class Sum>
 __global__ __launch_bounds__(kBlock) void k_preprocess_bwd(PreParams p, const uint32_t *__restrict__ tiles,
-                                                           const float *__restrict__ g2d,
+                                                           const Sum *__restrict__ g2d,
                                                            const float4 *__restrict__ shjac, flod_grads out) {
   __shared__ float4 s_sh[kBlock * kShRow4];   // 48 KB: the workgroup's SH gradient rows
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -783,39 +795,59 @@ __global__ __launch_bounds__(kBlock) void k_preprocess_bwd(PreParams p, const ui
   for (int f = threadIdx.x; f < nf; f += kBlock) dst[f] = s_sh[f];
 }
 
-hipError_t launch_preprocess_bwd(const PreParams &p, const uint32_t *tiles, const float *g2d,
+hipError_t launch_preprocess_bwd(const PreParams &p, const uint32_t *tiles, const void *g2d, bool wide,
                                  const float4 *shjac, const flod_grads &g, hipStream_t s) {
   const int64_t n = p.lv[0].n;
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_preprocess_bwd, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, p, tiles,
-                     g2d, shjac, g);
+  const dim3 grid((unsigned)((n + kBlock - 1) / kBlock));
+  if (wide)
+    hipLaunchKernelGGL(k_preprocess_bwd<double>, grid, dim3(kBlock), 0, s, p, tiles,
+                       reinterpret_cast<const double *>(g2d), shjac, g);
+  else
+    hipLaunchKernelGGL(k_preprocess_bwd<float>, grid, dim3(kBlock), 0, s, p, tiles,
+                       reinterpret_cast<const float *>(g2d), shjac, g);
   return hipGetLastError();
 }
 
-// The blend backward's per-Gaussian moment sums turned into dL/d(mu', conic a, b, c, opacity)
-// in place, with the stored FP32 conic and opacity (for inspection: the preprocess backward
-// applies the same factors with its FP64 conic).
+// The blend backward's per-Gaussian moment sums turned into dL/d(mu', conic a, b, c, opacity),
+// with the stored FP32 conic and opacity, in place where they are floats (for inspection: the
+// preprocess backward applies the same factors with its FP64 conic).
+template <class Sum>
 __global__ __launch_bounds__(kBlock) void k_g2d_from_moments(int64_t n, const uint32_t *__restrict__ tiles,
                                                              const float4 *__restrict__ xyab,
-                                                             const float4 *__restrict__ cop, float *__restrict__ g2d) {
+                                                             const float4 *__restrict__ cop,
+                                                             const Sum *sums, float *g2d) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n || tiles[i] == 0u) return;   // not rendered: zero sums, and no conic stored
+  if (i >= n) return;
+  const Sum *m = sums + i * kG2d;
   float *g = g2d + i * kG2d;
+  if (tiles[i] == 0u) {   // not rendered: zero sums, and no conic stored
+#pragma unroll
+    for (int c = 0; c < kG2d; ++c) g[c] = 0.0f;
+    return;
+  }
   const double a = xyab[i].z, b = xyab[i].w, c = cop[i].x, o = cop[i].y;
-  const double m_dx = g[0], m_dy = g[1];
+  const double m_dx = m[0], m_dy = m[1];
   g[0] = (float)(a * m_dx + b * m_dy);
   g[1] = (float)(b * m_dx + c * m_dy);
-  g[2] = (float)(-0.5 * (double)g[2]);
-  g[3] = (float)(-(double)g[3]);
-  g[4] = (float)(-0.5 * (double)g[4]);
-  g[5] = (float)((double)g[5] / o);
+  g[2] = (float)(-0.5 * (double)m[2]);
+  g[3] = (float)(-(double)m[3]);
+  g[4] = (float)(-0.5 * (double)m[4]);
+  g[5] = (float)((double)m[5] / o);
+#pragma unroll
+  for (int ch = 6; ch < kG2d; ++ch) g[ch] = (float)m[ch];
 }
 
 hipError_t launch_g2d_from_moments(int64_t n, const uint32_t *tiles, const float4 *xyab, const float4 *cop,
-                                   float *g2d, hipStream_t s) {
+                                   const void *sums, bool wide, float *g2d, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_g2d_from_moments, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, tiles,
-                     xyab, cop, g2d);
+  const dim3 grid((unsigned)((n + kBlock - 1) / kBlock));
+  if (wide)
+    hipLaunchKernelGGL(k_g2d_from_moments<double>, grid, dim3(kBlock), 0, s, n, tiles, xyab, cop,
+                       reinterpret_cast<const double *>(sums), g2d);
+  else
+    hipLaunchKernelGGL(k_g2d_from_moments<float>, grid, dim3(kBlock), 0, s, n, tiles, xyab, cop,
+                       reinterpret_cast<const float *>(sums), g2d);
   return hipGetLastError();
 }
 

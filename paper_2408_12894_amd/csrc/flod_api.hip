@@ -58,7 +58,7 @@ enum BufId {
   B_DKEY0, B_DKEY1, B_DVAL0, B_DVAL1, B_RECT, B_SRECT, B_SPANS,
   B_PAIR_ID, B_PAIR_MASK, B_CHUNKS, B_CHUNK_CNT, B_SUPERS, B_TILE_LEN, B_VALUES, B_TILE_IDS, B_BIN,
   B_HIST, B_SCAN, B_TOT, B_RANGES, B_COUNTERS,
-  B_G2D, B_SSIM, B_BLENDED, B_TILE_BLENDED, B_TILE_ORDER, B_SHJAC, B_COUNT
+  B_G2D, B_GRAD2D, B_SSIM, B_BLENDED, B_TILE_BLENDED, B_TILE_ORDER, B_SHJAC, B_COUNT
 };
 
 struct Saved {
@@ -72,7 +72,8 @@ struct Saved {
   const int32_t *n_contrib = nullptr;
   bool has_tile_ids = false;     // B_TILE_IDS holds the list's tile ids (see flod_ctx_view)
   bool has_grad2d = false;
-  bool grad2d_moments = false;   // B_G2D still holds the backward's moment sums (see flod_ctx_view)
+  bool grad2d_moments = false;   // the backward's moment sums in B_G2D are still to be turned into gradients
+  bool grad2d_wide = false;      // they are doubles, and the gradients go to B_GRAD2D (see flod_ctx_view)
   bool has_blended = false;      // the render listed its blended entries (the backward needs them)
 };
 
@@ -1143,12 +1144,13 @@ flod_status flod_render_backward(flod_ctx *ctx, const float *dL_dimage, flod_gra
   if (N == 0) return FLOD_OK;
   size_t extra = 0;
   const int n_tiles = sv.cam.tiles_x * sv.cam.tiles_y;
-  if (ensure(ctx, B_G2D, 9 * 4 * (size_t)N, s, &extra) != FLOD_OK ||
+  const bool wide = bwd_sums_wide(n_tiles);
+  if (ensure(ctx, B_G2D, 9 * (wide ? 8 : 4) * (size_t)N, s, &extra) != FLOD_OK ||
       ensure(ctx, B_TILE_ORDER, 4 * ((size_t)n_tiles + 2), s, &extra) != FLOD_OK) {
     ctx->required = ws_bytes(ctx) + extra;
     return FLOD_ERR_WORKSPACE;
   }
-  float *g2d = P<float>(ctx, B_G2D);
+  void *g2d = P<void>(ctx, B_G2D);
   uint32_t *order = P<uint32_t>(ctx, B_TILE_ORDER);
   hipEvent_t ev_a, ev_b;
   tm.dispatch(FLOD_STAGE_BLEND_BWD, &ev_a, &ev_b);
@@ -1165,11 +1167,12 @@ flod_status flod_render_backward(flod_ctx *ctx, const float *dL_dimage, flod_gra
   L.logits = sv.level.opacity_logits; L.sh = sv.level.sh;
   L.offset = 0; L.n = N; L.s_min = sv.level.s_min;
   p.n_total = N;
-  if (launch_preprocess_bwd(p, P<uint32_t>(ctx, B_TILES), g2d, P<float4>(ctx, B_SHJAC), *grads, s) != hipSuccess)
+  if (launch_preprocess_bwd(p, P<uint32_t>(ctx, B_TILES), g2d, wide, P<float4>(ctx, B_SHJAC), *grads, s) != hipSuccess)
     return FLOD_ERR_DEVICE;
   tm.end();
   ctx->saved.has_grad2d = true;
   ctx->saved.grad2d_moments = true;
+  ctx->saved.grad2d_wide = wide;
   return FLOD_OK;
 }
 
@@ -1215,15 +1218,21 @@ flod_status flod_ctx_view(const flod_ctx *ctx, flod_view *out) {
   out->conic_c_opacity_rg = P<float>(c, B_COP);
   out->blue = P<float>(c, B_BLUE);
   if (sv.has_grad2d && sv.grad2d_moments) {
-    // the first view after a backward turns its moment sums into the gradient, in place
-    if (hipSetDevice(ctx->device) != hipSuccess ||
-        launch_g2d_from_moments(sv.level.n, P<uint32_t>(c, B_TILES), P<float4>(c, B_XYAB), P<float4>(c, B_COP),
-                                P<float>(c, B_G2D), c->last_stream) != hipSuccess ||
+    // the first view after a backward turns its moment sums into the gradient
+    size_t extra = 0;
+    if (hipSetDevice(ctx->device) != hipSuccess) return FLOD_ERR_DEVICE;
+    if (sv.grad2d_wide && ensure(c, B_GRAD2D, 9 * 4 * (size_t)sv.level.n, c->last_stream, &extra) != FLOD_OK) {
+      c->required = ws_bytes(c) + extra;
+      return FLOD_ERR_WORKSPACE;
+    }
+    if (launch_g2d_from_moments(sv.level.n, P<uint32_t>(c, B_TILES), P<float4>(c, B_XYAB), P<float4>(c, B_COP),
+                                P<void>(c, B_G2D), sv.grad2d_wide, P<float>(c, sv.grad2d_wide ? B_GRAD2D : B_G2D),
+                                c->last_stream) != hipSuccess ||
         hipStreamSynchronize(c->last_stream) != hipSuccess)
       return FLOD_ERR_DEVICE;
     c->saved.grad2d_moments = false;
   }
-  out->grad2d = sv.has_grad2d ? P<float>(c, B_G2D) : nullptr;
+  out->grad2d = sv.has_grad2d ? P<float>(c, sv.grad2d_wide ? B_GRAD2D : B_G2D) : nullptr;
   out->blended = P<uint32_t>(c, B_BLENDED);
   out->tile_blended = P<uint32_t>(c, B_TILE_BLENDED);
   return FLOD_OK;

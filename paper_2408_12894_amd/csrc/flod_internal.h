@@ -310,20 +310,24 @@ hipError_t launch_blend(const uint2 *ranges, const uint32_t *values, const float
                         int32_t *n_blended, uint2 *blended, uint32_t *tile_blended, const uint32_t *order,
                         bool large, hipStream_t s);
 // order: n_tiles + 2 words of scratch (the backward's tile order and its counts of split tiles);
-// g2d: the n_g2d floats of gradient sums, zeroed here first; the kernel is timed by the events
-// (if given), its tile order and the zeroing are not
+// g2d: the n_g2d gradient sums, doubles where bwd_sums_wide, else floats, zeroed here first; the kernel
+// is timed by the events (if given), its tile order and the zeroing are not
 hipError_t launch_blend_bwd(const uint2 *ranges, const float4 *xyab, const float4 *cop, const float2 *blue,
                             const DevCamera &cam, const float bg[3], const float *final_T,
-                            const int32_t *n_contrib, const float *dL_dimage, float *g2d, int64_t n_g2d,
+                            const int32_t *n_contrib, const float *dL_dimage, void *g2d, int64_t n_g2d,
                             const uint2 *blended, const uint32_t *tile_blended, uint32_t *order,
                             hipStream_t s, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// whether the backward of a frame of that many tiles adds its gradient sums in FP64
+bool bwd_sums_wide(int n_tiles);
 // the most blocks the backward's split tiles add beyond one per tile
 int bwd_split_extra(int n_tiles);
-// The blend backward's per-Gaussian moment sums into dL/d(mu', conic) in place (inspection).
+// The blend backward's per-Gaussian moment sums (doubles when wide) into dL/d(mu', conic, opacity)
+// and the colour's, as floats, to g2d (inspection; floats in place).
 hipError_t launch_g2d_from_moments(int64_t n, const uint32_t *tiles, const float4 *xyab, const float4 *cop,
-                                   float *g2d, hipStream_t s);
+                                   const void *sums, bool wide, float *g2d, hipStream_t s);
 // shjac: the forward preprocess's Jacobians and pre-clamp colours (PreOut::shjac)
-hipError_t launch_preprocess_bwd(const PreParams &p, const uint32_t *tiles, const float *g2d,
+// (g2d: doubles when wide)
+hipError_t launch_preprocess_bwd(const PreParams &p, const uint32_t *tiles, const void *g2d, bool wide,
                                  const float4 *shjac, const flod_grads &g, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 // The kept Gaussians of several levels' bands, counted per workgroup: level k's workgroups are
