@@ -96,8 +96,7 @@ struct flod_ctx {
   unsigned long long *host_counts_dev = nullptr;
   uint32_t count_seq = 0;
   Saved saved;
-  bool far_depths = false;            // the last render had depths beyond the depth sort's three passes,
-                                      // so the next one launches four
+  int far_hold = 0;                   // renders that still launch the depth sort's fourth pass (see kFarHold)
   bool keep_backward = true;          // renders list their blended entries (flod_ctx_keep_backward_state)
   flod_stats stats{};
   // timing
@@ -396,17 +395,18 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   // render's number
   const bool direct = c->host_counts_dev != nullptr;
   const uint32_t seq = direct ? next_seq(c) : 0u;
-  auto totals = [&](int64_t guard_k, int64_t guard_p, bool to_host) {
+  auto totals = [&](int64_t guard_k, int64_t guard_p, bool to_host, bool near_only) {
     return FrameTotals{P<uint4>(c, B_BLOCKVIS), nb, counters, (unsigned long long)guard_k, (unsigned long long)guard_p,
-                       to_host ? c->host_counts_dev : nullptr, seq};
+                       to_host ? c->host_counts_dev : nullptr, seq, near_only};
   };
+  const bool three_passes = N > kSmallSort && c->far_hold == 0;
   auto depth_sort = [&](bool far) {
     uint32_t *dk[2] = {P<uint32_t>(c, B_DKEY0), P<uint32_t>(c, B_DKEY1)};
     uint32_t *dv[2] = {P<uint32_t>(c, B_DVAL0), P<uint32_t>(c, B_DVAL1)};
     const int64_t no_cap = 0xFFFFFFFEll;
     uint4 *sums = P<uint4>(c, B_BLOCKVIS);
     const DepthSort ds{P<uint32_t>(c, B_DEPTH), P<uint2>(c, B_RECT), P<uint2>(c, B_SRECT), sums, sums + nb,
-                       totals(speculate ? cap : no_cap, speculate ? cap_p : no_cap, direct), far};
+                       totals(speculate ? cap : no_cap, speculate ? cap_p : no_cap, direct, !far && N > kSmallSort), far};
     if (N <= kSmallSort) return launch_depth_sort_small(ds, N, nb, dv[0], s);
     return launch_radix_sort(dk, dv, counters + kCntVisible, N, 32, P<uint32_t>(c, B_HIST), P<uint32_t>(c, B_SCAN),
                              P<uint32_t>(c, B_TOT), &dres, s, &ds);
@@ -428,7 +428,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     if (launch_preprocess(p, o, s) != hipSuccess) return FLOD_ERR_DEVICE;
     tm.end();
     tm.begin(FLOD_STAGE_DEPTH_SORT);
-    if (depth_sort(c->far_depths) != hipSuccess) return FLOD_ERR_DEVICE;
+    if (depth_sort(!three_passes) != hipSuccess) return FLOD_ERR_DEVICE;
     // the count read-back: written by the totals themselves (direct), else copied
     if (!direct && (hipMemcpyAsync(c->host_counters, counters, 24, hipMemcpyDeviceToHost, s) != hipSuccess ||
                     mark_stream(c, s) != hipSuccess))
@@ -505,9 +505,10 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   c->stats.width = cam.W;
   c->stats.height = cam.H;
   if (K >= 0xFFFFFFFFull || n_pairs >= 0xFFFFFFFFull) return FLOD_ERR_OVERFLOW;
-  // depths beyond the three passes that were launched: the order is wrong, and is taken again
-  const bool again = far && !c->far_depths && N > kSmallSort;
-  c->far_depths = far;
+  // depths beyond the three passes that were launched: the order is taken again, and the tail, which
+  // found no pairs, enqueued again
+  const bool again = far && three_passes;
+  if (N > kSmallSort) c->far_hold = far ? kFarHold : c->far_hold > 0 ? c->far_hold - 1 : 0;
   if (again && depth_sort(true) != hipSuccess) return FLOD_ERR_DEVICE;
   if (again || !speculate || (int64_t)K > cap || (int64_t)n_pairs > cap_p) {
     if ((int64_t)K > cap || (int64_t)n_pairs > cap_p) {
@@ -528,7 +529,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
         c->required = ws_bytes(c) + extra;
         return st;
       }
-      if (speculate && launch_frame_totals(totals(cap, cap_p, false), s) != hipSuccess) return FLOD_ERR_DEVICE;
+      if (speculate && launch_frame_totals(totals(cap, cap_p, false, false), s) != hipSuccess) return FLOD_ERR_DEVICE;
     }
     if ((st = tail()) != FLOD_OK) return st;
   }

@@ -18,6 +18,9 @@ constexpr int kRadix = 1 << kRadixBits;   // 256 buckets per radix pass
 // 78 us at 857k keys, 26 against 35 at 8k.
 constexpr int kDepthBits = 9, kDepthRadix = 1 << kDepthBits, kDepthFarBits = 31;
 constexpr uint32_t kDepthBase = 0x3E000000u;
+// A frame sorted again after three passes pays for both sorts, so the next kFarHold frames start with
+// four: a camera that alternates between near and far views pays once.
+constexpr int kFarHold = 32;
 constexpr int64_t kSmallSort = 8192;      // candidates up to which one workgroup sorts the frame
 constexpr int kSortItems = 12;            // keys per thread in a radix pass (measured 8 / 12 / 16)
 constexpr int kSortTile = kBlock * kSortItems;   // 3072 keys per workgroup
@@ -143,6 +146,8 @@ enum : int {
 // visible candidates, instances K and pairs P, to the device counters and, when host_out is
 // given (coherent host memory), to the host. kCntPairs receives P when K <= cap_k and
 // P <= cap_p and 0 otherwise: kernels sized for those capacities read it and then do nothing.
+// near_only: 0 too when there are far candidates, whose order three passes leave wrong (the host sorts
+// again, with four, and takes the totals without it).
 // host_out receives six 64-bit words, each host_seq in its high half and in its low half the
 // visible count, the low and high halves of K and of P, and the count of far ones: system-scope stores of whole words,
 // so a host that polls them sees every word either old or complete and needs neither a copy
@@ -154,6 +159,7 @@ struct FrameTotals {
   unsigned long long cap_k, cap_p;
   unsigned long long *host_out;
   uint32_t host_seq;
+  bool near_only;
 };
 
 __device__ __forceinline__ void frame_totals(const FrameTotals &t) {
@@ -202,7 +208,7 @@ __device__ __forceinline__ void frame_totals(const FrameTotals &t) {
   t.counters[kCntFar] = (uint32_t)far;
   *reinterpret_cast<unsigned long long *>(t.counters + kCntTotal64) = k;
   *reinterpret_cast<unsigned long long *>(t.counters + kCntPairs64) = p;
-  t.counters[kCntPairs] = k <= t.cap_k && p <= t.cap_p ? (uint32_t)p : 0u;
+  t.counters[kCntPairs] = k <= t.cap_k && p <= t.cap_p && !(t.near_only && far) ? (uint32_t)p : 0u;
   if (t.host_out) {
     const unsigned long long tag = (unsigned long long)t.host_seq << 32;
     const unsigned long long w[6] = {tag | v, tag | (k & 0xFFFFFFFFull), tag | (k >> 32), tag | (p & 0xFFFFFFFFull),
