@@ -84,10 +84,12 @@ struct OrderShared {
   uint32_t split[2];
 };
 
-// The tile order as one workgroup of W waves (W >= 4: a thread per bucket).
+// The tile order as one workgroup of W waves (W >= 4: a thread per bucket): of the n tiles first,
+// first + step, first + 2 step ..., written at those places of the order (several workgroups make one of
+// a large frame between them, each of a like share of the tiles).
 template <int W, class Cost>
 __device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restrict__ order, TileSplit split,
-                                           OrderShared<W> &sh) {
+                                           OrderShared<W> &sh, int first = 0, int step = 1) {
   static_assert(64 * W >= kOrderBuckets, "a thread per bucket");
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   for (int k = tid; k < W * kOrderBuckets; k += 64 * W) (&sh.cnt[0][0])[k] = 0u;
@@ -103,7 +105,7 @@ __device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restric
   for (int base = t0 + lane; base < t1; base += 64 * kOrderLoads) {
     uint32_t c[kOrderLoads];
 #pragma unroll
-    for (int u = 0; u < kOrderLoads; ++u) c[u] = cost(min(base + 64 * u, t1 - 1));   // in bounds: base < t1
+    for (int u = 0; u < kOrderLoads; ++u) c[u] = cost(first + step * min(base + 64 * u, t1 - 1));   // in bounds: base < t1
 #pragma unroll
     for (int u = 0; u < kOrderLoads; ++u)
       if (base + 64 * u < t1) {
@@ -163,10 +165,11 @@ __device__ __forceinline__ void tile_order(Cost cost, int n, uint32_t *__restric
   for (int base = t0 + lane; base < t1; base += 64 * kOrderLoads) {
     uint32_t c[kOrderLoads];
 #pragma unroll
-    for (int u = 0; u < kOrderLoads; ++u) c[u] = cost(min(base + 64 * u, t1 - 1));   // in bounds: base < t1
+    for (int u = 0; u < kOrderLoads; ++u) c[u] = cost(first + step * min(base + 64 * u, t1 - 1));   // in bounds: base < t1
 #pragma unroll
     for (int u = 0; u < kOrderLoads; ++u)
-      if (base + 64 * u < t1) order[atomicAdd(&sh.cnt[w][cost_bucket(c[u])], 1u)] = (uint32_t)(base + 64 * u);
+      if (base + 64 * u < t1)
+        order[first + step * (int)atomicAdd(&sh.cnt[w][cost_bucket(c[u])], 1u)] = (uint32_t)(first + step * (base + 64 * u));
   }
   if (split.cap2 >= 0 && tid < 2) order[n + tid] = sh.split[tid];
 }

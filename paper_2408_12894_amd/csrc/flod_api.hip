@@ -280,7 +280,7 @@ flod_status check_level(const flod_level *lv) {
 
 flod_status check_camera(const flod_camera *cam) {
   if (!cam) return FLOD_ERR_INVALID_ARG;
-  if (cam->width <= 0 || cam->height <= 0 || cam->width > 16384 || cam->height > 16384) return FLOD_ERR_INVALID_ARG;
+  if (cam->width <= 0 || cam->height <= 0 || cam->width > kMaxSide || cam->height > kMaxSide) return FLOD_ERR_INVALID_ARG;
   if (!(cam->fx > 0.0f) || !(cam->fy > 0.0f) || !isfinite(cam->fx) || !isfinite(cam->fy)) return FLOD_ERR_INVALID_ARG;
   return FLOD_OK;
 }
@@ -354,7 +354,6 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     need(B_CHUNK_CNT, 256 * n);
   };
   const size_t hist_d = radix_hist_bytes(N, true), hist_p = pair_hist_bytes(cam, N);
-  const size_t hist = hist_d > hist_p ? hist_d : hist_p;
   need(B_XYAB, 16 * (size_t)N);
   need(B_COP, 16 * (size_t)N);
   need(B_BLUE, 8 * (size_t)N);
@@ -369,9 +368,10 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   need(B_RECT, 8 * (size_t)N);
   need(B_SRECT, 8 * (size_t)N);
   need(B_SPANS, 16 * (size_t)N);
-  need(B_HIST, hist);
-  need(B_SCAN, hist);
-  need(B_TOT, 4 * (size_t)(n_supers > kDepthRadix ? n_supers : kDepthRadix));
+  need(B_HIST, hist_d);
+  need(B_SCAN, hist_d > hist_p ? hist_d : hist_p);   // the pairs' counts are scanned in place
+  const size_t tot_d = 4 * (size_t)kDepthRadix, tot_p = pair_tot_bytes(cam);
+  need(B_TOT, tot_p > tot_d ? tot_p : tot_d);
   need(B_SUPERS, 8 * (size_t)n_supers);
   need_chunks();
   need(B_TILE_LEN, 4 * (size_t)n_tiles);
@@ -438,13 +438,12 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   // the tile lists of at most what the buffers hold, and the blend
   auto tail = [&]() -> flod_status {
     uint32_t *ids = dres ? P<uint32_t>(c, B_DVAL1) : P<uint32_t>(c, B_DVAL0);
-    uint32_t *hist_a = P<uint32_t>(c, B_HIST), *scan_a = P<uint32_t>(c, B_SCAN), *tot = P<uint32_t>(c, B_TOT);
+    uint32_t *scan_a = P<uint32_t>(c, B_SCAN), *tot = P<uint32_t>(c, B_TOT);
     uint32_t *tile_len = P<uint32_t>(c, B_TILE_LEN), *order = P<uint32_t>(c, B_TILE_ORDER);
     const int64_t max_chunks = chunk_capacity(cam, cap_p);
     if (N > 0) {
       tm.begin(FLOD_STAGE_OFFSETS);
-      if (launch_pair_offsets(ids, counters, P<uint2>(c, B_SRECT), bin_in(c), cam, N, hist_a, scan_a, tot,
-                              s) != hipSuccess)
+      if (launch_pair_offsets(ids, counters, P<uint2>(c, B_SRECT), bin_in(c), cam, N, scan_a, tot, s) != hipSuccess)
         return FLOD_ERR_DEVICE;
       tm.end();
       tm.begin(FLOD_STAGE_TILE_SORT);

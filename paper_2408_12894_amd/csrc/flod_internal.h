@@ -9,6 +9,7 @@
 namespace flod {
 
 constexpr int kTile = FLOD_TILE;          // 16x16 pixel tiles
+constexpr int kMaxSide = 16384;           // largest frame side
 constexpr int kBlock = 256;               // threads per workgroup (4 wave64)
 constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;   // 256 buckets per radix pass
@@ -29,8 +30,8 @@ constexpr int64_t kRadixBigSort = 4 << 20;
 constexpr int kSortItemsHuge = 16;        // 4096-key workgroups for sorts of kRadixHugeSort keys or more
 constexpr int64_t kRadixHugeSort = 32 << 20;
 constexpr int kSuper = 8;                 // a supertile is kSuper x kSuper tiles (one bit each of a 64-bit mask)
-constexpr int kSuperWindow = 512;         // supertiles counted in LDS at once
-constexpr int kPairBlock = 256;           // depth-sorted Gaussians per workgroup of the pair kernels
+constexpr int kSuperWindow = 512;         // supertiles whose pairs a workgroup places
+constexpr int kPairBlock = 256;           // depth-sorted Gaussians a workgroup of the pair kernels takes at once
 constexpr int kChunk = 256;               // pairs of one supertile expanded by one workgroup
 constexpr int kSpanBox = 16;              // largest footprint (tiles a side) whose row spans are stored
 constexpr int kPairRectMax = 16;          // largest rectangle (in supertiles) listed whole
@@ -277,18 +278,19 @@ hipError_t launch_depth_sort_small(const DepthSort &d, int64_t n, int blocks, ui
 hipError_t launch_radix_sort(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_ptr,
                              int64_t n_max, int bits, uint32_t *hist, uint32_t *scan,
                              uint32_t *tot, int *result_buf, hipStream_t s, const DepthSort *depth = nullptr);
-// Exclusive prefix of each of `rows` rows of ceil(*n_ptr / tile) counts, and the rows' sums.
+// Exclusive prefix of each of `rows` rows of ceil(*n_ptr / tile) counts (scan may be hist), and the
+// rows' sums.
 hipError_t launch_row_scan(const uint32_t *n_ptr, const uint32_t *hist, uint32_t *scan, uint32_t *tot, int rows,
                            int stride, int tile, hipStream_t s);
 // Binning through supertiles (tilebin.hip)
 int super_count(const DevCamera &cam);
-size_t pair_hist_bytes(const DevCamera &cam, int64_t n);       // bytes of its hist and scan arrays
+size_t pair_hist_bytes(const DevCamera &cam, int64_t n);       // bytes of its scan array
+size_t pair_tot_bytes(const DevCamera &cam);                   // and of its tot array
 int64_t chunk_capacity(const DevCamera &cam, int64_t pairs);   // the most chunks that many pairs make
 hipError_t launch_pair_offsets(const uint32_t *ids, const uint32_t *counters, const uint2 *srect, const BinIn &bin,
-                               const DevCamera &cam, int64_t n, uint32_t *hist, uint32_t *scan, uint32_t *tot,
-                               hipStream_t s);
+                               const DevCamera &cam, int64_t n, uint32_t *scan, uint32_t *tot, hipStream_t s);
 hipError_t launch_pair_place(const uint32_t *ids, uint32_t *counters, const uint2 *srect, const BinIn &bin,
-                             const DevCamera &cam, int64_t n, const uint32_t *scan, const uint32_t *tot,
+                             const DevCamera &cam, int64_t n, const uint32_t *scan, uint32_t *tot,
                              uint32_t *pair_id, unsigned long long *pair_mask, uint4 *chunks, uint2 *supers,
                              hipStream_t s);
 hipError_t launch_chunk_counts(const uint32_t *counters, const uint4 *chunks, const unsigned long long *pair_mask,

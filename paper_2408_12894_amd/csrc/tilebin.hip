@@ -6,8 +6,9 @@
 // the supertile's tiles it covers: a pair. Pairs are several times fewer than instances (1.6
 // per Gaussian against 9.8 instances at 1080p / 1M, 3.8 against 73 for the finest level at
 // 3840x2160), so what is moved per instance is only the final list entry:
-//   1. k_pair_hist   per workgroup of 256 depth-sorted Gaussians, its pairs per supertile
-//   2. k_rs_scan     per supertile, the exclusive prefix of those counts over the workgroups
+//   1. k_pair_hist   per column of 256 depth-sorted Gaussians (more in frames above 4K), its pairs per
+//                    supertile
+//   2. k_rs_scan     per supertile, the exclusive prefix of those counts over the columns
 //   3. k_pair_place  the pairs (Gaussian, mask), grouped by supertile and in depth order
 //                    inside it, and the descriptors of their chunks of 256
 //   4. k_chunk_count per chunk, the instances of each of the supertile's 64 tiles
@@ -32,6 +33,14 @@ namespace flod {
 constexpr int kPairWaves = kPairBlock / 64;
 constexpr int kPairWords = kPairBlock / 32;       // words of a bit per Gaussian of a workgroup
 constexpr int kWinPer = kSuperWindow / kPairBlock;   // supertiles of a window per thread
+// A column of the pair counts is kPairBlock Gaussians where all supertiles fit one window (frames up to
+// 3840x2160). Beyond, where a count per supertile and 256 Gaussians would take as much as 320 bytes per
+// Gaussian (16384x16384; 2.3 GB for the two arrays of 4.4M), it is as many times that as there are windows
+// (8 bytes per Gaussian again), while there are kColumnsMin columns to fill the device. More
+// Gaussians to a column than that leave too few workgroups to a frame of few windows (sixteen times 256 of
+// 1M Gaussians: 874 us a frame instead of 740 at 4096x2160, two windows).
+constexpr int kMostSupers = kMaxSide / (kTile * kSuper), kMostWindows = kMostSupers * kMostSupers / kSuperWindow;
+constexpr int kColumnBlocks = kMostWindows, kColumnsMin = 256;
 
 struct Supers {
   int tiles_x, tiles_y;
@@ -87,9 +96,9 @@ struct PairRows {
 };
 
 // ---------------------------------------------------------------------------------------
-// Pairs of each workgroup's 256 Gaussians per supertile: hist[s * stride + block], for the
-// per-supertile scan over the blocks. Supertiles are taken in windows that fit the LDS counts
-// (one window up to 4K frames). The columns of large footprints listed row by row are read where
+// Pairs of each column of `per` Gaussians (one workgroup) per supertile: hist[s * stride + column],
+// for the per-supertile scan over the columns; all supertiles' counts in LDS (64 KB at most). The
+// columns of large footprints listed row by row are read where
 // the preprocess stored them: recomputing their rows in FP64, a serial chain of up to 10 us in
 // the few waves that have one, took 17 instead of 8 us at 1M Gaussians / 1080p (0.001% of them)
 // and 63 instead of 29 at 2.5M / 3840x2160 (0.14%). What remains there is the 4.3M strided
@@ -99,46 +108,30 @@ struct PairRows {
 __global__ __launch_bounds__(kPairBlock) void k_pair_hist(const uint32_t *__restrict__ ids,
                                                           const uint32_t *__restrict__ counters,
                                                           const uint2 *__restrict__ srect, BinIn bin, Supers su,
-                                                          uint32_t *__restrict__ hist, int stride) {
-  __shared__ uint32_t s_cnt[kSuperWindow];
+                                                          uint32_t *__restrict__ hist, int stride, uint32_t per) {
+  extern __shared__ uint32_t s_cnt[];
   const uint32_t n = counters[kCntVisible];
   if (counters[kCntPairs] == 0u) return;   // no pairs, or more than the buffers hold
-  const uint32_t nb = (n + kPairBlock - 1) / kPairBlock;
+  const uint32_t nb = (n + per - 1) / per;
   const uint32_t b = xcd_block(blockIdx.x);
   if (b >= nb) return;
-  const int tid = threadIdx.x;
-  const uint32_t j = b * kPairBlock + tid;
-  PairRows r;
-  r.load(make_uint2(0u, 0u));
-  r.y1 = -1;
-  uint32_t g = 0u;
-  if (j < n) {
-    r.load(srect[j]);
-    if (r.banded) g = ids[j];
+  const uint32_t base = b * per, count = min(per, n - base);
+  for (int s = threadIdx.x; s < su.n; s += kPairBlock) s_cnt[s] = 0u;
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < count; i += kPairBlock) {
+    PairRows r;
+    r.load(srect[base + i]);
+    uint32_t g = 0u;
+    if (r.banded) g = ids[base + i];
     if (r.banded && !r.bands) r.load_footprint(bin, g, su.tiles_y);
-  }
-  for (int w0 = 0; w0 < su.n; w0 += kSuperWindow) {
-#pragma unroll
-    for (int k = 0; k < kWinPer; ++k) s_cnt[tid + k * kPairBlock] = 0u;
-    __syncthreads();
-    const int w1 = min(su.n, w0 + kSuperWindow);
     for (int sy = r.y0 / kSuper; sy * kSuper <= r.y1; ++sy) {
-      const int first = sy * su.nx;
-      if (first >= w1 || first + su.nx <= w0) continue;
       int c0, c1;
       r.columns(sy, bin, g, su.tiles_x, c0, c1);
-      c0 = max(c0, w0 - first);
-      c1 = min(c1, w1 - 1 - first);
-      for (int c = c0; c <= c1; ++c) atomicAdd(&s_cnt[first + c - w0], 1u);
+      for (int c = c0; c <= c1; ++c) atomicAdd(&s_cnt[sy * su.nx + c], 1u);
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kWinPer; ++k) {
-      const int s = w0 + tid + k * kPairBlock;
-      if (s < w1) hist[(size_t)s * stride + b] = s_cnt[s - w0];
-    }
-    __syncthreads();
   }
+  __syncthreads();
+  for (int s = threadIdx.x; s < su.n; s += kPairBlock) hist[(size_t)s * stride + b] = s_cnt[s];
 }
 
 // Row spans of footprints, the rows of a wave's Gaussians dealt to its lanes in order: those whose
@@ -202,9 +195,24 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t &a, uint32_t &b, uint3
   b = bb + ib - b;
 }
 
+// Position of the r-th set bit of m (r below its bit count).
+__device__ __forceinline__ uint32_t select_bit(unsigned long long m, uint32_t r) {
+  uint32_t at = 0u;
+#pragma unroll
+  for (int step = 32; step > 0; step >>= 1) {
+    const uint32_t c = (uint32_t)__popcll(m & ((1ull << step) - 1ull));
+    if (r >= c) {
+      r -= c;
+      m >>= step;
+      at += step;
+    }
+  }
+  return at;
+}
+
 // ---------------------------------------------------------------------------------------
-// The pairs, each at its supertile's start + the earlier workgroups' pairs there + its rank
-// among the workgroup's. Ranks: one bit per (supertile, Gaussian) in LDS, its prefix over the
+// The pairs, each at its supertile's start + the earlier columns' pairs there + its rank
+// among the column's. Ranks: one bit per (supertile, Gaussian) in LDS, its prefix over the
 // words of a supertile, and a bit count inside the word. Rows: read where the preprocess stored
 // them (16 bytes for a footprint of up to 16 x 16 tiles), else computed by the wave into LDS
 // (wave_row_spans; as many Gaussians at a time as fit, one at least). Masks: per supertile row
@@ -215,10 +223,19 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t &a, uint32_t &b, uint3
 // its rows in FP64 and assembling each mask bit range by bit range took 73 us at 1M Gaussians /
 // 1080p (1% of the footprints beyond 16 x 16 tiles) and 391 us at 2.5M / 3840x2160 (15%); this
 // 40 and 178, for 12 bytes fewer written per Gaussian by the preprocess.
+//
+// MANY (frames of more than kSuperWindow supertiles): a workgroup takes the pairs that a column of
+// `per` Gaussians makes in one window of kSuperWindow supertiles (blockIdx.y). It first marks the Gaussians whose
+// rectangles meet the window, then takes those 256 at a time, with the rows that lie in the
+// window. Every workgroup of 256 Gaussians going through all windows instead repeated the FP64
+// rows and the 16 KB of bits for each, mostly for a handful of pairs: 16384x16384 (32 windows)
+// 1,770 us with 2k Gaussians and 2,270 with 4.4M small ones, now 58 and 460.
 // ---------------------------------------------------------------------------------------
+template <bool MANY>
 __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
     const uint32_t *__restrict__ ids, uint32_t *counters, const uint2 *__restrict__ srect,
-    BinIn bin, Supers su, const uint32_t *__restrict__ scan, const uint32_t *__restrict__ tot, int stride, uint32_t *__restrict__ pair_id, unsigned long long *__restrict__ pair_mask,
+    BinIn bin, Supers su, const uint32_t *__restrict__ scan, const uint32_t *__restrict__ tot, int stride, uint32_t per,
+    const uint2 *__restrict__ starts, uint32_t *__restrict__ pair_id, unsigned long long *__restrict__ pair_mask,
     uint4 *__restrict__ chunks, uint2 *__restrict__ supers) {
   // word w of a supertile's bits at w ^ bits_at(s), which spreads 64 supertiles over the banks
   __shared__ uint32_t s_bits[kSuperWindow][kPairWords];
@@ -231,20 +248,26 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
     uint32_t span[kPairWaves][kSpanHold];
     uint4 chunk[kSuperWindow];   // first pair, pairs, first chunk, chunks
   } s_u;
+  constexpr int kMarks = MANY ? kColumnBlocks * kPairWaves : 1;
+  __shared__ unsigned long long s_mark[kMarks];   // the column's Gaussians that meet the window
+  __shared__ uint32_t s_first[kMarks];            // and those before each word
   uint4 *s_chunk = s_u.chunk;
   const auto bits_at = [](int s) { return (s >> 3) & (kPairWords - 1); };
   const uint32_t n = counters[kCntVisible];
   if (counters[kCntPairs] == 0u) return;
-  const uint32_t nb = (n + kPairBlock - 1) / kPairBlock;
+  if (!MANY) per = kPairBlock;
+  const uint32_t nb = (n + per - 1) / per;
   const uint32_t b = xcd_block(blockIdx.x);
   if (b >= nb) return;
   const int tid = threadIdx.x;
-  const uint32_t j = b * kPairBlock + tid;
+  const uint32_t base = b * per, count = min(per, n - base);
+  const int w0 = MANY ? (int)blockIdx.y * kSuperWindow : 0, w1 = min(su.n, w0 + kSuperWindow);
+  const int word = tid >> 5;
+  const uint32_t bit = 1u << (tid & 31);
+  const uint32_t marks = MANY ? (count + 63u) / 64u : 0u;
   PairRows r;
-  r.load(make_uint2(0u, 0u));
-  r.y1 = -1;
   uint32_t g = 0u;
-  if (j < n) {
+  const auto take = [&](uint32_t j) {
     g = ids[j];
     r.load(srect[j]);
     if (r.boxed) {
@@ -260,12 +283,35 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
     } else if (!r.full) {
       r.load_footprint(bin, g, su.tiles_y);
     }
+  };
+  const auto clear = [&]() {
+#pragma unroll
+    for (int k = 0; k < kWinPer; ++k)
+#pragma unroll
+      for (int w = 0; w < kPairWords; ++w) s_bits[tid * kWinPer + k][w] = 0u;
+  };
+  const auto none = [&]() {
+    r.load(make_uint2(0u, 0u));
+    r.y1 = -1;
+  };
+  none();
+  if (!MANY && (uint32_t)tid < count) take(base + tid);
+  if (MANY) {
+    const int r0 = w0 / su.nx, r1 = (w1 - 1) / su.nx;   // the window's supertile rows
+#pragma unroll 4
+    for (uint32_t i = tid; i < ((count + 63u) & ~63u); i += kPairBlock) {   // whole waves
+      const uint2 q = i < count ? srect[base + i] : make_uint2(0u, 0u);
+      PairRows t;
+      t.load(q);
+      const int c0 = t.x0 / kSuper, c1 = t.x1 / kSuper;
+      bool hit = false;
+      for (int sy = max(t.y0 / kSuper, r0); sy <= min(t.y1 / kSuper, r1); ++sy)
+        hit = hit || (sy * su.nx + c1 >= w0 && sy * su.nx + c0 < w1);
+      const unsigned long long m = __ballot(hit && i < count);
+      if ((tid & 63) == 0) s_mark[i >> 6] = m;
+    }
   }
-  const int word = tid >> 5;
-  const uint32_t bit = 1u << (tid & 31);
-  uint32_t carry_p = 0u, carry_c = 0u;
-  for (int w0 = 0; w0 < su.n; w0 += kSuperWindow) {
-    const int w1 = min(su.n, w0 + kSuperWindow);
+  {
     // thread t takes the window's supertiles kWinPer t .. kWinPer t + kWinPer - 1
     uint32_t t[kWinPer], sp = 0u, sc = 0u;
 #pragma unroll
@@ -277,8 +323,11 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
     }
     uint32_t tp, tc;
     block_excl_scan2(sp, sc, tp, tc);
-    sp += carry_p;
-    sc += carry_c;
+    if (MANY) {
+      const uint2 st = starts[blockIdx.y];
+      sp += st.x;
+      sc += st.y;
+    }
 #pragma unroll
     for (int k = 0; k < kWinPer; ++k) {
       const int s = tid * kWinPer + k;
@@ -287,32 +336,59 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
       s_chunk[s] = make_uint4(sp, t[k], sc, nc);
       sp += t[k];
       sc += nc;
-#pragma unroll
-      for (int w = 0; w < kPairWords; ++w) s_bits[s][w] = 0u;
     }
-    carry_p += tp;
-    carry_c += tc;
+    if (!MANY && b == 0u && tid == 0) counters[kCntChunks] = tc;
+    clear();
+  }
+  __syncthreads();
+  // the chunks' descriptors: supertile s by column s mod nb
+  for (uint32_t s = b + ((uint32_t)w0 > b ? ((uint32_t)w0 - b + nb - 1) / nb * nb : 0u); s < (uint32_t)w1; s += nb) {
+    const uint4 c = s_chunk[s - w0];
+    if (tid == 0) supers[s] = make_uint2(c.z, c.w);
+    for (uint32_t i = tid; i < c.w; i += kPairBlock)
+      chunks[c.z + i] = make_uint4(c.x + i * kChunk, min((uint32_t)kChunk, c.y - i * kChunk), s, 0u);
+  }
+  uint32_t todo = count;   // Gaussians to take: MANY, the marked ones
+  if (MANY) {
+    uint32_t before = (uint32_t)tid < marks ? (uint32_t)__popcll(s_mark[tid]) : 0u, zero = 0u, zeros;
+    block_excl_scan2(before, zero, todo, zeros);
+    if ((uint32_t)tid < marks) s_first[tid] = before;
     __syncthreads();
-    // the chunks' descriptors: supertile s by workgroup s mod nb
-    for (uint32_t s = b + ((uint32_t)w0 > b ? ((uint32_t)w0 - b + nb - 1) / nb * nb : 0u); s < (uint32_t)w1; s += nb) {
-      const uint4 c = s_chunk[s - w0];
-      if (tid == 0) supers[s] = make_uint2(c.z, c.w);
-      for (uint32_t i = tid; i < c.w; i += kPairBlock)
-        chunks[c.z + i] = make_uint4(c.x + i * kChunk, min((uint32_t)kChunk, c.y - i * kChunk), s, 0u);
+  }
+  // 256 Gaussians at a time (all of the column's unless MANY)
+  for (uint32_t at = 0u; at < todo; at += kPairBlock) {
+    if (MANY) {
+      none();
+      if (at + tid < todo) {
+        uint32_t k = 0u;   // the last word with at most at + tid marks before it
+#pragma unroll
+        for (uint32_t step = kMarks / 2; step > 0; step >>= 1)
+          if (k + step < marks && s_first[k + step] <= at + tid) k += step;
+        take(base + 64u * k + select_bit(s_mark[k], at + tid - s_first[k]));
+      }
+      if (at > 0u) {
+        clear();
+        __syncthreads();
+      }
     }
-    for (int sy = r.y0 / kSuper; sy * kSuper <= r.y1; ++sy) {
+    // its tile rows in the window's supertile rows
+    const int y0 = MANY ? max(r.y0, w0 / su.nx * kSuper) : r.y0;
+    const int y1 = MANY ? min(r.y1, (w1 - 1) / su.nx * kSuper + kSuper - 1) : r.y1;
+    for (int sy = y0 / kSuper; sy * kSuper <= y1; ++sy) {
       const int first = sy * su.nx;
-      if (first >= w1 || first + su.nx <= w0) continue;
       int c0, c1;
       r.columns(sy, bin, g, su.tiles_x, c0, c1);
-      c0 = max(c0, w0 - first);
-      c1 = min(c1, w1 - 1 - first);
+      if (MANY) {
+        c0 = max(c0, w0 - first);
+        c1 = min(c1, w1 - 1 - first);
+      }
       for (int c = c0; c <= c1; ++c) {
         const int s = first + c - w0;
         atomicOr(&s_bits[s][word ^ bits_at(s)], bit);
       }
     }
     __syncthreads();
+    uint32_t taken[kWinPer];   // of this thread's supertiles
 #pragma unroll
     for (int k = 0; k < kWinPer; ++k) {
       const int s = tid + k * kPairBlock;
@@ -323,24 +399,24 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
         acc += (uint32_t)__popc(s_bits[s][w ^ bits_at(s)]);
       }
       s_pre[s].v = make_uint2(p[0], p[1]);
+      taken[k] = acc;
     }
     __syncthreads();
     // this wave's Gaussians, those whose rows fit the spans' room at a time
     uint32_t *spans = s_u.span[tid >> 6];
-    bool pending = r.y1 >= r.y0;
+    bool pending = y1 >= y0;
     while (__any(pending)) {
-      const uint32_t need = pending && !r.full && !r.boxed ? (uint32_t)(r.y1 - r.y0 + 1) : 0u;
+      const uint32_t need = pending && !r.full && !r.boxed ? (uint32_t)(y1 - y0 + 1) : 0u;
       const uint32_t upto = wave_incl_scan(need);   // every lane takes part
       const bool now = pending && upto <= (uint32_t)kSpanHold;
       const uint32_t rows = now ? need : 0u;
       const uint32_t incl = wave_incl_scan(rows);
-      wave_row_spans(r.fp, r.y0, rows, incl, su.tiles_x, spans);
+      wave_row_spans(r.fp, y0, rows, incl, su.tiles_x, spans);
       wave_lds_fence();
       if (now) {
         const uint32_t *mine = spans + (incl - rows);
-        for (int sy = r.y0 / kSuper; sy * kSuper <= r.y1; ++sy) {
+        for (int sy = y0 / kSuper; sy * kSuper <= y1; ++sy) {
           const int first = sy * su.nx;
-          if (first >= w1 || first + su.nx <= w0) continue;
           int ra[kSuper], re[kSuper];   // first and last column, first above last for none
           int c0 = r.x0 / kSuper, c1 = r.x1 / kSuper;
           if (r.boxed) {
@@ -359,8 +435,8 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
 #pragma unroll
             for (int q = 0; q < kSuper; ++q) {
               const int ty = sy * kSuper + q;
-              const bool in = ty >= r.y0 && ty <= r.y1;
-              const uint32_t s = r.full ? (uint32_t)r.x0 | ((uint32_t)r.x1 << 16) : mine[in ? ty - r.y0 : 0];
+              const bool in = ty >= y0 && ty <= y1;
+              const uint32_t s = r.full ? (uint32_t)r.x0 | ((uint32_t)r.x1 << 16) : mine[in ? ty - y0 : 0];
               ra[q] = in ? (int)(s & 0xFFFFu) : 1;
               re[q] = in ? (int)(s >> 16) : 0;
               u0 = ra[q] <= re[q] ? min(u0, ra[q]) : u0;
@@ -371,8 +447,10 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
               c1 = u1 < 0 ? -1 : u1 / kSuper;
             }
           }
-          c0 = max(c0, w0 - first);
-          c1 = min(c1, w1 - 1 - first);
+          if (MANY) {
+            c0 = max(c0, w0 - first);
+            c1 = min(c1, w1 - 1 - first);
+          }
           for (int g0 = c0; g0 <= c1; g0 += 4) {
             uint32_t bits[kSuper];   // the row's tiles of four supertiles
 #pragma unroll
@@ -404,9 +482,42 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_pair_place(
       }
       wave_lds_fence();
     }
+    if (!MANY) break;
     __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kWinPer; ++k) s_goff[tid + k * kPairBlock] += taken[k];
   }
-  if (b == 0u && tid == 0) counters[kCntChunks] = carry_c;
+}
+
+// MANY: the first pair and the first chunk of each window of supertiles, and the chunks' count.
+__global__ __launch_bounds__(kSuperWindow) void k_window_starts(uint32_t *counters, const uint32_t *__restrict__ tot,
+                                                                Supers su, uint2 *__restrict__ starts) {
+  constexpr int W = kSuperWindow / 64;
+  __shared__ uint32_t s_p[kMostWindows][W], s_c[kMostWindows][W];
+  if (counters[kCntPairs] == 0u) return;
+  const int tid = threadIdx.x, windows = (su.n + kSuperWindow - 1) / kSuperWindow;
+  for (int k = 0; k < windows; ++k) {
+    const int s = k * kSuperWindow + tid;
+    const uint32_t t = s < su.n ? tot[s] : 0u;
+    const uint32_t p = wave_incl_scan(t), c = wave_incl_scan((t + kChunk - 1) / kChunk);
+    if ((tid & 63) == 63) {
+      s_p[k][tid >> 6] = p;
+      s_c[k][tid >> 6] = c;
+    }
+  }
+  __syncthreads();
+  if (tid > windows) return;
+  uint2 sum = make_uint2(0u, 0u);
+  for (int k = 0; k < tid; ++k)
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      sum.x += s_p[k][w];
+      sum.y += s_c[k][w];
+    }
+  if (tid < windows)
+    starts[tid] = sum;
+  else
+    counters[kCntChunks] = sum.y;
 }
 
 // A 64 x 64 bit matrix, one row per lane (bit j of lane i), transposed: lane j gets column j
@@ -566,10 +677,13 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_starts(const uint32_t *_
 // against 220 us), the indices placed per 32-bit half (208). Waves storing each tile's entries
 // by ballot, without LDS, took 230 us there and 28 for the 8.4M; runs begun at a 64-byte
 // boundary 210 and 23.
-// Workgroup 0 makes the blend's tile order instead, which no other kernel before the blend needs: four
-// waves, done within the expansion's time (the kernel unchanged at 157.6M, 8.4M and 0.7M entries) but
-// where large frames show little (2k Gaussians at 3840x2160: 6 -> 39 us, 51 -> 44 with the ranges).
+// The first workgroups make the blend's tile order instead, which no other kernel before the blend needs: four
+// waves for every kOrderTiles tiles, done within the expansion's time (the kernel unchanged at 157.6M, 8.4M and
+// 0.7M entries) but where large frames show little (2k Gaussians at 3840x2160: 6 -> 39 us, 51 -> 44 with
+// the ranges). One workgroup for all of a 16384x16384 frame's 1M tiles took 1,580 us of the kernel's, now 80 with the expansion.
 // ---------------------------------------------------------------------------------------
+constexpr int kOrderTiles = 32768;   // tiles per workgroup of the order (a 3840x2160 frame has 32,400)
+
 __global__ __launch_bounds__(kChunk) void k_chunk_expand(const uint32_t *__restrict__ counters,
                                                          const uint4 *__restrict__ chunks,
                                                          const uint32_t *__restrict__ pair_id,
@@ -578,22 +692,23 @@ __global__ __launch_bounds__(kChunk) void k_chunk_expand(const uint32_t *__restr
                                                          const uint2 *__restrict__ ranges, Supers su,
                                                          uint32_t *__restrict__ values,
                                                          const uint32_t *__restrict__ tile_len, int n_tiles,
-                                                         uint32_t *__restrict__ order) {
+                                                         uint32_t *__restrict__ order, uint32_t n_order) {
   constexpr int W = kChunk / 64;
   __shared__ __align__(16) uint8_t s_stage[kChunk * 64];
   __shared__ uint32_t s_id[kChunk];
   __shared__ uint32_t s_cnt[W][64];
   __shared__ uint32_t s_lbase[64], s_len[64], s_gbase[64];
-  if (blockIdx.x == 0) {
+  if (blockIdx.x < n_order) {
     static_assert(sizeof(OrderShared<W>) <= sizeof(s_stage), "the order's LDS in place of the staged indices");
-    tile_order<W>(CountCost{tile_len}, n_tiles, order, TileSplit{0.0f, 0.0f, -1, -1},
-                  *reinterpret_cast<OrderShared<W> *>(s_stage));
+    const int first = (int)blockIdx.x, step = (int)n_order;
+    tile_order<W>(CountCost{tile_len}, (n_tiles - first + step - 1) / step, order, TileSplit{0.0f, 0.0f, -1, -1},
+                  *reinterpret_cast<OrderShared<W> *>(s_stage), first, step);
     return;
   }
   if (counters[kCntPairs] == 0u) return;
   const uint32_t nc = counters[kCntChunks];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  for (uint32_t c = xcd_block(blockIdx.x - 1u); c < nc; c += gridDim.x - 1u) {
+  for (uint32_t c = xcd_block(blockIdx.x - n_order); c < nc; c += gridDim.x - n_order) {
     const uint4 d = chunks[c];
     const bool in = (uint32_t)tid < d.y;
     const unsigned long long m = in ? pair_mask[d.x + tid] : 0ull;
@@ -665,35 +780,67 @@ static Supers supers_of(const DevCamera &cam) {
   return s;
 }
 
-static int pair_stride(int64_t n) { return (int)(((n + kPairBlock - 1) / kPairBlock + 7) & ~(int64_t)7); }
+static int super_windows(const Supers &su) { return (su.n + kSuperWindow - 1) / kSuperWindow; }
+
+// Gaussians per column of the pair counts, of n candidates.
+static uint32_t pair_column(const Supers &su, int64_t n) {
+  if (su.n <= kSuperWindow) return kPairBlock;
+  const int64_t blocks = (n + kPairBlock - 1) / kPairBlock;
+  return (uint32_t)(kPairBlock * std::min<int64_t>(super_windows(su), (blocks + kColumnsMin - 1) / kColumnsMin));
+}
+
+static int64_t pair_columns(const Supers &su, int64_t n) {
+  const uint32_t per = pair_column(su, n);
+  return (n + per - 1) / per;
+}
+
+static int pair_stride(const Supers &su, int64_t n) { return (int)((pair_columns(su, n) + 7) & ~(int64_t)7); }
 
 int super_count(const DevCamera &cam) { return supers_of(cam).n; }
 
 size_t pair_hist_bytes(const DevCamera &cam, int64_t n) {
-  return 4 * (size_t)supers_of(cam).n * (size_t)pair_stride(n);
+  const Supers su = supers_of(cam);
+  return n > 0 ? 4 * (size_t)su.n * (size_t)pair_stride(su, n) : 0;
+}
+
+// the supertiles' totals, an even number of words, and the windows' starts
+static size_t tot_words(const Supers &su) { return ((size_t)su.n + 1) & ~(size_t)1; }
+
+size_t pair_tot_bytes(const DevCamera &cam) {
+  const Supers su = supers_of(cam);
+  return 4 * tot_words(su) + sizeof(uint2) * (size_t)super_windows(su);
 }
 
 int64_t chunk_capacity(const DevCamera &cam, int64_t pairs) { return pairs / kChunk + supers_of(cam).n; }
 
 hipError_t launch_pair_offsets(const uint32_t *ids, const uint32_t *counters, const uint2 *srect, const BinIn &bin,
-                               const DevCamera &cam, int64_t n, uint32_t *hist, uint32_t *scan, uint32_t *tot,
-                               hipStream_t s) {
+                               const DevCamera &cam, int64_t n, uint32_t *scan, uint32_t *tot, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const Supers su = supers_of(cam);
-  const int stride = pair_stride(n);
-  hipLaunchKernelGGL(k_pair_hist, dim3(xcd_grid((n + kPairBlock - 1) / kPairBlock)), dim3(kPairBlock), 0, s, ids,
-                     counters, srect, bin, su, hist, stride);
-  return launch_row_scan(counters + kCntVisible, hist, scan, tot, su.n, stride, kPairBlock, s);
+  const int stride = pair_stride(su, n);
+  const uint32_t per = pair_column(su, n);
+  hipLaunchKernelGGL(k_pair_hist, dim3(xcd_grid(pair_columns(su, n))), dim3(kPairBlock), 4 * (size_t)su.n, s, ids,
+                     counters, srect, bin, su, scan, stride, per);
+  return launch_row_scan(counters + kCntVisible, scan, scan, tot, su.n, stride, (int)per, s);
 }
 
 hipError_t launch_pair_place(const uint32_t *ids, uint32_t *counters, const uint2 *srect, const BinIn &bin,
-                             const DevCamera &cam, int64_t n, const uint32_t *scan, const uint32_t *tot,
+                             const DevCamera &cam, int64_t n, const uint32_t *scan, uint32_t *tot,
                              uint32_t *pair_id, unsigned long long *pair_mask, uint4 *chunks, uint2 *supers,
                              hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pair_place, dim3(xcd_grid((n + kPairBlock - 1) / kPairBlock)), dim3(kPairBlock), 0, s, ids,
-                     counters, srect, bin, supers_of(cam), scan, tot, pair_stride(n), pair_id, pair_mask, chunks,
-                     supers);
+  const Supers su = supers_of(cam);
+  const int windows = super_windows(su), stride = pair_stride(su, n);
+  const unsigned columns = xcd_grid(pair_columns(su, n));
+  uint2 *starts = reinterpret_cast<uint2 *>(tot + tot_words(su));
+  if (windows > 1) {
+    hipLaunchKernelGGL(k_window_starts, dim3(1), dim3(kSuperWindow), 0, s, counters, tot, su, starts);
+    hipLaunchKernelGGL(k_pair_place<true>, dim3(columns, (unsigned)windows), dim3(kPairBlock), 0, s, ids, counters,
+                       srect, bin, su, scan, tot, stride, pair_column(su, n), starts, pair_id, pair_mask, chunks, supers);
+  } else {
+    hipLaunchKernelGGL(k_pair_place<false>, dim3(columns), dim3(kPairBlock), 0, s, ids, counters, srect, bin, su, scan,
+                       tot, stride, (uint32_t)kPairBlock, nullptr, pair_id, pair_mask, chunks, supers);
+  }
   return hipGetLastError();
 }
 
@@ -726,9 +873,10 @@ hipError_t launch_chunk_expand(const uint32_t *counters, const uint4 *chunks, co
   const int n_tiles = cam.tiles_x * cam.tiles_y;
   if (n_tiles <= 0) return hipSuccess;
   // without candidates the order alone
-  const unsigned grid = 1u + xcd_grid(std::min<int64_t>(max_chunks, 8192));
+  const unsigned n_order = (unsigned)((n_tiles + kOrderTiles - 1) / kOrderTiles);
+  const unsigned grid = n_order + xcd_grid(std::min<int64_t>(max_chunks, 8192));
   hipLaunchKernelGGL(k_chunk_expand, dim3(grid), dim3(kChunk), 0, s, counters, chunks, pair_id,
-                     pair_mask, prefix, ranges, supers_of(cam), values, tile_len, n_tiles, order);
+                     pair_mask, prefix, ranges, supers_of(cam), values, tile_len, n_tiles, order, n_order);
   return hipGetLastError();
 }
 
