@@ -940,9 +940,9 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
     need(B_TILES, 4 * (size_t)n);          // the points around each
     need(B_RECT, 4 * (size_t)buckets);     // the run table's tags
     need(B_SRECT, 8 * (size_t)buckets);    // and runs
-    need(B_HIST, radix_hist_bytes(n));
-    need(B_SCAN, radix_hist_bytes(n));
-    need(B_TOT, 4 * (size_t)kRadix);
+    need(B_HIST, radix_hist_bytes(n, true));
+    need(B_SCAN, radix_hist_bytes(n, true));
+    need(B_TOT, 4 * (size_t)kDepthRadix);
   }
   need(B_COUNTERS, 4 * (size_t)kCntSlots);
   if (st != FLOD_OK) {
@@ -956,25 +956,24 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
   uint2 *runs = P<uint2>(ctx, B_SRECT);
   uint32_t *around = P<uint32_t>(ctx, B_TILES);
   unsigned long long *cost = reinterpret_cast<unsigned long long *>(counters + kCntTotal64);
+  unsigned long long *crowded = reinterpret_cast<unsigned long long *>(counters + kCntPairs64);
   const int sub_bits = 3 * prune_levels(n);
   if (d_op > 0.0f) {
     uint32_t *dk[2] = {P<uint32_t>(ctx, B_DKEY0), P<uint32_t>(ctx, B_DKEY1)};
     uint32_t *dv[2] = {P<uint32_t>(ctx, B_DVAL0), P<uint32_t>(ctx, B_DVAL1)};
     int res = 0;
-    if (launch_fill_u32(counters + kCntVisible, (uint32_t)n, 1, s) != hipSuccess ||
-        launch_fill_u32(counters + kCntTotal64, 0u, 2, s) != hipSuccess ||
-        launch_prune_keys(level->means, n, d_op, dk[0], dv[0], s) != hipSuccess ||
+    if (launch_prune_keys(level->means, n, d_op, dk[0], dv[0], ranges, tags, counters, s) != hipSuccess ||
         launch_radix_sort(dk, dv, counters + kCntVisible, n, bits + sub_bits, P<uint32_t>(ctx, B_HIST),
                           P<uint32_t>(ctx, B_SCAN), P<uint32_t>(ctx, B_TOT), &res, s) != hipSuccess ||
         launch_prune_gather(level->means, dv[res], n, P<float4>(ctx, B_XYAB), s) != hipSuccess ||
-        launch_ranges(dk[res], sub_bits, counters + kCntVisible, n, (int)buckets, ranges, s) != hipSuccess ||
+        launch_ranges(dk[res], sub_bits, counters + kCntVisible, n, ranges, s) != hipSuccess ||
         launch_prune_runs(dk[res], ranges, n, d_op, tags, runs, s) != hipSuccess ||
-        launch_prune_cost(pts, ranges, n, d_op, around, cost, s) != hipSuccess)
+        launch_prune_cost(pts, ranges, n, d_op, around, cost, crowded, s) != hipSuccess)
       return FLOD_ERR_DEVICE;
   }
   // the device refuses a scan beyond the limit (nothing is written); the host learns of it with
   // the kept count
-  if (launch_prune_query(pts, ranges, tags, runs, around, n, d_op, cost, keep, d_avg, s) != hipSuccess) return FLOD_ERR_DEVICE;
+  if (launch_prune_query(pts, ranges, tags, runs, around, n, d_op, cost, crowded, keep, d_avg, s) != hipSuccess) return FLOD_ERR_DEVICE;
   auto count = [&](uint32_t *bc) { return launch_mask_count(keep, n, bc, s); };
   auto no_copy = [&](int, const unsigned long long *, const flod_level &) { return hipSuccess; };
   Compaction job;

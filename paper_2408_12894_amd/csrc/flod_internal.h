@@ -135,7 +135,7 @@ struct AdamArgs {
 enum : int {
   kCntVisible = 0,      // u32 count of visible candidates
   kCntTotal64 = 2,      // u64 count of instances (or other totals; two u32 slots: 2, 3)
-  kCntPairs64 = 4,      // u64 count of (supertile, Gaussian) pairs (slots 4, 5)
+  kCntPairs64 = 4,      // u64 count of (supertile, Gaussian) pairs (or of crowded points; slots 4, 5)
   kCntPairs = 6,        // u32 count of pairs; 0 when instances or pairs exceed their buffers
   kCntChunks = 7,       // u32 count of chunks of pairs
   kCntFar = 1,          // u32 count of visible candidates beyond the depth sort's three passes
@@ -305,9 +305,9 @@ hipError_t launch_frame_totals(const FrameTotals &t, hipStream_t s);
 hipError_t launch_bin_records(int64_t n, const uint32_t *tiles, const uint2 *rect, const BinIn &in, float4 *out,
                               hipStream_t s);
 hipError_t launch_tile_ids(const uint2 *ranges, int n_tiles, uint32_t *tile_ids, hipStream_t s);
-// [start, end) of every bucket (id >> shift) in the sorted ids (ranges zeroed here first)
-hipError_t launch_ranges(const uint32_t *ids, int shift, const uint32_t *k_ptr, int64_t k_max, int n_ranges,
-                         uint2 *ranges, hipStream_t s);
+// [start, end) of every bucket (id >> shift) in the sorted ids (ranges zeroed beforehand)
+hipError_t launch_ranges(const uint32_t *ids, int shift, const uint32_t *k_ptr, int64_t k_max, uint2 *ranges,
+                         hipStream_t s);
 // large: the levels' scale floors make footprints large (a choice of kernel only)
 // blended: per tile, the (list position, Gaussian) pairs of the entries the forward blended
 // into some pixel, in list order at the start of the tile's range; tile_blended: their count
@@ -368,18 +368,20 @@ hipError_t launch_l1_backward(const float *x, const float *y, int64_t n, const d
                               hipStream_t s);
 int prune_table_bits(int64_t n);   // log2 of the overlap-pruning hash table size for n points
 int prune_levels(int64_t n);       // halvings of a cell its sort keys hold (3 bits each below the bucket)
-hipError_t launch_prune_keys(const float *means, int64_t n, float d_op, uint32_t *keys, uint32_t *vals,
-                             hipStream_t s);
+// ranges, tags: 2^prune_table_bits(n) slots each, cleared here with the counters the others use
+hipError_t launch_prune_keys(const float *means, int64_t n, float d_op, uint32_t *keys, uint32_t *vals, uint2 *ranges,
+                             uint32_t *tags, uint32_t *counters, hipStream_t s);
 hipError_t launch_prune_gather(const float *means, const uint32_t *sorted_vals, int64_t n, float4 *pts,
                                hipStream_t s);
-// around: per point in key order, the points in the 27 buckets around it (itself included)
+// around: per point in key order, the points in the 27 buckets around it (itself included); cost: their
+// sum; crowded: the points with many
 hipError_t launch_prune_cost(const float4 *pts, const uint2 *ranges, int64_t n, float d_op, uint32_t *around,
-                             unsigned long long *cost, hipStream_t s);
-// tags, runs: 2^prune_table_bits(n) slots each (tags zeroed here first)
+                             unsigned long long *cost, unsigned long long *crowded, hipStream_t s);
+// runs: as many slots as tags
 hipError_t launch_prune_runs(const uint32_t *keys, const uint2 *ranges, int64_t n, float d_op, uint32_t *tags,
                              uint2 *runs, hipStream_t s);
 hipError_t launch_prune_query(const float4 *pts, const uint2 *ranges, const uint32_t *tags, const uint2 *runs,
-                              const uint32_t *around, int64_t n, float d_op, const unsigned long long *cost, uint8_t *keep, double *d_avg,
-                              hipStream_t s);
+                              uint32_t *around, int64_t n, float d_op, const unsigned long long *cost,
+                              const unsigned long long *crowded, uint8_t *keep, double *d_avg, hipStream_t s);
 
 }  // namespace flod

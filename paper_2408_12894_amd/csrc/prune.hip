@@ -8,17 +8,17 @@
 // neighbour that can matter in the 27 cells around a Gaussian's own.
 //
 //   1. cell of each mean (FP64 floor of x / c, clamped to 21 bits per axis: a monotone map,
-//      so points closer than c along an axis stay in the same or adjacent cells), hashed to
-//      a table of T = 2^b >= n buckets (MurmurHash3's 64-bit finaliser, top b bits); below
+//      so points closer than c along an axis stay in the same or adjacent cells), hashed by
+//      blocks of cells to a table of T = 2^b >= n buckets (bucket_of); below
 //      the bucket in the key, the Morton index of the point's subcell (3 bits for each of
 //      up to three halvings of the cell);
 //   2. stable radix sort of (key, index), then the means gathered into key order (16 B per
 //      point, index in the fourth word), and per-bucket [start, end). The points of a subcell
 //      of any level are then consecutive too: their runs go to an open-addressed table, for
 //      the buckets and levels that are searched by subcell;
-//   3. a point with fewer than three others in the 27 cells around its own is kept. The others
-//      are searched by whole waves (k_prune_query), each group of points sharing a subcell
-//      among the candidates of the finest level whose subcells hold about one point or more.
+//   3. where points have few others in the 27 buckets around their own, a thread settles each
+//      (k_prune_few). The others are searched by whole waves (k_prune_query), each group of points
+//      sharing a subcell among the candidates of the finest level whose subcells hold about one point or more.
 //      Every point within a subcell's edge lies in the searched subcells, so when the third
 //      smallest distance found is below the edge the three are the true nearest; otherwise the
 //      next coarser level is searched, down to the 27 cells. Squared distances are FP64, from
@@ -57,18 +57,23 @@ __device__ __forceinline__ int32_t cell_of(float x, double inv_c) {
   return (int32_t)f;
 }
 
-// MurmurHash3 fmix64 finaliser over the packed cell coordinates.
+// A cell's bucket: 64 consecutive ones for each block of 4 x 4 x 4 cells, by the block's coordinates hashed
+// (MurmurHash3's fmix64 finaliser), and in them the cell's place in the block, permuted by another part of the
+// hash so that blocks on the same 64 meet evenly. The 27 cells around a point lie in at most
+// eight blocks, so their ranges and points come from a few cache lines: each cell hashed by itself, all of
+// flod_overlap_prune took 1,050 us for 1M points ten d_op apart and, one thread per point, 1,000, now 510.
 __device__ __forceinline__ uint32_t bucket_of(int32_t ix, int32_t iy, int32_t iz, int shift) {
-  const uint64_t m = (1ull << kCellBits) - 1;
-  uint64_t k = (((uint64_t)(ix + (1 << (kCellBits - 1))) & m) << (2 * kCellBits)) |
-               (((uint64_t)(iy + (1 << (kCellBits - 1))) & m) << kCellBits) |
-               ((uint64_t)(iz + (1 << (kCellBits - 1))) & m);
+  const uint64_t m = (1ull << (kCellBits - 2)) - 1;
+  const int32_t x = ix + (1 << (kCellBits - 1)), y = iy + (1 << (kCellBits - 1)), z = iz + (1 << (kCellBits - 1));
+  uint64_t k = (((uint64_t)(x >> 2) & m) << (2 * kCellBits)) | (((uint64_t)(y >> 2) & m) << kCellBits) |
+               ((uint64_t)(z >> 2) & m);
   k ^= k >> 33;
   k *= 0xff51afd7ed558ccdull;
   k ^= k >> 33;
   k *= 0xc4ceb9fe1a85ec53ull;
   k ^= k >> 33;
-  return (uint32_t)(k >> shift);
+  const uint32_t in = (uint32_t)(x & 3) | ((uint32_t)(y & 3) << 2) | ((uint32_t)(z & 3) << 4);
+  return ((uint32_t)(k >> (shift + 6)) << 6) | (in ^ ((uint32_t)k & 63u));
 }
 
 // Fine coordinate (eight per cell): its upper bits are cell_of's cell, since scaling by 8 is
@@ -85,9 +90,20 @@ __device__ __forceinline__ uint32_t morton(uint32_t x, uint32_t y, uint32_t z, i
   return m;
 }
 
+// The keys; and what the steps behind them find cleared: the buckets' ranges, the run table's tags, and in
+// the counters the count of keys, the size of the scan and the count of crowded points.
 __global__ __launch_bounds__(kBlock) void k_prune_keys(const float *means, int64_t n, Grid g, uint32_t *keys,
-                                                       uint32_t *vals) {
+                                                       uint32_t *vals, uint2 *ranges, uint32_t *tags,
+                                                       uint32_t *counters) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= (int64_t)1 << g.bits) return;   // at least n
+  ranges[i] = make_uint2(0u, 0u);
+  if (g.levels > 0) tags[i] = 0u;
+  if (i == 0) {
+    counters[kCntVisible] = (uint32_t)n;
+    *reinterpret_cast<unsigned long long *>(counters + kCntTotal64) = 0ull;
+    *reinterpret_cast<unsigned long long *>(counters + kCntPairs64) = 0ull;
+  }
   if (i >= n) return;
   const int32_t fx = fine_of(means[i * 3 + 0], g.inv_c);
   const int32_t fy = fine_of(means[i * 3 + 1], g.inv_c);
@@ -160,6 +176,12 @@ __device__ __forceinline__ double row_min16(double v) {
   return fmin(v, row_ror64<1>(v));
 }
 
+// d_avg from the three smallest squared distances, infinite unless they are within the radius.
+__device__ __forceinline__ double mean_of_three(double d1, double d2, double d3, double radius) {
+  const double d = sqrt(d3);
+  return d < radius ? ((sqrt(d1) + sqrt(d2)) + d) / 3.0 : (double)INFINITY;
+}
+
 constexpr int kPruneHold = 192;   // candidates held in LDS at once
 
 // One wave per `per` (at most 64) consecutive points in key order. The wave takes the points of one subcell after the other
@@ -186,12 +208,12 @@ __global__ __launch_bounds__(64) void k_prune_query(const float4 *__restrict__ p
   __shared__ uint32_t s_seen[128];
   if (*cost > kPruneMaxScan) return;   // refused: nothing is written
   const int lane = threadIdx.x, l16 = lane & 15, row = lane >> 4;
-  const int64_t p = (int64_t)blockIdx.x * per + lane;
-  const bool valid = lane < per && p < n;
+  const int64_t p = (int64_t)xcd_block(blockIdx.x) * per + lane;   // neighbours in key order share an XCD's L2
+  const bool valid = lane < per && p < n && around[p] != 0u;   // 0: settled by k_prune_few
   const float4 a = valid ? pts[p] : make_float4(0.f, 0.f, 0.f, 0.f);
   const int fx = fine_of(a.x, g.inv_c), fy = fine_of(a.y, g.inv_c), fz = fine_of(a.z, g.inv_c);
   int level = 0;   // the point's level: the finest its own bucket's count allows
-  bool pending = valid && around[p] > 3u;
+  bool pending = valid;
   if (pending) {
     const uint2 own = ranges[bucket_of(fx >> 3, fy >> 3, fz >> 3, g.shift)];
     while (level < g.levels && own.y - own.x >= subcell_min(level + 1)) ++level;
@@ -329,21 +351,22 @@ __global__ __launch_bounds__(64) void k_prune_query(const float4 *__restrict__ p
     }
   }
   if (!valid) return;
-  double avg = INFINITY;
-  const double d3 = sqrt(s_best[lane][2]);
-  if (d3 < radius) avg = ((sqrt(s_best[lane][0]) + sqrt(s_best[lane][1])) + d3) / 3.0;
+  const double avg = mean_of_three(s_best[lane][0], s_best[lane][1], s_best[lane][2], radius);
   const uint32_t j = __float_as_uint(a.w);
   keep[j] = (avg < d_op) ? 0 : 1;
   if (d_avg) d_avg[j] = avg;
 }
 
+constexpr uint32_t kPruneFew = 320;
+
 // Size of the neighbour scan over whole cells: per point its 27 buckets' occupancy (to around),
-// and their sum.
+// their sum and the count of those above kPruneFew.
 __global__ __launch_bounds__(kBlock) void k_prune_cost(const float4 *__restrict__ pts, const uint2 *__restrict__ ranges,
                                                        int64_t n, Grid g, uint32_t *__restrict__ around,
-                                                       unsigned long long *cost) {
+                                                       unsigned long long *cost, unsigned long long *crowded) {
   __shared__ unsigned long long s_sum[kBlock / 64];
-  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  __shared__ uint32_t s_crowd[kBlock / 64];
+  const int64_t p = (int64_t)xcd_block(blockIdx.x) * kBlock + threadIdx.x;
   unsigned long long c = 0;
   if (p < n) {
     const float4 a = pts[p];
@@ -356,14 +379,97 @@ __global__ __launch_bounds__(kBlock) void k_prune_cost(const float4 *__restrict_
         }
     around[p] = (uint32_t)(c < 0xFFFFFFFFull ? c : 0xFFFFFFFFull);
   }
+  const uint32_t crowd = (uint32_t)__popcll(__ballot(c > kPruneFew));
   for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
-  if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = c;
+  if ((threadIdx.x & 63) == 0) {
+    s_sum[threadIdx.x >> 6] = c;
+    s_crowd[threadIdx.x >> 6] = crowd;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    unsigned long long t = 0;
-    for (int w = 0; w < kBlock / 64; ++w) t += s_sum[w];
+    unsigned long long t = 0, m = 0;
+    for (int w = 0; w < kBlock / 64; ++w) {
+      t += s_sum[w];
+      m += s_crowd[w];
+    }
     atomicAdd(cost, t);
+    if (m) atomicAdd(crowded, m);
   }
+}
+
+// One thread per point where few points lie around: of kPruneFewFrom points or more (fewer leave most of the
+// device idle in long chains) of which at most one in 256 has more than kPruneFew in its 27 buckets, those
+// with that many or fewer are settled here, else those alone that have fewer than three others there. around is set to 0
+// for k_prune_query, whose waves take the points of one cell after the other, which costs where
+// they are few to a cell. A choice for the call as a whole: waves that find
+// some of their points settled take hardly less time. kTogether cells at a time: their ranges and
+// then their first points are loaded together.
+// All of flod_overlap_prune in us, points at random f d_op apart, one thread per point throughout | by
+// waves alone (each without the block hash) | now:
+//   300k, f = 10, 3, 2, 1     240 232 256 486 | 354 307 270 268 | 204 219 255 295
+//   1M                        953 739 539 1043 | 1032 814 604 673 | 507 412 566 631
+constexpr int64_t kPruneFewFrom = 32768;
+
+__global__ __launch_bounds__(kBlock) void k_prune_few(const float4 *__restrict__ pts, const uint2 *__restrict__ ranges,
+                                                      uint32_t *__restrict__ around, int64_t n, Grid g, double radius,
+                                                      double d_op, const unsigned long long *cost,
+                                                      const unsigned long long *crowded, uint8_t *keep,
+                                                      double *d_avg) {
+  constexpr int kTogether = 4;
+  if (*cost > kPruneMaxScan) return;   // refused: nothing is written
+  const int64_t p = (int64_t)xcd_block(blockIdx.x) * kBlock + threadIdx.x;
+  if (p >= n) return;
+  const uint32_t c = around[p];
+  if (c > (n >= kPruneFewFrom && *crowded <= (unsigned long long)n / 256u ? kPruneFew : 3u)) return;
+  const float4 a = pts[p];
+  double avg = INFINITY;
+  if (c > 3u) {
+    const double ax = a.x, ay = a.y, az = a.z;
+    const int32_t cx = cell_of(a.x, g.inv_c), cy = cell_of(a.y, g.inv_c), cz = cell_of(a.z, g.inv_c);
+    // the three smallest squared distances below the radius' and their points: a point met again, in a
+    // bucket that two of the cells share, is one of them or no nearer than they are
+    const double reach = radius * radius * (1.0 + 1e-12);
+    double b0 = reach, b1 = reach, b2 = reach;
+    uint32_t q0 = (uint32_t)p, q1 = q0, q2 = q0;
+    const auto meet = [&](uint32_t q, const float4 &b) {
+      const double ex = (double)b.x - ax, ey = (double)b.y - ay, ez = (double)b.z - az;
+      const double d = (ex * ex + ey * ey) + ez * ez;
+      if (!(d < b2) || q == (uint32_t)p || q == q0 || q == q1 || q == q2) return;
+      const bool first = d < b0, second = d < b1;
+      b2 = second ? b1 : d;
+      q2 = second ? q1 : q;
+      b1 = first ? b0 : second ? d : b1;
+      q1 = first ? q0 : second ? q : q1;
+      b0 = first ? d : b0;
+      q0 = first ? q : q0;
+    };
+    const auto bucket = [&](int k) { return bucket_of(cx + k % 3 - 1, cy + (k / 3) % 3 - 1, cz + k / 9 - 1, g.shift); };
+    for (int k0 = 0; k0 < 27; k0 += kTogether) {
+      uint2 r[kTogether];
+      float4 first[kTogether];
+#pragma unroll
+      for (int i = 0; i < kTogether; ++i) r[i] = k0 + i < 27 ? ranges[bucket(k0 + i)] : make_uint2(0u, 0u);
+#pragma unroll
+      for (int i = 0; i < kTogether; ++i) first[i] = pts[r[i].y > r[i].x ? r[i].x : (uint32_t)p];
+#pragma unroll
+      for (int i = 0; i < kTogether; ++i) {
+        if (r[i].y > r[i].x) meet(r[i].x, first[i]);
+        for (uint32_t q = r[i].x + 1; q < r[i].y; q += kTogether) {
+          float4 b[kTogether];
+#pragma unroll
+          for (int u = 0; u < kTogether; ++u) b[u] = pts[min(q + u, r[i].y - 1u)];
+#pragma unroll
+          for (int u = 0; u < kTogether; ++u)
+            if (q + u < r[i].y) meet(q + u, b[u]);
+        }
+      }
+    }
+    avg = mean_of_three(b0, b1, b2, radius);
+  }
+  around[p] = 0u;
+  const uint32_t j = __float_as_uint(a.w);
+  keep[j] = (avg < d_op) ? 0 : 1;
+  if (d_avg) d_avg[j] = avg;
 }
 
 __global__ __launch_bounds__(kBlock) void k_prune_none(int64_t n, uint8_t *keep, double *d_avg) {
@@ -381,8 +487,10 @@ int prune_table_bits(int64_t n) {
   return b;
 }
 
-// Halvings of a cell in the keys: a run's tag of bits + 3 levels + 1 bits fits 32.
+// Halvings of a cell in the keys: a run's tag of bits + 3 levels + 1 bits fits 32. None for up to 256 points,
+// whose keys then take one pass of the sort instead of three (20 points: 78 instead of 94 us in all).
 int prune_levels(int64_t n) {
+  if (n <= kRadix) return 0;
   const int l = (31 - prune_table_bits(n)) / 3;
   return l < kPruneLevels ? l : kPruneLevels;
 }
@@ -398,11 +506,12 @@ static Grid make_grid(double radius, int64_t n) {
 
 double prune_radius(float d_op) { return 3.0 * (double)d_op * (1.0 + 1e-9); }
 
-hipError_t launch_prune_keys(const float *means, int64_t n, float d_op, uint32_t *keys, uint32_t *vals,
-                             hipStream_t s) {
+hipError_t launch_prune_keys(const float *means, int64_t n, float d_op, uint32_t *keys, uint32_t *vals, uint2 *ranges,
+                             uint32_t *tags, uint32_t *counters, hipStream_t s) {
   if (n <= 0 || !(d_op > 0.0f)) return hipSuccess;
-  hipLaunchKernelGGL(k_prune_keys, dim3(grid_of(n)), dim3(kBlock), 0, s, means, n, make_grid(prune_radius(d_op), n),
-                     keys, vals);
+  const Grid g = make_grid(prune_radius(d_op), n);
+  hipLaunchKernelGGL(k_prune_keys, dim3(grid_of((int64_t)1 << g.bits)), dim3(kBlock), 0, s, means, n, g, keys, vals,
+                     ranges, tags, counters);
   return hipGetLastError();
 }
 
@@ -414,10 +523,10 @@ hipError_t launch_prune_gather(const float *means, const uint32_t *sorted_vals, 
 }
 
 hipError_t launch_prune_cost(const float4 *pts, const uint2 *ranges, int64_t n, float d_op, uint32_t *around,
-                             unsigned long long *cost, hipStream_t s) {
+                             unsigned long long *cost, unsigned long long *crowded, hipStream_t s) {
   if (n <= 0 || !(d_op > 0.0f)) return hipSuccess;
-  hipLaunchKernelGGL(k_prune_cost, dim3(grid_of(n)), dim3(kBlock), 0, s, pts, ranges, n,
-                     make_grid(prune_radius(d_op), n), around, cost);
+  hipLaunchKernelGGL(k_prune_cost, dim3(xcd_grid((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, pts, ranges, n,
+                     make_grid(prune_radius(d_op), n), around, cost, crowded);
   return hipGetLastError();
 }
 
@@ -425,28 +534,29 @@ hipError_t launch_prune_runs(const uint32_t *keys, const uint2 *ranges, int64_t 
                              uint2 *runs, hipStream_t s) {
   if (n <= 0 || !(d_op > 0.0f)) return hipSuccess;
   const Grid g = make_grid(prune_radius(d_op), n);
-  hipError_t e = launch_fill_u32(tags, 0u, (int64_t)1 << g.bits, s);
-  if (e != hipSuccess || g.levels == 0) return e;
+  if (g.levels == 0) return hipSuccess;
   hipLaunchKernelGGL(k_prune_runs, dim3(grid_of(n)), dim3(kBlock), 0, s, keys, ranges, n, g, tags,
                      reinterpret_cast<uint32_t *>(runs));
   return hipGetLastError();
 }
 
 hipError_t launch_prune_query(const float4 *pts, const uint2 *ranges, const uint32_t *tags, const uint2 *runs,
-                              const uint32_t *around, int64_t n, float d_op, const unsigned long long *cost, uint8_t *keep, double *d_avg,
-                              hipStream_t s) {
+                              uint32_t *around, int64_t n, float d_op, const unsigned long long *cost,
+                              const unsigned long long *crowded, uint8_t *keep, double *d_avg, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (!(d_op > 0.0f)) {
     hipLaunchKernelGGL(k_prune_none, dim3(grid_of(n)), dim3(kBlock), 0, s, n, keep, d_avg);
     return hipGetLastError();
   }
   const double radius = prune_radius(d_op);
+  hipLaunchKernelGGL(k_prune_few, dim3(xcd_grid((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, pts, ranges, around, n,
+                     make_grid(radius, n), radius, (double)d_op, cost, crowded, keep, d_avg);
   // points per wave: a wave takes its groups one after the other, each a chain of lookups, so
   // few points are spread over as many waves as the device holds (about 8,192): 69.6k points
   // at d_op 0.0125, mostly alone in their cell, take 50 us at 8 per wave, about 120 at 64
   int per = 64;
   while (per > 8 && n < (int64_t)per * 8192) per /= 2;
-  hipLaunchKernelGGL(k_prune_query, dim3((unsigned)((n + per - 1) / per)), dim3(64), 0, s, pts, ranges,
+  hipLaunchKernelGGL(k_prune_query, dim3(xcd_grid((n + per - 1) / per)), dim3(64), 0, s, pts, ranges,
                      reinterpret_cast<const uint4 *>(tags), runs, around, n, per,
                      make_grid(radius, n), radius, (double)d_op, cost, keep, d_avg);
   return hipGetLastError();

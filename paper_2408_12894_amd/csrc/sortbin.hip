@@ -578,7 +578,8 @@ hipError_t launch_radix_sort(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_p
   if (n_max <= 0) return hipSuccess;
   const auto run = [&](auto items) {
     constexpr int I = decltype(items)::value;
-    if (depth && !depth->far)
+    // nine-bit digits where that makes a pass fewer
+    if (depth ? !depth->far : (bits + kDepthBits - 1) / kDepthBits < (bits + kRadixBits - 1) / kRadixBits)
       radix_passes<kDepthBits, I>(keys, vals, n_ptr, n_max, bits, hist, scan, tot, result_buf, depth, s);
     else
       radix_passes<kRadixBits, I>(keys, vals, n_ptr, n_max, bits, hist, scan, tot, result_buf, depth, s);
@@ -654,10 +655,9 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_ranges(const uint32_t *ids, int shift, const uint32_t *k_ptr, int64_t k_max, int n_ranges,
-                         uint2 *ranges, hipStream_t s) {
-  hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t *>(ranges), 0u, 2 * (int64_t)n_ranges, s);
-  if (e != hipSuccess || k_max <= 0) return e;
+hipError_t launch_ranges(const uint32_t *ids, int shift, const uint32_t *k_ptr, int64_t k_max, uint2 *ranges,
+                         hipStream_t s) {
+  if (k_max <= 0) return hipSuccess;
   const int64_t threads = (k_max + 3) / 4;
   hipLaunchKernelGGL(k_ranges, dim3((unsigned)((threads + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, ids, shift,
                      k_ptr, ranges);
