@@ -23,12 +23,11 @@ constexpr uint32_t kDepthBase = 0x3E000000u;
 // four: a camera that alternates between near and far views pays once.
 constexpr int kFarHold = 32;
 constexpr int64_t kSmallSort = 8192;      // candidates up to which one workgroup sorts the frame
-constexpr int kSortItems = 12;            // keys per thread in a radix pass (measured 8 / 12 / 16)
-constexpr int kSortTile = kBlock * kSortItems;   // 3072 keys per workgroup
-constexpr int kSortItemsSmall = 8;        // 2048-key workgroups for sorts below kRadixBigSort (2 / 4 / 8)
-constexpr int64_t kRadixBigSort = 4 << 20;
-constexpr int kSortItemsHuge = 16;        // 4096-key workgroups for sorts of kRadixHugeSort keys or more
-constexpr int64_t kRadixHugeSort = 32 << 20;
+// Keys per thread in a radix pass: 2048-key workgroups below kRadixBigSort keys, 4096 from there on. The depth
+// sort with 8, 12 and 16 keys per thread: 1M candidates 66 73 72 us, 2M 102 100 100, 4.39M 191 181 178, 10M
+// 394 358 344, 40M 1606 1435 1361; overlap pruning as a whole differs by less than 2% between them.
+constexpr int kSortItems = 8, kSortItemsBig = 16;
+constexpr int64_t kRadixBigSort = 2 << 20;
 constexpr int kSuper = 8;                 // a supertile is kSuper x kSuper tiles (one bit each of a 64-bit mask)
 constexpr int kSuperWindow = 512;         // supertiles whose pairs a workgroup places
 constexpr int kPairBlock = 256;           // depth-sorted Gaussians a workgroup of the pair kernels takes at once

@@ -7,7 +7,7 @@
 //
 // The radix pass is a reduce-then-scan design (no inter-workgroup spinning, which would
 // need cross-XCD coherent flags): per-workgroup digit histograms, a per-digit scan over
-// workgroups, then a scatter in which each workgroup ranks its 3072 (or 2048) keys stably in LDS
+// workgroups, then a scatter in which each workgroup ranks its 2048 (or 4096) keys stably in LDS
 // (wave64 ballots over the digit bits), reorders them by digit in LDS and writes each
 // digit run contiguously.
 #include <algorithm>
@@ -115,9 +115,7 @@ hipError_t launch_scan_blocks(const ScanJobs &jobs, int n_jobs, uint32_t host_se
 // ---------------------------------------------------------------------------------------
 // All of a workgroup's keys are loaded before the first LDS update, so its loads are in
 // flight together. The count n is read first: grids are sized for the buffers' capacity,
-// which can far exceed n, and workgroups past n leave without reading their keys (loading
-// keys and values together with n, bounded by the capacity, here and in the scatter made the
-// tile sort at 1080p / 1M 10% slower).
+// which can far exceed n, and workgroups past n leave without reading their keys.
 //
 // FIRST (the depth sort's first pass): the keys are all n_all candidates' depth keys, read
 // directly, and keys equal to kDepthNone (candidates not rendered) are not counted. Each
@@ -255,9 +253,7 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restric
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // the count first (grids are sized for the capacity, which can far exceed it); then the
   // tile's keys and values, loaded together with the digit offsets below, so that their
-  // latencies overlap (the offsets issued ahead of the count, with the scan's first counts
-  // likewise, made the tile sort at 1080p / 1M 8% slower: a wait for the count then waits for
-  // the scattered offset rows too)
+  // latencies overlap (ahead of the count, a wait for it would wait for the scattered offset rows too)
   const uint32_t n = FIRST ? n_all : *n_ptr;
   const uint32_t nb = (n + TILE - 1) / TILE;
   const uint32_t b = xcd_block(blockIdx.x);
@@ -500,11 +496,8 @@ hipError_t launch_depth_sort_small(const DepthSort &d, int64_t n, int blocks, ui
   return hipGetLastError();
 }
 
-// Keys per thread from the sort's capacity (measured: 16 takes the 161M-key tile sort of level 5
-// at 3840x2160 from 2.05 to 1.83 ms, but is slower than 12 at 8.5M keys).
-int radix_items(int64_t n_max) {
-  return n_max >= kRadixHugeSort ? kSortItemsHuge : n_max >= kRadixBigSort ? kSortItems : kSortItemsSmall;
-}
+// Keys per thread from the sort's capacity.
+int radix_items(int64_t n_max) { return n_max >= kRadixBigSort ? kSortItemsBig : kSortItems; }
 
 static int64_t radix_stride(int64_t n_max) {
   const int64_t tile = (int64_t)kBlock * radix_items(n_max);
@@ -524,9 +517,7 @@ static FrameTotals first_totals(const DepthSort &d, int blocks) {
 
 // Sort (keys, vals) by the low `bits` bits of the keys; stable. Ping-pongs between
 // buffers [0] and [1]; *result_buf receives the index holding the result. hist and scan
-// hold radix_hist_bytes(n_max) each (16-byte aligned). Workgroups take 2048 keys below
-// kRadixBigSort keys of capacity, 3072 up to kRadixHugeSort and 4096 beyond. `depth`: see
-// DepthSort.
+// hold radix_hist_bytes(n_max) each (16-byte aligned). `depth`: see DepthSort.
 template <int RB, int ITEMS>
 static void radix_passes(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_ptr, int64_t n_max, int bits,
                          uint32_t *hist, uint32_t *scan, uint32_t *tot, int *cur_out, const DepthSort *depth,
@@ -584,11 +575,10 @@ hipError_t launch_radix_sort(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_p
     else
       radix_passes<kRadixBits, I>(keys, vals, n_ptr, n_max, bits, hist, scan, tot, result_buf, depth, s);
   };
-  switch (radix_items(n_max)) {
-    case kSortItemsHuge: run(std::integral_constant<int, kSortItemsHuge>{}); break;
-    case kSortItems: run(std::integral_constant<int, kSortItems>{}); break;
-    default: run(std::integral_constant<int, kSortItemsSmall>{}); break;
-  }
+  if (radix_items(n_max) == kSortItemsBig)
+    run(std::integral_constant<int, kSortItemsBig>{});
+  else
+    run(std::integral_constant<int, kSortItems>{});
   return hipGetLastError();
 }
 
