@@ -103,7 +103,7 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
 //  - predicated (PRED true): every entry's arithmetic runs with alpha 0 where it does not
 //    reach the pixel, without a branch: two VALU more for a pixel reached, but no exec-mask and
 //    branch latency between the entries, which is what a walk takes where the device has few
-//    waves per SIMD, and the better way too where footprints are large.
+//    waves per SIMD. Listing the blended entries costs it a wave-wide OR per group besides.
 // Both make the same operations in the same order on what a pixel blends. A pixel that stopped
 // has T kept and Tw = 0, so that further weights are 0. A weight of 0 may not meet a colour that
 // is not finite: batches that hold one select the sums instead.
@@ -362,17 +362,30 @@ __global__ __launch_bounds__(kTile * kTile) void k_blend(const uint2 *__restrict
   if (COUNT) n_blended[pix] = nbl;
 }
 
-constexpr int kFewTiles = 4096, kFewestTiles = 2048;
+// The way by the frame's tiles and by whether the blended entries are listed; us per kernel, the table's eight
+// predicated entries ahead | not ahead | four predicated | four by branches:
+//                                        listed                     not listed
+//   1M at 800x600, 1,900 tiles        80.0  81.9  94.2  94.8     70.7  73.4  81.0  92.7
+//   1M at 1000x700, 2,772             90.0  81.1  89.7  87.0     80.7  73.5  77.0  85.4
+//   500k, floor 0.0125, 1280x720     80.1  70.1  78.6  76.4     73.2  64.5  66.7  75.8
+//   100k uniform, 1600x900, 5,700     81.0  65.6  68.1  67.5     74.1  60.0  60.6  67.6
+//   1M at 1600x900                   125.9  98.5 105.4 100.0    115.6  90.3  92.1  98.2
+//   1M at 1920x1080, 8,160           160.8 121.9 125.2 120.1    148.6 114.6 111.0 118.2
+//   1M, thrice as large, 1920x1080   170.7 130.1 136.8 133.0    154.6 119.6 119.9 127.5
+//   1M at 3840x2160, 32,400              -     - 376.1 356.4        -     - 330.4 350.2
+//   1M, a third as large, 3840x2160      -     - 378.8 360.3        -     - 338.2 348.6
+//   200k, floor 0.05, 3840x2160          -     - 367.4 361.7        -     - 328.9 351.5
+// Above kFewTiles the sizes of the footprints (2 to 2,000 tiles each on average) did not matter to it.
+constexpr int kFewTiles = 6144, kFewestTiles = 2048;
 
 hipError_t launch_blend(const uint2 *ranges, const uint32_t *values, const float4 *xyab, const float4 *cop,
                         const float2 *blue, const DevCamera &cam, const float bg[3], float *image, float *final_T,
                         int32_t *n_contrib, int32_t *n_blended, uint2 *blended, uint32_t *tile_blended,
-                        const uint32_t *order, bool large, hipStream_t s) {
+                        const uint32_t *order, hipStream_t s) {
   const int n_tiles = cam.tiles_x * cam.tiles_y;
   // eight predicated entries per group while the frame has few waves for the device, read ahead where
-  // it has fewer still; beyond, four where the levels' scale floors make footprints large, else
-  // branches (see the table)
-  const int way = n_tiles <= kFewestTiles ? 0 : n_tiles <= kFewTiles ? 1 : large ? 2 : 3;
+  // it has fewer still; beyond, four, by branches where the blended entries are listed (see the table)
+  const int way = n_tiles <= kFewestTiles ? 0 : n_tiles <= kFewTiles ? 1 : blended ? 3 : 2;
   auto kernel = way == 0 ? n_blended ? k_blend<8, true, true, true> : k_blend<8, true, true, false>
                 : way == 1 ? n_blended ? k_blend<8, true, false, true> : k_blend<8, true, false, false>
                 : way == 2 ? n_blended ? k_blend<4, true, false, true> : k_blend<4, true, false, false>

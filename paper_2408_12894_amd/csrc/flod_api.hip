@@ -89,8 +89,8 @@ struct flod_ctx {
   bool has_stream = false;
   hipEvent_t ev_switch = nullptr;       // orders a call on a new stream after the last one
   size_t required = 0;
-  unsigned long long *host_counters = nullptr;   // pinned copy of the device counters' first 24 bytes
-  // coherent pinned memory the totals kernel writes the counts into, as five 64-bit words
+  unsigned long long *host_counters = nullptr;   // pinned copy of the device counters (64 bytes)
+  // coherent pinned memory the totals kernel writes the counts into, as six 64-bit words
   // tagged with the render's sequence number (null: copy instead), and its device address
   unsigned long long *host_counts = nullptr;
   unsigned long long *host_counts_dev = nullptr;
@@ -379,9 +379,6 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   need(B_TILE_BLENDED, 4 * (size_t)n_tiles);
   need(B_TILE_ORDER, 4 * ((size_t)n_tiles + 2));
   need(B_COUNTERS, 4 * (size_t)kCntSlots);
-  // every level's scale floor is at least eight pixels wide at unit depth
-  bool large = true;
-  for (int l = 0; l < p.n_levels; ++l) large = large && p.lv[l].s_min * cam.fx >= 8.0f;
   const bool jac = level && c->keep_backward;   // the colour Jacobians for the backward
   if (jac) need(B_SHJAC, 48 * (size_t)N);
   if (st != FLOD_OK) {
@@ -471,7 +468,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
     if (launch_blend(P<uint2>(c, B_RANGES), P<uint32_t>(c, B_VALUES), P<float4>(c, B_XYAB), P<float4>(c, B_COP),
                      P<float2>(c, B_BLUE), cam, bg, out->image, out->final_T, out->n_contrib, out->n_blended,
                      c->keep_backward ? P<uint2>(c, B_BLENDED) : nullptr,
-                     c->keep_backward ? P<uint32_t>(c, B_TILE_BLENDED) : nullptr, order, large, s) != hipSuccess)
+                     c->keep_backward ? P<uint32_t>(c, B_TILE_BLENDED) : nullptr, order, s) != hipSuccess)
       return FLOD_ERR_DEVICE;
     tm.end();
     return FLOD_OK;

@@ -307,7 +307,6 @@ hipError_t launch_tile_ids(const uint2 *ranges, int n_tiles, uint32_t *tile_ids,
 // [start, end) of every bucket (id >> shift) in the sorted ids (ranges zeroed beforehand)
 hipError_t launch_ranges(const uint32_t *ids, int shift, const uint32_t *k_ptr, int64_t k_max, uint2 *ranges,
                          hipStream_t s);
-// large: the levels' scale floors make footprints large (a choice of kernel only)
 // blended: per tile, the (list position, Gaussian) pairs of the entries the forward blended
 // into some pixel, in list order at the start of the tile's range; tile_blended: their count
 // (both may be null: the render keeps no backward state)
@@ -315,7 +314,7 @@ hipError_t launch_blend(const uint2 *ranges, const uint32_t *values, const float
                         const float4 *cop, const float2 *blue, const DevCamera &cam,
                         const float bg[3], float *image, float *final_T, int32_t *n_contrib,
                         int32_t *n_blended, uint2 *blended, uint32_t *tile_blended, const uint32_t *order,
-                        bool large, hipStream_t s);
+                        hipStream_t s);
 // order: n_tiles + 2 words of scratch (the backward's tile order and its counts of split tiles);
 // g2d: the n_g2d gradient sums, doubles where bwd_sums_wide, else floats, zeroed here first; the kernel
 // is timed by the events (if given), its tile order and the zeroing are not
