@@ -58,17 +58,21 @@ __device__ __forceinline__ float row_sum16(float v) {
 }
 
 // Frames of up to this many tiles are walked by workgroups of four waves, of two (k_blend_bwd_few),
-// larger ones by one wave per tile (k_blend_bwd); us per kernel:
-//                                       wave per tile   four waves  two waves
-//   2k Gaussians at 253x187, 192 tiles             49         17          27
-//   20k at 400x300, 475                           159         38          60
-//   50k at 640x360, 920                           150         66          72
-//   100k at 800x600, 1,900                        174        100          92
-//   clusters, 200k at 800x600                     221        152         132
-//   clusters, 300k at 1000x700, 2,772             199        206         176
-//   clusters, 500k at 1280x720, 3,600             130        223         185
-// (Waves per tile: the first six with the reduction's second round in DPP, as it was for them.)
-constexpr int kFewBwdTiles4 = 1024, kFewBwdTiles2 = 3071;
+// larger ones by one wave per tile (k_blend_bwd); us per kernel, wave per tile | two waves | four:
+//   tiles                          300          512x512, 1,024   640x480, 1,200   800x600, 1,900   880x640, 2,200
+//   100k uniform              272 118  72       164  81  79      163  95  90      132 101 115      128 115 127
+//   300k clusters             439 186 116       239 126 118      222 143 141      191 151 175      174 164 193
+//   500k, floor 0.0125        310 151  94       182 103  99      178 106 119      153 133 153      154 147 171
+//   1M clusters               483 196 120       272 149 142      235 157 168      200 182 211      192 199 232
+//   2k large                   77  35  22        63  31  29       60  31  38       57  44  53       55  51  60
+//   40k, floor 0.05           197  99  61       156  75  60      139  68  75      135  85 102      128  97 115
+//   tiles                     960x640, 2,400    1000x700, 2,772  1024x768, 3,072  1280x720, 3,600
+//   100k uniform              122 120           120 127          112 130          113 170
+//   300k clusters             163 181           159 189          155 201          149 239
+//   500k, floor 0.0125        150 159           138 172          142 181          135 217
+//   1M clusters               183 218           183 224          175 236          161 278
+//   40k, floor 0.05           119 108           124 117          126 121          119 153
+constexpr int kFewBwdTiles4 = 1024, kFewBwdTiles2 = 2304;
 
 bool bwd_sums_wide(int n_tiles) { return n_tiles <= kFewBwdTiles2; }
 
