@@ -953,7 +953,7 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
   uint2 *runs = P<uint2>(ctx, B_SRECT);
   uint32_t *around = P<uint32_t>(ctx, B_TILES);
   unsigned long long *cost = reinterpret_cast<unsigned long long *>(counters + kCntTotal64);
-  unsigned long long *crowded = reinterpret_cast<unsigned long long *>(counters + kCntPairs64);
+  unsigned long long *sums = P<unsigned long long>(ctx, B_TOT);   // after the sort
   const int sub_bits = 3 * prune_levels(n);
   if (d_op > 0.0f) {
     uint32_t *dk[2] = {P<uint32_t>(ctx, B_DKEY0), P<uint32_t>(ctx, B_DKEY1)};
@@ -962,15 +962,15 @@ flod_status flod_overlap_prune(flod_ctx *ctx, const flod_level *level, float d_o
     if (launch_prune_keys(level->means, n, d_op, dk[0], dv[0], ranges, tags, counters, s) != hipSuccess ||
         launch_radix_sort(dk, dv, counters + kCntVisible, n, bits + sub_bits, P<uint32_t>(ctx, B_HIST),
                           P<uint32_t>(ctx, B_SCAN), P<uint32_t>(ctx, B_TOT), &res, s) != hipSuccess ||
-        launch_prune_gather(level->means, dv[res], n, P<float4>(ctx, B_XYAB), s) != hipSuccess ||
+        launch_prune_gather(level->means, dv[res], n, P<float4>(ctx, B_XYAB), sums, s) != hipSuccess ||
         launch_ranges(dk[res], sub_bits, counters + kCntVisible, n, ranges, s) != hipSuccess ||
         launch_prune_runs(dk[res], ranges, n, d_op, tags, runs, s) != hipSuccess ||
-        launch_prune_cost(pts, ranges, n, d_op, around, cost, crowded, s) != hipSuccess)
+        launch_prune_cost(pts, ranges, n, d_op, around, sums, s) != hipSuccess)
       return FLOD_ERR_DEVICE;
   }
   // the device refuses a scan beyond the limit (nothing is written); the host learns of it with
   // the kept count
-  if (launch_prune_query(pts, ranges, tags, runs, around, n, d_op, cost, crowded, keep, d_avg, s) != hipSuccess) return FLOD_ERR_DEVICE;
+  if (launch_prune_query(pts, ranges, tags, runs, around, n, d_op, sums, cost, keep, d_avg, s) != hipSuccess) return FLOD_ERR_DEVICE;
   auto count = [&](uint32_t *bc) { return launch_mask_count(keep, n, bc, s); };
   auto no_copy = [&](int, const unsigned long long *, const flod_level &) { return hipSuccess; };
   Compaction job;

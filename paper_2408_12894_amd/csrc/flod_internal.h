@@ -134,7 +134,7 @@ struct AdamArgs {
 enum : int {
   kCntVisible = 0,      // u32 count of visible candidates
   kCntTotal64 = 2,      // u64 count of instances (or other totals; two u32 slots: 2, 3)
-  kCntPairs64 = 4,      // u64 count of (supertile, Gaussian) pairs (or of crowded points; slots 4, 5)
+  kCntPairs64 = 4,      // u64 count of (supertile, Gaussian) pairs (slots 4, 5)
   kCntPairs = 6,        // u32 count of pairs; 0 when instances or pairs exceed their buffers
   kCntChunks = 7,       // u32 count of chunks of pairs
   kCntFar = 1,          // u32 count of visible candidates beyond the depth sort's three passes
@@ -369,17 +369,18 @@ int prune_levels(int64_t n);       // halvings of a cell its sort keys hold (3 b
 // ranges, tags: 2^prune_table_bits(n) slots each, cleared here with the counters the others use
 hipError_t launch_prune_keys(const float *means, int64_t n, float d_op, uint32_t *keys, uint32_t *vals, uint2 *ranges,
                              uint32_t *tags, uint32_t *counters, hipStream_t s);
+// sums: kDepthRadix words, cleared here
 hipError_t launch_prune_gather(const float *means, const uint32_t *sorted_vals, int64_t n, float4 *pts,
-                               hipStream_t s);
-// around: per point in key order, the points in the 27 buckets around it (itself included); cost: their
-// sum; crowded: the points with many
+                               unsigned long long *sums, hipStream_t s);
+// around: per point in key order, the points in the 27 buckets around it (itself included); sums: parts of
+// their sum, which the query writes to cost, and of the count of points with many
 hipError_t launch_prune_cost(const float4 *pts, const uint2 *ranges, int64_t n, float d_op, uint32_t *around,
-                             unsigned long long *cost, unsigned long long *crowded, hipStream_t s);
+                             unsigned long long *sums, hipStream_t s);
 // runs: as many slots as tags
 hipError_t launch_prune_runs(const uint32_t *keys, const uint2 *ranges, int64_t n, float d_op, uint32_t *tags,
                              uint2 *runs, hipStream_t s);
 hipError_t launch_prune_query(const float4 *pts, const uint2 *ranges, const uint32_t *tags, const uint2 *runs,
-                              uint32_t *around, int64_t n, float d_op, const unsigned long long *cost,
-                              const unsigned long long *crowded, uint8_t *keep, double *d_avg, hipStream_t s);
+                              uint32_t *around, int64_t n, float d_op, const unsigned long long *sums,
+                              unsigned long long *cost, uint8_t *keep, double *d_avg, hipStream_t s);
 
 }  // namespace flod

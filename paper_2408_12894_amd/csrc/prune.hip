@@ -61,7 +61,7 @@ __device__ __forceinline__ int32_t cell_of(float x, double inv_c) {
 // (MurmurHash3's fmix64 finaliser), and in them the cell's place in the block, permuted by another part of the
 // hash so that blocks on the same 64 meet evenly. The 27 cells around a point lie in at most
 // eight blocks, so their ranges and points come from a few cache lines: each cell hashed by itself, all of
-// flod_overlap_prune took 1,050 us for 1M points ten d_op apart and, one thread per point, 1,000, now 510.
+// flod_overlap_prune took 1,050 us for 1M points ten d_op apart and, one thread per point, 1,000, now 490.
 __device__ __forceinline__ uint32_t bucket_of(int32_t ix, int32_t iy, int32_t iz, int shift) {
   const uint64_t m = (1ull << (kCellBits - 2)) - 1;
   const int32_t x = ix + (1 << (kCellBits - 1)), y = iy + (1 << (kCellBits - 1)), z = iz + (1 << (kCellBits - 1));
@@ -90,8 +90,8 @@ __device__ __forceinline__ uint32_t morton(uint32_t x, uint32_t y, uint32_t z, i
   return m;
 }
 
-// The keys; and what the steps behind them find cleared: the buckets' ranges, the run table's tags, and in
-// the counters the count of keys, the size of the scan and the count of crowded points.
+// The keys; and what the steps behind them find cleared: the buckets' ranges, the run table's tags and the
+// count of keys.
 __global__ __launch_bounds__(kBlock) void k_prune_keys(const float *means, int64_t n, Grid g, uint32_t *keys,
                                                        uint32_t *vals, uint2 *ranges, uint32_t *tags,
                                                        uint32_t *counters) {
@@ -99,11 +99,7 @@ __global__ __launch_bounds__(kBlock) void k_prune_keys(const float *means, int64
   if (i >= (int64_t)1 << g.bits) return;   // at least n
   ranges[i] = make_uint2(0u, 0u);
   if (g.levels > 0) tags[i] = 0u;
-  if (i == 0) {
-    counters[kCntVisible] = (uint32_t)n;
-    *reinterpret_cast<unsigned long long *>(counters + kCntTotal64) = 0ull;
-    *reinterpret_cast<unsigned long long *>(counters + kCntPairs64) = 0ull;
-  }
+  if (i == 0) counters[kCntVisible] = (uint32_t)n;
   if (i >= n) return;
   const int32_t fx = fine_of(means[i * 3 + 0], g.inv_c);
   const int32_t fy = fine_of(means[i * 3 + 1], g.inv_c);
@@ -114,9 +110,16 @@ __global__ __launch_bounds__(kBlock) void k_prune_keys(const float *means, int64
   vals[i] = (uint32_t)i;
 }
 
+// The size of the neighbour scan and the count of crowded points (k_prune_cost), in kPruneSums parts on
+// cache lines of their own: added to one word each, the workgroups' atomics took 56 us for 500k points (31 for
+// the size alone), in parts 20.
+constexpr int kPruneSums = 16, kSumStride = 16;
+static_assert(kPruneSums * kSumStride * sizeof(unsigned long long) <= kDepthRadix * sizeof(uint32_t), "in the sort's totals");
+
 __global__ __launch_bounds__(kBlock) void k_prune_gather(const float *means, const uint32_t *sorted_vals, int64_t n,
-                                                         float4 *pts) {
+                                                         float4 *pts, unsigned long long *sums) {
   const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (p < kPruneSums * kSumStride) sums[p] = 0ull;
   if (p >= n) return;
   const uint32_t j = sorted_vals[p];
   pts[p] = make_float4(means[(int64_t)j * 3 + 0], means[(int64_t)j * 3 + 1], means[(int64_t)j * 3 + 2],
@@ -360,10 +363,10 @@ __global__ __launch_bounds__(64) void k_prune_query(const float4 *__restrict__ p
 constexpr uint32_t kPruneFew = 320;
 
 // Size of the neighbour scan over whole cells: per point its 27 buckets' occupancy (to around),
-// their sum and the count of those above kPruneFew.
+// and in parts their sum and the count of those above kPruneFew.
 __global__ __launch_bounds__(kBlock) void k_prune_cost(const float4 *__restrict__ pts, const uint2 *__restrict__ ranges,
                                                        int64_t n, Grid g, uint32_t *__restrict__ around,
-                                                       unsigned long long *cost, unsigned long long *crowded) {
+                                                       unsigned long long *sums) {
   __shared__ unsigned long long s_sum[kBlock / 64];
   __shared__ uint32_t s_crowd[kBlock / 64];
   const int64_t p = (int64_t)xcd_block(blockIdx.x) * kBlock + threadIdx.x;
@@ -392,8 +395,9 @@ __global__ __launch_bounds__(kBlock) void k_prune_cost(const float4 *__restrict_
       t += s_sum[w];
       m += s_crowd[w];
     }
-    atomicAdd(cost, t);
-    if (m) atomicAdd(crowded, m);
+    unsigned long long *part = sums + (blockIdx.x % kPruneSums) * kSumStride;
+    atomicAdd(&part[0], t);
+    if (m) atomicAdd(&part[1], m);
   }
 }
 
@@ -406,21 +410,36 @@ __global__ __launch_bounds__(kBlock) void k_prune_cost(const float4 *__restrict_
 // then their first points are loaded together.
 // All of flod_overlap_prune in us, points at random f d_op apart, one thread per point throughout | by
 // waves alone (each without the block hash) | now:
-//   300k, f = 10, 3, 2, 1     240 232 256 486 | 354 307 270 268 | 204 219 255 295
-//   1M                        953 739 539 1043 | 1032 814 604 673 | 507 412 566 631
+//   300k, f = 10, 3, 2, 1     245 240 264 490 | 361 315 284 276 | 194 207 243 269
+//   1M                        960 743 551 1044 | 1044 819 617 687 | 486 379 535 557
 constexpr int64_t kPruneFewFrom = 32768;
 
 __global__ __launch_bounds__(kBlock) void k_prune_few(const float4 *__restrict__ pts, const uint2 *__restrict__ ranges,
                                                       uint32_t *__restrict__ around, int64_t n, Grid g, double radius,
-                                                      double d_op, const unsigned long long *cost,
-                                                      const unsigned long long *crowded, uint8_t *keep,
-                                                      double *d_avg) {
+                                                      double d_op, const unsigned long long *sums,
+                                                      unsigned long long *cost, uint8_t *keep, double *d_avg) {
   constexpr int kTogether = 4;
-  if (*cost > kPruneMaxScan) return;   // refused: nothing is written
+  __shared__ unsigned long long s_sum[2];
+  if (threadIdx.x < 64) {
+    const bool in = threadIdx.x < kPruneSums;
+    unsigned long long t = in ? sums[threadIdx.x * kSumStride] : 0ull, m = in ? sums[threadIdx.x * kSumStride + 1] : 0ull;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      t += __shfl_xor(t, o, 64);
+      m += __shfl_xor(m, o, 64);
+    }
+    if (threadIdx.x == 0) {
+      s_sum[0] = t;
+      s_sum[1] = m;
+      if (blockIdx.x == 0) *cost = t;   // for k_prune_query and the host
+    }
+  }
+  __syncthreads();
+  if (s_sum[0] > kPruneMaxScan) return;   // refused: nothing is written
   const int64_t p = (int64_t)xcd_block(blockIdx.x) * kBlock + threadIdx.x;
   if (p >= n) return;
   const uint32_t c = around[p];
-  if (c > (n >= kPruneFewFrom && *crowded <= (unsigned long long)n / 256u ? kPruneFew : 3u)) return;
+  if (c > (n >= kPruneFewFrom && s_sum[1] <= (unsigned long long)n / 256u ? kPruneFew : 3u)) return;
   const float4 a = pts[p];
   double avg = INFINITY;
   if (c > 3u) {
@@ -516,17 +535,17 @@ hipError_t launch_prune_keys(const float *means, int64_t n, float d_op, uint32_t
 }
 
 hipError_t launch_prune_gather(const float *means, const uint32_t *sorted_vals, int64_t n, float4 *pts,
-                               hipStream_t s) {
+                               unsigned long long *sums, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_prune_gather, dim3(grid_of(n)), dim3(kBlock), 0, s, means, sorted_vals, n, pts);
+  hipLaunchKernelGGL(k_prune_gather, dim3(grid_of(n)), dim3(kBlock), 0, s, means, sorted_vals, n, pts, sums);
   return hipGetLastError();
 }
 
 hipError_t launch_prune_cost(const float4 *pts, const uint2 *ranges, int64_t n, float d_op, uint32_t *around,
-                             unsigned long long *cost, unsigned long long *crowded, hipStream_t s) {
+                             unsigned long long *sums, hipStream_t s) {
   if (n <= 0 || !(d_op > 0.0f)) return hipSuccess;
   hipLaunchKernelGGL(k_prune_cost, dim3(xcd_grid((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, pts, ranges, n,
-                     make_grid(prune_radius(d_op), n), around, cost, crowded);
+                     make_grid(prune_radius(d_op), n), around, sums);
   return hipGetLastError();
 }
 
@@ -541,8 +560,8 @@ hipError_t launch_prune_runs(const uint32_t *keys, const uint2 *ranges, int64_t 
 }
 
 hipError_t launch_prune_query(const float4 *pts, const uint2 *ranges, const uint32_t *tags, const uint2 *runs,
-                              uint32_t *around, int64_t n, float d_op, const unsigned long long *cost,
-                              const unsigned long long *crowded, uint8_t *keep, double *d_avg, hipStream_t s) {
+                              uint32_t *around, int64_t n, float d_op, const unsigned long long *sums,
+                              unsigned long long *cost, uint8_t *keep, double *d_avg, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (!(d_op > 0.0f)) {
     hipLaunchKernelGGL(k_prune_none, dim3(grid_of(n)), dim3(kBlock), 0, s, n, keep, d_avg);
@@ -550,7 +569,7 @@ hipError_t launch_prune_query(const float4 *pts, const uint2 *ranges, const uint
   }
   const double radius = prune_radius(d_op);
   hipLaunchKernelGGL(k_prune_few, dim3(xcd_grid((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, pts, ranges, around, n,
-                     make_grid(radius, n), radius, (double)d_op, cost, crowded, keep, d_avg);
+                     make_grid(radius, n), radius, (double)d_op, sums, cost, keep, d_avg);
   // points per wave: a wave takes its groups one after the other, each a chain of lookups, so
   // few points are spread over as many waves as the device holds (about 8,192): 69.6k points
   // at d_op 0.0125, mostly alone in their cell, take 50 us at 8 per wave, about 120 at 64
