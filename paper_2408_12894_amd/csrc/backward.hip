@@ -270,7 +270,8 @@ __device__ __forceinline__ void bwd_part(
             // a band of rows that no lane's pixel takes part in adds exact zeros and keeps T and V:
             // its half of the arithmetic is skipped (the kernel is bound by VALU issue; 1080p / 1M
             // 165 -> 155 us, 720p / 500k 137 -> 129; two bands at a time 161 and 131). The registers
-            // stay at those of six waves per SIMD (at five the skip lost: 200 us)
+            // stay at those of six waves per SIMD (at five the skip lost: 200 us; at six one register spills,
+            // stored once and loaded back once a batch)
             if (PPT > 1 && !(live & (1u << k))) continue;
             const float alpha = aev[k], dy = dyv[k];
             const float Ti = T[k] * __builtin_amdgcn_rcpf(1.0f - alpha);

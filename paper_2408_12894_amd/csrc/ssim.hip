@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_ssim_reduce(const double2 *_
 }
 
 // Three waves per SIMD: unbounded it took 182 registers (48 us against 44 at 3 x 1920 x 1080; at
-// four it spills, 89 us).
+// four 89 us, with spills all over; at three an address spills, loaded back once a step).
 __global__ __launch_bounds__(kBlock, 3) void k_ssim_bwd(SsimArgs a, const float *__restrict__ gmap, bool vec,
                                                      const double *dloss, float *__restrict__ dx) {
   __shared__ SsimColumns<3> s_col;
@@ -372,21 +372,26 @@ static SsimArgs ssim_args(const float *x, const float *y, int C, int H, int W, f
   return a;
 }
 
+constexpr int64_t kSsimFew = 1024;
+
 int64_t ssim_blocks(int C, int H, int W) {
-  return (int64_t)((W + kLossTile - 1) / kLossTile) * ((H + kLossTile - 1) / kLossTile) * C;
+  return std::max<int64_t>(kSsimFew, (int64_t)((W + kLossTile - 1) / kLossTile) * ((H + kLossTile - 1) / kLossTile) * C);
 }
 
 // Steps per workgroup: four, which read 26 rows for 16, or fewer (14 rows for four) for images
-// that would leave the device mostly idle. There are never more workgroups than the 16 x 16 tiles
-// that ssim_blocks counts (the caller's room for their sums).
+// that would leave the device mostly idle with them (up to kSsimFew workgroups; as few as an image's
+// 16 x 16 tiles, 1 x 16 x 16 took 22.8 us forward and backward, one workgroup's four steps, and 3 x 500 x 16
+// 24.8, now 16.4 and 15.6). There are never more workgroups than ssim_blocks (the caller's room for their
+// sums). Narrow high images keep most of a tile's columns idle (3 x 8000 x 16 62 us, of 16 x 16 tiles 27): going
+// through them down their columns took 35, and leaving idle waves out spilled in the backward (44 -> 53 us at
+// 3 x 1920 x 1080).
 static dim3 ssim_grid(SsimArgs &a) {
   auto count = [&](int steps) {
     return (int64_t)a.tiles_x * ((a.H + kSsimRun * steps - 1) / (kSsimRun * steps)) * a.C;
   };
   static_assert(kSsimRun * kSsimSteps >= kLossTile && kSsimOut >= kLossTile, "ssim_blocks bounds the workgroups");
-  const int64_t most = std::min<int64_t>(ssim_blocks(a.C, a.H, a.W), 1024);
   a.steps = kSsimSteps;
-  while (a.steps > 1 && count(a.steps / 2) <= most) a.steps /= 2;
+  while (a.steps > 1 && count(a.steps / 2) <= kSsimFew) a.steps /= 2;
   return dim3((unsigned)a.tiles_x, (unsigned)(count(a.steps) / a.C / a.tiles_x), (unsigned)a.C);
 }
 
