@@ -30,7 +30,10 @@
  * are known, while the rest of the frame is still queued (FLOD_COUNT_COPY=1 in the
  * environment when a context is created selects the copy). It then fills the
  * statistics and, when K exceeded the capacity, grows the buffers and enqueues the frame's
- * tail again. A context's first render, with no buffers yet, waits for K before the tail.
+ * tail again; likewise when the frame has a depth that the sort's three passes do not cover
+ * (beyond 8192), which the device reports with K = 0 for the tail it was given: it is sorted
+ * by four, as the context's next 32 frames are from the start. A context's first render, with
+ * no buffers yet, waits for K before the tail.
  * A context may be used on different streams from one call to the next: a call on a stream
  * other than the one the context last used first makes its stream wait (an event, no host
  * wait) for the work already enqueued on the previous one, so no buffer is reused, grown or
@@ -180,7 +183,7 @@ flod_status flod_select_compact(flod_ctx *ctx, const flod_level *levels, int n_l
    removal changes another's neighbours). A level of fewer than four Gaussians keeps all.
    keep: device uint8[n], 1 = keep, 0 = remove. d_avg: device double[n] or NULL; receives
    d_avg exactly when the three nearest lie within 3 d_op (1 + 1e-9), +inf otherwise (such a
-   Gaussian is kept). n_keep: host, the number kept. Workspace about 48 B per Gaussian plus
+   Gaussian is kept). n_keep: host, the number kept. Workspace about 40 B per Gaussian plus
    20 B per hash bucket (2^ceil(log2 n) buckets). One host synchronisation (the count) and
    one check of the neighbour-search size: when the means are so dense relative to d_op
    that the scan would exceed 2^36 distance evaluations, returns FLOD_ERR_UNSUPPORTED
@@ -298,8 +301,9 @@ flod_status flod_level_transition(flod_ctx *ctx, const flod_level *in, float s_m
    the clamp (48 bytes; the backward reads no SH coefficients). Returns
    FLOD_ERR_UNSUPPORTED after a selective render, after a render that kept no backward state
    (flod_ctx_keep_backward_state) or when no render preceded it; FLOD_ERR_INVALID_ARG for
-   a NULL array or d_quats / d_sh not 16-byte aligned. FP32
-   atomic accumulation: results are deterministic up to summation order. */
+   a NULL array or d_quats / d_sh not 16-byte aligned. The
+   per-Gaussian sums are atomic additions, in FP64 for frames small enough to be walked by
+   several waves per tile and in FP32 beyond: deterministic up to summation order. */
 flod_status flod_render_backward(flod_ctx *ctx, const float *dL_dimage, flod_grads *grads,
                                  void *stream);
 
@@ -358,11 +362,13 @@ enum {
   FLOD_STAGE_DEPTH_SORT,      /* radix sort by depth; its first pass compacts the visible
                                  set and takes the frame's counts (read by the host),
                                  its last writes the tile rectangles in depth order    */
-  FLOD_STAGE_OFFSETS,         /* offsets of each workgroup's pairs per supertile     */
-  FLOD_STAGE_EMIT,            /* the tile lists, from the grouped pairs              */
+  FLOD_STAGE_OFFSETS,         /* pairs (supertile of 8 x 8 tiles, Gaussian) counted per
+                                 column of depth-sorted Gaussians, and their offsets   */
+  FLOD_STAGE_EMIT,            /* the tile lists, from the grouped pairs, and the blend's
+                                 tile order                                           */
   FLOD_STAGE_TILE_SORT,       /* pairs grouped by supertile in depth order, their
                                  instances counted per tile                           */
-  FLOD_STAGE_RANGES,          /* per-tile [start, end) and the blend's tile order    */
+  FLOD_STAGE_RANGES,          /* per-tile [start, end)                               */
   FLOD_STAGE_BLEND,           /* front-to-back compositing (eq. 2)                   */
   FLOD_STAGE_BLEND_BWD,       /* reverse compositing kernel (its tile order excluded) */
   FLOD_STAGE_PREPROCESS_BWD,  /* chain rule to the 3D attributes                     */

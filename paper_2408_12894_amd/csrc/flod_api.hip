@@ -70,7 +70,7 @@ struct Saved {
   float bg[3] = {0, 0, 0};
   const float *final_T = nullptr;
   const int32_t *n_contrib = nullptr;
-  bool has_tile_ids = false;     // B_TILE_IDS holds the list's tile ids (see flod_ctx_view)
+  bool has_inspection = false;     // B_TILE_IDS and B_BIN are those of the last render (see flod_ctx_view)
   bool has_grad2d = false;
   bool grad2d_moments = false;   // the backward's moment sums in B_G2D are still to be turned into gradients
   bool grad2d_wide = false;      // they are doubles, and the gradients go to B_GRAD2D (see flod_ctx_view)
@@ -333,7 +333,7 @@ flod_status render_common(flod_ctx *c, PreParams &p, int64_t *n_selected, const 
   if (use_stream(c, s) != hipSuccess) return FLOD_ERR_DEVICE;
   c->saved.valid = false;
   c->saved.has_grad2d = false;
-  c->saved.has_tile_ids = false;
+  c->saved.has_inspection = false;
   timing_flush(c);
   StageTimer tm(c, s);
   const int64_t N = p.n_total;
@@ -1184,7 +1184,7 @@ flod_status flod_ctx_view(const flod_ctx *ctx, flod_view *out) {
   const Saved &sv = ctx->saved;
   memset(out, 0, sizeof(*out));
   if (!sv.valid) return FLOD_ERR_UNSUPPORTED;
-  if (!sv.has_tile_ids) {
+  if (!sv.has_inspection) {
     // the render writes neither the list's tile ids nor the binning records: the first view after
     // it does, from the ranges and from what the records repeat
     size_t extra = 0;
@@ -1202,7 +1202,7 @@ flod_status flod_ctx_view(const flod_ctx *ctx, flod_view *out) {
                            c->last_stream) != hipSuccess ||
         hipStreamSynchronize(c->last_stream) != hipSuccess)
       return FLOD_ERR_DEVICE;
-    c->saved.has_tile_ids = true;
+    c->saved.has_inspection = true;
   }
   out->tile_ids = P<uint32_t>(c, B_TILE_IDS);
   out->values = P<uint32_t>(c, B_VALUES);

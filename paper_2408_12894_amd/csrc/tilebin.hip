@@ -3,8 +3,8 @@
 // The list the blend reads holds, per tile, the Gaussians whose footprint reaches it in depth
 // order. Instead of emitting one (tile, Gaussian) record per instance and sorting those K
 // records by tile, a Gaussian is listed once per supertile it reaches, with a 64-bit mask of
-// the supertile's tiles it covers: a pair. Pairs are several times fewer than instances (1.6
-// per Gaussian against 9.8 instances at 1080p / 1M, 3.8 against 73 for the finest level at
+// the supertile's tiles it covers: a pair. Pairs are several times fewer than instances (1.7
+// per Gaussian against 9.9 instances at 1080p / 1M, 3.8 against 73 for the finest level at
 // 3840x2160), so what is moved per instance is only the final list entry:
 //   1. k_pair_hist   per column of 256 depth-sorted Gaussians (more in frames above 4K), its pairs per
 //                    supertile
