@@ -76,8 +76,9 @@ def survey_work(step, N, K, P, tiles, pi_walk, pi_blend):
 
 # Steps that this design does otherwise than the table supposes: the table prices one record per
 # instance, emitted, sorted and searched for the tiles' bounds, but here an instance is first
-# written in its final place. They are priced by what the design itself moves.
-OWN_BYTES_STEPS = ("S3 scan", "S4 duplicate", "S5 sort", "S6 ranges")
+# written in its final place; and a gradient row that reads the 192 B of SH coefficients, where
+# the forward's colour Jacobian (48 B) stands in. They are priced by what the design itself moves.
+OWN_BYTES_STEPS = ("S3 scan", "S4 duplicate", "S5 sort", "S6 ranges", "S9 preprocess backward")
 
 
 def step_work(step, N, n_vis, K, P, tiles, pi_walk, pi_blend):
