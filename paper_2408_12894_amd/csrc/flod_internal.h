@@ -23,11 +23,15 @@ constexpr uint32_t kDepthBase = 0x3E000000u;
 // four: a camera that alternates between near and far views pays once.
 constexpr int kFarHold = 32;
 constexpr int64_t kSmallSort = 8192;      // candidates up to which one workgroup sorts the frame
-// Keys per thread in a radix pass: 2048-key workgroups below kRadixBigSort keys, 4096 from there on. The depth
-// sort with 8, 12 and 16 keys per thread: 1M candidates 66 73 72 us, 2M 102 100 100, 4.39M 191 181 178, 10M
-// 394 358 344, 40M 1606 1435 1361; overlap pruning as a whole differs by less than 2% between them.
-constexpr int kSortItems = 8, kSortItemsBig = 16;
-constexpr int64_t kRadixBigSort = 2 << 20;
+// Keys per thread in a radix pass: 2048-key workgroups below kRadixBigSort keys of capacity, 3072 up to
+// kRadixHugeSort, 4096 from there on. The grids are sized for the capacity, but after the first pass only the
+// visible keys are left: larger workgroups gain where most are visible and lose where few are. The
+// depth sort with 8 | 12 | 16 keys per thread, us, most candidates visible, then a tenth of them: 1.5M 86 87
+// 91, 52 57 63; 3M 144 134 131, 67 70 75; 4.5M 203 188 187, 80 80 87; 10M 12 against 16 368 365, 117 121; 24M 889
+// 850, 221 216; selected from 2.5M (a sixth visible) 63 64 68, from 4.2M 89 83 89. Overlap pruning as a
+// whole differs by less than 2% between them.
+constexpr int kSortItems = 8, kSortItemsBig = 12, kSortItemsHuge = 16;
+constexpr int64_t kRadixBigSort = 4 << 20, kRadixHugeSort = 32 << 20;
 constexpr int kSuper = 8;                 // a supertile is kSuper x kSuper tiles (one bit each of a 64-bit mask)
 constexpr int kSuperWindow = 512;         // supertiles whose pairs a workgroup places
 constexpr int kPairBlock = 256;           // depth-sorted Gaussians a workgroup of the pair kernels takes at once

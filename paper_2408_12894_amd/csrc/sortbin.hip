@@ -7,7 +7,7 @@
 //
 // The radix pass is a reduce-then-scan design (no inter-workgroup spinning, which would
 // need cross-XCD coherent flags): per-workgroup digit histograms, a per-digit scan over
-// workgroups, then a scatter in which each workgroup ranks its 2048 (or 4096) keys stably in LDS
+// workgroups, then a scatter in which each workgroup ranks its 2048 (3072, 4096) keys stably in LDS
 // (wave64 ballots over the digit bits), reorders them by digit in LDS and writes each
 // digit run contiguously.
 #include <algorithm>
@@ -497,7 +497,9 @@ hipError_t launch_depth_sort_small(const DepthSort &d, int64_t n, int blocks, ui
 }
 
 // Keys per thread from the sort's capacity.
-int radix_items(int64_t n_max) { return n_max >= kRadixBigSort ? kSortItemsBig : kSortItems; }
+int radix_items(int64_t n_max) {
+  return n_max >= kRadixHugeSort ? kSortItemsHuge : n_max >= kRadixBigSort ? kSortItemsBig : kSortItems;
+}
 
 static int64_t radix_stride(int64_t n_max) {
   const int64_t tile = (int64_t)kBlock * radix_items(n_max);
@@ -575,10 +577,11 @@ hipError_t launch_radix_sort(uint32_t *keys[2], uint32_t *vals[2], uint32_t *n_p
     else
       radix_passes<kRadixBits, I>(keys, vals, n_ptr, n_max, bits, hist, scan, tot, result_buf, depth, s);
   };
-  if (radix_items(n_max) == kSortItemsBig)
-    run(std::integral_constant<int, kSortItemsBig>{});
-  else
-    run(std::integral_constant<int, kSortItems>{});
+  switch (radix_items(n_max)) {
+    case kSortItemsHuge: run(std::integral_constant<int, kSortItemsHuge>{}); break;
+    case kSortItemsBig: run(std::integral_constant<int, kSortItemsBig>{}); break;
+    default: run(std::integral_constant<int, kSortItems>{}); break;
+  }
   return hipGetLastError();
 }
 
