@@ -104,7 +104,7 @@ FLOPS_BLEND_BWD = 46
 # step_1080p_1M_hbm_counters.md). A figure holds only for the kernel sources it was taken
 # with: the sha256 over the listed files must match, else the traffic is reported as null.
 PROFILED_TRAFFIC = {
-    "blend_bwd": {"bytes": 370875023, "sha256": "de85ef5b67f9b9536c6bfde714ca8821cca6a6946f1b72f4f1f407e135f36afb",
+    "blend_bwd": {"bytes": 370858165, "sha256": "40e74a9f524fb2d1736195f7c2d4f99cdb47e85487a9f9d6e65dd5fb918553f3",
                   "sources": ['paper_2408_12894_amd/csrc/backward.hip', 'paper_2408_12894_amd/csrc/blend_common.h', 'paper_2408_12894_amd/csrc/project.h', 'paper_2408_12894_amd/csrc/flod_internal.h']},
 }
 
